@@ -10,6 +10,7 @@
 #include "dqrm.h"
 #include "dqrm_device.hpp"
 #include "dqrm_fwd.hpp"
+#include "dqrm_dedupe.hpp"
 #include "dqrm_bwd.hpp"
 #include "dqrm_update.hpp"
 #include "dqrm_merge.hpp"
@@ -80,10 +81,8 @@ int32_t check_batch(const dqrm_tables_t *tb, const int64_t *indices, const int64
 
 // ---- workspace layout of dqrm_embbag_bwd -------------------------------------
 struct WsLayout {
-    size_t off_table_base, off_table_nuniq, off_table_nchunk, off_table_nsingle, off_totals, off_bag_of_pos, off_sorted_bag,
-        off_chunk_local, off_single_local, off_chunk_desc, off_chunk_bags, off_single_desc, off_run_key, off_run_pos,
-        off_merged_key, off_merged_pos, off_head_of_seg, off_seg_count, off_partial_full,
-        off_partial_last, off_absmax_slots, total;
+    size_t off_part_info, off_totals, off_part_key, off_part_pos, off_part_start, off_sorted_bag, off_chunk_local, off_single_local, off_chunk_desc, off_chunk_bags,
+        off_single_desc, off_seg_count, off_partial_full, off_partial_last, off_absmax_slots, total;
 };
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -98,12 +97,13 @@ WsLayout ws_layout(int32_t T, int32_t D, int64_t N)
         o = align_up(o + bytes, 256);
         return at;
     };
-    L.off_table_base = take(t * sizeof(int));
-    L.off_table_nuniq = take(t * sizeof(int));
-    L.off_table_nchunk = take(t * sizeof(int));
-    L.off_table_nsingle = take(t * sizeof(int));
+    L.off_part_info = take((size_t)dqrm::kMaxParts * 2 * sizeof(int4));
     L.off_totals = take(4 * sizeof(int));
-    L.off_bag_of_pos = take(n * sizeof(int));
+    // (only a batch of more than kDdTile lookups is partitioned)
+    const size_t big = N > dqrm::kDdTile ? n : 0;
+    L.off_part_key = take(big * sizeof(unsigned));
+    L.off_part_pos = take(big * sizeof(unsigned short));
+    L.off_part_start = take(big ? t * dqrm::kDdTiles * dqrm::kDdRanges * sizeof(unsigned short) : 0);
     L.off_sorted_bag = take(n * sizeof(int));
     // (the lists have a slot even for an empty batch: the summing kernels request their first entries before they
     // know the counts)
@@ -113,13 +113,6 @@ WsLayout ws_layout(int32_t T, int32_t D, int64_t N)
     L.off_chunk_desc = take(n1 * 16);
     L.off_chunk_bags = take((n / 2 + 1) * DQRM_SEG_CHUNK * sizeof(int));
     L.off_single_desc = take(n1 * 16);
-    // (the large-table path exists only for batches that can hold a large table)
-    const size_t big = N > dqrm::kDdCap ? n : 0;
-    L.off_run_key = take(big * sizeof(int));
-    L.off_run_pos = take(big * sizeof(int));
-    L.off_merged_key = take(big * sizeof(int));
-    L.off_merged_pos = take(big * sizeof(int));
-    L.off_head_of_seg = take(big ? (big + t + 1) * sizeof(int) : 0);
     L.off_seg_count = take(slots * sizeof(int));
     L.off_partial_full = take(slots * (size_t)D * sizeof(float));
     L.off_partial_last = take(slots * (size_t)D * sizeof(float));
@@ -132,23 +125,17 @@ dqrm::BwdWs ws_views(void *workspace, const WsLayout &L)
 {
     char *b = static_cast<char *>(workspace);
     dqrm::BwdWs w;
-    w.table_base = reinterpret_cast<int *>(b + L.off_table_base);
-    w.table_nuniq = reinterpret_cast<int *>(b + L.off_table_nuniq);
-    w.table_nchunk = reinterpret_cast<int *>(b + L.off_table_nchunk);
-    w.table_nsingle = reinterpret_cast<int *>(b + L.off_table_nsingle);
+    w.part_info = reinterpret_cast<int4 *>(b + L.off_part_info);
     w.totals = reinterpret_cast<int *>(b + L.off_totals);
-    w.bag_of_pos = reinterpret_cast<int *>(b + L.off_bag_of_pos);
+    w.part_key = reinterpret_cast<unsigned *>(b + L.off_part_key);
+    w.part_pos = reinterpret_cast<unsigned short *>(b + L.off_part_pos);
+    w.part_start = reinterpret_cast<unsigned short *>(b + L.off_part_start);
     w.sorted_bag = reinterpret_cast<int *>(b + L.off_sorted_bag);
     w.chunk_local = reinterpret_cast<int4 *>(b + L.off_chunk_local);
     w.single_local = reinterpret_cast<int4 *>(b + L.off_single_local);
     w.chunk_desc = reinterpret_cast<int4 *>(b + L.off_chunk_desc);
     w.chunk_bags = reinterpret_cast<int *>(b + L.off_chunk_bags);
     w.single_desc = reinterpret_cast<int4 *>(b + L.off_single_desc);
-    w.run_key = reinterpret_cast<unsigned *>(b + L.off_run_key);
-    w.run_pos = reinterpret_cast<int *>(b + L.off_run_pos);
-    w.merged_key = reinterpret_cast<unsigned *>(b + L.off_merged_key);
-    w.merged_pos = reinterpret_cast<int *>(b + L.off_merged_pos);
-    w.head_of_seg = reinterpret_cast<int *>(b + L.off_head_of_seg);
     w.seg_count = reinterpret_cast<int *>(b + L.off_seg_count);
     w.partial_full = reinterpret_cast<float *>(b + L.off_partial_full);
     w.partial_last = reinterpret_cast<float *>(b + L.off_partial_last);
@@ -389,7 +376,6 @@ int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t nu
     }
     dqrm::DedupeArgs da;
     std::memset(&da, 0, sizeof(da));
-    int64_t largest = 0; // no table of any batch has more lookups than this
     for (int i = 0; i < num_batches; ++i) {
         const dqrm_dedupe_batch_t &b = batches[i];
         dqrm::DedupeBatch &o = da.b[i];
@@ -398,7 +384,6 @@ int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t nu
         o.N = b.num_indices;
         o.limit = b.max_table_lookups > 0 ? std::min<int32_t>(b.max_table_lookups, DQRM_MAX_TABLE_LOOKUPS)
                                           : DQRM_MAX_TABLE_LOOKUPS;
-        largest = std::max<int64_t>(largest, std::min<int64_t>(b.num_indices, o.limit));
         o.ws = ws_views(b.workspace, ws_layout(T, D, b.num_indices));
         o.sorted_pos = b.sorted_pos;
         o.tuo = b.table_uniq_offsets;
@@ -410,14 +395,49 @@ int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t nu
     da.T = T;
     da.B = batch;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // a table of more than kDdCap lookups is sorted in tiles (grid z), which dedupe_large_kernel merges
-    const int tiles = (int)std::max<int64_t>(1, (largest + dqrm::kDdCap - 1) / dqrm::kDdCap);
-    hipLaunchKernelGGL(dqrm::dedupe_kernel, dim3(T, num_batches, tiles), dim3(dqrm::kDdThreads), 0, st, da);
-    if (tiles > 1) {
-        hipLaunchKernelGGL(dqrm::dedupe_merge_kernel, dim3(T, num_batches, tiles), dim3(dqrm::kDdThreads), 0, st, da);
-        hipLaunchKernelGGL(dqrm::dedupe_large_kernel, dim3(T, num_batches), dim3(dqrm::kDdThreads), 0, st, da);
+    // How many ranges a table's rows are cut into, and the workgroup: by the lookups of an average table (a table of more
+    // is sorted all the same, if need be piece by piece).  Measured (us, with dedupe_finish_kernel):
+    //   26 tables x  2048 lookups:  8 ranges of 512 threads 15.7 (1 range 19.1; one 1024-thread workgroup per table, the
+    //                               sort without ranges that this replaces: 25)
+    //   26 tables x  8192:          8 ranges of 1024 threads 22 (1: 41, 16: 30; without ranges 42)
+    //   208 tables x 8192 (eight batches): 1 range 55 (2: 64, 8: 100; without ranges 61)
+    //   208 tables x 1024:          1 range 18 (8: 63)
+    // so: a workgroup per CU or a little less, at least 256 lookups to a range, and no more than fit the LDS.
+    const int64_t avg = (max_n + T - 1) / T, wgs = (int64_t)T * num_batches;
+    const int64_t most_parts = dqrm::kMaxParts / T;
+    int64_t least_n = max_n;
+    for (int i = 0; i < num_batches; ++i) least_n = std::min<int64_t>(least_n, da.b[i].N);
+    // From two tiles per table on every range's workgroup reading the whole table costs more than sorting the tiles by
+    // range first: 26 x 65536 lookups 132 us, against 215 with 8 ranges that each read everything.
+    const bool partition = avg > 2 * dqrm::kDdTile && least_n > dqrm::kDdTile && most_parts >= 8;
+    int64_t parts = partition ? 32 : std::max<int64_t>(std::min<int64_t>({num_cus() / wgs, avg / 256, 16}), (avg - 1) / 8192 * 2);
+    parts = std::max<int64_t>(1, std::min(parts, most_parts));
+    da.parts = (int)parts;
+    da.bags_per_part = (int)((batch + parts - 1) / parts);
+    da.by_parts = dqrm::FastDiv::make((unsigned)parts);
+    da.even = dqrm::FastDiv::make((unsigned)std::max<int64_t>(1, max_n / ((int64_t)T * batch)));
+    // The segment sums of bags of several lookups are faster over a list ordered by chunk length (26 tables x 65536 lookups:
+    // 116 us, in sorted order 157; 13 x 10500: 21.6, 23.2), those of bags of one over one in sorted order (26 x 8192: 25.4, by
+    // length 27.4).
+    da.by_length = max_n >= (int64_t)T * batch * 3 / 2;
+    const dim3 grid(T, num_batches, (unsigned)parts);
+    if (partition) {
+        int64_t most = 0; // lookups of any table
+        for (int i = 0; i < num_batches; ++i) most = std::max<int64_t>(most, std::min<int64_t>(da.b[i].N, da.b[i].limit));
+        hipLaunchKernelGGL(dqrm::dedupe_partition_kernel, dim3(T, num_batches, (unsigned)((most + dqrm::kDdTile - 1) / dqrm::kDdTile)),
+                           dim3(dqrm::kDdPartThreads), 0, st, da);
+        hipLaunchKernelGGL((dqrm::dedupe_kernel<1024, 8192, true>), grid, dim3(1024), 0, st, da);
+    } else if (avg <= 512) {
+        hipLaunchKernelGGL((dqrm::dedupe_kernel<256, 2048, false>), grid, dim3(256), 0, st, da);
+    } else if (avg <= 4096 && parts > 1) {
+        hipLaunchKernelGGL((dqrm::dedupe_kernel<512, 4096, false>), grid, dim3(512), 0, st, da);
+    } else {
+        hipLaunchKernelGGL((dqrm::dedupe_kernel<1024, 8192, false>), grid, dim3(1024), 0, st, da);
     }
-    hipLaunchKernelGGL(dqrm::dedupe_finish_kernel, dim3(grid_for(max_n, dqrm::kSegThreads, 2), num_batches),
+    // (2 workgroups per CU for one batch, 8 for eight: 256 per batch then; with 512 each the scans in front of the work take
+    // 3 us longer)
+    const int finish_blocks = std::min(grid_for(max_n, dqrm::kSegThreads, 2), std::max(1, num_cus() * 8 / num_batches));
+    hipLaunchKernelGGL(dqrm::dedupe_finish_kernel, dim3(finish_blocks, num_batches),
                        dim3(dqrm::kSegThreads), 0, st, da);
     DQRM_HIP_CHECK(hipGetLastError());
     return DQRM_OK;

@@ -1,837 +1,22 @@
-// Backward: dedupe (sort by table,row,position) -> segment-sum = the sparse
-// "specified sparsity" gradient of Sec. 4.3 / the gradient-quantisation appendix.
+// Segment sums: the "specified sparsity" gradient of Sec. 4.3 / the gradient-quantisation appendix, from the work lists
+// that dqrm_dedupe leaves in the workspace (dqrm_dedupe.hpp).
 //
-// Kernel 1 (dedupe_kernel): one 1024-thread workgroup per table sorts the
-//   table's lookups in LDS with a stable 8-bit LSD radix sort (keys stay in
-//   registers between passes; ranks come from per-wave digit counters and a
-//   wave-wide match of equal digits), marks segment heads and chunk heads,
-//   and writes table-local segment / chunk lists plus the table's counts.
-//   A table of more than kDdCap lookups is sorted in tiles by several workgroups;
-//   dedupe_merge_kernel merges the sorted tiles and dedupe_large_kernel builds the
-//   same lists from the merged order.
-// Kernel 2 (dedupe_finish_kernel): turns the per-table counts into offsets (T is
-//   small, every workgroup repeats the scan), writes the index-only outputs
-//   (unique rows, segment offsets, table offsets, count) and one dense list of
-//   16-byte chunk descriptors over all tables.
-// Kernels 1-2 need only the batch's indices; they form dqrm_dedupe.
-// Kernel 3 (segment_sum_kernel): one lane group per chunk (<= DQRM_SEG_CHUNK
-//   consecutive contributions of one segment) adds its gradient rows left to
-//   right.  A segment of one chunk is final.  The chunks of a longer segment park
-//   their sums and count themselves in on the segment's counter; the wave of the
-//   chunk that arrives last adds the segment's chunk sums in chunk order.  Which
-//   wave that is depends on scheduling; what it computes does not.
-// Kernel 4 (absmax_finalize_kernel): folds the per-table maxima.
-// segment_sum_multi_kernel / absmax_finalize_multi_kernel: kernels 3 and 4 for several batches in one launch.
+// segment_sum_kernel: one lane group per chunk (<= DQRM_SEG_CHUNK consecutive contributions of one segment) adds its
+//   gradient rows left to right.  A segment of one chunk is final.  The chunks of a longer segment park their sums and
+//   count themselves in on the segment's counter; the wave of the chunk that arrives last adds the segment's chunk sums
+//   in chunk order.  Which wave that is depends on scheduling; what it computes does not.
+// absmax_finalize_kernel: folds the per-table maxima.
+// segment_sum_multi_kernel / absmax_finalize_multi_kernel: the same for several batches in one launch.
 #pragma once
 
+#include "dqrm_dedupe.hpp"
 #include "dqrm_device.hpp"
 
 namespace dqrm {
 
-constexpr int kDdThreads = 1024;
-constexpr int kDdWaves = kDdThreads / kWave;                      // 16
-constexpr int kDdCap = 16384;                     // lookups one workgroup sorts in LDS
-constexpr int kDdMaxRounds = kDdCap / kDdThreads; // 16 items per thread at most
-static_assert(DQRM_MAX_TABLE_LOOKUPS % kDdCap == 0 && DQRM_MAX_TABLE_LOOKUPS / DQRM_SEG_CHUNK < 4096,
-              "tiles of the large-table path; the chunk descriptor holds 12 bits of chunk count");
-constexpr int kSegThreads = 256;   // dedupe_finish_kernel
 constexpr int kSumThreads = 256;   // segment_sum_kernel
 constexpr int kSegBatch = 16;      // gradient rows requested before the first is added
 constexpr int kSumBlocksPerCu = 4; // grid of segment_sum_kernel, in workgroups per CU (128 registers per lane)
-
-// Views into the caller's workspace (all device pointers).
-struct BwdWs {
-    int *table_base;          // [T]   first lookup position of the table
-    int *table_nuniq;         // [T]
-    int *table_nchunk;        // [T]   chunks other than singles
-    int *table_nsingle;       // [T]   rows looked up exactly once
-    int *bag_of_pos;          // [N]   bag (within its table) of every lookup position
-    int *sorted_bag;          // [N]   bag of every sorted lookup
-    int4 *chunk_local;        // [N]   table-local chunk lists (table t's start at its first lookup position)
-    int4 *single_local;       // [N]   table-local lists of singles: {sorted position, bag, segment, row}
-    int4 *chunk_desc;         // [N]   dense chunk list over all tables, as the summing kernels read it
-    int *chunk_bags;          // [N/2 + 1][32] bags of chunk c's lookups, so that they can be read before its descriptor
-    int4 *single_desc;        // [N]   dense list of singles: {bag, global segment, table, -}
-    int *totals;              // [3]   chunks, segments, singles
-    // tables with more than kDdCap lookups (present only if N > kDdCap): the sorted tiles, then, in the same two
-    // arrays, segment index and segment start of every merged position; the merged order; the segments' heads
-    unsigned *run_key;        // [N]   / int seg_idx[N]
-    int *run_pos;             // [N]   / int seg_start[N]
-    unsigned *merged_key;     // [N]
-    int *merged_pos;          // [N]   position inside the table of every merged item
-    int *head_of_seg;         // [N + T + 1] sorted index of each segment's head; table t's list starts at (first lookup position + t)
-    int *seg_count;           // [N/32 + 2] chunks of a segment of more than one chunk that have parked their sum, filed
-                              //       under (sorted position of the segment's head / 32); zero between uses
-    float *partial_full;      // [(N/32 + 2) * D] sum of a full chunk of a segment of more than one chunk
-    float *partial_last;      // [(N/32 + 2) * D] sum of the last chunk of such a segment
-    float *absmax_slots;      // [T][kAbsmaxSlots] running maxima, one 128-byte line per entry
-};
-
-// A chunk = up to DQRM_SEG_CHUNK consecutive sorted lookups of one segment.  Its
-// descriptor is one 16-byte record, so that the summing kernels need a single
-// load to know their work:
-//   x  global sorted position of the chunk's first lookup
-//   y  len (bits 0..7) | index of the chunk inside its segment (bits 8..19) |
-//      chunks in the segment (bits 20..31)
-//   z  table-local index of the segment
-//   w  table-local row of the segment
-__device__ __forceinline__ int4 make_chunk_desc(int gstart, int len, int kchunk, int nchunks, int seg, unsigned row)
-{
-    return make_int4(gstart, len | (kchunk << 8) | (nchunks << 20), seg, (int)row);
-}
-__device__ __forceinline__ int desc_len(const int4 &d) { return d.y & 0xFF; }
-__device__ __forceinline__ int desc_kchunk(const int4 &d) { return (d.y >> 8) & 0xFFF; }
-__device__ __forceinline__ int desc_nchunks(const int4 &d) { return (int)((unsigned)d.y >> 20); }
-
-// One launch can dedupe several batches (blockIdx.y picks the batch): the work
-// depends only on the indices, and a table's sort occupies a single CU, so the
-// batches of the next few steps fill the chip where one batch would use T CUs.
-struct DedupeBatch {
-    const int64_t *indices;
-    const int64_t *offsets;
-    int64_t N;
-    int limit; // lookups a table may have: DQRM_MAX_TABLE_LOOKUPS or the caller's smaller bound
-    BwdWs ws;
-    int32_t *sorted_pos;
-    int32_t *tuo;
-    int32_t *num_unique;
-    int64_t *uniq_rows;
-    int32_t *seg_offsets;
-};
-struct DedupeArgs {
-    DedupeBatch b[DQRM_MAX_DEDUPE_BATCHES];
-    const int64_t *row_offsets;
-    int T, B;
-};
-
-__global__ __launch_bounds__(kDdThreads) void dedupe_kernel(DedupeArgs args)
-{
-    const DedupeBatch &bt = args.b[blockIdx.y];
-    const int64_t *__restrict__ indices = bt.indices;
-    const int64_t *__restrict__ offsets = bt.offsets;
-    const int64_t *__restrict__ row_offsets = args.row_offsets;
-    const int T = args.T, B = args.B;
-    const int64_t N = bt.N;
-    const BwdWs ws = bt.ws;
-    int32_t *__restrict__ sorted_pos = bt.sorted_pos;
-    (void)T;
-
-    __shared__ unsigned skey[kDdCap];        // 64 KB
-    __shared__ unsigned short spos[kDdCap];  // 32 KB
-    __shared__ unsigned cnt[kDdWaves * 256]; // 16 KB, cnt[wave * 256 + digit]
-    __shared__ unsigned short shead[kDdCap + 2]; // 32 KB, sorted index of each segment's head (+ end sentinel)
-    __shared__ int s_w[kDdWaves];
-    __shared__ int s_w2[kDdWaves];
-
-    const int t = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1);
-    const int wave = tid / kWave;
-    const unsigned long long lt_mask = (1ull << lane) - 1ull;
-
-    const long long rows_ll = row_offsets[t + 1] - row_offsets[t];
-    const unsigned rows_t = (unsigned)rows_ll; // host checked: 0 <= rows <= DQRM_MAX_TABLE_ROWS
-
-    // ---- table extent in the lookup list --------------------------------
-    long long lo = offsets[(long long)t * B], hi = offsets[(long long)(t + 1) * B];
-    bool disabled = false; // a table with unusable extents contributes nothing
-    if (lo < 0 || hi > N || lo > hi) {
-        if (tid == 0 && blockIdx.z == 0) report(DQRM_ERR_BAD_OFFSETS, t, lo);
-        lo = lo < 0 ? 0 : (lo > N ? N : lo);
-        disabled = true;
-    } else if (hi - lo > bt.limit) {
-        if (tid == 0 && blockIdx.z == 0) report(DQRM_ERR_CAPACITY, t, hi - lo);
-        disabled = true;
-    }
-    if (disabled) hi = lo;
-    const int base = (int)lo;
-    // A table of up to kDdCap lookups is this workgroup's (blockIdx.z = 0) from start to end.  A larger one is cut
-    // into tiles of kDdCap consecutive lookups: workgroup z sorts tile z and leaves the sorted run in the workspace;
-    // dedupe_merge_kernel merges the runs and dedupe_large_kernel does the rest.
-    const bool large = hi - lo > kDdCap;
-    const int tile = (int)blockIdx.z;
-    if (!large && tile > 0) return;
-    const long long first = lo + (large ? (long long)tile * kDdCap : 0ll); // my first lookup
-    if (large && first >= hi) return;
-    const int n = (int)(large ? (hi - first < kDdCap ? hi - first : (long long)kDdCap) : hi - lo);
-    const bool does_bags = !disabled && (!large || tile == 0);
-
-    // ---- phase 0: bag of every lookup position ---------------------------
-    // The table's keys are requested first (wave-striped: item i = wave * per_wave + r * 64 + lane), so that they
-    // travel while the bags are looked at; items past the end re-read the last key and are dropped in phase 1.
-    const int rounds = (n + kDdThreads - 1) / kDdThreads; // 0..16, same for the whole block
-    const int per_wave = rounds * kWave;
-    long long raw[kDdMaxRounds];
-#pragma unroll
-    for (int r = 0; r < kDdMaxRounds; ++r) {
-        raw[r] = 0;
-        if (r < rounds) raw[r] = indices[first + min(wave * per_wave + r * kWave + lane, n - 1)]; // (n >= 1 here)
-    }
-    // When every bag of the table holds exactly one lookup (the usual DLRM
-    // batch) the bag of position p is p itself and nothing needs to be stored.
-    constexpr int kBagBatch = 8;
-    bool one_each = !disabled && !large && (n == B);
-    if (does_bags) {
-        for (int b0 = 0; b0 < B; b0 += kDdThreads * kBagBatch) {
-            long long s[kBagBatch], e[kBagBatch];
-#pragma unroll
-            for (int q = 0; q < kBagBatch; ++q) {
-                const int b = b0 + q * kDdThreads + tid;
-                s[q] = lo + b;
-                e[q] = s[q] + 1;
-                if (b < B) {
-                    s[q] = offsets[(long long)t * B + b];
-                    e[q] = offsets[(long long)t * B + b + 1];
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < kBagBatch; ++q) {
-                const int b = b0 + q * kDdThreads + tid;
-                if (b < B && (s[q] < lo || e[q] > hi || s[q] > e[q]))
-                    report(DQRM_ERR_BAD_OFFSETS, t, (long long)t * B + b);
-                if (s[q] != lo + b || e[q] != s[q] + 1) one_each = false;
-            }
-        }
-    }
-    one_each = __syncthreads_and(one_each ? 1 : 0) != 0;
-    if (does_bags && !one_each) {
-        for (int b = tid; b < B; b += kDdThreads) {
-            long long s = offsets[(long long)t * B + b], e = offsets[(long long)t * B + b + 1];
-            s = s < lo ? lo : (s > hi ? hi : s);
-            e = e < s ? s : (e > hi ? hi : e);
-            for (long long p = s; p < e; ++p) ws.bag_of_pos[p] = b;
-        }
-    }
-
-    // ---- phase 1: keys checked and narrowed ------------------------------
-    unsigned key[kDdMaxRounds];
-    unsigned pos[kDdMaxRounds];
-#pragma unroll
-    for (int r = 0; r < kDdMaxRounds; ++r) {
-        key[r] = rows_t; // sentinel: sorts after every valid row
-        pos[r] = 0;
-        if (r < rounds) {
-            const int i = wave * per_wave + r * kWave + lane;
-            pos[r] = (unsigned)i;
-            if (i < n) {
-                const long long v = raw[r];
-                if (v < 0 || v >= rows_ll)
-                    report(DQRM_ERR_INDEX_OUT_OF_RANGE, t, v);
-                else
-                    key[r] = (unsigned)v;
-            }
-        }
-    }
-    // ---- phase 2: stable LSD radix sort, 8 bits per pass -----------------
-    const int nbits = 32 - __clz(rows_t | 1u); // bit width of the sentinel (>= 1)
-    const int passes = (nbits + 7) / 8;
-    for (int p = 0; p < passes; ++p) {
-        const int shift = 8 * p;
-        for (int k = tid; k < kDdWaves * 256; k += kDdThreads) cnt[k] = 0;
-        __syncthreads();
-        // (the rank inside the wave's digit group rides in the upper half of pos[]:
-        //  both are below 16384)
-#pragma unroll
-        for (int r = 0; r < kDdMaxRounds; ++r) {
-            if (r < rounds) {
-                const unsigned d = (key[r] >> shift) & 255u;
-                const unsigned long long peers = match_any8(d);
-                const unsigned prev = cnt[wave * 256 + d];
-                pos[r] |= (prev + (unsigned)__popcll(peers & lt_mask)) << 16;
-                if ((peers & lt_mask) == 0ull) cnt[wave * 256 + d] = prev + (unsigned)__popcll(peers);
-            }
-        }
-        __syncthreads();
-        // exclusive scan of the counters in (digit, wave) order: thread k owns
-        // digit k/4, waves 4*(k%4) .. 4*(k%4)+3
-        {
-            const int d = tid >> 2, w0 = (tid & 3) * 4;
-            unsigned c0 = cnt[(w0 + 0) * 256 + d], c1 = cnt[(w0 + 1) * 256 + d], c2 = cnt[(w0 + 2) * 256 + d],
-                     c3 = cnt[(w0 + 3) * 256 + d];
-            int total;
-            int ex = block_excl_scan_add<kDdWaves>((int)(c0 + c1 + c2 + c3), lane, wave, s_w, &total);
-            cnt[(w0 + 0) * 256 + d] = (unsigned)ex;
-            cnt[(w0 + 1) * 256 + d] = (unsigned)ex + c0;
-            cnt[(w0 + 2) * 256 + d] = (unsigned)ex + c0 + c1;
-            cnt[(w0 + 3) * 256 + d] = (unsigned)ex + c0 + c1 + c2;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < kDdMaxRounds; ++r) {
-            if (r < rounds) {
-                const unsigned d = (key[r] >> shift) & 255u;
-                const unsigned rank = cnt[wave * 256 + d] + (pos[r] >> 16);
-                skey[rank] = key[r];
-                spos[rank] = (unsigned short)pos[r];
-            }
-        }
-        __syncthreads();
-        if (p + 1 < passes) {
-#pragma unroll
-            for (int r = 0; r < kDdMaxRounds; ++r) {
-                if (r < rounds) {
-                    const int i = wave * per_wave + r * kWave + lane;
-                    key[r] = skey[i];
-                    pos[r] = spos[i];
-                }
-            }
-        }
-        // the next pass clears cnt and synchronises before anything is overwritten
-    }
-    if (large) { // the sorted run of this tile; positions counted from the table's first lookup
-        for (int i = tid; i < n; i += kDdThreads) {
-            ws.run_key[first + i] = skey[i];
-            ws.run_pos[first + i] = tile * kDdCap + (int)spos[i];
-        }
-        return;
-    }
-
-    // ---- phase 3: segment heads and chunk heads ---------------------------
-    // (skey / spos now hold the table's rounds*1024 items in sorted order;
-    //  entries that are padding or had a bad index carry the sentinel key.)
-    // Per item, packed into one word to keep the register count down:
-    //   bits 0..14  segment index + 1      bits 15..29  sorted index of the segment's head + 1
-    //   bit  30     valid                  bit  31      head of its segment
-    unsigned info[kDdMaxRounds];
-    auto info_seg = [](unsigned w) { return (int)(w & 0x7FFFu) - 1; };
-    auto info_start = [](unsigned w) { return (int)((w >> 15) & 0x7FFFu) - 1; };
-    auto info_valid = [](unsigned w) { return (w >> 30) & 1u; };
-    auto info_head = [](unsigned w) { return w >> 31; };
-    int carry_heads = 0, carry_start = -1, carry_valid = 0;
-#pragma unroll
-    for (int r = 0; r < kDdMaxRounds; ++r) {
-        info[r] = 0;
-    }
-#pragma unroll
-    for (int r = 0; r < kDdMaxRounds; ++r) {
-        if (r < rounds) {
-            const int i = wave * per_wave + r * kWave + lane;
-            const unsigned k = skey[i];
-            const bool valid = k < rows_t;
-            const bool head = valid && (i == 0 || skey[i - 1] != k);
-            const int h = wave_incl_scan_add(head ? 1 : 0, lane) + carry_heads; // heads up to here, this wave
-            const int st = max(wave_incl_scan_max(head ? i : -1, lane), carry_start);
-            carry_heads = wave_last(h);
-            carry_start = wave_last(st);
-            carry_valid += __popcll(__ballot(valid));
-            info[r] = (unsigned)h | ((unsigned)(st + 1) << 15) | (valid ? 1u << 30 : 0u) | (head ? 1u << 31 : 0u);
-        }
-    }
-    // across waves: exclusive head count, running maximum of head positions
-    __syncthreads();
-    if (lane == 0) {
-        s_w[wave] = carry_heads;
-        s_w2[wave] = carry_start;
-    }
-    __syncthreads();
-    int heads_before = 0, start_before = -1, n_uniq = 0;
-#pragma unroll
-    for (int w = 0; w < kDdWaves; ++w) {
-        if (w < wave) {
-            heads_before += s_w[w];
-            start_before = max(start_before, s_w2[w]);
-        }
-        n_uniq += s_w[w];
-    }
-    __syncthreads();
-    if (lane == 0) s_w[wave] = carry_valid;
-    __syncthreads();
-    int n_valid = 0;
-#pragma unroll
-    for (int w = 0; w < kDdWaves; ++w) n_valid += s_w[w];
-
-    // segment heads leave their sorted index in LDS, so that every item can find
-    // the end of its segment
-#pragma unroll
-    for (int r = 0; r < kDdMaxRounds; ++r) {
-        if (r < rounds) {
-            const int i = wave * per_wave + r * kWave + lane;
-            const int seg = (int)(info[r] & 0x7FFFu) + heads_before - 1;     // -1 .. 16383
-            const int start = max(info_start(info[r]), start_before);        // -1 .. 16383
-            info[r] = (unsigned)(seg + 1) | ((unsigned)(start + 1) << 15) | (info[r] & 0xC0000000u);
-            if (info_head(info[r])) shead[seg] = (unsigned short)i;
-        }
-    }
-    if (tid == 0) shead[n_uniq] = (unsigned short)n_valid; // end sentinel (n_valid <= 16384 fits)
-    __syncthreads();
-
-    // chunk heads: every DQRM_SEG_CHUNK-th item of a segment, counted from its
-    // head.  Two classes, listed separately: "single" = a row looked up exactly
-    // once (the common case, no summation needed), and all other chunks.  One
-    // scan counts both (bits 0..14: singles, bits 16..30: the others; each <= 16384);
-    // bits 15 / 31 of the stored word then mark what the item itself is.
-    unsigned chunk_of[kDdMaxRounds];
-    int carry_chunks = 0;
-#pragma unroll
-    for (int r = 0; r < kDdMaxRounds; ++r) {
-        chunk_of[r] = 0;
-        if (r < rounds) {
-            const int i = wave * per_wave + r * kWave + lane;
-            const bool chead = info_valid(info[r]) && (((i - info_start(info[r])) % DQRM_SEG_CHUNK) == 0);
-            const bool single = chead && info_head(info[r]) && ((int)shead[info_seg(info[r]) + 1] == i + 1);
-            const int c = wave_incl_scan_add(chead ? (single ? 1 : 0x10000) : 0, lane) + carry_chunks;
-            carry_chunks = wave_last(c);
-            chunk_of[r] = (unsigned)c | (chead ? (single ? 1u << 15 : 1u << 31) : 0u);
-        }
-    }
-    __syncthreads();
-    if (lane == 0) s_w[wave] = carry_chunks;
-    __syncthreads();
-    int singles_before = 0, chunks_before = 0, n_single = 0, n_chunk = 0;
-#pragma unroll
-    for (int w = 0; w < kDdWaves; ++w) {
-        const int x = s_w[w];
-        if (w < wave) {
-            singles_before += x & 0x7FFF;
-            chunks_before += x >> 16;
-        }
-        n_single += x & 0x7FFF;
-        n_chunk += x >> 16;
-    }
-
-    // ---- phase 4: write the table-local lists -------------------------------
-    if (!one_each) {
-        // bag of every sorted lookup: gathered first, all at once, so that the loads overlap
-#pragma unroll
-        for (int r = 0; r < kDdMaxRounds; ++r) {
-            if (r < rounds) {
-                const int i = wave * per_wave + r * kWave + lane;
-                if (info_valid(info[r])) {
-                    int b = ws.bag_of_pos[base + spos[i]];
-                    b = b < 0 ? 0 : (b >= B ? B - 1 : b);
-                    ws.sorted_bag[base + i] = b;
-                }
-            }
-        }
-        __syncthreads(); // the singles below read their own entry back
-    }
-#pragma unroll
-    for (int r = 0; r < kDdMaxRounds; ++r) {
-        if (r < rounds) {
-            const int i = wave * per_wave + r * kWave + lane;
-            const int p = spos[i];
-            if (i < n) sorted_pos[base + i] = base + p;
-            if (one_each && info_valid(info[r])) ws.sorted_bag[base + i] = p < B ? p : B - 1;
-            const int seg = info_seg(info[r]);
-            if (chunk_of[r] & (1u << 31)) { // head of a chunk that is not a single
-                const int c = (int)((chunk_of[r] >> 16) & 0x7FFFu) + chunks_before - 1;
-                const int s0 = info_start(info[r]), s1 = shead[seg + 1];
-                const int len = min(DQRM_SEG_CHUNK, s1 - i);
-                const int nchunks = (s1 - s0 + DQRM_SEG_CHUNK - 1) / DQRM_SEG_CHUNK;
-                ws.chunk_local[base + c] =
-                    make_chunk_desc(base + i, len, (i - s0) / DQRM_SEG_CHUNK, nchunks, seg, skey[i]);
-                // the arrival counter of a segment of more than one chunk starts at zero
-                if (i == s0 && nchunks > 1) ws.seg_count[(base + i) / DQRM_SEG_CHUNK] = 0;
-            }
-            if (chunk_of[r] & (1u << 15)) { // a row looked up exactly once
-                const int c = (int)(chunk_of[r] & 0x7FFFu) + singles_before - 1;
-                const int b = one_each ? (p < B ? p : B - 1) : ws.sorted_bag[base + i];
-                ws.single_local[base + c] = make_int4(base + i, b, seg, (int)skey[i]);
-            }
-        }
-    }
-    if (tid == 0) {
-        ws.table_base[t] = base;
-        ws.table_nuniq[t] = n_uniq;
-        ws.table_nchunk[t] = n_chunk;
-        ws.table_nsingle[t] = n_single;
-    }
-    if (tid < kAbsmaxSlots) *absmax_slot(ws.absmax_slots, t, tid) = 0.0f;
-}
-
-// Step 1 for a table of more than kDdCap lookups, one workgroup per sorted tile (run): every item of the run finds
-// its place in the table's sorted order on its own -- its index in its own run plus, per other run, the number of
-// that run's keys below it (equal keys of earlier runs count as below, which keeps equal keys in lookup order).
-// Each other run in turn is staged in LDS and searched by the run's items, kept in registers, four searches in step
-// (a fixed number of halvings, no branch).
-__global__ __launch_bounds__(kDdThreads) void dedupe_merge_kernel(DedupeArgs args)
-{
-    const DedupeBatch &bt = args.b[blockIdx.y];
-    const int B = args.B;
-    const int64_t N = bt.N;
-    const BwdWs ws = bt.ws;
-    __shared__ unsigned s_run[kDdCap]; // 64 KB: the run that is being searched
-    constexpr int kItems = kDdCap / kDdThreads; // 16 per thread
-    const int t = blockIdx.x, r = blockIdx.z, tid = threadIdx.x;
-    const long long lo = bt.offsets[(long long)t * B], hi = bt.offsets[(long long)(t + 1) * B];
-    if (lo < 0 || hi > N || lo > hi || hi - lo > bt.limit || hi - lo <= kDdCap) return;
-    const int n = (int)(hi - lo), base = (int)lo;
-    const int runs = (n + kDdCap - 1) / kDdCap;
-    if (r >= runs) return;
-    const int len = min(kDdCap, n - r * kDdCap); // my run
-    unsigned key[kItems];
-    int rank[kItems];
-#pragma unroll
-    for (int q = 0; q < kItems; ++q) {
-        const int j = min(q * kDdThreads + tid, len - 1);
-        key[q] = ws.run_key[base + r * kDdCap + j];
-        rank[q] = j;
-    }
-    for (int r2 = 0; r2 < runs; ++r2) {
-        if (r2 == r) continue; // (block-uniform)
-        const int len2 = min(kDdCap, n - r2 * kDdCap);
-        const bool ties_below = r2 < r;
-        __syncthreads(); // (the searches of the run staged before are over)
-        for (int i = tid; i < kDdCap; i += kDdThreads) s_run[i] = i < len2 ? ws.run_key[base + r2 * kDdCap + i] : 0xFFFFFFFFu;
-        __syncthreads();
-#pragma unroll
-        for (int q0 = 0; q0 < kItems; q0 += 4) {
-            int below[4] = {0, 0, 0, 0};
-#pragma unroll 1
-            for (int step = kDdCap; step >= 1; step >>= 1) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int idx = below[q] + step; // are the first idx keys of the run all below mine?
-                    const unsigned k2 = s_run[min(idx, kDdCap) - 1];
-                    const bool yes = idx <= len2 && (ties_below ? k2 <= key[q0 + q] : k2 < key[q0 + q]);
-                    below[q] = yes ? idx : below[q];
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) rank[q0 + q] += below[q];
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < kItems; ++q) {
-        const int j = q * kDdThreads + tid;
-        if (j < len) {
-            ws.merged_key[base + rank[q]] = key[q];
-            ws.merged_pos[base + rank[q]] = ws.run_pos[base + r * kDdCap + j];
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Tables with more than kDdCap lookups: dedupe_kernel has sorted their tiles of kDdCap consecutive lookups and
-// dedupe_merge_kernel (above) has merged the runs; one workgroup per (table, batch) now
-//  1. walks the merged order in slabs of one item per thread, carrying the counts from slab to slab: segment
-//     heads, segment index and start of every item, the list of the heads;
-//  2. walks it again for the chunk heads and singles (a segment's end is the next segment's head, known now) and
-//     writes the same table-local lists and counts as dedupe_kernel does for a small table.
-// Everything between the steps goes through global memory of the workspace, read back by the same workgroup
-// after a barrier.  Slower per lookup than the in-LDS path; it exists so that no table size up to
-// DQRM_MAX_TABLE_LOOKUPS is refused.
-__global__ __launch_bounds__(kDdThreads) void dedupe_large_kernel(DedupeArgs args)
-{
-    const DedupeBatch &bt = args.b[blockIdx.y];
-    const int64_t *__restrict__ offsets = bt.offsets;
-    const int B = args.B;
-    const int64_t N = bt.N;
-    const BwdWs ws = bt.ws;
-    __shared__ int s_w[kDdWaves];
-    __shared__ int s_w2[kDdWaves];
-
-    const int t = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const long long rows_ll = args.row_offsets[t + 1] - args.row_offsets[t];
-    const unsigned rows_t = (unsigned)rows_ll;
-    const long long lo = offsets[(long long)t * B], hi = offsets[(long long)(t + 1) * B];
-    // (unusable extents and tables beyond the limit were reported and closed by dedupe_kernel)
-    if (lo < 0 || hi > N || lo > hi || hi - lo > bt.limit || hi - lo <= kDdCap) return;
-    const int n = (int)(hi - lo), base = (int)lo;
-    const int runs = (n + kDdCap - 1) / kDdCap;
-
-    // (the runs are not read again: their arrays now take segment index and start of every item)
-
-    // A slab is kRounds x kDdThreads consecutive items, wave-striped as in dedupe_kernel: wave w owns the slab's items
-    // w * kRounds * 64 ..., item (round r, lane l) = that + r * 64 + l.  A wave carries its counts from round to round by
-    // itself; the waves meet once per slab.
-    // ---- 1. segment heads, index and start of every item
-    int *seg_idx = reinterpret_cast<int *>(ws.run_key) + base, *seg_start = ws.run_pos + base;
-    int *head_of = ws.head_of_seg + base + t;
-    int carry_heads = 0, carry_start = -1, n_valid = 0;
-    {
-        constexpr int kRounds = 8, kSlab = kRounds * kDdThreads, kPerWave = kRounds * kWave;
-        for (int s0 = 0; s0 < n; s0 += kSlab) {
-            unsigned k_of[kRounds], prev_of[kRounds];
-#pragma unroll
-            for (int r = 0; r < kRounds; ++r) {
-                const int i = s0 + wave * kPerWave + r * kWave + lane;
-                k_of[r] = i < n ? ws.merged_key[base + i] : rows_t;
-                prev_of[r] = (i > 0 && i < n) ? ws.merged_key[base + i - 1] : 0u;
-            }
-            int h_of[kRounds], st_of[kRounds];
-            int wave_heads = 0, wave_start = -1, wave_valid = 0;
-#pragma unroll
-            for (int r = 0; r < kRounds; ++r) {
-                const int i = s0 + wave * kPerWave + r * kWave + lane;
-                const bool valid = i < n && k_of[r] < rows_t;
-                const bool head = valid && (i == 0 || prev_of[r] != k_of[r]);
-                h_of[r] = wave_incl_scan_add(head ? 1 : 0, lane) + wave_heads; // heads up to here, this wave and slab
-                st_of[r] = max(wave_incl_scan_max(head ? i : -1, lane), wave_start);
-                wave_heads = wave_last(h_of[r]);
-                wave_start = wave_last(st_of[r]);
-                wave_valid += __popcll(__ballot(valid));
-                h_of[r] = head ? h_of[r] : -h_of[r] - 1; // (the sign tells a head; valid or not is read off k_of)
-            }
-            __syncthreads(); // (s_w / s_w2 of the previous slab have been read)
-            if (lane == 0) {
-                s_w[wave] = wave_heads | (wave_valid << 16); // both at most 512
-                s_w2[wave] = wave_start;
-            }
-            __syncthreads();
-            int heads_before = 0, start_before = -1, heads_slab = 0, valid_slab = 0, start_slab = -1;
-#pragma unroll
-            for (int w = 0; w < kDdWaves; ++w) {
-                const int x = s_w[w];
-                if (w < wave) {
-                    heads_before += x & 0xFFFF;
-                    start_before = max(start_before, s_w2[w]);
-                }
-                heads_slab += x & 0xFFFF;
-                valid_slab += x >> 16;
-                start_slab = max(start_slab, s_w2[w]);
-            }
-#pragma unroll
-            for (int r = 0; r < kRounds; ++r) {
-                const int i = s0 + wave * kPerWave + r * kWave + lane;
-                if (i < n) {
-                    const bool valid = k_of[r] < rows_t, head = h_of[r] >= 0;
-                    const int h = head ? h_of[r] : -h_of[r] - 1;
-                    seg_idx[i] = valid ? carry_heads + heads_before + h - 1 : -1;
-                    seg_start[i] = max(max(carry_start, start_before), st_of[r]);
-                    if (head) head_of[carry_heads + heads_before + h - 1] = i;
-                }
-            }
-            carry_heads += heads_slab;
-            carry_start = max(carry_start, start_slab);
-            n_valid += valid_slab;
-        }
-    }
-    const int n_uniq = carry_heads;
-    if (tid == 0) head_of[n_uniq] = n_valid; // end of the last segment
-    __syncthreads();
-
-    // ---- 2. chunk heads and singles, the table-local lists
-    int carry_single = 0, carry_chunk = 0;
-    {
-        constexpr int kRounds = 8, kSlab = kRounds * kDdThreads, kPerWave = kRounds * kWave;
-        for (int s0 = 0; s0 < n; s0 += kSlab) {
-            int seg_of[kRounds], start_of[kRounds], p_of[kRounds], end_of[kRounds], bag_of[kRounds];
-            unsigned key_of[kRounds];
-#pragma unroll
-            for (int r = 0; r < kRounds; ++r) {
-                const int i = min(s0 + wave * kPerWave + r * kWave + lane, n - 1);
-                seg_of[r] = seg_idx[i];
-                start_of[r] = seg_start[i];
-                p_of[r] = ws.merged_pos[base + i];
-                key_of[r] = ws.merged_key[base + i];
-            }
-#pragma unroll
-            for (int r = 0; r < kRounds; ++r) {
-                if (s0 + wave * kPerWave + r * kWave + lane >= n) seg_of[r] = -1;
-                end_of[r] = head_of[max(seg_of[r], 0) + 1]; // (the list's region has that entry even if n_uniq = 0)
-                bag_of[r] = ws.bag_of_pos[base + p_of[r]];
-            }
-            // one scan counts both kinds (bits 0..15: singles, bits 16..31: the other chunk heads; each <= 8192 a slab)
-            int c_of[kRounds];
-            int wave_count = 0;
-#pragma unroll
-            for (int r = 0; r < kRounds; ++r) {
-                const int i = s0 + wave * kPerWave + r * kWave + lane;
-                const bool valid = seg_of[r] >= 0;
-                const bool chead = valid && ((i - start_of[r]) % DQRM_SEG_CHUNK) == 0;
-                const bool single = chead && i == start_of[r] && end_of[r] == i + 1;
-                c_of[r] = wave_incl_scan_add(chead ? (single ? 1 : 0x10000) : 0, lane) + wave_count;
-                wave_count = wave_last(c_of[r]);
-                // what the item itself is rides in p_of's spare bits (a position inside the table is below 2^17)
-                p_of[r] |= chead ? (single ? 1 << 30 : 1 << 29) : 0;
-            }
-            __syncthreads(); // (s_w of the previous slab has been read)
-            if (lane == 0) s_w[wave] = wave_count;
-            __syncthreads();
-            int singles_before = 0, chunks_before = 0, singles_slab = 0, chunks_slab = 0;
-#pragma unroll
-            for (int w = 0; w < kDdWaves; ++w) {
-                const int x = s_w[w];
-                if (w < wave) {
-                    singles_before += x & 0xFFFF;
-                    chunks_before += x >> 16;
-                }
-                singles_slab += x & 0xFFFF;
-                chunks_slab += x >> 16;
-            }
-#pragma unroll
-            for (int r = 0; r < kRounds; ++r) {
-                const int i = s0 + wave * kPerWave + r * kWave + lane;
-                if (i >= n) continue;
-                const int seg = seg_of[r], start = start_of[r], end = end_of[r], p = p_of[r] & 0x1FFFFFFF;
-                const bool is_single = (p_of[r] >> 30) & 1, is_chunk = (p_of[r] >> 29) & 1;
-                bt.sorted_pos[base + i] = base + p;
-                int b = 0;
-                if (seg >= 0) {
-                    b = bag_of[r];
-                    b = b < 0 ? 0 : (b >= B ? B - 1 : b);
-                    ws.sorted_bag[base + i] = b;
-                }
-                if (is_chunk) {
-                    const int c = carry_chunk + chunks_before + (c_of[r] >> 16) - 1;
-                    const int nchunks = (end - start + DQRM_SEG_CHUNK - 1) / DQRM_SEG_CHUNK;
-                    ws.chunk_local[base + c] = make_chunk_desc(base + i, min(DQRM_SEG_CHUNK, end - i),
-                                                               (i - start) / DQRM_SEG_CHUNK, nchunks, seg, key_of[r]);
-                    if (i == start && nchunks > 1) ws.seg_count[(base + i) / DQRM_SEG_CHUNK] = 0;
-                }
-                if (is_single) {
-                    const int c = carry_single + singles_before + (c_of[r] & 0xFFFF) - 1;
-                    ws.single_local[base + c] = make_int4(base + i, b, seg, (int)key_of[r]);
-                }
-            }
-            carry_single += singles_slab;
-            carry_chunk += chunks_slab;
-        }
-    }
-    if (tid == 0) {
-        ws.table_base[t] = base;
-        ws.table_nuniq[t] = n_uniq;
-        ws.table_nchunk[t] = carry_chunk;
-        ws.table_nsingle[t] = carry_single;
-    }
-    if (tid < kAbsmaxSlots) *absmax_slot(ws.absmax_slots, t, tid) = 0.0f;
-}
-
-// ---------------------------------------------------------------------------
-// Kernel 2 of dqrm_dedupe: table-local lists -> one dense, global chunk list and
-// the index-only outputs (unique rows, segment offsets, table offsets, count).
-
-// Turns the per-table counts into offsets in LDS (every block does this; T is
-// small).  s_tuo / s_tco / s_tso receive T+1 entries (segments, chunks, singles),
-// s_base T.
-__device__ __forceinline__ void table_offsets_to_lds(const BwdWs &ws, int T, int *s_tuo, int *s_tco, int *s_tso,
-                                                     int *s_base, int *s_w)
-{
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    if (T <= kWave) {
-        // the usual case: one wave scans the counts, no block-wide scan needed
-        if (wave == 0) {
-            int u = 0, c = 0, g = 0;
-            if (lane < T) {
-                u = ws.table_nuniq[lane];
-                c = ws.table_nchunk[lane];
-                g = ws.table_nsingle[lane];
-                s_base[lane] = ws.table_base[lane];
-            }
-            const int iu = wave_incl_scan_add(u, lane), ic = wave_incl_scan_add(c, lane),
-                      ig = wave_incl_scan_add(g, lane);
-            if (lane < T) {
-                s_tuo[lane] = iu - u;
-                s_tco[lane] = ic - c;
-                s_tso[lane] = ig - g;
-            }
-            if (lane == T - 1) {
-                s_tuo[T] = iu;
-                s_tco[T] = ic;
-                s_tso[T] = ig;
-            }
-        }
-        __syncthreads();
-        return;
-    }
-    // kSegThreads threads, each owns a run of consecutive tables
-    constexpr int kPer = (DQRM_MAX_TABLES + kSegThreads - 1) / kSegThreads; // 4
-    int u[kPer], c[kPer], g[kPer], su = 0, sc = 0, sg = 0;
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        const int t = tid * kPer + q;
-        u[q] = c[q] = g[q] = 0;
-        if (t < T) {
-            u[q] = ws.table_nuniq[t];
-            c[q] = ws.table_nchunk[t];
-            g[q] = ws.table_nsingle[t];
-            s_base[t] = ws.table_base[t];
-        }
-        su += u[q];
-        sc += c[q];
-        sg += g[q];
-    }
-    int tot_u, tot_c, tot_g;
-    int eu = block_excl_scan_add<kSegThreads / kWave>(su, lane, wave, s_w, &tot_u);
-    int ec = block_excl_scan_add<kSegThreads / kWave>(sc, lane, wave, s_w, &tot_c);
-    int eg = block_excl_scan_add<kSegThreads / kWave>(sg, lane, wave, s_w, &tot_g);
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        const int t = tid * kPer + q;
-        if (t < T) {
-            s_tuo[t] = eu;
-            s_tco[t] = ec;
-            s_tso[t] = eg;
-        }
-        eu += u[q];
-        ec += c[q];
-        eg += g[q];
-    }
-    if (tid == 0) {
-        s_tuo[T] = tot_u;
-        s_tco[T] = tot_c;
-        s_tso[T] = tot_g;
-    }
-    __syncthreads();
-}
-
-// Dense chunk descriptor, as the summing kernels read it:
-//   x  global sorted position of the chunk's first lookup
-//   y  len | index of the chunk inside its segment | chunks in the segment (as above)
-//   z  global index of the segment (row of `values`)
-//   w  table
-// Dense single descriptor: x bag, y global index of the segment, z table.
-__global__ __launch_bounds__(kSegThreads) void dedupe_finish_kernel(DedupeArgs args)
-{
-    struct {
-        BwdWs ws;
-        int32_t *tuo;
-        int32_t *num_unique;
-        int64_t *uniq_rows;
-        int32_t *seg_offsets;
-        int64_t N;
-        int T;
-    } a = {args.b[blockIdx.y].ws,        args.b[blockIdx.y].tuo,         args.b[blockIdx.y].num_unique,
-           args.b[blockIdx.y].uniq_rows, args.b[blockIdx.y].seg_offsets, args.b[blockIdx.y].N,
-           args.T};
-    __shared__ int s_tco[DQRM_MAX_TABLES + 1];
-    __shared__ int s_tso[DQRM_MAX_TABLES + 1];
-    __shared__ int s_tuo[DQRM_MAX_TABLES + 1];
-    __shared__ int s_base[DQRM_MAX_TABLES];
-    __shared__ int s_w[kSegThreads / kWave];
-    const int T = a.T;
-    table_offsets_to_lds(a.ws, T, s_tuo, s_tco, s_tso, s_base, s_w);
-    const int C = s_tco[T], U = s_tuo[T], S = s_tso[T];
-    if (blockIdx.x == 0) {
-        for (int k = threadIdx.x; k <= T; k += kSegThreads) a.tuo[k] = s_tuo[k];
-        if (threadIdx.x == 0) {
-            *a.num_unique = U;
-            a.seg_offsets[U] = (int32_t)a.N;
-            a.ws.totals[0] = C;
-            a.ws.totals[1] = U;
-            a.ws.totals[2] = S;
-        }
-    }
-    const int first = (int)(blockIdx.x * kSegThreads + threadIdx.x), step = (int)(gridDim.x * kSegThreads);
-    for (int c = first; c < C; c += step) {
-        const int t = table_of(s_tco, T, c);
-        const int4 d = a.ws.chunk_local[s_base[t] + (c - s_tco[t])];
-        const int j = s_tuo[t] + d.z;
-        if (desc_kchunk(d) == 0) { // first chunk of its segment: d.x is the segment's head
-            a.uniq_rows[j] = (int64_t)(unsigned)d.w;
-            a.seg_offsets[j] = d.x;
-        }
-        a.ws.chunk_desc[c] = make_int4(d.x, d.y, j, t);
-    }
-    // the bags of chunk c's lookups at a place that depends on c alone (a chunk has at least two lookups,
-    // so there are at most N / 2 chunks): DQRM_SEG_CHUNK consecutive threads per chunk
-    for (int64_t w = first; w < (int64_t)C * DQRM_SEG_CHUNK; w += step) {
-        const int c = (int)(w / DQRM_SEG_CHUNK), i = (int)(w % DQRM_SEG_CHUNK);
-        const int t = table_of(s_tco, T, c);
-        const int4 d = a.ws.chunk_local[s_base[t] + (c - s_tco[t])];
-        if (i < desc_len(d)) a.ws.chunk_bags[w] = a.ws.sorted_bag[d.x + i];
-    }
-    for (int c = first; c < S; c += step) {
-        const int t = table_of(s_tso, T, c);
-        const int4 d = a.ws.single_local[s_base[t] + (c - s_tso[t])]; // {sorted position, bag, segment, row}
-        const int j = s_tuo[t] + d.z;
-        a.uniq_rows[j] = (int64_t)(unsigned)d.w;
-        a.seg_offsets[j] = d.x;
-        a.ws.single_desc[c] = make_int4(d.y, j, t, 0);
-    }
-}
 
 // ---------------------------------------------------------------------------
 // dqrm_segment_sum: chunk sums, then the combine of long segments, then absmax.

@@ -1,0 +1,890 @@
+// dqrm_dedupe: sort a batch's lookups by (table, row, position), find the distinct rows, and build the work lists of
+// the segment sums (the sparse-tensor coalescing of Sec. 4.3).  It needs only the batch's indices.
+//
+// Kernel 1 (dedupe_kernel): the rows of a table are cut into `parts` ranges, one workgroup per (batch, table, range).
+//   A workgroup reads all of its table's lookups, keeps those of its range in lookup order (LDS), counts those below
+//   it (that is where its piece of the sorted order starts: no workgroup waits for another), sorts what it kept with a
+//   stable LSD radix sort in LDS, and writes its piece of the sorted order and its own lists of chunks and singles.
+//   A range with more lookups than the LDS holds is taken in pieces.
+//   Tables of very many lookups are first sorted by range, a tile of lookups per workgroup (dedupe_partition_kernel), so
+//   that a range's workgroup reads only its own.
+// Kernel 2 (dedupe_finish_kernel): turns the workgroups' counts into offsets (there are at most kMaxParts of them,
+//   every workgroup repeats the scan), writes the index-only outputs (unique rows, segment offsets, table offsets,
+//   count) and one dense list of 16-byte chunk descriptors over all tables.
+#pragma once
+
+#include "dqrm_device.hpp"
+
+namespace dqrm {
+
+constexpr int kMaxParts = 1024;    // (table, range) pairs per batch, at most
+constexpr int kDdTile = 8192;      // lookups of a table that a workgroup of dedupe_partition_kernel takes
+constexpr int kDdTiles = DQRM_MAX_TABLE_LOOKUPS / kDdTile; // of a table, at most
+constexpr int kDdRanges = 64;      // ranges of a partitioned table, at most
+constexpr int kDdPartThreads = 1024;
+constexpr int kSegThreads = 256;   // dedupe_finish_kernel
+static_assert(DQRM_MAX_TABLES <= kMaxParts && DQRM_MAX_TABLE_LOOKUPS <= 65536 && DQRM_MAX_TABLE_LOOKUPS / DQRM_SEG_CHUNK < 4096,
+              "a part per table at least; positions inside a table are 16 bits; the chunk descriptor holds 12 bits of chunk count");
+
+// Views into the caller's workspace (all device pointers).
+struct BwdWs {
+    // [kMaxParts][2] per (table, range): {first sorted position, segments, chunks other than singles, singles}, then how many
+    // chunks of each length class there are, 16 bits each
+    int4 *part_info;
+    // the lookups of tiles of kDdTile, each sorted by range (dedupe_partition_kernel; only for batches of more than kDdTile)
+    unsigned *part_key;       // [N]   rows (or the number of rows, for a bad index)
+    unsigned short *part_pos; // [N]   positions inside the table
+    unsigned short *part_start; // [T][kDdTiles][kDdRanges] first item of each range inside the tile
+    int *sorted_bag;          // [N]   bag of every sorted lookup
+    int4 *chunk_local;        // [N]   chunk lists of the parts (each starts at the part's first sorted position)
+    int4 *single_local;       // [N]   their lists of singles: {sorted position, bag, segment, row}
+    int4 *chunk_desc;         // [N]   dense chunk list over all tables, as the summing kernels read it
+    int *chunk_bags;          // [N/2 + 1][32] bags of chunk c's lookups, so that they can be read before its descriptor
+    int4 *single_desc;        // [N]   dense list of singles: {bag, global segment, table, -}
+    int *totals;              // [3]   chunks, segments, singles
+    int *seg_count;           // [N/32 + 2] chunks of a segment of more than one chunk that have parked their sum, filed
+                              //       under (sorted position of the segment's head / 32); zero between uses
+    float *partial_full;      // [(N/32 + 2) * D] sum of a full chunk of a segment of more than one chunk
+    float *partial_last;      // [(N/32 + 2) * D] sum of the last chunk of such a segment
+    float *absmax_slots;      // [T][kAbsmaxSlots] running maxima, one 128-byte line per entry
+};
+
+// A chunk = up to DQRM_SEG_CHUNK consecutive sorted lookups of one segment.  Its
+// descriptor is one 16-byte record, so that the summing kernels need a single
+// load to know their work:
+//   x  global sorted position of the chunk's first lookup
+//   y  len (bits 0..7) | index of the chunk inside its segment (bits 8..19) |
+//      chunks in the segment (bits 20..31)
+//   z  index of the segment inside its part (bits 0..15) | rank of the chunk among the part's chunks of its length class
+//   w  table-local row of the segment
+__device__ __forceinline__ int4 make_chunk_desc(int gstart, int len, int kchunk, int nchunks, int seg, int rank, unsigned row)
+{
+    return make_int4(gstart, len | (kchunk << 8) | (nchunks << 20), seg | (rank << 16), (int)row);
+}
+// The dense list is in sorted order, or (DedupeArgs::by_length) the short chunks of all tables come first: the groups of a
+// wave of the summing kernel then add up chunks of about the same length.
+constexpr int kChunkClasses = 5;
+__device__ __forceinline__ int chunk_class(int len) { return len > 24 ? 4 : len > 16 ? 3 : len > 8 ? 2 : len > 4 ? 1 : 0; }
+__device__ __forceinline__ int desc_len(const int4 &d) { return d.y & 0xFF; }
+__device__ __forceinline__ int desc_kchunk(const int4 &d) { return (d.y >> 8) & 0xFFF; }
+__device__ __forceinline__ int desc_nchunks(const int4 &d) { return (int)((unsigned)d.y >> 20); }
+
+// One launch can dedupe several batches (blockIdx.y picks the batch).
+struct DedupeBatch {
+    const int64_t *indices;
+    const int64_t *offsets;
+    int64_t N;
+    int limit; // lookups a table may have: DQRM_MAX_TABLE_LOOKUPS or the caller's smaller bound
+    BwdWs ws;
+    int32_t *sorted_pos;
+    int32_t *tuo;
+    int32_t *num_unique;
+    int64_t *uniq_rows;
+    int32_t *seg_offsets;
+};
+struct DedupeArgs {
+    DedupeBatch b[DQRM_MAX_DEDUPE_BATCHES];
+    const int64_t *row_offsets;
+    int T, B;
+    int parts; // ranges per table, T * parts <= kMaxParts
+    int bags_per_part; // ceil(B / parts)
+    int by_length;     // the order of the dense chunk list, see chunk_class
+    FastDiv by_parts;
+    FastDiv even; // by the lookups of a bag if all bags of the launch hold equally many (a guess), else by 1
+};
+
+// bits set below my lane / up to and including it
+__device__ __forceinline__ int mask_rank(unsigned long long m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+
+// the last bag b of [0, B) with off(b) <= p, for a non-decreasing off with off(0) <= p
+template <typename Off>
+__device__ __forceinline__ int find_bag(Off off, int B, int p)
+{
+    int bag = 0;
+    for (int step = 1 << (31 - __clz(B)); step >= 1; step >>= 1) {
+        const int b = bag + step;
+        if (b < B && (int)off(b) <= p) bag = b;
+    }
+    return bag;
+}
+
+// A table's lookups [lo, lo + n) in the batch, by its bags' offsets; n = 0 if they make no sense or are too many (then
+// bad_code / bad_value say why).
+struct TableExtent {
+    long long lo;
+    int n, bad_code;
+    long long bad_value;
+    __device__ __forceinline__ TableExtent(const int64_t *bag_offsets, int B, int64_t N, int limit)
+    {
+        lo = bag_offsets[0];
+        const long long hi = bag_offsets[B];
+        const bool bad = lo < 0 || hi > N || lo > hi, many = !bad && hi - lo > limit;
+        bad_code = bad ? DQRM_ERR_BAD_OFFSETS : (many ? DQRM_ERR_CAPACITY : 0);
+        bad_value = bad ? lo : hi - lo;
+        n = bad || many ? 0 : (int)(hi - lo);
+        lo = lo < 0 ? 0 : (lo > N ? N : lo);
+    }
+};
+
+// A wave-uniform number that the compiler takes for a new one.  (Two unrolled loops that leave at the same round would
+// otherwise be compiled as one path per round through both.)
+__device__ __forceinline__ int opaque(int v)
+{
+    asm volatile("" : "+s"(v));
+    return v;
+}
+// the same for a number of the lane
+__device__ __forceinline__ int opaque_lane(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// The lanes of the wave whose digit of `bits` bits equals mine (all 64 lanes active).  Per bit: the lanes whose bit is set
+// (ballot) against my own bit spread over a word (0 or all ones, a signed one-bit field extract): the lanes whose bit
+// equals mine are ~(ballot ^ mine), and gfx950 folds that and the running AND into one three-input bit operation per
+// 32-bit half.  (Measured against a table of lane masks in LDS, one atomic OR and one read per lane: that took 15 % longer
+// over a whole sort, the conflicts of frequent digits cost more than the ballots.)
+__device__ __forceinline__ unsigned long long match_digit(unsigned d, int bits)
+{
+    unsigned lo = ~0u, hi = ~0u;
+    for (int b = 0; b < bits; ++b) {
+        unsigned mine = (unsigned)(int)__builtin_amdgcn_sbfe(d, b, 1);
+        asm volatile("" : "+v"(mine)); // (keeps the compiler from deriving the ballot from d again: a shift more per bit)
+        const unsigned long long bal = __ballot(mine != 0u);
+        lo &= ~((unsigned)bal ^ mine);
+        hi &= ~((unsigned)(bal >> 32) ^ mine);
+    }
+    return ((unsigned long long)hi << 32) | lo;
+}
+
+// Where the items of each digit go, for the wave's items of a sorting pass: after the items of smaller digits and those
+// of the same digit in earlier waves.  cnt: a row of 256 counts per wave (complete); a lane owns four digits.  Every wave
+// adds up all rows by itself, which saves the barriers of a shared scan.  *starts = the digits' first places.
+template <int WAVES>
+__device__ __forceinline__ uint2 digit_places(const unsigned short *cnt, int wave, int lane, uint2 *starts)
+{
+    unsigned all01 = 0, all23 = 0, my01 = 0, my23 = 0; // (two 16-bit sums a word: at most 8192 each)
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        const uint2 c = *reinterpret_cast<const uint2 *>(cnt + w * 256 + 4 * lane);
+        if (w < wave) {
+            my01 += c.x;
+            my23 += c.y;
+        }
+        all01 += c.x;
+        all23 += c.y;
+    }
+    const unsigned n0 = all01 & 0xFFFFu, n1 = all01 >> 16, n2 = all23 & 0xFFFFu, n3 = all23 >> 16;
+    const unsigned sum = n0 + n1 + n2 + n3;
+    const unsigned e0 = (unsigned)wave_incl_scan_add((int)sum, lane) - sum, e1 = e0 + n0, e2 = e1 + n1, e3 = e2 + n2;
+    *starts = make_uint2(e0 | (e1 << 16), e2 | (e3 << 16));
+    return make_uint2(starts->x + my01, starts->y + my23);
+}
+
+// Tables of many lookups: dedupe_kernel would read all of them in every range's workgroup.  Here a workgroup takes a tile
+// of kDdTile lookups and sorts it by range (one stable pass of the radix sort), so that a range's workgroup finds its
+// lookups in one run per tile.
+__global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(DedupeArgs args)
+{
+    constexpr int kWaves = kDdPartThreads / kWave, kItems = kDdTile / kDdPartThreads;
+    __shared__ __align__(16) unsigned s_key[kDdTile];
+    __shared__ unsigned short s_pos[kDdTile];
+    __shared__ __align__(16) unsigned short cnt[kWaves * 256], place[kWaves * 256];
+    const DedupeBatch &bt = args.b[blockIdx.y];
+    const int t = blockIdx.x, tile = blockIdx.z, B = args.B;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const unsigned rows_t = (unsigned)(args.row_offsets[t + 1] - args.row_offsets[t]);
+    const TableExtent x(bt.offsets + (long long)t * B, B, bt.N, bt.limit); // (its problems: dedupe_kernel reports them)
+    const int len = min(kDdTile, x.n - tile * kDdTile);
+    if (len <= 0) return;
+    const int rounds = (len + kDdPartThreads - 1) / kDdPartThreads;
+    const int wave_at = wave * rounds * kWave;
+    const char *src = reinterpret_cast<const char *>(bt.indices + x.lo + tile * kDdTile);
+    long long raw[kItems];
+    const int rounds_1 = opaque(rounds);
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        if (r >= rounds_1) break;
+        raw[r] = *reinterpret_cast<const long long *>(src + (unsigned)min(wave_at + r * kWave + lane, len - 1) * 8u);
+    }
+    unsigned short *my_cnt = cnt + wave * 256, *my_place = place + wave * 256;
+    *reinterpret_cast<uint2 *>(my_cnt + 4 * lane) = make_uint2(0u, 0u);
+    const int bits = 32 - __clz(args.parts); // (the digit `parts` is the padding's)
+    const unsigned share = args.by_parts.div(rows_t) + 1u;
+    const float per_share = 1.0f / (float)share;
+    unsigned key[kItems], rank[kItems]; // rank: place inside the wave's items of the digit, digit in the upper half
+    bool bad_index = false;
+    long long bad_value = 0;
+    const int rounds_2 = opaque(rounds);
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        if (r >= rounds_2) break;
+        const bool exists = wave_at + r * kWave + lane < len;
+        key[r] = (unsigned long long)raw[r] < rows_t ? (unsigned)raw[r] : rows_t;
+        if (exists && key[r] == rows_t) bad_index = true, bad_value = raw[r];
+        // the range, key / share: at most 63, so the rounded quotient is at most one off
+        int d = (int)((float)key[r] * per_share);
+        const int rest = (int)(key[r] - (unsigned)d * share);
+        d += rest < 0 ? -1 : (rest >= (int)share ? 1 : 0);
+        if (!exists) d = args.parts; // (padding: after every range)
+        const unsigned long long peers = match_digit((unsigned)d, bits);
+        const unsigned prev = my_cnt[d];
+        const int before = mask_rank(peers);
+        rank[r] = (prev + (unsigned)before) | ((unsigned)d << 16);
+        if (before == 0) my_cnt[d] = (unsigned short)(prev + (unsigned)__popcll(peers));
+    }
+    if (bad_index) report(DQRM_ERR_INDEX_OUT_OF_RANGE, t, bad_value);
+    __syncthreads();
+    uint2 starts;
+    *reinterpret_cast<uint2 *>(my_place + 4 * lane) = digit_places<kWaves>(cnt, wave, lane, &starts);
+    if (wave == 0 && 4 * lane < kDdRanges)
+        *reinterpret_cast<uint2 *>(bt.ws.part_start + ((int64_t)t * kDdTiles + tile) * kDdRanges + 4 * lane) = starts;
+    const int rounds_3 = opaque(rounds);
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        if (r >= rounds_3) break;
+        const unsigned to = my_place[rank[r] >> 16] + (rank[r] & 0xFFFFu);
+        s_key[to] = key[r];
+        s_pos[to] = (unsigned short)(wave_at + r * kWave + lane);
+    }
+    __syncthreads();
+    unsigned *out_key = bt.ws.part_key + x.lo + tile * kDdTile;
+    unsigned short *out_pos = bt.ws.part_pos + x.lo + tile * kDdTile;
+    for (int i = tid; i < len; i += kDdPartThreads) {
+        out_key[i] = s_key[i];
+        out_pos[i] = (unsigned short)(tile * kDdTile + s_pos[i]);
+    }
+}
+
+constexpr int kDdStack = 192;     // pending range ends
+constexpr int kDdPivotDepth = 96; // pending ranges beyond which a range is halved instead of split at a sampled row
+static_assert(kDdPivotDepth + 2 + 32 <= kDdStack, "halving ends at a range of one row");
+
+// (The loops over a thread's items leave at the first round that does not exist, and those after the sort are not
+// unrolled: most launches have one or two rounds, every line of code is fetched anew by every launch, and a kernel
+// this short waits for its code as much as for its data.)
+// PARTITIONED: the table's lookups come from dedupe_partition_kernel, a run of this range per tile.
+template <int THREADS, int CAP, bool PARTITIONED>
+__global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
+{
+    constexpr int kWaves = THREADS / kWave, kCap = CAP;
+    constexpr int kDdItems = CAP / THREADS; // lookups a thread requests at a time, and sorts
+    static_assert(kCap % THREADS == 0 && kCap <= 8192, "ranks are 16 bits");
+    // the kept lookups, twice (a sorting pass moves them from one half to the other): key relative to the range, position
+    // inside the table
+    __shared__ __align__(16) unsigned s_key[2][kCap + 4];
+    __shared__ unsigned short s_pos[2][kCap], s_rank[kCap];
+    // digit counters, a row of 256 per wave, and where the wave's items of each digit go
+    __shared__ __align__(16) unsigned short cnt[kWaves * 256], place[kWaves * 256];
+    __shared__ unsigned long long s_heads[kCap / kWave];
+    __shared__ int s_scan[2][kWaves];
+    __shared__ int4 s_x[kWaves];
+    __shared__ int s_class[kChunkClasses]; // chunks of each length class so far
+    __shared__ unsigned s_stack[kDdStack];
+    __shared__ unsigned s_pivot;
+
+    const DedupeBatch &bt = args.b[blockIdx.y];
+    const int64_t *__restrict__ indices = bt.indices;
+    const int64_t *__restrict__ offsets = bt.offsets;
+    const int B = args.B;
+    const int64_t N = bt.N;
+    const BwdWs &ws = bt.ws;
+    int32_t *__restrict__ sorted_pos = bt.sorted_pos;
+
+    const int t = blockIdx.x, part = blockIdx.z; // consecutive workgroups: different tables
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+
+    const unsigned rows_t = (unsigned)(args.row_offsets[t + 1] - args.row_offsets[t]); // host: <= DQRM_MAX_TABLE_ROWS
+
+    const int64_t *__restrict__ bag_offsets = offsets + (long long)t * B;
+    const TableExtent x(bag_offsets, B, N, bt.limit);
+    const long long lo = x.lo;
+    const int n = x.n, base = (int)lo;
+    // A problem of the data is kept here and reported at one place (one problem per thread and kind of work is enough: only
+    // the first of all is recorded).
+    int bad_code = part == 0 && tid == 0 ? x.bad_code : 0;
+    long long bad_value = x.bad_value;
+
+    // My range of the keys [0, rows_t]: a row, or rows_t for a lookup whose index is out of range (those sort after
+    // every row, and the part that holds them reports them).
+    const unsigned share = args.by_parts.div(rows_t) + 1u;
+    const unsigned range_lo = min((unsigned)part * share, rows_t + 1u), range_hi = min(range_lo + share, rows_t + 1u);
+
+    // The lookups to look at: all of the table's, or those of my range, tile by tile: item i of tile w's run is item
+    // run_first[w] + i of mine and lies at run_from[w] + i (both wave-uniform).
+    int count = n, run_below = 0;
+    int run_first[kDdTiles], run_from[kDdTiles];
+    if constexpr (PARTITIONED) {
+        const int tile_len = min(kDdTile, n - lane * kDdTile); // (lanes are tiles)
+        int s = 0, e = 0;
+        if (lane < kDdTiles && tile_len > 0) {
+            const unsigned short *st = ws.part_start + ((int64_t)t * kDdTiles + lane) * kDdRanges;
+            s = min((int)st[part], tile_len);
+            e = part + 1 < args.parts ? min((int)st[part + 1], tile_len) : tile_len;
+        }
+        const int incl = wave_incl_scan_add(e - s, lane), below_incl = wave_incl_scan_add(s, lane);
+        const int first = incl - (e - s), from = base + lane * kDdTile + s - first;
+        count = __builtin_amdgcn_readlane(incl, kDdTiles - 1);
+        run_below = __builtin_amdgcn_readlane(below_incl, kDdTiles - 1);
+#pragma unroll
+        for (int w = 0; w < kDdTiles; ++w) {
+            run_first[w] = __builtin_amdgcn_readlane(first, w);
+            run_from[w] = __builtin_amdgcn_readlane(from, w);
+        }
+    }
+    // a wave's share of a scan step: as few rounds as the step's lookups need
+    const int scan_rounds = (min(count, kDdItems * THREADS) + THREADS - 1) / THREADS;
+    const int scan_step = scan_rounds * THREADS;
+    // The keys of a step's lookups, wave-striped (item r of a lane: wave_first + r * 64 + lane, so that a wave's items
+    // are consecutive); requested one step ahead.  Lookups past the end re-read the last one.
+    const int wave_first = wave * scan_rounds * kWave;
+    const int64_t *__restrict__ my_indices = indices + base;
+    struct Lookup {
+        long long index;   // not PARTITIONED: as given
+        unsigned row, pos; // PARTITIONED: checked, and where it was
+    };
+    Lookup raw[kDdItems];
+    auto request = [&](int i, Lookup &l) {
+        i = min(i, count - 1);
+        if constexpr (PARTITIONED) {
+            int at = run_from[0];
+#pragma unroll
+            for (int w = 1; w < kDdTiles; ++w) at = i >= run_first[w] ? run_from[w] : at;
+            l.row = ws.part_key[at + i];
+            l.pos = ws.part_pos[at + i];
+        } else {
+            l.index = *reinterpret_cast<const long long *>(reinterpret_cast<const char *>(my_indices) + (unsigned)i * 8u);
+        }
+    };
+    auto row_of = [&](const Lookup &l) {
+        if constexpr (PARTITIONED) return l.row;
+        return (unsigned long long)l.index < rows_t ? (unsigned)l.index : rows_t;
+    };
+    auto request_step = [&](int i0, int lane) {
+#pragma unroll
+        for (int r = 0; r < kDdItems; ++r) raw[r] = Lookup{}; // (or what a step leaves alone would stay alive from the one before)
+        const int scan_rounds_4 = opaque(scan_rounds);
+#pragma unroll
+        for (int r = 0; r < kDdItems; ++r) {
+            if (r >= scan_rounds_4) break;
+            request(i0 + r * kWave + lane, raw[r]);
+        }
+    };
+    if (range_lo < range_hi && count > 0) request_step(wave_first, lane);
+
+    // ---- bags.  The parts share the check of their order.  Where the bags hold equally many lookups each (the usual
+    // batches), the bag of a lookup is guessed and the guess looked up; otherwise it is found among the
+    // bags' first positions: in LDS, all of them or (if they do not fit) some, and then among those between where they are.
+    const bool even = (unsigned long long)args.even.d * (unsigned)B == (unsigned)n; // (host: the divisor is N / (T B))
+    const int sparse = max(0, 32 - __clz((B - 1) / kCap)); // every 2^sparse-th bag's offset fits
+    if (n > 0) {
+        const int b_lo = min(args.bags_per_part * part, B), b_hi = min(b_lo + args.bags_per_part, B);
+        for (int b0 = b_lo + tid; b0 < b_hi; b0 += 4 * THREADS) { // (four at a time, all requested before the first is looked at)
+            long long s[4], e[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int b = min(b0 + q * THREADS, b_hi - 1);
+                s[q] = bag_offsets[b];
+                e[q] = bag_offsets[b + 1];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int b = min(b0 + q * THREADS, b_hi - 1);
+                if (s[q] < lo || e[q] > lo + n || s[q] > e[q]) bad_code = DQRM_ERR_BAD_OFFSETS, bad_value = (long long)t * B + b;
+            }
+        }
+    }
+    if (bad_code != 0) report(bad_code, t, bad_value);
+    if (part == 0 && tid < kAbsmaxSlots) *absmax_slot(ws.absmax_slots, t, tid) = 0.0f;
+    if (tid < kChunkClasses) s_class[tid] = 0; // (read after more barriers)
+    auto search_bag = [&](const unsigned short *soff, int p) {
+        if (even) return find_bag([&](int b) { return bag_offsets[b] - lo; }, B, p); // (the guess was wrong)
+        const int hint = p < 65535 ? find_bag([&](int b) { return soff[b]; }, ((B - 1) >> sparse) + 1, p) << sparse : 0;
+        if (sparse == 0 && p < 65535) return hint; // (position 65535 cannot be told from an empty bag at 65536 in 16 bits)
+        return hint + find_bag([&](int b) { return bag_offsets[hint + b] - lo; }, p < 65535 ? min(1 << sparse, B - hint) : B, p);
+    };
+    auto stage_offsets = [&](unsigned short *soff, int tid) {
+        for (int b = tid; b << sparse < B; b += THREADS) {
+            const long long s = bag_offsets[b << sparse] - lo;
+            soff[b] = (unsigned short)(s < 0 ? 0 : (s > 65535 ? 65535 : (int)s));
+        }
+    };
+
+    int n_uniq = 0, n_chunk = 0, n_single = 0; // this part's lists so far
+    int part_base = -1;                        // first sorted position of the part
+    unsigned cur = range_lo, end = range_hi;
+    int depth = 0;
+    bool requested = true; // the first keys are on their way
+    const int tid_ = tid;
+    while (cur < end) {
+        // (Nearly always one round, and its arrays start at zero: what an unfinished loop leaves undefined would be carried
+        // from round to round.  Nothing that depends on the lane is worth keeping in registers for the next round either.)
+        const int tid = opaque_lane(tid_), lane = tid & (kWave - 1);
+        // ---- 1. the lookups of [cur, end), in lookup order, to LDS; how many lie below -----------------------------
+        const unsigned width = end - cur;
+        if (!requested && count > 0) request_step(wave_first, lane);
+        requested = false;
+        int m = 0, below = run_below;
+        // (a partitioned range of one row is known to hold just that row: if it is long, it need not be looked over first)
+        const bool known = PARTITIONED && range_hi - range_lo == 1u && count > kCap;
+        if (known) m = count;
+        for (int i0 = known ? count : 0, par = 0; i0 < count; i0 += scan_step, par ^= 1) {
+            unsigned key[kDdItems] = {}, pos[kDdItems] = {};
+            bool bad_index = false;
+            int mine = 0; // kept (low half) and below (high half), each at most 512 a wave and 8192 a workgroup
+            const int scan_rounds_5 = opaque(scan_rounds);
+#pragma unroll
+            for (int r = 0; r < kDdItems; ++r) {
+                if (r >= scan_rounds_5) break;
+                key[r] = row_of(raw[r]);
+                pos[r] = raw[r].pos;
+                if (i0 + wave_first + r * kWave + lane >= count) key[r] = ~0u; // no lookup: in no range and below none
+                if (!PARTITIONED && key[r] == rows_t && end > rows_t) bad_index = true, bad_value = raw[r].index;
+                mine += __popcll(__ballot(key[r] - cur < width));
+                mine += __popcll(__ballot(key[r] < cur)) << 16;
+            }
+            if (bad_index) report(DQRM_ERR_INDEX_OUT_OF_RANGE, t, bad_value);
+            if (i0 + scan_step < count) request_step(i0 + scan_step + wave_first, lane);
+            if (lane == 0) s_scan[par][wave] = mine;
+            __syncthreads();
+            const int x = lane < kWaves ? s_scan[par][lane] : 0;
+            const int incl = wave_incl_scan_add(x, lane);
+            const int total = __builtin_amdgcn_readlane(incl, kWaves - 1);
+            int dst = m + ((__builtin_amdgcn_readlane(incl, wave) - mine) & 0xFFFF);
+            const int scan_rounds_6 = opaque(scan_rounds);
+#pragma unroll
+            for (int r = 0; r < kDdItems; ++r) {
+                if (r >= scan_rounds_6) break;
+                const bool in = key[r] - cur < width;
+                const unsigned long long mask = __ballot(in);
+                const int d = dst + mask_rank(mask);
+                if (in && d < kCap) {
+                    s_key[0][d] = key[r] - cur;
+                    s_pos[0][d] = (unsigned short)(PARTITIONED ? pos[r] : (unsigned)(i0 + wave_first + r * kWave + lane));
+                }
+                dst += __popcll(mask);
+            }
+            m += total & 0xFFFF;
+            below += total >> 16;
+        }
+        __syncthreads();
+        const int at = base + below; // sorted position of the range's first lookup
+        if (part_base < 0) part_base = at;
+
+        if (m > kCap && width > 1) {
+            // ---- more than fits: three ranges around a row from the middle of what was kept (a row so hot that it
+            // alone overflows the LDS is that row sooner or later, and a range of one row needs no sort)
+            unsigned pivot = cur + width / 2;
+            const bool sampled = depth < kDdPivotDepth;
+            if (sampled) {
+                if (wave == 0) {
+                    const unsigned k = s_key[0][lane * (kCap / kWave)];
+                    int rank = 0;
+                    for (int j = 0; j < kWave; ++j) {
+                        const unsigned o = (unsigned)__builtin_amdgcn_readlane((int)k, j);
+                        rank += o < k || (o == k && j < lane);
+                    }
+                    if (rank == kWave / 2) s_pivot = k;
+                }
+                __syncthreads();
+                pivot = cur + s_pivot;
+            }
+            if (tid == 0) s_stack[depth] = end;
+            ++depth;
+            if (sampled && pivot + 1 < end) {
+                if (tid == 0) s_stack[depth] = pivot + 1;
+                ++depth;
+            }
+            __syncthreads();
+            if (sampled && pivot == cur) { // the first of the three is empty: go on with the row itself
+                --depth;
+                end = s_stack[depth];
+            } else {
+                end = pivot;
+            }
+            __syncthreads();
+            continue;
+        }
+
+        if (m > kCap) {
+            // ---- one row (or the bad indices) with more lookups than the LDS holds: they are in order as they come
+            const bool valid = cur < rows_t;
+            unsigned short *soff = reinterpret_cast<unsigned short *>(s_key[0]);
+            if (!even) {
+                stage_offsets(soff, tid); // (what was kept of the lookups is not needed)
+                __syncthreads();
+            }
+            int done = 0;
+            request_step(wave_first, lane);
+            for (int i0 = 0, par = 0; i0 < count; i0 += scan_step, par ^= 1) {
+                unsigned long long in[kDdItems] = {};
+                int pos[kDdItems] = {}, mine = 0;
+                const int scan_rounds_7 = opaque(scan_rounds);
+#pragma unroll
+                for (int r = 0; r < kDdItems; ++r) {
+                    if (r >= scan_rounds_7) break;
+                    const int i = i0 + wave_first + r * kWave + lane;
+                    in[r] = __ballot(i < count && row_of(raw[r]) == cur);
+                    pos[r] = PARTITIONED ? (int)raw[r].pos : i;
+                    mine += __popcll(in[r]);
+                }
+                if (i0 + scan_step < count) request_step(i0 + scan_step + wave_first, lane);
+                if (lane == 0) s_scan[par][wave] = mine;
+                __syncthreads(); // (and the step before this one has been written out)
+                const int incl = wave_incl_scan_add(lane < kWaves ? s_scan[par][lane] : 0, lane);
+                int dst = __builtin_amdgcn_readlane(incl, wave) - mine;
+                const int scan_rounds_8 = opaque(scan_rounds);
+#pragma unroll
+                for (int r = 0; r < kDdItems; ++r) {
+                    if (r >= scan_rounds_8) break;
+                    if ((in[r] >> lane) & 1ull) s_pos[0][dst + mask_rank(in[r])] = (unsigned short)pos[r];
+                    dst += __popcll(in[r]);
+                }
+                __syncthreads();
+                const int kept = __builtin_amdgcn_readlane(incl, kWaves - 1);
+                for (int k = tid; k < kept; k += THREADS) {
+                    const int p = s_pos[0][k], d = at + done + k;
+                    sorted_pos[d] = base + p;
+                    int bag = (int)args.even.div((unsigned)p);
+                    if (!even || bag_offsets[bag] > lo + p || lo + p >= bag_offsets[bag + 1]) bag = search_bag(soff, p);
+                    if (valid) ws.sorted_bag[d] = bag;
+                }
+                done += kept;
+            }
+            if (valid) {
+                const int nchunks = (m + DQRM_SEG_CHUNK - 1) / DQRM_SEG_CHUNK;
+                const int last_len = m - (nchunks - 1) * DQRM_SEG_CHUNK, last_class = chunk_class(last_len);
+                constexpr int kFull = kChunkClasses - 1; // class of a full chunk
+                const int long_rank = s_class[kFull], last_rank = last_class == kFull ? long_rank + nchunks - 1 : s_class[last_class];
+                for (int c = tid; c < nchunks; c += THREADS)
+                    ws.chunk_local[part_base + n_chunk + c] =
+                        make_chunk_desc(at + c * DQRM_SEG_CHUNK, c + 1 < nchunks ? DQRM_SEG_CHUNK : last_len, c, nchunks, n_uniq,
+                                        c + 1 < nchunks ? long_rank + c : last_rank, cur);
+                __syncthreads();
+                if (tid == 0) {
+                    ws.seg_count[at / DQRM_SEG_CHUNK] = 0;
+                    s_class[kFull] += nchunks - 1;
+                    s_class[last_class] += 1;
+                }
+                n_uniq += 1;
+                n_chunk += nchunks;
+            }
+        } else if (m > 0) {
+            // ---- 2. stable LSD radix sort of the m items, at most 8 bits per pass ------------------------------------
+            const int rounds = (m + THREADS - 1) / THREADS; // 1 .. kDdItems, the same for the whole workgroup
+            const int wave_at = wave * rounds * kWave;      // this wave's first item
+            const int nbits = width > 1 && m > 1 ? 32 - __clz(width - 1) : 0;
+            const int passes = (nbits + 7) / 8;
+            const int bits = passes > 0 ? (nbits + passes - 1) / passes : 0;
+            const unsigned digit_mask = (1u << bits) - 1u;
+            unsigned short *my_cnt = cnt + wave * 256, *my_place = place + wave * 256;
+            int half = 0;
+            if (passes > 0) // padding: the largest digit in every pass and last in line, so it stays last
+                for (int i = m + tid; i < rounds * THREADS; i += THREADS) s_key[0][i] = ~0u;
+            for (int p = 0; p < passes; ++p, half ^= 1) {
+                const int shift = bits * p;
+                const unsigned *from_key = s_key[half];
+                const unsigned short *from_pos = s_pos[half];
+                unsigned *to_key = s_key[half ^ 1];
+                unsigned short *to_pos = s_pos[half ^ 1];
+                // (a wave's row of counters is its own: no barrier between clearing and counting)
+                *reinterpret_cast<uint2 *>(my_cnt + 4 * lane) = make_uint2(0u, 0u);
+                if (p == 0) __syncthreads(); // the padding is there
+#pragma unroll 1
+                for (int i = wave_at + lane, r = 0; r < rounds; ++r, i += kWave) {
+                    const unsigned d = (from_key[i] >> shift) & digit_mask;
+                    const unsigned long long peers = match_digit(d, bits);
+                    const unsigned prev = my_cnt[d];
+                    const int rank = mask_rank(peers);
+                    s_rank[i] = (unsigned short)(prev + (unsigned)rank); // rank inside the wave's items of this digit
+                    if (rank == 0) my_cnt[d] = (unsigned short)(prev + (unsigned)__popcll(peers));
+                }
+                __syncthreads();
+                uint2 starts;
+                *reinterpret_cast<uint2 *>(my_place + 4 * lane) = digit_places<kWaves>(cnt, wave, lane, &starts);
+#pragma unroll 1
+                for (int i = wave_at + lane, r = 0; r < rounds; ++r, i += kWave) {
+                    const unsigned k = from_key[i];
+                    const int to = my_place[(k >> shift) & digit_mask] + s_rank[i];
+                    to_key[to] = k;
+                    to_pos[to] = from_pos[i];
+                }
+                __syncthreads();
+            }
+            const unsigned *skey = s_key[half];
+            const unsigned short *spos = s_pos[half];
+            // the room of the keys' other half: the segments' first items, then the bags' first positions
+            unsigned short *shead = reinterpret_cast<unsigned short *>(s_key[half ^ 1]), *soff = shead + kCap + 2;
+            // the guessed bags' offsets are requested now, for all items at once, and looked at when the heads are known
+            long long bag_lo[kDdItems] = {}, bag_hi[kDdItems] = {};
+            if (even) {
+                const int rounds_9 = opaque(rounds);
+#pragma unroll
+                for (int r = 0; r < kDdItems; ++r) {
+                    if (r >= rounds_9) break;
+                    const int i = wave_at + r * kWave + lane;
+                    const unsigned g = args.even.div(i < m ? spos[i] : 0u); // below B, as the position is below n
+                    bag_lo[r] = bag_offsets[g];
+                    bag_hi[r] = bag_offsets[g + 1u];
+                }
+            } else {
+                stage_offsets(soff, tid);
+            }
+
+            // ---- 3. segment heads --------------------------------------------------------------------------------------
+            const unsigned bad_key = rows_t - cur; // (what the bad indices carry; at least width where there can be none)
+            int wave_heads = 0, wave_valid = 0;
+#pragma unroll 1
+            for (int r = 0; r < rounds; ++r) {
+                const int i = wave_at + r * kWave + lane;
+                const unsigned k = skey[i], prev = skey[max(i - 1, 0)];
+                const bool valid = k < bad_key && i < m;
+                const unsigned long long heads = __ballot(valid && (i == 0 || k != prev));
+                if (lane == 0) s_heads[wave * rounds + r] = heads;
+                wave_heads += __popcll(heads);
+                wave_valid += __popcll(__ballot(valid));
+            }
+            if (lane == 0) s_x[wave] = make_int4(wave_heads, wave_valid, 0, 0);
+            __syncthreads();
+            int heads_before, seg_count, valid_count; // (the valid items come first)
+            {
+                const int4 x = s_x[lane & (kWaves - 1)];
+                const int incl = wave_incl_scan_add(lane < kWaves ? (x.x | (x.y << 16)) : 0, lane);
+                const int total = __builtin_amdgcn_readlane(incl, kWaves - 1);
+                seg_count = total & 0xFFFF;
+                valid_count = total >> 16;
+                heads_before = (__builtin_amdgcn_readlane(incl, wave) & 0xFFFF) - wave_heads;
+            }
+            {
+                int seg = heads_before;
+#pragma unroll 1
+                for (int r = 0; r < rounds; ++r) {
+                    const unsigned long long heads = s_heads[wave * rounds + r];
+                    if ((heads >> lane) & 1ull) shead[seg + mask_rank(heads)] = (unsigned short)(wave_at + r * kWave + lane);
+                    seg += __popcll(heads);
+                }
+            }
+            if (tid == 0) shead[seg_count] = (unsigned short)valid_count; // end of the last segment
+            // bags (the guessed ones first; bags of other lengths that happen to add up to the same number are searched)
+            bool search = !even;
+            if (even) {
+                const int rounds_10 = opaque(rounds);
+#pragma unroll
+                for (int r = 0; r < kDdItems; ++r) {
+                    if (r >= rounds_10) break;
+                    const int i = wave_at + r * kWave + lane, p = i < m ? (int)spos[i] : 0;
+                    const int bag = (int)args.even.div((unsigned)p);
+                    search |= bag_lo[r] > lo + p || lo + p >= bag_hi[r];
+                    s_rank[i] = (unsigned short)bag;
+                    if (i < valid_count) ws.sorted_bag[at + i] = bag;
+                }
+            } else {
+                __syncthreads(); // (the staged offsets)
+            }
+            if (search) {
+#pragma unroll 1
+                for (int i = wave_at + lane, r = 0; r < rounds; ++r, i += kWave) {
+                    const int bag = search_bag(soff, i < m ? (int)spos[i] : 0);
+                    s_rank[i] = (unsigned short)bag;
+                    if (i < valid_count) ws.sorted_bag[at + i] = bag;
+                }
+            }
+            __syncthreads();
+
+            // ---- 4. the part's piece of the sorted order and its lists.  Chunk heads: every DQRM_SEG_CHUNK-th item of a
+            // segment, counted from its head.  Two classes, listed separately: "single" = a row looked up exactly once (the
+            // common case, no summation needed), and all others.  Both lists in sorted order: counted first, then written.
+            // (In the order in which the waves get there, the segment sums of 26 tables x 8192 lookups of one bag each take
+            // 28.5 us instead of 25.4.)
+            int chunk_at = 0, single_at = 0;
+            for (int writes = 0; writes < 2; ++writes) {
+                int seg_before = heads_before - 1, wave_chunks = 0, wave_singles = 0;
+#pragma unroll 1
+                for (int r = 0; r < rounds; ++r) {
+                    const unsigned long long heads = s_heads[wave * rounds + r];
+                    const int i = wave_at + r * kWave + lane;
+                    const bool valid = i < valid_count;
+                    const int seg = max(seg_before + mask_rank(heads) + (int)((heads >> lane) & 1ull), 0);
+                    seg_before += __popcll(heads);
+                    const int start = shead[seg], seg_end = shead[min(seg + 1, seg_count)];
+                    const bool chead = valid && ((i - start) % DQRM_SEG_CHUNK) == 0;
+                    const bool single = chead && i == start && seg_end == i + 1;
+                    const unsigned long long singles = __ballot(single), chunks = __ballot(chead && !single);
+                    if (writes) { // (wave-uniform)
+                        const int p = i < m ? (int)spos[i] : 0;
+                        // (more bags than 16 bits tell: this thread's own store is read back)
+                        const int bag = B <= 65536 ? (int)s_rank[i] : (valid ? ws.sorted_bag[at + i] : 0);
+                        const unsigned row = cur + skey[i];
+                        if (i < m) sorted_pos[at + i] = base + p;
+                        if (single)
+                            ws.single_local[single_at + wave_singles + mask_rank(singles)] = make_int4(at + i, bag, n_uniq + seg, (int)row);
+                        if (chead && !single) {
+                            const int nchunks = (seg_end - start + DQRM_SEG_CHUNK - 1) / DQRM_SEG_CHUNK;
+                            const int len = min(DQRM_SEG_CHUNK, seg_end - i);
+                            ws.chunk_local[chunk_at + wave_chunks + mask_rank(chunks)] =
+                                make_chunk_desc(at + i, len, (i - start) / DQRM_SEG_CHUNK, nchunks, n_uniq + seg,
+                                                args.by_length ? atomicAdd(&s_class[chunk_class(len)], 1) : 0, row);
+                            // the arrival counter of a segment of more than one chunk starts at zero
+                            if (i == start && nchunks > 1) ws.seg_count[(at + i) / DQRM_SEG_CHUNK] = 0;
+                        }
+                    }
+                    wave_chunks += __popcll(chunks);
+                    wave_singles += __popcll(singles);
+                }
+                if (writes) break;
+                if (lane == 0) s_x[wave] = make_int4(wave_chunks, wave_singles, 0, 0);
+                __syncthreads();
+                const int4 x = s_x[lane & (kWaves - 1)];
+                const int incl = wave_incl_scan_add(lane < kWaves ? (x.x | (x.y << 16)) : 0, lane); // (at most 8192 each)
+                const int total = __builtin_amdgcn_readlane(incl, kWaves - 1), before = __builtin_amdgcn_readlane(incl, wave);
+                chunk_at = part_base + n_chunk + (before & 0xFFFF) - wave_chunks;
+                single_at = part_base + n_single + (before >> 16) - wave_singles;
+                n_chunk += total & 0xFFFF;
+                n_single += total >> 16;
+            }
+            n_uniq += seg_count;
+        }
+
+        // ---- the next pending range
+        cur = end;
+        if (depth > 0) {
+            __syncthreads(); // (the LDS is free again)
+            --depth;
+            end = s_stack[depth];
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int4 *info = ws.part_info + 2 * (t * args.parts + part);
+        info[0] = make_int4(max(part_base, 0), n_uniq, n_chunk, n_single);
+        info[1] = make_int4(s_class[0] | (s_class[1] << 16), s_class[2] | (s_class[3] << 16), s_class[4], 0);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Kernel 2 of dqrm_dedupe: the parts' lists -> one dense, global chunk list and the index-only outputs (unique rows,
+// segment offsets, table offsets, count).
+//
+// Dense chunk descriptor, as the summing kernels read it:
+//   x  global sorted position of the chunk's first lookup
+//   y  len | index of the chunk inside its segment | chunks in the segment (as above)
+//   z  global index of the segment (row of `values`)
+//   w  table
+// Dense single descriptor: x bag, y global index of the segment, z table.
+__global__ __launch_bounds__(kSegThreads) void dedupe_finish_kernel(DedupeArgs args)
+{
+    const DedupeBatch &a = args.b[blockIdx.y];
+    const BwdWs &ws = a.ws;
+    // exclusive sums over the parts: segments, chunks, singles, chunks of each class (V + 1 entries each); and the parts'
+    // first sorted positions
+    constexpr int kSums = 3 + kChunkClasses, kWaves = kSegThreads / kWave;
+    __shared__ int s_sum[kSums][kMaxParts + 1], s_base[kMaxParts];
+    __shared__ int s_w[kSums][kWaves];
+    const int *s_uniq = s_sum[0], *s_chunk = s_sum[1], *s_single = s_sum[2];
+    const int T = args.T, parts = args.parts, V = T * parts;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    {
+        const int per = (V + kSegThreads - 1) / kSegThreads; // consecutive parts per thread
+        auto counts_of = [&](int v, int (&c)[kSums]) {
+            const int4 x = ws.part_info[2 * v], y = ws.part_info[2 * v + 1];
+            c[0] = x.y, c[1] = x.z, c[2] = x.w;
+            c[3] = y.x & 0xFFFF, c[4] = (int)((unsigned)y.x >> 16), c[5] = y.y & 0xFFFF, c[6] = (int)((unsigned)y.y >> 16), c[7] = y.z;
+            s_base[v] = x.x;
+        };
+        static_assert(kChunkClasses == 5, "counts_of");
+        int mine[kSums] = {}, c[kSums];
+        for (int v = tid * per; v < min((tid + 1) * per, V); ++v) {
+            counts_of(v, c);
+#pragma unroll
+            for (int k = 0; k < kSums; ++k) mine[k] += c[k];
+        }
+        int before[kSums];
+#pragma unroll
+        for (int k = 0; k < kSums; ++k) {
+            const int incl = wave_incl_scan_add(mine[k], lane);
+            if (lane == kWave - 1) s_w[k][wave] = incl;
+            before[k] = incl - mine[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSums; ++k)
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) before[k] += w < wave ? s_w[k][w] : 0;
+        for (int v = tid * per; v < min((tid + 1) * per, V); ++v) {
+            if (per > 1) counts_of(v, c); // (one part per thread: they are still here)
+#pragma unroll
+            for (int k = 0; k < kSums; ++k) {
+                s_sum[k][v] = before[k];
+                before[k] += c[k];
+                if (v == V - 1) s_sum[k][V] = before[k];
+            }
+        }
+        __syncthreads();
+    }
+    const int C = s_chunk[V], U = s_uniq[V], S = s_single[V];
+    if (blockIdx.x == 0) {
+        for (int k = tid; k <= T; k += kSegThreads) a.tuo[k] = s_uniq[k * parts];
+        if (tid == 0) {
+            *a.num_unique = U;
+            a.seg_offsets[U] = (int32_t)a.N;
+            ws.totals[0] = C;
+            ws.totals[1] = U;
+            ws.totals[2] = S;
+        }
+    }
+    const int first = (int)(blockIdx.x * kSegThreads) + tid, step = (int)(gridDim.x * kSegThreads);
+    // Chunks, kChunksPerWave consecutive ones per wave: their descriptors (a lane each, the other lanes along for the
+    // ride), then the bags of their lookups at a place that depends on the chunk's index alone (a chunk has at least
+    // two lookups, so there are at most N / 2 chunks): half a wave per chunk.
+    constexpr int kChunksPerWave = 8;
+    for (int c0 = first / kWave * kChunksPerWave; c0 < C; c0 += step / kWave * kChunksPerWave) {
+        const int c = min(c0 + (lane & (kChunksPerWave - 1)), C - 1);
+        const int v = table_of(s_chunk, V, c);
+        const int4 d = ws.chunk_local[s_base[v] + (c - s_chunk[v])];
+        const int j = s_uniq[v] + (d.z & 0xFFFF);
+        // its place in the dense list; by length: after the chunks of shorter classes, then those of its own in earlier parts
+        int place = c;
+        if (args.by_length) {
+            const int cls = chunk_class(desc_len(d));
+            place = s_sum[3 + cls][v] + (int)((unsigned)d.z >> 16);
+#pragma unroll
+            for (int k = 0; k + 1 < kChunkClasses; ++k) place += k < cls ? s_sum[3 + k][V] : 0;
+        }
+        if (lane < kChunksPerWave && c0 + lane < C) {
+            if (desc_kchunk(d) == 0) { // first chunk of its segment: d.x is the segment's head
+                a.uniq_rows[j] = (int64_t)(unsigned)d.w;
+                a.seg_offsets[j] = d.x;
+            }
+            ws.chunk_desc[place] = make_int4(d.x, d.y, j, (int)args.by_parts.div((unsigned)v));
+        }
+        int bag[kChunksPerWave / 2], to[kChunksPerWave / 2];
+        const int i = lane & (DQRM_SEG_CHUNK - 1);
+#pragma unroll
+        for (int q = 0; q < kChunksPerWave / 2; ++q) {
+            const int from = 2 * q + (lane >> 5);
+            const int x = __shfl(d.x, from, kWave), len = __shfl(desc_len(d), from, kWave);
+            to[q] = __shfl(place, from, kWave);
+            bag[q] = ws.sorted_bag[x + min(i, len - 1)];
+        }
+#pragma unroll
+        for (int q = 0; q < kChunksPerWave / 2; ++q)
+            if (c0 + 2 * q + (lane >> 5) < C) // (past the chunk's end: its last bag again)
+                ws.chunk_bags[(int64_t)to[q] * DQRM_SEG_CHUNK + i] = bag[q];
+    }
+    for (int c = first; c < S; c += step) {
+        const int v = table_of(s_single, V, c);
+        const int4 d = ws.single_local[s_base[v] + (c - s_single[v])]; // {sorted position, bag, segment, row}
+        const int j = s_uniq[v] + d.z;
+        a.uniq_rows[j] = (int64_t)(unsigned)d.w;
+        a.seg_offsets[j] = d.x;
+        ws.single_desc[c] = make_int4(d.y, j, (int)args.by_parts.div((unsigned)v), 0);
+    }
+}
+
+} // namespace dqrm

@@ -1,0 +1,107 @@
+"""dqrm_dedupe at the sizes where its split of a table's rows into ranges changes hands: the table sizes around the ranges
+(fewer rows than ranges, one row, a hot row that overflows what a workgroup sorts in LDS), the lookups per table at which
+another workgroup size or the tile-by-tile partition takes over, bags of equal and unequal length and more bags than fit the
+LDS, bad indices at every kind of place.  Everything is an integer: exact equality with the oracle, except where indices are
+bad, which the oracle does not take (numpy's stable sort then)."""
+import numpy as np
+import pytest
+
+from gen import Workload
+from helpers import GpuRun, assert_exact
+
+pytestmark = pytest.mark.gpu
+
+
+def _dedupe(wl, idx, off, B):
+    run = GpuRun(wl.row_offsets, wl.D, np.zeros((wl.R, wl.D), np.float32), B, len(idx), with_packed=False, want_codes=False)
+    run.upload_batch(idx, off)
+    b = run.bufs
+    b.workspace.fill_(0xA5)  # (whatever is in it)
+    run.dq.dqrm_dedupe(run.tables, run.idx, run.off, B, b.sorted_pos, b.uniq_rows, b.seg_offsets, b.table_uniq_offsets,
+                       b.num_unique, b.workspace)
+    U = int(b.num_unique.cpu().item())
+    return run, dict(U=np.array([U]), sorted_pos=b.sorted_pos.cpu().numpy()[:len(idx)], uniq_rows=b.uniq_rows.cpu().numpy()[:U],
+                     seg_offsets=b.seg_offsets.cpu().numpy()[:U + 1], table_uniq_offsets=b.table_uniq_offsets.cpu().numpy())
+
+
+def _expected(wl, idx, off, B):
+    """From the definition: a stable sort by (table, row), bad rows last in their table and in no segment."""
+    pos, rows, seg, tuo = [], [], [], [0]
+    for t in range(wl.T):
+        lo, hi = int(off[t * B]), int(off[(t + 1) * B])
+        v, n = idx[lo:hi], int(wl.cards[t])
+        key = np.where((v < 0) | (v >= n), n, v)
+        order = np.argsort(key, kind="stable")
+        k = key[order]
+        heads = np.flatnonzero((k < n) & (np.concatenate([[-1], k[:-1]]) != k))
+        pos.append(lo + order)
+        rows.append(k[heads])
+        seg.append(lo + heads)
+        tuo.append(tuo[-1] + len(heads))
+    cat = np.concatenate
+    return dict(U=np.array([tuo[-1]]), sorted_pos=cat(pos).astype(np.int32), uniq_rows=cat(rows).astype(np.int64),
+                seg_offsets=cat(seg + [[len(idx)]]).astype(np.int32), table_uniq_offsets=np.array(tuo, np.int32))
+
+
+# lookups per table; tables: one row, fewer rows than ranges, as many as a digit has values and one more, many
+@pytest.mark.parametrize("n", [1, 63, 512, 513, 2047, 4096, 4097, 8192, 8193, 16384, 16385, 65535, 65536])
+@pytest.mark.parametrize("cards", [(1, 3, 255, 40), (256, 257, 7_000_003)], ids=["tiny", "large"])
+def test_lookups_per_table(n, cards):
+    cards = np.array(cards, np.int64)
+    T = len(cards)
+    wl = Workload(name="ranges", T=T, D=8, B=n, alpha=1.05, seed=n + T, cards=cards)
+    idx, off = wl.batch(0)
+    print(f"ranges: {n} lookups in each of {cards.tolist()}", flush=True)
+    run, got = _dedupe(wl, idx, off, n)
+    for k, v in _expected(wl, idx, off, n).items():
+        assert_exact(got[k], v, f"n={n} {k}")
+    assert run.status()[0] == 0
+
+
+@pytest.mark.parametrize("n,threads", [(400, 256), (3000, 512), (8000, 1024), (40000, 1024)])
+@pytest.mark.parametrize("bags", ["ragged", "pairs", "pretend", "sparse"])
+def test_hot_rows_and_bags(n, threads, bags):
+    """One table with nearly all of the batch's lookups (more than its share, so a range overflows the LDS and is taken in
+    pieces), most of them to one row at the front, in the middle or at the end of its rows; the bags of equal length, of
+    unequal length, of unequal length adding up as if they were equal, and many more bags than lookups."""
+    T, big = 3, min(3 * n - 2, 65536)
+    rng = np.random.default_rng(n + len(bags))
+    B = {"ragged": 777, "pairs": (big + 1) // 2, "pretend": big // 5, "sparse": 20011}[bags]
+    cards = np.array([2000, 50, 100_000], np.int64)
+    for hot in (0, 49_999, 99_999):
+        if bags == "pairs":
+            lens = np.full(B, 2, np.int64)
+        elif bags == "pretend":
+            lens = np.full(B, 5, np.int64)
+            lens[: B // 2] += 1
+            lens[B - B // 2:] -= 1
+        else:
+            lens = np.bincount(rng.integers(0, B, big), minlength=B).astype(np.int64)
+        lens = np.concatenate([(np.arange(B) == 0), (np.arange(B) == B - 1), lens]).astype(np.int64)
+        off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        m = int(off[-1]) - 2
+        last = rng.integers(0, 100_000, m)
+        last[rng.random(m) < 0.7] = hot
+        last[rng.random(m) < 0.2] = min(hot + 1, 99_999)
+        last[rng.random(m) < 0.01] = 100_000  # bad: past the end
+        last[rng.random(m) < 0.01] = -7
+        idx = np.concatenate([[1999], [0], last]).astype(np.int64)
+        wl = Workload(name="hot", T=T, D=8, B=B, alpha=1.05, seed=1, cards=cards)
+        print(f"hot row {hot}, {m} lookups in {B} bags ({bags})", flush=True)
+        run, got = _dedupe(wl, idx, off, B)
+        for k, v in _expected(wl, idx, off, B).items():
+            assert_exact(got[k], v, f"n={n} hot={hot} {bags} {k}")
+        code, tb, val = run.status()
+        assert code == run.dq.ERR_INDEX_OUT_OF_RANGE and tb == 2 and val in (100_000, -7)
+        # the bags reach the segment sums: gradients that name their bag (sums of integers below 2^24, exact)
+        g = np.zeros((B, T, 8), np.float32)
+        g[:, 2, 0] = np.arange(B) % 251
+        run.upload_batch(idx, off, g)
+        b = run.bufs
+        run.dq.dqrm_segment_sum(run.tables, B, len(idx), run.grad, b.values, b.g_absmax, b.workspace)
+        bag = np.repeat(np.arange(B), np.diff(off[2 * B:]))
+        good = (last >= 0) & (last < 100_000)
+        want = np.bincount(last[good], weights=(bag[good] % 251).astype(np.float64), minlength=100_000)
+        s0 = int(got["table_uniq_offsets"][2])
+        rows = got["uniq_rows"][s0:]
+        assert_exact(b.values.cpu().numpy()[s0:s0 + len(rows), 0].astype(np.float64), want[rows], f"n={n} hot={hot} {bags} sums")
