@@ -944,6 +944,29 @@ hipError_t linear_bwd_input(hipStream_t st, const float *dZ, const float *W, con
     return launch_gemm_group<dqrm::kOpRC, dqrm::kOpWideVec>(st, grp);
 }
 
+// The interaction, forward or backward: one wave per sample, as many waves per workgroup as the LDS holds.  Vectors of a
+// multiple of 4 floats are read 16 bytes at a time (from any 4-byte boundary).
+hipError_t launch_interact(hipStream_t st, const dqrm::InteractArgs &ia, bool backward, int lin_floats)
+{
+    const int V = ia.T + 1;
+    const size_t per = sizeof(float) * (backward ? dqrm::inter_wave_floats_bwd(V, ia.D)
+                                                 : dqrm::inter_wave_floats(V, ia.D, lin_floats ? ia.lin_k : 0));
+    const size_t shared = sizeof(float) * (size_t)lin_floats;
+    const int waves = (int)std::min<size_t>(dqrm::kInterWaves, (dqrm::kInterLdsBytes - shared) / per); // (>= 1: at most 37 KB)
+    const dim3 grid((ia.B + waves - 1) / waves), block(waves * dqrm::kWave);
+    const size_t lds = shared + waves * per;
+    void (*k)(dqrm::InteractArgs);
+    const bool vec = ia.D % 4 == 0;
+    if (V <= 32)
+        k = backward ? (vec ? dqrm::interact_bwd_kernel<1, true> : dqrm::interact_bwd_kernel<1, false>)
+                     : (vec ? dqrm::interact_fwd_kernel<1, true> : dqrm::interact_fwd_kernel<1, false>);
+    else
+        k = backward ? (vec ? dqrm::interact_bwd_kernel<2, true> : dqrm::interact_bwd_kernel<2, false>)
+                     : (vec ? dqrm::interact_fwd_kernel<2, true> : dqrm::interact_fwd_kernel<2, false>);
+    hipLaunchKernelGGL(k, grid, block, lds, st, ia);
+    return hipGetLastError();
+}
+
 // One layer's weight-gradient product  [dZ^T * X | dZ^T * 1]  ([out][in + 1], the last column is the bias
 // gradient) with the batch dimension cut into `splits` slices: partials[s][out][in + 1].
 dqrm::GemmArgs weight_grad_problem(const float *dZ, const float *X, float *partials, int B, int in, int out, int splits)
@@ -1037,11 +1060,12 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
     }
 
     // ---- forward
-    // The bottom MLP's last layer rides along in the interaction kernels when its input is short enough for their LDS
-    // (its product is tiny: 64 -> 16 in the paper's Kaggle model), and a first layer with a short reduction (the
-    // 13 dense features) has a kernel of its own: both are all launch cost as products on the matrix cores.
+    // The bottom MLP's last layer rides along in the interaction kernels while its weights are few (64 -> 16 in the
+    // paper's Kaggle model; every sample reads them all), and a first layer with a short reduction (the 13 dense
+    // features) has a kernel of its own: both are all launch cost as products on the matrix cores.
     const int bl_last = m->bot_layers - 1;
-    const bool ride = m->bot_dims[bl_last] <= dqrm::kInterMaxLinK;
+    const int lin_floats = (int)std::min<int64_t>((int64_t)D * dqrm::inter_lin_pitch(m->bot_dims[bl_last]), 1 << 20);
+    const bool ride = lin_floats <= dqrm::kInterLinFloats;
     const float *x = dense_x;
     for (int l = 0; l < m->bot_layers - (ride ? 1 : 0); ++l) {
         const int in = m->bot_dims[l], out = m->bot_dims[l + 1];
@@ -1062,8 +1086,7 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
         ia.lin_x = x, ia.lin_w = bot_wf[bl_last], ia.lin_b = m->bot_b[bl_last], ia.lin_y = F(L.bot_act[bl_last]);
         ia.lin_k = m->bot_dims[bl_last];
     }
-    hipLaunchKernelGGL(dqrm::interact_fwd_kernel, dim3(B), dim3(dqrm::kInterThreads),
-                       dqrm::interact_lds_bytes(T, D, false, ride ? ia.lin_k : 0), st, ia);
+    DQRM_HIP_CHECK(launch_interact(st, ia, false, ride ? lin_floats : 0));
     x = F(L.R);
     const int last = m->top_layers - 1;
     for (int l = 0; l < last; ++l) {
@@ -1093,8 +1116,7 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
     ia.bot = bot_out, ia.dR = F(L.dR), ia.dbot = F(L.bot_dz[bl_last]), ia.demb = grad_emb, ia.bot_mask = bot_out;
     const bool ride_back = ride && bl_last > 0; // (a first layer's input gradient is not needed)
     if (ride_back) ia.lin_mask = F(L.bot_act[bl_last - 1]), ia.lin_dx = F(L.bot_dz[bl_last - 1]);
-    hipLaunchKernelGGL(dqrm::interact_bwd_kernel, dim3(B), dim3(dqrm::kInterThreads), dqrm::interact_lds_bytes(T, D, true), st,
-                       ia);
+    DQRM_HIP_CHECK(launch_interact(st, ia, true, 0));
     for (int l = bl_last - (ride_back ? 1 : 0); l > 0; --l)
         DQRM_HIP_CHECK(linear_bwd_input(st, F(L.bot_dz[l]), bot_wf[l], F(L.bot_act[l - 1]), F(L.bot_dz[l - 1]), B,
                                         m->bot_dims[l], m->bot_dims[l + 1]));

@@ -762,16 +762,36 @@ struct InteractArgs {
     int lin_k;
 };
 
-constexpr int kInterThreads = 128;
+constexpr int kInterThreads = 256; // at most; a wave per sample
+constexpr int kInterWaves = kInterThreads / kWave;
 constexpr int kInterMaxV = 64;      // vectors per sample, at most (host)
 constexpr int kInterMaxZ = 64 * 64; // V * D floats, at most (host)
+constexpr int kInterLdsBytes = 64 * 1024; // of a workgroup, at most
 
-// dynamic LDS of the two kernels below (at most ~33 KB: V <= 64, V * D <= 4096)
-constexpr int kInterMaxLinK = 1024; // widest input of a bottom layer that rides along (host)
-inline size_t interact_lds_bytes(int T, int D, bool backward, int lin_k = 0)
+// Layout of a wave's LDS: the sample's vectors, rows of Dp = D rounded up to 8 floats (zeros past D) and a pitch of
+// Dp + 4 (the lanes of a wave read 16 bytes of different rows: a pitch that is a multiple of the bank count would put
+// them all into the same banks); the backward kernel adds the symmetric matrix of pair gradients.
+__host__ __device__ inline int inter_dp(int D) { return (D + 7) & ~7; }
+__host__ __device__ inline int inter_pitch(int D) { return inter_dp(D) + 4; }
+__host__ __device__ inline int inter_tiles(int V) { return (V + 31) / 32; }
+__host__ __device__ inline int inter_sp(int V) { return 32 * inter_tiles(V) + 4; } // pitch of the pair-gradient matrix
+// The bottom MLP's last layer rides along in these kernels while its weights are few: every sample's wave reads them all
+// (from LDS in the forward, from the first-level cache in the backward).  Rows of 4 * odd floats: the 16 outputs that a
+// wave computes at a time then start in different banks.
+__host__ __device__ inline int inter_lin_pitch(int K)
 {
-    const int V = T + 1;
-    return sizeof(float) * ((backward ? (size_t)V * D + (size_t)V * (V | 1) + (size_t)D : (size_t)V * (D + 1)) + (size_t)lin_k);
+    const int q = (K + 3) / 4;
+    return 4 * (q | 1);
+}
+constexpr int kInterLinFloats = 4096; // weights (with their padding) of a layer that rides along, at most (host)
+// floats of LDS per wave: forward (lin_k: the riding layer's input width, or 0), backward
+__host__ __device__ inline int inter_wave_floats(int V, int D, int lin_k)
+{
+    return V * inter_pitch(D) + (lin_k ? inter_lin_pitch(lin_k) : 0);
+}
+__host__ __device__ inline int inter_wave_floats_bwd(int V, int D)
+{
+    return V * inter_pitch(D) + 32 * inter_tiles(V) * inter_sp(V);
 }
 
 // pair index p -> (i, j), i > j, p = i(i-1)/2 + j
@@ -783,102 +803,262 @@ __device__ __forceinline__ void pair_of(int p, int &i, int &j)
     j = p - i * (i - 1) / 2;
 }
 
+// What the lanes of a wave wrote to their LDS may be read by its other lanes from here on: the wave's LDS operations
+// complete in order, so this only keeps the compiler from moving them.
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Vectors 1 .. T of a sample (T * D consecutive floats) into rows 1 .. T of z, by one wave.  request() asks for the first
+// kAhead loads per lane, so that they travel beside whatever else the kernel needs first; settle() does the rest.
+template <bool VEC>
+struct InterRows {
+    static constexpr int kAhead = 8;
+    Float4Dw q[kAhead];
+    const float *emb;
+    int cols, count, lane;
+
+    __device__ __forceinline__ void load(int e0)
+    {
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const int e = min(e0 + k * kWave, count - 1);
+            if (VEC)
+                q[k] = *reinterpret_cast<const Float4Dw *>(emb + 4ll * e);
+            else
+                q[k][0] = emb[e];
+        }
+    }
+    __device__ __forceinline__ void request(const float *from, int T, int D, int my_lane)
+    {
+        emb = from, lane = my_lane, cols = VEC ? D / 4 : D, count = T * cols;
+        load(lane);
+    }
+    __device__ __forceinline__ void settle(float *z, int pitch)
+    {
+        const int dr = kWave / cols, dc = kWave - dr * cols;
+        int r = lane / cols, c = lane - r * cols;
+        for (int e0 = lane;;) {
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                if (e0 + k * kWave < count) {
+                    float *at = z + (1 + r) * pitch + (VEC ? 4 * c : c);
+                    if (VEC)
+                        *reinterpret_cast<float4 *>(at) = make_float4(q[k][0], q[k][1], q[k][2], q[k][3]);
+                    else
+                        *at = q[k][0];
+                }
+                r += dr, c += dc;
+                if (c >= cols) c -= cols, ++r;
+            }
+            e0 += kAhead * kWave;
+            if (e0 >= count) break;
+            load(e0);
+        }
+    }
+};
+
+// One wave per sample, V <= 32 NT.  The pair products are the lower triangle of Z * Z^T on the matrix cores; both operands
+// are the same registers (lane l holds Z[l % 32][.] as a row of A and as a column of B), read from LDS 16 bytes at a
+// time.  Rows past V re-read the last vector: their products are not stored.  A tile's product s pairs the elements s and
+// Dp / 2 + s of the vectors.
+// What bounds it: reading the embeddings (54.5 MB at 27 vectors of 64 x 8192 samples).  There, with the bottom MLP's last layer
+// (256 -> 64) as a product of its own: 22 us (kernel alone); dot products with a thread each and that layer's weights read again
+// for every sample took 90 us.
+template <int NT, bool VEC>
 __global__ __launch_bounds__(kInterThreads) void interact_fwd_kernel(InteractArgs a)
 {
-    // rows one float apart from a multiple of the bank count: the lanes of a wave read different rows at the
-    // same d, and with a pitch of D = 16 all of them would fall into two banks
-    extern __shared__ float inter_lds[]; // V * (D + 1) (+ lin_k) floats (interact_lds_bytes)
-    float *z = inter_lds;
-    const int b = blockIdx.x, V = a.T + 1, D = a.D, pitch = D + 1;
-    if (a.lin_w) {
-        // the embeddings travel while the layer is computed: 8 threads per output, each a strided eighth of the sum
-        for (int e = D + (int)threadIdx.x; e < V * D; e += kInterThreads) {
-            const int i = e / D, d = e - i * D;
-            z[i * pitch + d] = a.emb[(long long)b * a.T * D + (e - D)];
+    extern __shared__ __align__(16) float inter_lds[]; // weights of the riding layer, then inter_wave_floats() per wave
+    const int V = a.T + 1, D = a.D, Dp = inter_dp(D), pitch = inter_pitch(D), K = a.lin_k;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), waves = (int)blockDim.x / kWave;
+    const int lp = inter_lin_pitch(K), lin = a.lin_w ? D * lp : 0;
+    const int b = (int)blockIdx.x * waves + wave;
+    const bool live = b < a.B;
+    float *z = inter_lds + lin + wave * inter_wave_floats(V, D, a.lin_w ? K : 0);
+    const long long bc = min(b, a.B - 1);
+    InterRows<VEC> rows;
+    rows.request(a.emb + bc * a.T * D, a.T, D, lane);
+    const float *first = a.lin_w ? a.lin_x + bc * K : a.bot + bc * D; // input of the riding layer, or vector 0 itself
+    const int nf = a.lin_w ? K : D;
+    const float f0 = first[min(lane, nf - 1)];
+    if (a.lin_w) { // (all waves of the workgroup)
+        for (int e = threadIdx.x; e < D * K; e += blockDim.x) {
+            const int d = e / K;
+            inter_lds[d * lp + (e - d * K)] = a.lin_w[e];
         }
-        float *xin = inter_lds + V * pitch; // lin_k floats
-        const int K = a.lin_k;
-        for (int k = threadIdx.x; k < K; k += kInterThreads) xin[k] = a.lin_x[(long long)b * K + k];
         __syncthreads();
-        for (int e0 = 0; e0 < D * 8; e0 += kInterThreads) { // (kInterThreads is a multiple of 8: teams stay whole)
-            const int e = e0 + (int)threadIdx.x;
-            const int d = min(e >> 3, D - 1), part = e & 7;
-            const float *w = a.lin_w + (long long)d * K;
+    }
+    if (!live) return;
+    float *r = a.R + (long long)b * (D + V * (V - 1) / 2);
+    rows.settle(z, pitch);
+    if (a.lin_w) {
+        float *x = z + V * pitch; // lp floats
+        if (lane < K) x[lane] = f0;
+        for (int k = lane + kWave; k < K; k += kWave) x[k] = first[k];
+        wave_lds_order();
+        // 4 lanes per output, each a strided quarter of the sum
+        for (int d0 = 0; d0 < D; d0 += kWave / 4) {
+            const int d = d0 + (lane >> 2), part = lane & 3;
+            const float *w = inter_lds + min(d, D - 1) * lp;
+            const float bias = a.lin_b[min(d, D - 1)];
             float s = 0.0f;
-            for (int k = part; k < K; k += 8) s = __builtin_fmaf(xin[k], w[k], s);
+            for (int k = part; k < K; k += 4) s = __builtin_fmaf(x[k], w[k], s);
             s += __shfl_xor(s, 1, kWave);
             s += __shfl_xor(s, 2, kWave);
-            s += __shfl_xor(s, 4, kWave);
-            if (part == 0 && e < D * 8) {
-                const float y = fmaxf(s + a.lin_b[d], 0.0f);
+            if (part == 0 && d < D) {
+                const float y = fmaxf(s + bias, 0.0f);
                 z[d] = y;
                 a.lin_y[(long long)b * D + d] = y;
+                r[d] = y;
             }
         }
     } else {
-        for (int e = threadIdx.x; e < V * D; e += kInterThreads) {
-            const int i = e / D, d = e - i * D;
-            z[i * pitch + d] = e < D ? a.bot[(long long)b * D + e] : a.emb[(long long)b * a.T * D + (e - D)];
+        if (lane < D) z[lane] = r[lane] = f0;
+        for (int d = lane + kWave; d < D; d += kWave) z[d] = r[d] = first[d];
+    }
+    if (Dp != D)
+        for (int e = lane; e < V * (Dp - D); e += kWave) z[e / (Dp - D) * pitch + D + e % (Dp - D)] = 0.0f;
+    wave_lds_order();
+    const int w = lane & 31, h = lane >> 5;
+    floatx16 acc[NT == 1 ? 1 : 3]; // tiles (0, 0), (1, 0), (1, 1)
+#pragma unroll
+    for (int t = 0; t < (NT == 1 ? 1 : 3); ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.0f;
+    const float *z0 = z + min(w, V - 1) * pitch + h * (Dp / 2), *z1 = z + min(32 + w, V - 1) * pitch + h * (Dp / 2);
+#pragma unroll 4
+    for (int s = 0; s < Dp / 2; s += 4) {
+        const float4 q4 = *reinterpret_cast<const float4 *>(z0 + s);
+        const float q[4] = {q4.x, q4.y, q4.z, q4.w};
+        if (NT == 1) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(q[k], q[k], acc[0], 0, 0, 0);
+        } else {
+            const float4 p4 = *reinterpret_cast<const float4 *>(z1 + s);
+            const float p[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(q[k], q[k], acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(p[k], q[k], acc[1], 0, 0, 0);
+                acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(p[k], p[k], acc[2], 0, 0, 0);
+            }
         }
     }
-    __syncthreads();
-    const int P = V * (V - 1) / 2, W = D + P;
-    float *r = a.R + (long long)b * W;
-    for (int e = threadIdx.x; e < W; e += kInterThreads) {
-        if (e < D) {
-            r[e] = z[e];
-        } else {
-            int i, j;
-            pair_of(e - D, i, j);
-            const float *zi = z + i * pitch, *zj = z + j * pitch;
-            float s = 0.0f;
-            for (int d = 0; d < D; ++d) s += zi[d] * zj[d];
-            r[e] = s;
+    // lane l holds column j = l % 32 and rows 8 (v / 4) + 4 (l / 32) + v % 4 of a tile
+#pragma unroll
+    for (int t = 0; t < (NT == 1 ? 1 : 3); ++t) {
+        const int i0 = t == 0 ? 0 : 32, j = (t == 2 ? 32 : 0) + w;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int i = i0 + 8 * (v >> 2) + 4 * h + (v & 3);
+            if (i < V && j < i) r[D + i * (i - 1) / 2 + j] = acc[t][v];
         }
     }
 }
 
-// dZ[i] = sum over j != i of dP(i, j) * Z[j]  (+ dR[0..D) for i = 0): the pair gradients are spread into a
-// symmetric V x V matrix with a zero diagonal first, so that the sum runs over all j without a case distinction
-// (terms in the order j = 0 .. V-1).
+// dZ[i] = sum over j != i of dP(i, j) * Z[j]  (+ dR[0..D) for i = 0): the pair gradients are spread into a symmetric
+// matrix S with a zero diagonal (and zeros past V), and dZ = S * Z goes to the matrix cores, a wave per sample (vectors past
+// V are zeros in both).
+// What bounds it: reading the embeddings and writing their gradients (109 MB at 27 vectors of 64 x 8192 samples).  There:
+// 35 us; a thread per element with the sum from LDS took 86 us.
+template <int NT, bool VEC>
 __global__ __launch_bounds__(kInterThreads) void interact_bwd_kernel(InteractArgs a)
 {
-    extern __shared__ float inter_lds[]; // V * D + V * (V | 1) + D floats (interact_lds_bytes)
-    const int b = blockIdx.x, V = a.T + 1, D = a.D, vp = V | 1; // odd pitch
-    float *z = inter_lds, *dpf = inter_lds + V * D, *dzl = dpf + V * vp; // dzl: D floats, the gradient w.r.t. bot
-    const int P = V * (V - 1) / 2, W = D + P;
-    for (int e = threadIdx.x; e < V * D; e += kInterThreads)
-        z[e] = e < D ? a.bot[(long long)b * D + e] : a.emb[(long long)b * a.T * D + (e - D)];
-    const float *dr = a.dR + (long long)b * W;
-    for (int p = threadIdx.x; p < P; p += kInterThreads) {
+    extern __shared__ __align__(16) float inter_lds[]; // inter_wave_floats_bwd() per wave
+    const int V = a.T + 1, D = a.D, pitch = inter_pitch(D), sp = inter_sp(V);
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    const int b = (int)blockIdx.x * ((int)blockDim.x / kWave) + wave;
+    if (b >= a.B) return; // (no barrier below)
+    float *S = inter_lds + wave * inter_wave_floats_bwd(V, D), *z = S + 32 * NT * sp;
+    const int P = V * (V - 1) / 2;
+    const float *dr = a.dR + (long long)b * (D + P);
+    // everything is requested before the first wait
+    InterRows<VEC> rows;
+    rows.request(a.emb + (long long)b * a.T * D, a.T, D, lane);
+    constexpr int kPairsAhead = 8;
+    float g[kPairsAhead];
+#pragma unroll
+    for (int k = 0; k < kPairsAhead; ++k) g[k] = dr[D + min(lane + k * kWave, P - 1)];
+    const float f0 = a.bot[(long long)b * D + min(lane, D - 1)];
+    for (int e = lane; e < 32 * NT * sp / 4; e += kWave) reinterpret_cast<float4 *>(S)[e] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    wave_lds_order();
+    auto spread = [&](int p, float x) {
         int i, j;
         pair_of(p, i, j);
-        const float g = dr[D + p];
-        dpf[i * vp + j] = g;
-        dpf[j * vp + i] = g;
-    }
-    for (int i = threadIdx.x; i < V; i += kInterThreads) dpf[i * vp + i] = 0.0f;
-    __syncthreads();
-    for (int e = threadIdx.x; e < V * D; e += kInterThreads) {
-        const int i = e / D, d = e - i * D;
-        float s = (i == 0) ? dr[d] : 0.0f;
-        const float *row = dpf + i * vp, *col = z + d;
-        for (int j = 0; j < V; ++j) s += row[j] * col[j * D];
-        if (i == 0) {
-            const long long off = (long long)b * D + d;
-            if (a.bot_mask) s = a.bot_mask[off] > 0.0f ? s : 0.0f;
-            a.dbot[off] = s;
-            dzl[d] = s;
-        } else {
-            a.demb[(long long)b * a.T * D + (e - D)] = s;
+        S[i * sp + j] = x;
+        S[j * sp + i] = x;
+    };
+#pragma unroll
+    for (int k = 0; k < kPairsAhead; ++k)
+        if (lane + k * kWave < P) spread(lane + k * kWave, g[k]);
+    for (int p = lane + kPairsAhead * kWave; p < P; p += kWave) spread(p, dr[D + p]);
+    rows.settle(z, pitch);
+    if (lane < D) z[lane] = f0;
+    for (int d = lane + kWave; d < D; d += kWave) z[d] = a.bot[(long long)b * D + d];
+    wave_lds_order();
+    const int w = lane & 31, h = lane >> 5;
+    float mine[NT][NT][16]; // this lane's 16 elements of S per tile: row l % 32, columns 16 (l / 32) + s
+#pragma unroll
+    for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+        for (int tk = 0; tk < NT; ++tk)
+#pragma unroll
+            for (int s = 0; s < 16; s += 4) {
+                const float4 q = *reinterpret_cast<const float4 *>(S + (32 * ti + w) * sp + 32 * tk + 16 * h + s);
+                mine[ti][tk][s] = q.x, mine[ti][tk][s + 1] = q.y, mine[ti][tk][s + 2] = q.z, mine[ti][tk][s + 3] = q.w;
+            }
+    for (int d0 = 0; d0 < D; d0 += 32) {
+        const int d = d0 + w;
+        const bool in = d < D;
+        const float *zc = z + min(d, D - 1);
+        floatx16 acc[NT];
+#pragma unroll
+        for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[ti][v] = 0.0f;
+#pragma unroll
+        for (int tk = 0; tk < NT; ++tk) {
+            float x[16];
+#pragma unroll
+            for (int s = 0; s < 16; ++s) {
+                const int k = 32 * tk + 16 * h + s;
+                const float q = zc[min(k, V - 1) * pitch];
+                x[s] = k < V ? q : 0.0f;
+            }
+#pragma unroll
+            for (int s = 0; s < 16; ++s)
+#pragma unroll
+                for (int ti = 0; ti < NT; ++ti)
+                    acc[ti] = __builtin_amdgcn_mfma_f32_32x32x2f32(mine[ti][tk][s], x[s], acc[ti], 0, 0, 0);
         }
+        // lane l holds column d = d0 + l % 32 and rows 8 (v / 4) + 4 (l / 32) + v % 4 of a tile
+#pragma unroll
+        for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int i = 32 * ti + 8 * (v >> 2) + 4 * h + (v & 3);
+                if (!in || i >= V) continue;
+                if (i == 0) {
+                    const long long off = (long long)b * D + d;
+                    float s = acc[ti][v] + dr[d];
+                    if (a.bot_mask) s = a.bot_mask[off] > 0.0f ? s : 0.0f;
+                    a.dbot[off] = s;
+                    z[d] = s; // (this column of z has been used: the gradient w.r.t. bot takes row 0's place)
+                } else {
+                    a.demb[((long long)b * a.T + (i - 1)) * D + d] = acc[ti][v];
+                }
+            }
     }
     if (a.lin_w && a.lin_dx) { // on to the input gradient of the bottom MLP's last layer
-        __syncthreads();
+        wave_lds_order();
         const int K = a.lin_k;
-        for (int k = threadIdx.x; k < K; k += kInterThreads) {
+        for (int k = lane; k < K; k += kWave) {
             float s = 0.0f;
-            for (int d = 0; d < D; ++d) s = __builtin_fmaf(dzl[d], a.lin_w[(long long)d * K + k], s);
+            for (int d = 0; d < D; ++d) s = __builtin_fmaf(z[d], a.lin_w[(long long)d * K + k], s);
             if (a.lin_mask) s = a.lin_mask[(long long)b * K + k] > 0.0f ? s : 0.0f;
             a.lin_dx[(long long)b * K + k] = s;
         }

@@ -1,0 +1,64 @@
+"""The dense step's kernels at the edges of their tiles, against the float64 oracle: interactions of 2 .. 64 vectors of odd and
+even widths, and layers whose widths and batch fall on, just below and just above the tiles of the products."""
+import math
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _model(rng, T, D, bot, top):
+    V = T + 1
+    bot, top = list(bot) + [D], [D + V * (V - 1) // 2] + list(top) + [1]
+    layers = lambda dims: ([(rng.standard_normal((o, i)) * math.sqrt(2.0 / (i + o))).astype(np.float32)  # noqa: E731
+                            for i, o in zip(dims[:-1], dims[1:])],
+                           [(rng.standard_normal(o) * math.sqrt(1.0 / o)).astype(np.float32) for o in dims[1:]])
+    return (bot, *layers(bot), top, *layers(top))
+
+
+def _check(oracle, T, D, B, bot, top, seed=7):
+    import torch
+    import paper_2410_20046_amd as dq
+
+    print(f"T={T} D={D} B={B} bot={bot} top={top}", flush=True)
+    rng = np.random.default_rng(seed)
+    bot_dims, bw, bb, top_dims, tw, tb = _model(rng, T, D, bot, top)
+    x = np.exp(rng.standard_normal((B, bot_dims[0]))).astype(np.float32)
+    y = (rng.random(B) < 0.25).astype(np.float32)
+    emb = (rng.standard_normal((B, T, D)) * 0.25).astype(np.float32)
+    dev = torch.device("cuda:0")
+    m = dq.DenseModel(T, D, bot_dims, bw, bb, top_dims, tw, tb, dev)
+    ws = torch.empty(dq.dqrm_dense_workspace_bytes(m, B), dtype=torch.uint8, device=dev)
+    loss = torch.zeros(1, dtype=torch.float32, device=dev)
+    # both start 4 bytes past a 16-byte boundary
+    buf = torch.zeros(2 * (B * T * D + 8), dtype=torch.float32, device=dev)
+    n = B * T * D
+    emb_d, grad = buf[1:1 + n].view(B, T, D), buf[(n + 8) // 4 * 4 + 1:][:n].view(B, T, D)
+    emb_d.copy_(torch.from_numpy(emb))
+    dq.dqrm_dense_step(m, B, torch.from_numpy(x).to(dev), emb_d, torch.from_numpy(y).to(dev), 1.0, loss, grad, ws)
+    torch.cuda.synchronize()
+    f64 = lambda l: [np.ascontiguousarray(a, np.float64) for a in l]  # noqa: E731
+    BW, BB, TW, TB = f64(bw), f64(bb), f64(tw), f64(tb)
+    loss_o, grad_o = oracle.dense_step(bot_dims, BW, BB, top_dims, TW, TB, x, emb, y, 1.0)
+    assert abs(float(loss.item()) - loss_o) <= 1e-5 * max(1.0, abs(loss_o))
+    # Up to 8 products in a row, each a sum of at most ~2000 terms with a relative error of about sqrt(2000) * 2^-24 =
+    # 2.7e-6: 2e-5 of the 2-norm.  A pre-activation within that of zero may flip its ReLU's derivative: five times that.
+    close = lambda got, exp, what: (np.linalg.norm(got.astype(np.float64) - exp) <= 1e-4 * np.linalg.norm(exp)) or pytest.fail(  # noqa: E731
+        f"{what}: {np.linalg.norm(got.astype(np.float64) - exp) / np.linalg.norm(exp):.3g}")
+    close(grad.cpu().numpy(), grad_o.reshape(B, T, D), "grad_emb")
+    for name, got, before, exp in (("bot_w", m.bot_w, bw, BW), ("bot_b", m.bot_b, bb, BB), ("top_w", m.top_w, tw, TW), ("top_b", m.top_b, tb, TB)):
+        for l, (g, w, e) in enumerate(zip(got, before, exp)):
+            # the step itself (learning rate 1): the rounding of the weights is one part in 2^24 of them
+            step, want = g.cpu().numpy().astype(np.float64) - w, e - w
+            slack = 2.0 ** -24 * np.linalg.norm(w)
+            err = np.linalg.norm(step - want)
+            assert err <= 1e-4 * np.linalg.norm(want) + 2 * slack, (name, l, err, np.linalg.norm(want), slack)
+
+
+@pytest.mark.parametrize("T,D,B,bot", [
+    (1, 1, 3, [4]), (1, 16, 5, [13, 20]), (30, 12, 9, [13, 24]), (31, 20, 21, [13, 32]), (32, 8, 33, [9, 8]), (33, 24, 18, [13, 300]),
+    (63, 64, 70, [13, 64]), (40, 7, 37, [5, 11]), (2, 130, 40, [13, 16]), (1, 1500, 6, [3]), (26, 64, 130, [13, 512, 256]),
+    (5, 33, 64, [17, 120]), (15, 256, 24, [7, 8])])
+def test_interaction_shapes(oracle, T, D, B, bot):
+    _check(oracle, T, D, B, bot, [16])
