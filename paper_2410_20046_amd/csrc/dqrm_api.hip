@@ -808,20 +808,41 @@ int64_t dense_param_count(const dqrm_dense_model_t *m)
     return p;
 }
 
-// Slices of the batch dimension in the weight-gradient products (all layers share one launch): as many as bring
-// the launch's wave tiles to about one per SIMD of the chip -- more slices only add partial tiles to write and to
-// add up again (Kaggle model at batch 2048: 2 slices 185 us per step, 4: 188, 8: 189, 16: 192) -- with at least
-// two reduction slabs per slice, and at least two slices (the kernel stores partial tiles only when the reduction is
-// split; a slice may be empty).
+// A layer whose weight gradient [out][in] takes tiles of 64x64 (a workgroup each); narrower ones go by 32x32, and
+// their bias gradient is a column of the product.
+bool weight_grad_tile64(int in, int out) { return in >= 64 && out >= 64; }
+
+int64_t weight_grad_tiles(int in, int out) // per slice of the batch; 32x32 tiles: four to a workgroup
+{
+    return weight_grad_tile64(in, out) ? (int64_t)((out + 63) / 64) * ((in + 63) / 64)
+                                       : (int64_t)((out + 31) / 32) * ((in + 1 + 31) / 32);
+}
+
+// Slices of the batch dimension in the weight-gradient products (all layers share one launch).  A workgroup per CU
+// walks its slice in 1.7 us per 128 samples (a slab of 64x64 products for each of its four waves), so the slices
+// that fill whole rounds of the chip are wanted; a slice costs its partial tiles, written and added up again, at about
+// 4 TB/s.  At least one pair of slabs per wave and slice, and at least two slices (the kernel stores partial tiles only
+// when the reduction is split; a slice may be empty).
 int dense_splits(const dqrm_dense_model_t *m, int batch)
 {
-    int64_t tiles = 0;
-    for (int l = 0; l < m->bot_layers; ++l) tiles += (int64_t)((m->bot_dims[l + 1] + 31) / 32) * ((m->bot_dims[l] + 1 + 31) / 32);
-    for (int l = 0; l < m->top_layers; ++l) tiles += (int64_t)((m->top_dims[l + 1] + 31) / 32) * ((m->top_dims[l] + 1 + 31) / 32);
-    const int64_t simds = (int64_t)num_cus() * 4;
-    int64_t s = (simds + tiles / 2) / std::max<int64_t>(tiles, 1);
-    s = std::min<int64_t>(s, batch / (2 * dqrm::kGemmBK));
-    return (int)std::max<int64_t>(2, std::min<int64_t>(s, kDenseMaxSplits));
+    int64_t blocks = 0;
+    double params = 0;
+    auto add = [&](int in, int out) {
+        const int64_t t = weight_grad_tiles(in, out);
+        blocks += weight_grad_tile64(in, out) ? t : (t + dqrm::kGemmWaves - 1) / dqrm::kGemmWaves;
+        params += (double)out * (in + 1);
+    };
+    for (int l = 0; l < m->bot_layers; ++l) add(m->bot_dims[l], m->bot_dims[l + 1]);
+    for (int l = 0; l < m->top_layers; ++l) add(m->top_dims[l], m->top_dims[l + 1]);
+    const int64_t cus = num_cus();
+    int best = 2;
+    double best_us = 0;
+    for (int s = 2; s <= kDenseMaxSplits; ++s) {
+        if (s > 2 && (int64_t)s * 2 * dqrm::kGemmBK * dqrm::kGemmWaves > batch) break;
+        const double us = (double)((blocks * s + cus - 1) / cus) * batch / s / 128 * 1.7 + s * params * 8 / 4e6;
+        if (s == 2 || us < best_us) best = s, best_us = us;
+    }
+    return best;
 }
 
 int32_t check_dense_model(const dqrm_dense_model_t *m, int32_t batch)
@@ -879,38 +900,39 @@ DenseLayout dense_layout(const dqrm_dense_model_t *m, int32_t batch)
 }
 
 // A_MODE / B_MODE: how A / B lie in memory and are read (dqrm::kOpRC: the reduction index is the unit-stride one;
-// kOpWide, kOpWideVec: the 32-wide index i / j is).  One launch for all problems of the group.
+// kOpWide, kOpWideVec: the 32-wide index i / j is).
 template <int A_MODE, int B_MODE>
-hipError_t launch_gemm_group(hipStream_t st, dqrm::GemmGroup &grp)
+hipError_t launch_gemm(hipStream_t st, const dqrm::GemmArgs &g)
 {
-    int tiles = 0;
-    for (int q = 0; q < grp.count; ++q) {
-        dqrm::GemmArgs &g = grp.p[q];
-        if (g.b_ones_last && B_MODE != dqrm::kOpWide) return hipErrorInvalidValue; // only that form serves the virtual column
-        g.tile_begin = tiles;
-        tiles += ((g.M + 31) / 32) * ((g.N + 31) / 32) * g.splits;
-    }
-    grp.total_tiles = tiles;
-    if (tiles == 0) return hipSuccess;
-    if (grp.count > 1) {
-        hipLaunchKernelGGL((dqrm::gemm_wave_group_kernel<A_MODE, B_MODE>),
-                           dim3((tiles + dqrm::kGemmWaves - 1) / dqrm::kGemmWaves), dim3(dqrm::kGemmThreads), 0, st, grp);
-        return hipGetLastError();
-    }
     dqrm::GemmOne one;
-    one.p = grp.p[0];
-    one.total_tiles = tiles;
+    one.p = g;
     // A product with fewer tiles than the chip has SIMDs (4 per CU) leaves some of them idle: let 2 or 4 waves
     // share a tile, each with a slice of the reduction (at least one pair of slabs each), up to one wave per
     // SIMD.  (Measured: beyond that, slices cost more than they bring.)
+    const int pairs = g.K / (2 * dqrm::kGemmBK), simds = num_cus() * 4;
+    one.total_tiles = ((g.M + 31) / 32) * ((g.N + 31) / 32);
     one.kslices = 1;
-    if (one.p.splits == 1) {
-        const int pairs = one.p.K / (2 * dqrm::kGemmBK);
-        while (one.kslices < 4 && tiles * one.kslices * 2 <= num_cus() * 4 && pairs >= one.kslices * 2) one.kslices *= 2;
-    }
-    const int waves = tiles * one.kslices;
+    while (one.kslices < 4 && one.total_tiles * one.kslices * 2 <= simds && pairs >= one.kslices * 2) one.kslices *= 2;
+    const int waves = one.total_tiles * one.kslices;
     hipLaunchKernelGGL((dqrm::gemm_wave_kernel<A_MODE, B_MODE>), dim3((waves + dqrm::kGemmWaves - 1) / dqrm::kGemmWaves),
                        dim3(dqrm::kGemmThreads), 0, st, one);
+    return hipGetLastError();
+}
+
+// the weight gradients of a group of layers in one launch
+hipError_t launch_weight_grads(hipStream_t st, dqrm::GemmGroup &grp)
+{
+    int blocks = 0;
+    for (int q = 0; q < grp.count; ++q) {
+        dqrm::GemmArgs &g = grp.p[q];
+        g.block_begin = blocks;
+        if (g.tile64)
+            blocks += ((g.M + 63) / 64) * ((g.N + 63) / 64) * g.splits;
+        else
+            blocks += (((g.M + 31) / 32) * ((g.N + 31) / 32) * g.splits + dqrm::kGemmWaves - 1) / dqrm::kGemmWaves;
+    }
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(dqrm::gemm_split_group_kernel, dim3(blocks), dim3(dqrm::kGemmThreads), 0, st, grp);
     return hipGetLastError();
 }
 
@@ -918,30 +940,26 @@ hipError_t launch_gemm_group(hipStream_t st, dqrm::GemmGroup &grp)
 hipError_t linear_fwd(hipStream_t st, const float *X, const float *W, const float *b, float *Y, int B, int in, int out,
                 bool relu)
 {
-    dqrm::GemmGroup grp{};
-    dqrm::GemmArgs &g = grp.p[0];
-    grp.count = 1;
+    dqrm::GemmArgs g{};
     g.A = X, g.a_si = in, g.a_sr = 1;
     g.B = W, g.b_sr = 1, g.b_sj = in;
     g.C = Y, g.c_si = out, g.c_sj = 1;
     g.M = B, g.N = out, g.K = in;
     g.bias = b, g.relu = relu ? 1 : 0, g.splits = 1, g.k_per_split = in;
-    return launch_gemm_group<dqrm::kOpRC, dqrm::kOpRC>(st, grp);
+    return launch_gemm<dqrm::kOpRC, dqrm::kOpRC>(st, g);
 }
 
 // dX[B][in] = (dZ[B][out] * W[out][in]) masked by (mask[B][in] > 0)
 hipError_t linear_bwd_input(hipStream_t st, const float *dZ, const float *W, const float *mask, float *dX, int B, int in,
                       int out)
 {
-    dqrm::GemmGroup grp{};
-    dqrm::GemmArgs &g = grp.p[0];
-    grp.count = 1;
+    dqrm::GemmArgs g{};
     g.A = dZ, g.a_si = out, g.a_sr = 1;
     g.B = W, g.b_sr = in, g.b_sj = 1;
     g.C = dX, g.c_si = in, g.c_sj = 1;
     g.M = B, g.N = in, g.K = out;
     g.mask = mask, g.splits = 1, g.k_per_split = out;
-    return launch_gemm_group<dqrm::kOpRC, dqrm::kOpWideVec>(st, grp);
+    return launch_gemm<dqrm::kOpRC, dqrm::kOpWideVec>(st, g);
 }
 
 // The interaction, forward or backward: one wave per sample, as many waves per workgroup as the LDS holds.  Vectors of a
@@ -975,8 +993,12 @@ dqrm::GemmArgs weight_grad_problem(const float *dZ, const float *X, float *parti
     per = (per + dqrm::kGemmBK - 1) / dqrm::kGemmBK * dqrm::kGemmBK;
     dqrm::GemmArgs g{};
     g.A = dZ, g.a_si = 1, g.a_sr = out;
-    g.B = X, g.b_sr = in, g.b_sj = 1, g.b_ones_last = 1;
-    g.M = out, g.N = in + 1, g.K = B;
+    g.B = X, g.b_sr = in, g.b_sj = 1;
+    g.M = out, g.K = B;
+    if (weight_grad_tile64(in, out))
+        g.N = in, g.tile64 = 1;
+    else
+        g.N = in + 1, g.b_ones_last = 1;
     g.splits = splits; // exactly the slices the workspace holds; slices past the batch come out as zeros
     g.k_per_split = per, g.P = partials;
     return g;
@@ -1142,7 +1164,7 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
     auto flush = [&](bool ends_step) {
         if (wg.count == 0 && !ends_step) return;
         if (ends_step) sg.loss_terms = F(L.loss_terms), sg.loss = loss, sg.batch = B; // one more block
-        hipError_t e = launch_gemm_group<dqrm::kOpWide, dqrm::kOpWide>(st, wg);
+        hipError_t e = launch_weight_grads(st, wg);
         if (e != hipSuccess && launch_err == hipSuccess) launch_err = e;
         const unsigned blocks = (unsigned)std::min<long long>((sg.total + 255) / 256, 2048);
         const dim3 last_grid(blocks + (ends_step ? 1u : 0u));

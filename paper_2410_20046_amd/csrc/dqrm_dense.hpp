@@ -32,8 +32,8 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // edge are clamped and the value is replaced by 0 (or by 1 for the virtual
 // all-ones last column of B).
 //
-// Several products can share one launch (the weight gradients of all layers):
-// the waves are dealt over the tiles of all problems.  With splits > 1 the
+// Several split products can share one launch (the weight gradients of all layers):
+// the workgroups are dealt over the tiles of all problems.  With splits > 1 the
 // reduction is cut: slice z covers r in [z*k_per_split, ...) and stores its raw
 // partial tile to P[z][M][N]; sgd_from_partials_kernel adds the slices in order.
 // With kslices > 1 (one product per launch) the waves of a workgroup share tiles
@@ -53,13 +53,14 @@ struct GemmArgs {
     int splits;        // slices of the reduction (1: the epilogue above; > 1: partial tiles to P)
     int k_per_split;   // reduction length per slice (multiple of 32), K if not split
     float *P;          // [splits][M][N] partial tiles when split
-    int tile_begin;    // first wave-tile of this problem in the launch (filled by the launcher)
+    int tile64;        // split product in tiles of 64x64: P has N + 1 columns, the last one is sum_r A(i,r)
+    int block_begin;   // first workgroup of this problem in a group (filled by the launcher)
 };
 
 constexpr int kGemmMaxGroup = 16;
 struct GemmGroup {
     GemmArgs p[kGemmMaxGroup];
-    int count, total_tiles;
+    int count;
 };
 
 constexpr int kGemmThreads = 256;
@@ -193,15 +194,18 @@ __device__ __forceinline__ void slab_settle_fast(SlabRegs &x, const SlabRegs &st
     }
 }
 
-// the tile `tile` (and, with ks > 1, the slice wave % ks of its reduction) of problem g, by one wave
+// LDS of the workgroup: per wave, the pieces through which A and B are turned
+constexpr int kGemmTurnFloats = 32 * kGemmPitch;
+constexpr int kGemmLdsFloats = kGemmWaves * 2 * kGemmTurnFloats;
+
+// the tile `local` (and, with ks > 1, the slice wave % ks of its reduction) of problem g, by one wave
 template <int A_MODE, int B_MODE>
-__device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int tile, bool live, int ks, int wave, int lane)
+__device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int local, bool live, int ks, int wave, int lane,
+                                               float *lds_all)
 {
     constexpr bool A_RC = A_MODE == kOpRC, B_RC = B_MODE == kOpRC;
-    __shared__ __align__(16) float turn[kGemmWaves][2][32 * kGemmPitch]; // per wave: LDS pieces of A and B
     const int kz = wave & (ks - 1);
     const int tiles_j = (g.N + 31) / 32, tiles_i = (g.M + 31) / 32;
-    int local = tile - g.tile_begin;
     const int z = local / (tiles_i * tiles_j);
     local -= z * tiles_i * tiles_j;
     const int i_first = (local / tiles_j) * 32, j_first = (local % tiles_j) * 32; // first row / column this tile stores
@@ -223,7 +227,7 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int tile, bool
     const bool whole = (A_MODE != kOpWideVec || i0 + 32 <= g.M) && (B_MODE != kOpWideVec || j0 + 32 <= g.N);
     const int ia = min(i0 + w, g.M - 1), jb = min(j0 + w, n_mem - 1);
     const bool ones = g.b_ones_last && j0 + w == g.N - 1;
-    float *lds_a = turn[wave][0], *lds_b = turn[wave][1];
+    float *lds_a = lds_all + wave * 2 * kGemmTurnFloats, *lds_b = lds_a + kGemmTurnFloats;
     // (requested now, used in the epilogue)
     const float bias_j = (g.bias && g.splits <= 1) ? g.bias[min(j0 + w, g.N - 1)] : 0.0f;
     // ... and so is the mask of this lane's 16 outputs (rows and columns past the edge re-read the last ones)
@@ -330,7 +334,7 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int tile, bool
 
     // the slices of a tile meet: slice 0 adds the others' accumulators in order and goes on alone
     if (ks > 1) {
-        float *mine = &turn[wave][0][0];
+        float *mine = lds_a;
         if (kz > 0) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) mine[v * kWave + lane] = acc[v];
@@ -338,7 +342,7 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int tile, bool
         __syncthreads();
         if (kz > 0 || !live) return;
         for (int k = 1; k < ks; ++k) {
-            const float *other = &turn[wave + k][0][0];
+            const float *other = lds_a + k * 2 * kGemmTurnFloats;
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[v] += other[v * kWave + lane];
         }
@@ -369,6 +373,131 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int tile, bool
     }
 }
 
+// ---- split products in tiles of 64x64 (the weight gradients) ---------------------------------------------------
+// A wave with a 32x32 tile reads 8 KB for every 16 products (1024 matrix-core cycles): with one such wave on each
+// SIMD that is 32 bytes per cycle and CU out of the L2 and what lies behind it.  Four accumulators halve the bytes
+// per product, and a slab's 64 products (4096 cycles) cover the way from memory: the next slab is loaded
+// into place while one is multiplied.  A workgroup has a tile, each of its waves a quarter of the slice's reduction; then every wave finishes one
+// of the tile's four quadrants (the quarters added in their order).  The rows' sums (the bias gradient) ride along in
+// the matrix cores' shadow: as a column of ones they took a whole column of tiles wherever the width is a multiple of 64.
+// Measured: the Terabyte shape's five wide layers at batch 8192 (12.4 GFLOP) 207 -> 171 us (60 -> 73 TFLOP/s), the Kaggle
+// shape's at 2048 (1.96 GFLOP) 35.0 -> 34.5.  Both are bound by the fp32 matrix instructions, at about 70 % of their nominal
+// rate, plus the rounds' beginnings and ends.
+// (Tiles of 64x64 for the layers' own products, X W^T and dZ W: 8192x512x512 50.7 -> 51.8 us, 2048x512x512
+// 16.5 -> 20.8: these products are bound by the rate of the fp32 matrix instructions, and a single wave on a SIMD has
+// none to fill in for its LDS turns.)
+//
+// M and N are at least 64 (host), so every tile is whole: the last one of a dimension is moved back to the edge and
+// stores only what is its own.  The operands' wide indices are the unit-stride ones (kOpWide).
+// LDS: per wave its four quadrants, then every wave's row sums.
+constexpr int kGemm64WaveFloats = 4 * 16 * kWave;
+constexpr int kGemm64LdsFloats = kGemmWaves * (kGemm64WaveFloats + kWave);
+
+__device__ __forceinline__ void gemm_split_tile64(const GemmArgs &g, int local, int wave, int lane, float *lds_all)
+{
+    const int tiles_j = (g.N + 63) / 64, tiles_i = (g.M + 63) / 64;
+    const int z = local / (tiles_i * tiles_j);
+    local -= z * tiles_i * tiles_j;
+    const int i_first = (local / tiles_j) * 64, j_first = (local % tiles_j) * 64;
+    const int i0 = min(i_first, g.M - 64), j0 = min(j_first, g.N - 64);
+    // the slice (empty past the end of the reduction), and this wave's quarter of it in whole pairs of slabs
+    const int z_begin = min(z * g.k_per_split, g.K), z_end = min(z_begin + g.k_per_split, g.K);
+    const int k_per_wave = (z_end - z_begin + 2 * kGemmBK * kGemmWaves - 1) / (2 * kGemmBK * kGemmWaves) * (2 * kGemmBK);
+    const int r_begin = min(z_begin + wave * k_per_wave, z_end), r_end = min(r_begin + k_per_wave, z_end);
+    const int w = lane & 31, h = lane >> 5;
+
+    floatx16 acc[4]; // quadrant 2 * (row half) + (column half)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[q][v] = 0.0f;
+    float row_sum[2] = {0.0f, 0.0f};
+
+    struct Slab {
+        SlabRegs a[2], b[2];
+    };
+    Slab x, y;
+    auto fetch = [&](Slab &t, int r0) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            slab_load_direct<false>(t.a[q], g.A, g.a_si, g.a_sr, i0 + 32 * q + w, r0, 0, h, false);
+            slab_load_direct<false>(t.b[q], g.B, g.b_sj, g.b_sr, j0 + 32 * q + w, r0, 0, h, false);
+        }
+    };
+    auto products = [&](const Slab &t, int s_from, int s_to) {
+#pragma unroll
+        for (int s = s_from; s < s_to; ++s) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(t.a[q >> 1].v[s], t.b[q & 1].v[s], acc[q], 0, 0, 0);
+            row_sum[0] += t.a[0].v[s], row_sum[1] += t.a[1].v[s];
+        }
+    };
+
+    // pairs of whole slabs; a request past the last pair re-reads the last slab (harmless, and no branch)
+    int r0 = r_begin;
+    const int r_pairs = r_begin + (r_end - r_begin) / (2 * kGemmBK) * (2 * kGemmBK);
+    if (r0 < r_pairs) {
+        const int r_last = r_pairs - kGemmBK;
+        fetch(x, r0);
+        __builtin_amdgcn_sched_barrier(0);
+        for (; r0 < r_pairs; r0 += 2 * kGemmBK) {
+            products(x, 0, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(y, r0 + kGemmBK);
+            products(x, 1, 16);
+            __builtin_amdgcn_sched_barrier(0);
+            products(y, 0, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(x, min(r0 + 2 * kGemmBK, r_last));
+            products(y, 1, 16);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // what is left: at most one whole and one partial slab, clamped (zeros past the end)
+    for (; r0 < r_end; r0 += kGemmBK) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            slab_load_direct<true>(x.a[q], g.A, g.a_si, g.a_sr, i0 + 32 * q + w, r0, r_end, h, false);
+            slab_load_direct<true>(x.b[q], g.B, g.b_sj, g.b_sr, j0 + 32 * q + w, r0, r_end, h, false);
+        }
+        products(x, 0, 16);
+    }
+
+    // the quarters meet: wave q finishes quadrant q
+    float *mine = lds_all + wave * kGemm64WaveFloats;
+    float *sums = lds_all + kGemmWaves * kGemm64WaveFloats;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) row_sum[q] += __shfl_xor(row_sum[q], 32);
+    sums[wave * kWave + lane] = h ? row_sum[1] : row_sum[0];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mine[(q * 16 + v) * kWave + lane] = acc[q][v];
+    __syncthreads();
+    floatx16 sum;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum[v] = lds_all[(wave * 16 + v) * kWave + lane];
+    for (int k = 1; k < kGemmWaves; ++k)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sum[v] += lds_all[k * kGemm64WaveFloats + (wave * 16 + v) * kWave + lane];
+
+    float *p = g.P + (long long)z * g.M * (g.N + 1);
+    const int i = i0 + 32 * (wave >> 1) + 4 * h, j = j0 + 32 * (wave & 1) + w;
+    if (j >= j_first) { // (a moved tile stores only its own rows and columns)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int iv = i + 8 * (v >> 2) + (v & 3);
+            if (iv >= i_first) p[(long long)iv * (g.N + 1) + j] = sum[v];
+        }
+    }
+    if (wave == 0 && j_first == 0 && i0 + lane >= i_first) {
+        float t = 0.0f;
+        for (int k = 0; k < kGemmWaves; ++k) t += sums[k * kWave + lane];
+        p[(long long)(i0 + lane) * (g.N + 1) + g.N] = t;
+    }
+}
+
 // With kslices > 1 the waves of a workgroup meet at a barrier inside: a wave past the last tile stays, takes the
 // last tile with an empty reduction and stores nothing.
 struct GemmOne {
@@ -380,28 +509,36 @@ struct GemmOne {
 template <int A_MODE, int B_MODE>
 __global__ __launch_bounds__(kGemmThreads) void gemm_wave_kernel(GemmOne one)
 {
+    __shared__ __align__(16) float lds[kGemmLdsFloats];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave); // wave-uniform, and known to be
     const int ks = one.kslices;
-    int tile = ((int)blockIdx.x * kGemmWaves + wave) / ks;
+    const int tile = ((int)blockIdx.x * kGemmWaves + wave) / ks;
     const bool live = tile < one.total_tiles;
     if (!live && ks == 1) return;
-    gemm_wave_tile<A_MODE, B_MODE>(one.p, min(tile, one.total_tiles - 1), live, ks, wave, lane);
+    gemm_wave_tile<A_MODE, B_MODE>(one.p, min(tile, one.total_tiles - 1), live, ks, wave, lane, lds);
 }
 
-// several products in one launch (kslices == 1)
-template <int A_MODE, int B_MODE>
-__global__ __launch_bounds__(kGemmThreads) void gemm_wave_group_kernel(GemmGroup grp)
+// several split products in one launch (kOpWide operands): a workgroup has one 64x64 tile or four of 32x32.  Two
+// workgroups to a CU: one's first loads and last sums run beside the other's products.
+__global__ __launch_bounds__(kGemmThreads, 2) void gemm_split_group_kernel(GemmGroup grp)
 {
+    __shared__ __align__(16) float lds[kGemm64LdsFloats > kGemmLdsFloats ? kGemm64LdsFloats : kGemmLdsFloats];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-    const int tile = (int)blockIdx.x * kGemmWaves + wave;
-    if (tile >= grp.total_tiles) return; // whole waves leave; no barrier inside with one slice
     int pi = 0;
 #pragma unroll 1
     for (int q = 1; q < grp.count; ++q)
-        if (tile >= grp.p[q].tile_begin) pi = q;
-    gemm_wave_tile<A_MODE, B_MODE>(grp.p[pi], tile, true, 1, wave, lane);
+        if ((int)blockIdx.x >= grp.p[q].block_begin) pi = q;
+    const GemmArgs &g = grp.p[pi];
+    const int local = (int)blockIdx.x - g.block_begin;
+    if (g.tile64) {
+        gemm_split_tile64(g, local, wave, lane, lds);
+    } else {
+        const int tile = local * kGemmWaves + wave;
+        if (tile >= ((g.M + 31) / 32) * ((g.N + 31) / 32) * g.splits) return; // whole waves leave; no barrier inside
+        gemm_wave_tile<kOpWide, kOpWide>(g, tile, true, 1, wave, lane, lds);
+    }
 }
 
 // ---- a layer with a short input (the bottom MLP's first: 13 dense features) -------------------------------

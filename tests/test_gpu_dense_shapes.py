@@ -17,7 +17,7 @@ def _model(rng, T, D, bot, top):
     return (bot, *layers(bot), top, *layers(top))
 
 
-def _check(oracle, T, D, B, bot, top, seed=7):
+def _check(oracle, T, D, B, bot, top, seed=7, margin=False):
     import torch
     import paper_2410_20046_amd as dq
 
@@ -25,6 +25,10 @@ def _check(oracle, T, D, B, bot, top, seed=7):
     rng = np.random.default_rng(seed)
     bot_dims, bw, bb, top_dims, tw, tb = _model(rng, T, D, bot, top)
     x = np.exp(rng.standard_normal((B, bot_dims[0]))).astype(np.float32)
+    if margin:  # biases of +-1 and sums of some 0.05: no pre-activation near zero, half of the units on
+        x = rng.uniform(0.5, 2.0, x.shape).astype(np.float32)
+        bw, tw = [w * np.float32(0.02) for w in bw], [w * np.float32(0.02) for w in tw]
+        bb, tb = [np.sign(b) for b in bb], [np.sign(b) for b in tb]
     y = (rng.random(B) < 0.25).astype(np.float32)
     emb = (rng.standard_normal((B, T, D)) * 0.25).astype(np.float32)
     dev = torch.device("cuda:0")
@@ -62,3 +66,14 @@ def _check(oracle, T, D, B, bot, top, seed=7):
     (5, 33, 64, [17, 120]), (15, 256, 24, [7, 8])])
 def test_interaction_shapes(oracle, T, D, B, bot):
     _check(oracle, T, D, B, bot, [16])
+
+
+# The weight gradients' 64x64 tiles: layers just below, at and above one and two tiles, batches of one sample, one partial
+# slab and many slices.  Among the 2 million pre-activations of
+# such a batch about 2e6 * 2.7e-6 * 0.8 = 4 lie within their rounding of zero, and each ReLU so flipped moves the embedding
+# gradients by some 1e-3 of their norm; large batches therefore keep every pre-activation away from zero.
+@pytest.mark.parametrize("T,D,B,bot,top", [
+    (3, 64, 65, [13, 64, 64], [64, 65]), (2, 8, 1, [64, 128], [64, 64]), (3, 70, 129, [65, 64, 128], [63, 64, 127, 128]),
+    (2, 8, 2085, [13, 300], [321, 257]), (2, 16, 8200, [16], [120, 260]), (2, 16, 4160, [64], [160, 256, 64])])
+def test_product_tiles(oracle, T, D, B, bot, top):
+    _check(oracle, T, D, B, bot, top, margin=B > 1000)
