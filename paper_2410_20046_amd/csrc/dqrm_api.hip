@@ -919,6 +919,12 @@ hipError_t launch_gemm(hipStream_t st, const dqrm::GemmArgs &g)
     return hipGetLastError();
 }
 
+// Samples per workgroup of the short-input layer: two workgroups per CU (4 waves of 2), within the kernel's limits.
+int small_k_samples(int batch)
+{
+    return std::min(dqrm::kSmallKMaxSamples, std::max(dqrm::kSmallKMinSamples, batch / (2 * num_cus())));
+}
+
 // the weight gradients of a group of layers in one launch
 hipError_t launch_weight_grads(hipStream_t st, dqrm::GemmGroup &grp)
 {
@@ -1094,7 +1100,8 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
         if (in <= dqrm::kSmallKMax && out % 4 == 0 && aligned(m->bot_b[l], 16)) {
             dqrm::SmallKArgs sk{};
             sk.X = x, sk.W = bot_wf[l], sk.bias = m->bot_b[l], sk.Y = F(L.bot_act[l]), sk.B = B, sk.N = out, sk.K = in, sk.relu = 1;
-            hipLaunchKernelGGL(dqrm::linear_small_k_kernel, dim3((B + dqrm::kSmallKSamples - 1) / dqrm::kSmallKSamples),
+            sk.samples = small_k_samples(B);
+            hipLaunchKernelGGL(dqrm::linear_small_k_kernel, dim3((B + sk.samples - 1) / sk.samples),
                                dim3(dqrm::kSmallKThreads), 0, st, sk);
             DQRM_HIP_CHECK(hipGetLastError());
         } else {

@@ -544,22 +544,25 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_split_group_kernel(GemmG
 // ---- a layer with a short input (the bottom MLP's first: 13 dense features) -------------------------------
 // Y[b][o] = act(sum_k X[b][k] * W[o][k] + bias[o]) for K <= kSmallKMax: a product with a reduction this short is
 // all launch and edge handling on the matrix cores.  A thread owns four consecutive outputs: their 4 K weights stay
-// in registers while the thread walks the workgroup's kSmallKSamples samples, whose inputs sit in LDS.
+// in registers while the thread walks the workgroup's samples, whose inputs sit in LDS.
 constexpr int kSmallKMax = 16;
 constexpr int kSmallKThreads = 128;
-constexpr int kSmallKSamples = 4; // samples per workgroup
+// Samples per workgroup, from the least to the most (small_k_samples()).  Every workgroup reads all weights, in 4 K loads a
+// thread whose lanes lie 16 K bytes apart: 64 cache lines each, which cost more than everything else at 4 samples of a
+// large batch: 8192x13 -> 512 takes 21.7 us with 4 samples to a workgroup, 12.9 with 16 (2048 samples, 4: 8.2).
+constexpr int kSmallKMinSamples = 4, kSmallKMaxSamples = 16;
 struct SmallKArgs {
     const float *X, *W, *bias;
     float *Y;
-    int B, N, K, relu; // N a multiple of 4, bias and Y 16-byte aligned (host)
+    int B, N, K, relu, samples; // N a multiple of 4, bias and Y 16-byte aligned (host)
 };
 
 __global__ __launch_bounds__(kSmallKThreads) void linear_small_k_kernel(SmallKArgs a)
 {
-    __shared__ float xs[kSmallKSamples * kSmallKMax];
+    __shared__ float xs[kSmallKMaxSamples * kSmallKMax];
     const int N = a.N, K = a.K;
-    const int b0 = (int)blockIdx.x * kSmallKSamples, nb = min(kSmallKSamples, a.B - b0);
-    for (int e = threadIdx.x; e < kSmallKSamples * kSmallKMax; e += kSmallKThreads) {
+    const int b0 = (int)blockIdx.x * a.samples, nb = min(a.samples, a.B - b0); // samples <= kSmallKMaxSamples (host)
+    for (int e = threadIdx.x; e < a.samples * kSmallKMax; e += kSmallKThreads) {
         const int bl = e / kSmallKMax, k = e % kSmallKMax;
         xs[e] = (bl < nb && k < K) ? a.X[(long long)(b0 + bl) * K + k] : 0.0f;
     }

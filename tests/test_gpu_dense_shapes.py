@@ -77,3 +77,10 @@ def test_interaction_shapes(oracle, T, D, B, bot):
     (2, 8, 2085, [13, 300], [321, 257]), (2, 16, 8200, [16], [120, 260]), (2, 16, 4160, [64], [160, 256, 64])])
 def test_product_tiles(oracle, T, D, B, bot, top):
     _check(oracle, T, D, B, bot, top, margin=B > 1000)
+
+
+# The short-input layer takes 4 samples to a workgroup while that fills 2 workgroups per CU, then up to 16: remainders of 8,
+# 16 and 16 samples (on 256 CUs).
+@pytest.mark.parametrize("B", [4099, 8195, 9001])
+def test_short_input_layer(oracle, B):
+    _check(oracle, 2, 8, B, [13, 68], [16], margin=True)
