@@ -112,22 +112,43 @@ __device__ __forceinline__ int find_bag(Off off, int B, int p)
 }
 
 // A table's lookups [lo, lo + n) in the batch, by its bags' offsets; n = 0 if they make no sense or are too many (then
-// bad_code / bad_value say why).
+// bad_code / bad_value say why), or if an earlier table has some of them.
 struct TableExtent {
     long long lo;
     int n, bad_code;
     long long bad_value;
-    __device__ __forceinline__ TableExtent(const int64_t *bag_offsets, int B, int64_t N, int limit)
-    {
-        lo = bag_offsets[0];
-        const long long hi = bag_offsets[B];
-        const bool bad = lo < 0 || hi > N || lo > hi, many = !bad && hi - lo > limit;
-        bad_code = bad ? DQRM_ERR_BAD_OFFSETS : (many ? DQRM_ERR_CAPACITY : 0);
-        bad_value = bad ? lo : hi - lo;
-        n = bad || many ? 0 : (int)(hi - lo);
-        lo = lo < 0 ? 0 : (lo > N ? N : lo);
-    }
 };
+
+// All threads of the workgroup call this (t: wave-uniform; s_back: an LDS word per wave).  Tables share lookups only where a
+// boundary between tables lies before the one in front of it (the table that it ends reports that): whether there is one before
+// t is looked up for all tables at once, and only then is t compared with each of them.
+template <int THREADS>
+__device__ __forceinline__ TableExtent table_extent(const int64_t *offsets, int t, int B, int64_t N, int limit, int tid, int *s_back)
+{
+    constexpr int kWaves = THREADS / kWave;
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    bool back = false;
+    for (int s = tid; s < t; s += THREADS) back |= offsets[(long long)s * B] > offsets[(long long)(s + 1) * B];
+    const long long lo = offsets[(long long)t * B], hi = offsets[(long long)(t + 1) * B];
+    const bool bad = lo < 0 || hi > N || lo > hi, many = !bad && hi - lo > limit;
+    TableExtent x;
+    x.bad_code = bad ? DQRM_ERR_BAD_OFFSETS : (many ? DQRM_ERR_CAPACITY : 0);
+    x.bad_value = bad ? lo : hi - lo;
+    x.n = bad || many ? 0 : (int)(hi - lo);
+    x.lo = lo < 0 ? 0 : (lo > N ? N : lo);
+    const bool wave_back = __any(back);
+    if (lane == 0) s_back[wave] = wave_back;
+    __syncthreads();
+    if (__any(s_back[lane & (kWaves - 1)])) { // (the number of waves is a power of two)
+        bool shared = false;
+        for (int s = lane; s < t; s += kWave) {
+            const long long l = offsets[(long long)s * B], h = offsets[(long long)(s + 1) * B];
+            shared |= l >= 0 && l <= h && h <= N && h - l <= limit && l < hi && lo < h;
+        }
+        if (__any(shared)) x.n = 0;
+    }
+    return x;
+}
 
 // A wave-uniform number that the compiler takes for a new one.  (Two unrolled loops that leave at the same round would
 // otherwise be compiled as one path per round through both.)
@@ -194,11 +215,12 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
     __shared__ __align__(16) unsigned s_key[kDdTile];
     __shared__ unsigned short s_pos[kDdTile];
     __shared__ __align__(16) unsigned short cnt[kWaves * 256], place[kWaves * 256];
+    __shared__ int s_back[kWaves];
     const DedupeBatch &bt = args.b[blockIdx.y];
     const int t = blockIdx.x, tile = blockIdx.z, B = args.B;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const unsigned rows_t = (unsigned)(args.row_offsets[t + 1] - args.row_offsets[t]);
-    const TableExtent x(bt.offsets + (long long)t * B, B, bt.N, bt.limit); // (its problems: dedupe_kernel reports them)
+    const TableExtent x = table_extent<kDdPartThreads>(bt.offsets, t, B, bt.N, bt.limit, tid, s_back); // (its problems: dedupe_kernel reports them)
     const int len = min(kDdTile, x.n - tile * kDdTile);
     if (len <= 0) return;
     const int rounds = (len + kDdPartThreads - 1) / kDdPartThreads;
@@ -286,6 +308,7 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
     __shared__ int s_class[kChunkClasses]; // chunks of each length class so far
     __shared__ unsigned s_stack[kDdStack];
     __shared__ unsigned s_pivot;
+    __shared__ int s_back[kWaves];
 
     const DedupeBatch &bt = args.b[blockIdx.y];
     const int64_t *__restrict__ indices = bt.indices;
@@ -303,7 +326,7 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
     const unsigned rows_t = (unsigned)(args.row_offsets[t + 1] - args.row_offsets[t]); // host: <= DQRM_MAX_TABLE_ROWS
 
     const int64_t *__restrict__ bag_offsets = offsets + (long long)t * B;
-    const TableExtent x(bag_offsets, B, N, bt.limit);
+    const TableExtent x = table_extent<THREADS>(offsets, t, B, N, bt.limit, tid, s_back);
     const long long lo = x.lo;
     const int n = x.n, base = (int)lo;
     // A problem of the data is kept here and reported at one place (one problem per thread and kind of work is enough: only

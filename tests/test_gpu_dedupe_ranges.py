@@ -105,3 +105,55 @@ def test_hot_rows_and_bags(n, threads, bags):
         s0 = int(got["table_uniq_offsets"][2])
         rows = got["uniq_rows"][s0:]
         assert_exact(b.values.cpu().numpy()[s0:s0 + len(rows), 0].astype(np.float64), want[rows], f"n={n} hot={hot} {bags} sums")
+
+
+# Boundaries between tables that go backwards: the table that ends before it begins is reported and skipped, and so is a later one
+# that has lookups of an earlier one (the distinct rows would outgrow the outputs otherwise).  Tables per kind of lookup for such a
+# boundary: one step of a workgroup, several; lookups for the plain and the partitioned sort.
+@pytest.mark.parametrize("T,n,B", [(4, 100, 10), (5, 40_000, 500), (100, 60, 7), (700, 30, 3)])
+def test_tables_that_share_lookups(T, n, B):
+    bound = np.arange(T + 1, dtype=np.int64) * n
+    bound[T - 2:] -= n // 2  # table T - 3 ends where it began less half a table; T - 2 shares that half with T - 4
+    bound[T - 2:] -= n
+    if T > 4:
+        bound[1], bound[2] = n + n // 3, n + n // 4  # and table 1 ends before it begins; table 2 shares a few with table 0
+    N = int(bound.max())
+    off = np.concatenate([np.linspace(bound[t], bound[t + 1], B + 1)[:-1].astype(np.int64) for t in range(T)] + [bound[-1:]])
+    cards = np.full(T, 40, np.int64)
+    idx = np.random.default_rng(T).integers(0, 40, N).astype(np.int64)
+    keep = []
+    for t in range(T):
+        lo, hi = int(bound[t]), int(bound[t + 1])
+        sane = [(int(bound[s]), int(bound[s + 1])) for s in range(t) if bound[s] <= bound[s + 1]]
+        keep.append(lo <= hi and not any(l < hi and lo < h for l, h in sane))
+    assert 0 < sum(keep) < T - 1
+    print(f"shared lookups: {T} tables, {sum(keep)} kept, {N} lookups", flush=True)
+    wl = Workload(name="shared", T=T, D=8, B=B, alpha=1.05, seed=1, cards=cards)
+    spare = 4096
+    run = GpuRun(wl.row_offsets, 8, np.zeros((wl.R, 8), np.float32), B, N + spare, with_packed=False, want_codes=False)
+    run.upload_batch(idx, off)
+    b, dq = run.bufs, run.dq
+    for x in (b.sorted_pos, b.uniq_rows, b.seg_offsets):
+        x.fill_(-9)
+    b.workspace.fill_(0xA5)
+    dq.dqrm_dedupe(run.tables, run.idx, run.off, B, b.sorted_pos, b.uniq_rows, b.seg_offsets, b.table_uniq_offsets, b.num_unique,
+                   b.workspace)
+    pos, rows, tuo = np.full(N + spare, -9, np.int32), [], [0]
+    for t in range(T):
+        lo, hi = int(bound[t]), int(bound[t + 1])
+        u = np.zeros(0, np.int64)
+        if keep[t]:
+            pos[lo:hi] = lo + np.argsort(idx[lo:hi], kind="stable")
+            u = np.unique(idx[lo:hi])
+        rows.append(u)
+        tuo.append(tuo[-1] + len(u))
+    U = tuo[-1]
+    assert int(b.num_unique.cpu().item()) == U
+    assert_exact(b.table_uniq_offsets.cpu().numpy(), np.array(tuo, np.int32), "table_uniq_offsets")
+    assert_exact(b.sorted_pos.cpu().numpy(), pos, "sorted_pos")
+    got = b.uniq_rows.cpu().numpy()
+    assert_exact(got[:U], np.concatenate(rows), "uniq_rows")
+    assert (got[U:] == -9).all() and (b.seg_offsets.cpu().numpy()[U + 1:] == -9).all()
+    used = dq.dqrm_embbag_bwd_workspace_bytes(T, 8, B, N)
+    assert (b.workspace[used:] == 0xA5).all().item()
+    assert run.status()[0] == dq.ERR_BAD_OFFSETS
