@@ -97,7 +97,7 @@ WsLayout ws_layout(int32_t T, int32_t D, int64_t N)
         o = align_up(o + bytes, 256);
         return at;
     };
-    L.off_part_info = take((size_t)dqrm::kMaxParts * 2 * sizeof(int4));
+    L.off_part_info = take((size_t)dqrm::kMaxSlots * 2 * sizeof(int4));
     L.off_totals = take(4 * sizeof(int));
     // (only a batch of more than kDdTile lookups is partitioned)
     const size_t big = N > dqrm::kDdTile ? n : 0;
@@ -164,6 +164,17 @@ int grid_for(int64_t work_items, int threads, int blocks_per_cu)
     if (want > cap) want = cap;
     if (want < 1) want = 1;
     return (int)want;
+}
+
+template <bool EXTRA>
+void launch_dedupe(int cap, dim3 grid, hipStream_t st, const dqrm::DedupeArgs &da)
+{
+    if (cap == 2048)
+        hipLaunchKernelGGL((dqrm::dedupe_kernel<256, 2048, false, EXTRA>), grid, dim3(256), 0, st, da);
+    else if (cap == 4096)
+        hipLaunchKernelGGL((dqrm::dedupe_kernel<512, 4096, false, EXTRA>), grid, dim3(512), 0, st, da);
+    else
+        hipLaunchKernelGGL((dqrm::dedupe_kernel<1024, 8192, false, EXTRA>), grid, dim3(1024), 0, st, da);
 }
 
 template <bool PACKED>
@@ -420,25 +431,42 @@ int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t nu
     // 116 us, in sorted order 157; 13 x 10500: 21.6, 23.2), those of bags of one over one in sorted order (26 x 8192: 25.4, by
     // length 27.4).
     da.by_length = max_n >= (int64_t)T * batch * 3 / 2;
-    const dim3 grid(T, num_batches, (unsigned)parts);
+    int64_t most = 0; // lookups of any table
+    for (int i = 0; i < num_batches; ++i) most = std::max<int64_t>(most, std::min<int64_t>(da.b[i].N, da.b[i].limit));
+    // A table far above the average would leave its few ranges' workgroups at work alone, each with piece after piece to take,
+    // the more so if its popular rows lie close together: a table of more than the LDS holds (and a quarter above the average) has
+    // ranges of half the LDS each, as many as that takes, chosen so that they hold about equally many lookups.  The workgroups of
+    // those beyond `parts` look up in the tables' boundaries which table is theirs.  Measured (us, with dedupe_finish_kernel; in
+    // brackets the `parts` equally wide ranges that every table has otherwise):
+    //   255 tables x  128 lookups and one of 65536: 261 (7600); one of 16384: 70 (670)
+    //    25 tables x 2048 and one of 65536:          75 (472); 25 x 512 and one of 16384: 51 (135)
+    // where no table has that many: 26 x 2048 18.9 (18.5), 26 x 8192 32.4 (31.8).  A bound on a table's lookups spares that.
+    const int cap = avg <= 512 ? 2048 : (avg <= 4096 && parts > 1 ? 4096 : 8192);
+    const int64_t light = std::max<int64_t>(cap, avg + avg / 4);
+    const bool uneven = !partition && most > light;
+    if (uneven) {
+        const int64_t room = dqrm::kMaxSlots - T * parts;
+        const int64_t per_range = std::max<int64_t>({cap / 2, DQRM_MAX_TABLE_LOOKUPS / dqrm::kDdMaxRanges, (max_n + room - 1) / room});
+        da.light = (int)light;
+        da.per_range = (int)std::min<int64_t>(per_range, DQRM_MAX_TABLE_LOOKUPS);
+        // the sum over the tables above `light` of ceil(n / per_range) - parts, at most
+        da.extra = (int)std::min(max_n / per_range, max_n / light * std::max<int64_t>(0, (most + per_range - 1) / per_range - parts));
+    }
+    const dim3 grid(T, num_batches, (unsigned)(parts + (da.extra + T - 1) / T));
     if (partition) {
-        int64_t most = 0; // lookups of any table
-        for (int i = 0; i < num_batches; ++i) most = std::max<int64_t>(most, std::min<int64_t>(da.b[i].N, da.b[i].limit));
         hipLaunchKernelGGL(dqrm::dedupe_partition_kernel, dim3(T, num_batches, (unsigned)((most + dqrm::kDdTile - 1) / dqrm::kDdTile)),
                            dim3(dqrm::kDdPartThreads), 0, st, da);
-        hipLaunchKernelGGL((dqrm::dedupe_kernel<1024, 8192, true>), grid, dim3(1024), 0, st, da);
-    } else if (avg <= 512) {
-        hipLaunchKernelGGL((dqrm::dedupe_kernel<256, 2048, false>), grid, dim3(256), 0, st, da);
-    } else if (avg <= 4096 && parts > 1) {
-        hipLaunchKernelGGL((dqrm::dedupe_kernel<512, 4096, false>), grid, dim3(512), 0, st, da);
+        hipLaunchKernelGGL((dqrm::dedupe_kernel<1024, 8192, true, false>), grid, dim3(1024), 0, st, da);
+    } else if (uneven) {
+        launch_dedupe<true>(cap, grid, st, da);
     } else {
-        hipLaunchKernelGGL((dqrm::dedupe_kernel<1024, 8192, false>), grid, dim3(1024), 0, st, da);
+        launch_dedupe<false>(cap, grid, st, da);
     }
     // (2 workgroups per CU for one batch, 8 for eight: 256 per batch then; with 512 each the scans in front of the work take
     // 3 us longer)
     const int finish_blocks = std::min(grid_for(max_n, dqrm::kSegThreads, 2), std::max(1, num_cus() * 8 / num_batches));
-    hipLaunchKernelGGL(dqrm::dedupe_finish_kernel, dim3(finish_blocks, num_batches),
-                       dim3(dqrm::kSegThreads), 0, st, da);
+    hipLaunchKernelGGL(da.extra > 0 ? dqrm::dedupe_finish_kernel<true> : dqrm::dedupe_finish_kernel<false>,
+                       dim3(finish_blocks, num_batches), dim3(dqrm::kSegThreads), dqrm::finish_lds_bytes(da), st, da);
     DQRM_HIP_CHECK(hipGetLastError());
     return DQRM_OK;
 }

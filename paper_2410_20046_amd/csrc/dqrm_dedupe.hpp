@@ -17,7 +17,10 @@
 
 namespace dqrm {
 
-constexpr int kMaxParts = 1024;    // (table, range) pairs per batch, at most
+constexpr int kMaxParts = 1024;    // (table, range) pairs per batch where every table has equally many ranges, at most
+constexpr int kMaxSlots = 1280;    // with the further ranges of tables of very many lookups
+constexpr int kDdSample = 512;     // lookups of such a table that its ranges are chosen by
+constexpr int kDdMaxRanges = 64;   // its ranges, at most
 constexpr int kDdTile = 8192;      // lookups of a table that a workgroup of dedupe_partition_kernel takes
 constexpr int kDdTiles = DQRM_MAX_TABLE_LOOKUPS / kDdTile; // of a table, at most
 constexpr int kDdRanges = 64;      // ranges of a partitioned table, at most
@@ -28,8 +31,9 @@ static_assert(DQRM_MAX_TABLES <= kMaxParts && DQRM_MAX_TABLE_LOOKUPS <= 65536 &&
 
 // Views into the caller's workspace (all device pointers).
 struct BwdWs {
-    // [kMaxParts][2] per (table, range): {first sorted position, segments, chunks other than singles, singles}, then how many
-    // chunks of each length class there are, 16 bits each
+    // [kMaxSlots][2] per (table, range), those every table has first: {first sorted position, segments, chunks other than
+    // singles, singles}, then how many chunks of each length class there are, 16 bits each, and in w (of a further range) its place
+    // in the order of all
     int4 *part_info;
     // the lookups of tiles of kDdTile, each sorted by range (dedupe_partition_kernel; only for batches of more than kDdTile)
     unsigned *part_key;       // [N]   rows (or the number of rows, for a bad index)
@@ -41,7 +45,7 @@ struct BwdWs {
     int4 *chunk_desc;         // [N]   dense chunk list over all tables, as the summing kernels read it
     int *chunk_bags;          // [N/2 + 1][32] bags of chunk c's lookups, so that they can be read before its descriptor
     int4 *single_desc;        // [N]   dense list of singles: {bag, global segment, table, -}
-    int *totals;              // [3]   chunks, segments, singles
+    int *totals;              // [4]   chunks, segments, singles; further ranges (if there can be any)
     int *seg_count;           // [N/32 + 2] chunks of a segment of more than one chunk that have parked their sum, filed
                               //       under (sorted position of the segment's head / 32); zero between uses
     float *partial_full;      // [(N/32 + 2) * D] sum of a full chunk of a segment of more than one chunk
@@ -88,6 +92,9 @@ struct DedupeArgs {
     int T, B;
     int parts; // ranges per table, T * parts <= kMaxParts
     int bags_per_part; // ceil(B / parts)
+    int light;         // a table of more lookups has its ranges chosen by a sample, and further ones
+    int per_range;     // as far as it has fewer than one per so many lookups
+    int extra;         // further ranges of all tables of a batch, at most (0: no table can have any)
     int by_length;     // the order of the dense chunk list, see chunk_class
     FastDiv by_parts;
     FastDiv even; // by the lookups of a bag if all bags of the launch hold equally many (a guess), else by 1
@@ -147,7 +154,83 @@ __device__ __forceinline__ TableExtent table_extent(const int64_t *offsets, int 
         }
         if (__any(shared)) x.n = 0;
     }
+    x.n = __builtin_amdgcn_readfirstlane(x.n); // (wave-uniform, and known to be)
     return x;
+}
+
+// Further ranges of a table of n lookups.  Together a batch's tables have no more than DedupeArgs::extra (host) where their
+// boundaries are in order; where they are not, none has any.
+__device__ __forceinline__ int extra_ranges(const DedupeArgs &a, int n)
+{
+    return n > a.light ? max((n + a.per_range - 1) / a.per_range - a.parts, 0) : 0;
+}
+
+// The e-th further range of a batch: its table and its number among the table's ranges (table -1: there are fewer).  The first
+// one's workgroup leaves in totals[3] how many there are.  All threads of the workgroup call this; s_w: an LDS word per wave,
+// s_found: two.
+template <int THREADS>
+__device__ __forceinline__ int2 find_extra(const DedupeArgs &a, const DedupeBatch &bt, int e, int tid, int *s_w, int *s_found)
+{
+    constexpr int kWaves = THREADS / kWave;
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int per = (a.T + THREADS - 1) / THREADS; // consecutive tables per thread
+    bool back = false;
+    auto count_of = [&](int t) {
+        const long long lo = bt.offsets[(long long)t * a.B], hi = bt.offsets[(long long)(t + 1) * a.B];
+        back |= lo > hi;
+        return lo >= 0 && lo <= hi && hi <= bt.N && hi - lo <= bt.limit ? extra_ranges(a, (int)(hi - lo)) : 0;
+    };
+    int mine = 0;
+#pragma unroll 1
+    for (int t = tid * per; t < min((tid + 1) * per, a.T); ++t) mine += count_of(t);
+    const int incl = wave_incl_scan_add(mine, lane);
+    if (tid == 0) s_found[0] = -1;
+    if (lane == kWave - 1) s_w[wave] = incl;
+    const bool any_back = __syncthreads_or(back ? 1 : 0) != 0;
+    const int waves_incl = wave_incl_scan_add(lane < kWaves ? s_w[lane] : 0, lane);
+    const int total = __builtin_amdgcn_readlane(waves_incl, kWaves - 1);
+    int before = incl - mine + (wave > 0 ? __builtin_amdgcn_readlane(waves_incl, max(wave - 1, 0)) : 0);
+    if (e == 0 && tid == 0) bt.ws.totals[3] = any_back ? 0 : total;
+    if (e >= before && e < before + mine) // (one thread)
+#pragma unroll 1
+        for (int t = tid * per; t < min((tid + 1) * per, a.T); ++t) {
+            const int count = count_of(t);
+            if (e >= before && e < before + count) s_found[0] = t, s_found[1] = a.parts + e - before;
+            before += count;
+        }
+    __syncthreads();
+    const int2 r = make_int2(__builtin_amdgcn_readfirstlane(s_found[0]), __builtin_amdgcn_readfirstlane(s_found[1]));
+    return any_back ? make_int2(-1, 0) : r;
+}
+
+// Range `part` of `ranges` of a table of very many lookups, [x, y): between two of kDdSample of its keys (s_sample, all
+// written), so that the ranges hold about equally many lookups wherever in the table the popular rows lie.  A key that
+// bounds several ranges has the first of them to itself.  All threads of the workgroup call this.
+template <int THREADS>
+__device__ __forceinline__ uint2 sampled_range(const unsigned *s_sample, int part, int ranges, unsigned rows_t, int tid, unsigned *s_split)
+{
+#pragma unroll 1
+    for (int j = tid; j < kDdSample; j += THREADS) {
+        const unsigned k = s_sample[j];
+        int rank = 0;
+#pragma unroll 2
+        for (int i = 0; i < kDdSample; i += 4) {
+            const uint4 o = *reinterpret_cast<const uint4 *>(s_sample + i);
+            rank += (o.x < k || (o.x == k && i < j)) + (o.y < k || (o.y == k && i + 1 < j)) + (o.z < k || (o.z == k && i + 2 < j)) +
+                    (o.w < k || (o.w == k && i + 3 < j));
+        }
+#pragma unroll
+        for (int b = -1; b < 2; ++b) // the keys that bound this range and the one before it
+            if ((part + b) > 0 && part + b < ranges && rank == (part + b) * kDdSample / ranges) s_split[b + 1] = k;
+    }
+    __syncthreads();
+    auto bound = [&](int b) { // of part + b and the range in front of it
+        const int p = part + b;
+        if (p <= 0) return 0u;
+        if (p >= ranges) return rows_t + 1u;
+        return s_split[b + 1] + (p > 1 && s_split[b + 1] == s_split[b] ? 1u : 0u);
+    };
+    return make_uint2(bound(0), bound(1));
 }
 
 // A wave-uniform number that the compiler takes for a new one.  (Two unrolled loops that leave at the same round would
@@ -290,7 +373,8 @@ static_assert(kDdPivotDepth + 2 + 32 <= kDdStack, "halving ends at a range of on
 // unrolled: most launches have one or two rounds, every line of code is fetched anew by every launch, and a kernel
 // this short waits for its code as much as for its data.)
 // PARTITIONED: the table's lookups come from dedupe_partition_kernel, a run of this range per tile.
-template <int THREADS, int CAP, bool PARTITIONED>
+// EXTRA: a table may have more than DedupeArgs::light lookups (a kernel of its own, as the others pay for its code otherwise).
+template <int THREADS, int CAP, bool PARTITIONED, bool EXTRA>
 __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
 {
     constexpr int kWaves = THREADS / kWave, kCap = CAP;
@@ -318,10 +402,18 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
     const BwdWs &ws = bt.ws;
     int32_t *__restrict__ sorted_pos = bt.sorted_pos;
 
-    const int t = blockIdx.x, part = blockIdx.z; // consecutive workgroups: different tables
+    int t = blockIdx.x, part = blockIdx.z; // consecutive workgroups: different tables
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    if (EXTRA && part >= args.parts) {
+        const int e = (part - args.parts) * args.T + t;
+        if (e >= args.extra) return;
+        const int2 r = find_extra<THREADS>(args, bt, e, tid, s_scan[0], s_scan[1]);
+        if (r.x < 0) return;
+        t = r.x, part = r.y;
+        __syncthreads(); // (s_scan is free again)
+    }
 
     const unsigned rows_t = (unsigned)(args.row_offsets[t + 1] - args.row_offsets[t]); // host: <= DQRM_MAX_TABLE_ROWS
 
@@ -335,9 +427,29 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
     long long bad_value = x.bad_value;
 
     // My range of the keys [0, rows_t]: a row, or rows_t for a lookup whose index is out of range (those sort after
-    // every row, and the part that holds them reports them).
+    // every row, and the part that holds them reports them).  The ranges of most tables are equally wide.
     const unsigned share = args.by_parts.div(rows_t) + 1u;
-    const unsigned range_lo = min((unsigned)part * share, rows_t + 1u), range_hi = min(range_lo + share, rows_t + 1u);
+    unsigned range_lo = min((unsigned)part * share, rows_t + 1u), range_hi = min(range_lo + share, rows_t + 1u);
+    static_assert(!PARTITIONED || !EXTRA, "a partitioned table's ranges are equally wide");
+    bool sampled = EXTRA && n > args.light;
+    if (__builtin_expect(sampled, 0)) {
+        bool back = false;
+#pragma unroll 1
+        for (int s = tid; s < args.T; s += THREADS) back |= offsets[(long long)s * B] > offsets[(long long)(s + 1) * B];
+        sampled = !__syncthreads_or(back ? 1 : 0);
+    }
+    if (__builtin_expect(sampled, 0)) {
+        unsigned *s_sample = s_key[1];
+#pragma unroll 1
+        for (int j = tid; j < kDdSample; j += THREADS) { // (n is at least kDdSample: host)
+            const long long v = indices[lo + (unsigned)j * (unsigned)n / kDdSample];
+            s_sample[j] = (unsigned long long)v < rows_t ? (unsigned)v : rows_t;
+        }
+        __syncthreads();
+        const uint2 r = sampled_range<THREADS>(s_sample, part, args.parts + extra_ranges(args, n), rows_t, tid, s_stack);
+        range_lo = (unsigned)__builtin_amdgcn_readfirstlane((int)r.x), range_hi = (unsigned)__builtin_amdgcn_readfirstlane((int)r.y);
+        __syncthreads(); // (the LDS is free again)
+    }
 
     // The lookups to look at: all of the table's, or those of my range, tile by tile: item i of tile w's run is item
     // run_first[w] + i of mine and lies at run_from[w] + i (both wave-uniform).
@@ -784,9 +896,12 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
     }
     __syncthreads();
     if (tid == 0) {
-        int4 *info = ws.part_info + 2 * (t * args.parts + part);
+        const int e = ((int)blockIdx.z - args.parts) * args.T + (int)blockIdx.x; // (a further range's number; the others have none)
+        const bool further = EXTRA && (int)blockIdx.z >= args.parts;
+        int4 *info = ws.part_info + 2 * (further ? args.T * args.parts + e : t * args.parts + (int)blockIdx.z);
+        const int w = further ? (t + 1) * args.parts + e : 0;
         info[0] = make_int4(max(part_base, 0), n_uniq, n_chunk, n_single);
-        info[1] = make_int4(s_class[0] | (s_class[1] << 16), s_class[2] | (s_class[3] << 16), s_class[4], 0);
+        info[1] = make_int4(s_class[0] | (s_class[1] << 16), s_class[2] | (s_class[3] << 16), s_class[4], w);
     }
 }
 
@@ -800,30 +915,77 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
 //   z  global index of the segment (row of `values`)
 //   w  table
 // Dense single descriptor: x bag, y global index of the segment, z table.
+// its dynamic LDS
+inline size_t finish_lds_bytes(const DedupeArgs &a)
+{
+    const size_t most = (size_t)a.T * a.parts + a.extra;
+    return sizeof(int) * ((3 + kChunkClasses) * (most + 1) + most) + (a.extra ? 2 * sizeof(unsigned short) * most : 0);
+}
+
+template <bool EXTRA>
 __global__ __launch_bounds__(kSegThreads) void dedupe_finish_kernel(DedupeArgs args)
 {
     const DedupeBatch &a = args.b[blockIdx.y];
     const BwdWs &ws = a.ws;
-    // exclusive sums over the parts: segments, chunks, singles, chunks of each class (V + 1 entries each); and the parts'
-    // first sorted positions
+    // exclusive sums over the parts in their order: segments, chunks, singles, chunks of each class (V + 1 entries each); the
+    // parts' first sorted positions; with further ranges, the parts' tables and which part_info is whose
     constexpr int kSums = 3 + kChunkClasses, kWaves = kSegThreads / kWave;
-    __shared__ int s_sum[kSums][kMaxParts + 1], s_base[kMaxParts];
+    extern __shared__ int finish_lds[]; // finish_lds_bytes()
     __shared__ int s_w[kSums][kWaves];
-    const int *s_uniq = s_sum[0], *s_chunk = s_sum[1], *s_single = s_sum[2];
-    const int T = args.T, parts = args.parts, V = T * parts;
+    const int T = args.T, parts = args.parts, most = T * parts + args.extra;
+    int *s_base = finish_lds + kSums * (most + 1);
+    unsigned short *s_table = reinterpret_cast<unsigned short *>(s_base + most), *s_order = s_table + most;
+    auto s_sum = [&](int k) { return finish_lds + k * (most + 1); };
+    const int *s_uniq = s_sum(0), *s_chunk = s_sum(1), *s_single = s_sum(2);
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    int V = T * parts;
+    // (requested beside the number of further ranges, which is nearly always zero)
+    int per = (V + kSegThreads - 1) / kSegThreads; // consecutive parts per thread
+    int4 x = ws.part_info[2 * min(tid * per, V - 1)], y = ws.part_info[2 * min(tid * per, V - 1) + 1];
+    const int more = EXTRA ? __builtin_amdgcn_readfirstlane(ws.totals[3]) : 0;
+    if (EXTRA && __builtin_expect(more > 0, 0)) {
+        // a further range knows its place, and with it its table; another one comes behind the further ones of earlier tables
+        int *table = finish_lds; // (the sums are not there yet)
+        for (int e = tid; e < more; e += kSegThreads) {
+            const int place = ws.part_info[2 * (V + e) + 1].w;
+            table[e] = (int)args.by_parts.div((unsigned)(place - e)) - 1;
+            s_order[place] = (unsigned short)(V + e);
+            s_table[place] = (unsigned short)table[e];
+        }
+        __syncthreads();
+        for (int v = tid; v < V; v += kSegThreads) {
+            const int t = (int)args.by_parts.div((unsigned)v);
+            int lo = 0, hi = more; // the first one of table t or behind it
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (table[mid] < t) lo = mid + 1;
+                else hi = mid;
+            }
+            s_order[v + lo] = (unsigned short)v;
+            s_table[v + lo] = (unsigned short)t;
+        }
+        __syncthreads();
+        V += more;
+        per = (V + kSegThreads - 1) / kSegThreads;
+        const int id = s_order[min(tid * per, V - 1)];
+        x = ws.part_info[2 * id], y = ws.part_info[2 * id + 1];
+    }
+    auto table_of_part = [&](int v) { return EXTRA && more > 0 ? (int)s_table[v] : (int)args.by_parts.div((unsigned)v); };
     {
-        const int per = (V + kSegThreads - 1) / kSegThreads; // consecutive parts per thread
-        auto counts_of = [&](int v, int (&c)[kSums]) {
-            const int4 x = ws.part_info[2 * v], y = ws.part_info[2 * v + 1];
+        const int first = tid * per, end = min(first + per, V);
+        int mine[kSums] = {}, c[kSums];
+        auto counts = [&](int v) { // of part v, into c
+            if (v > first || per > 1) {
+                const int id = EXTRA && more > 0 ? s_order[v] : v;
+                x = ws.part_info[2 * id], y = ws.part_info[2 * id + 1];
+            }
             c[0] = x.y, c[1] = x.z, c[2] = x.w;
             c[3] = y.x & 0xFFFF, c[4] = (int)((unsigned)y.x >> 16), c[5] = y.y & 0xFFFF, c[6] = (int)((unsigned)y.y >> 16), c[7] = y.z;
             s_base[v] = x.x;
         };
-        static_assert(kChunkClasses == 5, "counts_of");
-        int mine[kSums] = {}, c[kSums];
-        for (int v = tid * per; v < min((tid + 1) * per, V); ++v) {
-            counts_of(v, c);
+        static_assert(kChunkClasses == 5, "counts");
+        for (int v = first; v < end; ++v) {
+            counts(v);
 #pragma unroll
             for (int k = 0; k < kSums; ++k) mine[k] += c[k];
         }
@@ -839,21 +1001,27 @@ __global__ __launch_bounds__(kSegThreads) void dedupe_finish_kernel(DedupeArgs a
         for (int k = 0; k < kSums; ++k)
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) before[k] += w < wave ? s_w[k][w] : 0;
-        for (int v = tid * per; v < min((tid + 1) * per, V); ++v) {
-            if (per > 1) counts_of(v, c); // (one part per thread: they are still here)
+        for (int v = first; v < end; ++v) {
+            if (per > 1) counts(v); // (one part per thread: they are still here)
 #pragma unroll
             for (int k = 0; k < kSums; ++k) {
-                s_sum[k][v] = before[k];
+                s_sum(k)[v] = before[k];
                 before[k] += c[k];
-                if (v == V - 1) s_sum[k][V] = before[k];
+                if (v == V - 1) s_sum(k)[V] = before[k];
             }
         }
         __syncthreads();
     }
     const int C = s_chunk[V], U = s_uniq[V], S = s_single[V];
     if (blockIdx.x == 0) {
-        for (int k = tid; k <= T; k += kSegThreads) a.tuo[k] = s_uniq[k * parts];
+        if (EXTRA && more > 0)
+            for (int v = tid; v < V; v += kSegThreads) {
+                if (v == 0 || s_table[v] != s_table[v - 1]) a.tuo[s_table[v]] = s_uniq[v];
+            }
+        else
+            for (int k = tid; k < T; k += kSegThreads) a.tuo[k] = s_uniq[k * parts];
         if (tid == 0) {
+            a.tuo[T] = U;
             *a.num_unique = U;
             a.seg_offsets[U] = (int32_t)a.N;
             ws.totals[0] = C;
@@ -861,12 +1029,12 @@ __global__ __launch_bounds__(kSegThreads) void dedupe_finish_kernel(DedupeArgs a
             ws.totals[2] = S;
         }
     }
-    const int first = (int)(blockIdx.x * kSegThreads) + tid, step = (int)(gridDim.x * kSegThreads);
+    const int at = (int)(blockIdx.x * kSegThreads) + tid, step = (int)(gridDim.x * kSegThreads);
     // Chunks, kChunksPerWave consecutive ones per wave: their descriptors (a lane each, the other lanes along for the
     // ride), then the bags of their lookups at a place that depends on the chunk's index alone (a chunk has at least
     // two lookups, so there are at most N / 2 chunks): half a wave per chunk.
     constexpr int kChunksPerWave = 8;
-    for (int c0 = first / kWave * kChunksPerWave; c0 < C; c0 += step / kWave * kChunksPerWave) {
+    for (int c0 = at / kWave * kChunksPerWave; c0 < C; c0 += step / kWave * kChunksPerWave) {
         const int c = min(c0 + (lane & (kChunksPerWave - 1)), C - 1);
         const int v = table_of(s_chunk, V, c);
         const int4 d = ws.chunk_local[s_base[v] + (c - s_chunk[v])];
@@ -875,16 +1043,16 @@ __global__ __launch_bounds__(kSegThreads) void dedupe_finish_kernel(DedupeArgs a
         int place = c;
         if (args.by_length) {
             const int cls = chunk_class(desc_len(d));
-            place = s_sum[3 + cls][v] + (int)((unsigned)d.z >> 16);
+            place = s_sum(3 + cls)[v] + (int)((unsigned)d.z >> 16);
 #pragma unroll
-            for (int k = 0; k + 1 < kChunkClasses; ++k) place += k < cls ? s_sum[3 + k][V] : 0;
+            for (int k = 0; k + 1 < kChunkClasses; ++k) place += k < cls ? s_sum(3 + k)[V] : 0;
         }
         if (lane < kChunksPerWave && c0 + lane < C) {
             if (desc_kchunk(d) == 0) { // first chunk of its segment: d.x is the segment's head
                 a.uniq_rows[j] = (int64_t)(unsigned)d.w;
                 a.seg_offsets[j] = d.x;
             }
-            ws.chunk_desc[place] = make_int4(d.x, d.y, j, (int)args.by_parts.div((unsigned)v));
+            ws.chunk_desc[place] = make_int4(d.x, d.y, j, table_of_part(v));
         }
         int bag[kChunksPerWave / 2], to[kChunksPerWave / 2];
         const int i = lane & (DQRM_SEG_CHUNK - 1);
@@ -900,13 +1068,13 @@ __global__ __launch_bounds__(kSegThreads) void dedupe_finish_kernel(DedupeArgs a
             if (c0 + 2 * q + (lane >> 5) < C) // (past the chunk's end: its last bag again)
                 ws.chunk_bags[(int64_t)to[q] * DQRM_SEG_CHUNK + i] = bag[q];
     }
-    for (int c = first; c < S; c += step) {
+    for (int c = at; c < S; c += step) {
         const int v = table_of(s_single, V, c);
         const int4 d = ws.single_local[s_base[v] + (c - s_single[v])]; // {sorted position, bag, segment, row}
         const int j = s_uniq[v] + d.z;
         a.uniq_rows[j] = (int64_t)(unsigned)d.w;
         a.seg_offsets[j] = d.x;
-        ws.single_desc[c] = make_int4(d.y, j, (int)args.by_parts.div((unsigned)v), 0);
+        ws.single_desc[c] = make_int4(d.y, j, table_of_part(v), 0);
     }
 }
 

@@ -157,3 +157,89 @@ def test_tables_that_share_lookups(T, n, B):
     used = dq.dqrm_embbag_bwd_workspace_bytes(T, 8, B, N)
     assert (b.workspace[used:] == 0xA5).all().item()
     assert run.status()[0] == dq.ERR_BAD_OFFSETS
+
+
+def _sums_exact(run, idx, off, B, cards, got, what):
+    """The bags and the chunk lists, through the segment sums: gradients that name their bag (sums of integers below 2^24, exact)."""
+    T = len(cards)
+    g = np.zeros((B, T, 8), np.float32)
+    g[:, :, 0] = np.arange(B)[:, None] % 61
+    run.upload_batch(idx, off, g)
+    b = run.bufs
+    run.dq.dqrm_segment_sum(run.tables, B, len(idx), run.grad, b.values, b.g_absmax, b.workspace)
+    values = b.values.cpu().numpy()[:int(got["U"][0]), 0].astype(np.float64)
+    for t in range(T):
+        lo, hi = int(off[t * B]), int(off[(t + 1) * B])
+        v, bag = idx[lo:hi], np.repeat(np.arange(B), np.diff(off[t * B:(t + 1) * B + 1]))
+        good = (v >= 0) & (v < cards[t])
+        want = np.bincount(v[good], weights=(bag[good] % 61).astype(np.float64), minlength=int(cards[t]))
+        s, e = got["table_uniq_offsets"][t:t + 2]
+        assert_exact(values[s:e], want[got["uniq_rows"][s:e]], f"{what} sums of table {t}")
+
+
+def _uneven(seed, per_table, cards, B, alike, hot=None, bad=0.0):
+    """A batch with per_table[t] lookups of table t: bags of random lengths, or (alike) as equal as they can be; popular rows
+    first in every table, and `hot` of a large table's lookups to one of its rows."""
+    rng = np.random.default_rng(seed)
+    idx, lens = [], []
+    for n, r in zip(per_table, cards):
+        v = np.minimum((rng.random(n) ** 4 * r).astype(np.int64), r - 1)
+        if n > 4096:
+            if hot:
+                v[rng.random(n) < hot] = r // 3
+            v[rng.random(n) < bad] = r + 5
+            v[rng.random(n) < bad] = -1
+        idx.append(v)
+        lens.append(np.diff(np.arange(B + 1) * n // B) if alike else np.bincount(rng.integers(0, B, n), minlength=B))
+    off = np.concatenate([[0], np.cumsum(np.concatenate(lens))]).astype(np.int64)
+    return np.concatenate(idx).astype(np.int64), off
+
+
+# Tables with far more lookups than the others: their further ranges and the order of all ranges, at each of the workgroups, for
+# one such table and several (first, last, neighbours), with few rows, a hot row and bad indices; up to the most tables.
+@pytest.mark.parametrize("per_table,B", [
+    ([128] * 40 + [65536] + [3000] + [128] * 3, 128), ([65536] + [1] * 1023, 16), ([100] * 300 + [2049, 4097, 20_000], 100),
+    ([2048] * 25 + [65536], 512), ([16_385] + [2048] * 12 + [30_000, 30_000], 700), ([65536, 1, 2, 65536], 8192),
+    ([8192] * 12 + [40_000, 37_000, 65536], 3000), ([9000] * 20 + [65535], 9000), ([600] * 1000 + [40_000, 50_000], 600)])
+@pytest.mark.parametrize("kind", ["plain", "hot", "few"])
+def test_uneven_tables(per_table, B, kind):
+    T = len(per_table)
+    cards = np.where(np.array(per_table) > 4096, {"plain": 200_000, "hot": 5000, "few": 7}[kind], 300).astype(np.int64)
+    idx, off = _uneven(T, per_table, cards, B, kind == "plain", hot=0.6 if kind == "hot" else None, bad=0.02 if kind == "hot" else 0.0)
+    wl = Workload(name="uneven", T=T, D=8, B=B, alpha=1.05, seed=1, cards=cards)
+    print(f"uneven: {T} tables of up to {max(per_table)} lookups ({kind})", flush=True)
+    run, got = _dedupe(wl, idx, off, B)
+    for k, v in _expected(wl, idx, off, B).items():
+        assert_exact(got[k], v, f"{kind} {k}")
+    _sums_exact(run, idx, off, B, cards, got, kind)
+    assert (run.status()[0] != 0) == (kind == "hot")
+
+
+# Batches of one launch: their tables' sizes differ from batch to batch; partitioned ones; more tables than are ever partitioned.
+@pytest.mark.parametrize("batches", [
+    [[128] * 30, [128] * 29 + [60_000], [60_000] + [1] * 29], [[17_000, 16_500, 20_000], [65536, 16_400, 10_000]],
+    [[16_500] * 140]], ids=["uneven", "partitioned", "many"])
+def test_batches_of_one_launch(batches):
+    T, B = len(batches[0]), 900
+    cards = np.full(T, 3000, np.int64)
+    wl = Workload(name="batches", T=T, D=8, B=B, alpha=1.05, seed=1, cards=cards)
+    data = [_uneven(k, p, cards, B, False) for k, p in enumerate(batches)]
+    print(f"batches of {[len(i) for i, _ in data]} lookups in {T} tables", flush=True)
+    most = max(len(i) for i, _ in data)
+    runs = []
+    for idx, off in data:
+        run = GpuRun(wl.row_offsets, 8, np.zeros((wl.R, 8), np.float32), B, most, with_packed=False, want_codes=False)
+        run.upload_batch(idx, off)
+        run.bufs.workspace.fill_(0xA5)
+        runs.append(run)
+    b = [r.bufs for r in runs]
+    runs[0].dq.dqrm_dedupe_multi(runs[0].tables, B, [(r.idx, r.off, x.sorted_pos, x.uniq_rows, x.seg_offsets, x.table_uniq_offsets,
+                                                      x.num_unique, x.workspace) for r, x in zip(runs, b)])
+    for (idx, off), r, x in zip(data, runs, b):
+        U = int(x.num_unique.cpu().item())
+        got = dict(U=np.array([U]), sorted_pos=x.sorted_pos.cpu().numpy()[:len(idx)], uniq_rows=x.uniq_rows.cpu().numpy()[:U],
+                   seg_offsets=x.seg_offsets.cpu().numpy()[:U + 1], table_uniq_offsets=x.table_uniq_offsets.cpu().numpy())
+        for k, v in _expected(wl, idx, off, B).items():
+            assert_exact(got[k], v, k)
+        _sums_exact(r, idx, off, B, cards, got, "batch")
+    assert runs[0].status()[0] == 0
