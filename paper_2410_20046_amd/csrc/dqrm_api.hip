@@ -418,10 +418,15 @@ int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t nu
     const int64_t most_parts = dqrm::kMaxParts / T;
     int64_t least_n = max_n;
     for (int i = 0; i < num_batches; ++i) least_n = std::min<int64_t>(least_n, da.b[i].N);
+    int64_t most = 0; // lookups of any table
+    for (int i = 0; i < num_batches; ++i) most = std::max<int64_t>(most, std::min<int64_t>(da.b[i].N, da.b[i].limit));
     // From two tiles per table on every range's workgroup reading the whole table costs more than sorting the tiles by
     // range first: 26 x 65536 lookups 132 us, against 215 with 8 ranges that each read everything.
     const bool partition = avg > 2 * dqrm::kDdTile && least_n > dqrm::kDdTile && most_parts >= 8;
-    int64_t parts = partition ? 32 : std::max<int64_t>(std::min<int64_t>({num_cus() / wgs, avg / 256, 16}), (avg - 1) / 8192 * 2);
+    // Where the tables alone are workgroups for half of the CUs or more, none is cut (dedupe_table_kernel): 208 x 8192 lookups 60
+    // (dedupe_kernel, one range: 67), 1024 x 4096 181 (187); with fewer lookups dedupe_kernel's shorter code counts for more.
+    const bool whole = !partition && avg > 2048 && most <= dqrm::kTableCap && num_cus() <= wgs * 2;
+    int64_t parts = whole ? 1 : partition ? 32 : std::max<int64_t>(std::min<int64_t>({num_cus() / wgs, avg / 256, 16}), (avg - 1) / 8192 * 2);
     parts = std::max<int64_t>(1, std::min(parts, most_parts));
     da.parts = (int)parts;
     da.bags_per_part = (int)((batch + parts - 1) / parts);
@@ -431,8 +436,6 @@ int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t nu
     // 116 us, in sorted order 157; 13 x 10500: 21.6, 23.2), those of bags of one over one in sorted order (26 x 8192: 25.4, by
     // length 27.4).
     da.by_length = max_n >= (int64_t)T * batch * 3 / 2;
-    int64_t most = 0; // lookups of any table
-    for (int i = 0; i < num_batches; ++i) most = std::max<int64_t>(most, std::min<int64_t>(da.b[i].N, da.b[i].limit));
     // A table far above the average would leave its few ranges' workgroups at work alone, each with piece after piece to take,
     // the more so if its popular rows lie close together: a table of more than the LDS holds (and a quarter above the average) has
     // ranges of half the LDS each, as many as that takes, chosen so that they hold about equally many lookups.  The workgroups of
@@ -443,7 +446,7 @@ int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t nu
     // where no table has that many: 26 x 2048 18.9 (18.5), 26 x 8192 32.4 (31.8).  A bound on a table's lookups spares that.
     const int cap = avg <= 512 ? 2048 : (avg <= 4096 && parts > 1 ? 4096 : 8192);
     const int64_t light = std::max<int64_t>(cap, avg + avg / 4);
-    const bool uneven = !partition && most > light;
+    const bool uneven = !partition && !whole && most > light;
     if (uneven) {
         const int64_t room = dqrm::kMaxSlots - T * parts;
         const int64_t per_range = std::max<int64_t>({cap / 2, DQRM_MAX_TABLE_LOOKUPS / dqrm::kDdMaxRanges, (max_n + room - 1) / room});
@@ -457,6 +460,8 @@ int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t nu
         hipLaunchKernelGGL(dqrm::dedupe_partition_kernel, dim3(T, num_batches, (unsigned)((most + dqrm::kDdTile - 1) / dqrm::kDdTile)),
                            dim3(dqrm::kDdPartThreads), 0, st, da);
         hipLaunchKernelGGL((dqrm::dedupe_kernel<1024, 8192, true, false>), grid, dim3(1024), 0, st, da);
+    } else if (whole) {
+        hipLaunchKernelGGL(dqrm::dedupe_table_kernel, grid, dim3(dqrm::kTableThreads), 0, st, da);
     } else if (uneven) {
         launch_dedupe<true>(cap, grid, st, da);
     } else {

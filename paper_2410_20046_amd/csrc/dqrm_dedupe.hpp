@@ -1,7 +1,7 @@
 // dqrm_dedupe: sort a batch's lookups by (table, row, position), find the distinct rows, and build the work lists of
 // the segment sums (the sparse-tensor coalescing of Sec. 4.3).  It needs only the batch's indices.
 //
-// Kernel 1 (dedupe_kernel): the rows of a table are cut into `parts` ranges, one workgroup per (batch, table, range).
+// Kernel 1 (dedupe_kernel; dedupe_table_kernel where the tables alone fill the chip): the rows of a table are cut into `parts` ranges, one workgroup per (batch, table, range).
 //   A workgroup reads all of its table's lookups, keeps those of its range in lookup order (LDS), counts those below
 //   it (that is where its piece of the sorted order starts: no workgroup waits for another), sorts what it kept with a
 //   stable LSD radix sort in LDS, and writes its piece of the sorted order and its own lists of chunks and singles.
@@ -117,6 +117,51 @@ __device__ __forceinline__ int find_bag(Off off, int B, int p)
     }
     return bag;
 }
+
+// The bags of a table's lookups: where they all hold equally many (`even`, a guess) a lookup's bag follows from its position;
+// otherwise it is found among the bags' first positions, every 2^sparse-th of them in LDS, and then among those between.
+struct BagSearch {
+    const int64_t *bag_offsets; // of the table, B + 1
+    long long lo;               // its first lookup
+    int B, sparse;
+    bool even;
+
+    // a bag of [b_lo, b_hi) that does not lie behind the one in front of it and inside the table's n lookups, or -1
+    template <int THREADS>
+    __device__ __forceinline__ int disorder(int b_lo, int b_hi, int n, int tid) const
+    {
+        int bad = -1;
+        for (int b0 = b_lo + tid; b0 < b_hi; b0 += 4 * THREADS) { // (four at a time, all requested before the first is looked at)
+            long long s[4], e[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int b = min(b0 + q * THREADS, b_hi - 1);
+                s[q] = bag_offsets[b];
+                e[q] = bag_offsets[b + 1];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (s[q] < lo || e[q] > lo + n || s[q] > e[q]) bad = min(b0 + q * THREADS, b_hi - 1);
+        }
+        return bad;
+    }
+    template <int THREADS>
+    __device__ __forceinline__ void stage(unsigned short *soff, int tid) const
+    {
+        for (int b = tid; b << sparse < B; b += THREADS) {
+            const long long s = bag_offsets[b << sparse] - lo;
+            soff[b] = (unsigned short)(s < 0 ? 0 : (s > 65535 ? 65535 : (int)s));
+        }
+    }
+    // (after a wrong guess nothing is staged)
+    __device__ __forceinline__ int find(const unsigned short *soff, int p) const
+    {
+        if (even) return find_bag([&](int b) { return bag_offsets[b] - lo; }, B, p);
+        const int hint = p < 65535 ? find_bag([&](int b) { return soff[b]; }, ((B - 1) >> sparse) + 1, p) << sparse : 0;
+        if (sparse == 0 && p < 65535) return hint; // (position 65535 cannot be told from an empty bag at 65536 in 16 bits)
+        return hint + find_bag([&](int b) { return bag_offsets[hint + b] - lo; }, p < 65535 ? min(1 << sparse, B - hint) : B, p);
+    }
+};
 
 // A table's lookups [lo, lo + n) in the batch, by its bags' offsets; n = 0 if they make no sense or are too many (then
 // bad_code / bad_value say why), or if an earlier table has some of them.
@@ -517,40 +562,15 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
     // batches), the bag of a lookup is guessed and the guess looked up; otherwise it is found among the
     // bags' first positions: in LDS, all of them or (if they do not fit) some, and then among those between where they are.
     const bool even = (unsigned long long)args.even.d * (unsigned)B == (unsigned)n; // (host: the divisor is N / (T B))
-    const int sparse = max(0, 32 - __clz((B - 1) / kCap)); // every 2^sparse-th bag's offset fits
+    const BagSearch bags{bag_offsets, lo, B, max(0, 32 - __clz((B - 1) / kCap)), even};
     if (n > 0) {
         const int b_lo = min(args.bags_per_part * part, B), b_hi = min(b_lo + args.bags_per_part, B);
-        for (int b0 = b_lo + tid; b0 < b_hi; b0 += 4 * THREADS) { // (four at a time, all requested before the first is looked at)
-            long long s[4], e[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int b = min(b0 + q * THREADS, b_hi - 1);
-                s[q] = bag_offsets[b];
-                e[q] = bag_offsets[b + 1];
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int b = min(b0 + q * THREADS, b_hi - 1);
-                if (s[q] < lo || e[q] > lo + n || s[q] > e[q]) bad_code = DQRM_ERR_BAD_OFFSETS, bad_value = (long long)t * B + b;
-            }
-        }
+        const int b = bags.disorder<THREADS>(b_lo, b_hi, n, tid);
+        if (b >= 0) bad_code = DQRM_ERR_BAD_OFFSETS, bad_value = (long long)t * B + b;
     }
     if (bad_code != 0) report(bad_code, t, bad_value);
     if (part == 0 && tid < kAbsmaxSlots) *absmax_slot(ws.absmax_slots, t, tid) = 0.0f;
     if (tid < kChunkClasses) s_class[tid] = 0; // (read after more barriers)
-    auto search_bag = [&](const unsigned short *soff, int p) {
-        if (even) return find_bag([&](int b) { return bag_offsets[b] - lo; }, B, p); // (the guess was wrong)
-        const int hint = p < 65535 ? find_bag([&](int b) { return soff[b]; }, ((B - 1) >> sparse) + 1, p) << sparse : 0;
-        if (sparse == 0 && p < 65535) return hint; // (position 65535 cannot be told from an empty bag at 65536 in 16 bits)
-        return hint + find_bag([&](int b) { return bag_offsets[hint + b] - lo; }, p < 65535 ? min(1 << sparse, B - hint) : B, p);
-    };
-    auto stage_offsets = [&](unsigned short *soff, int tid) {
-        for (int b = tid; b << sparse < B; b += THREADS) {
-            const long long s = bag_offsets[b << sparse] - lo;
-            soff[b] = (unsigned short)(s < 0 ? 0 : (s > 65535 ? 65535 : (int)s));
-        }
-    };
-
     int n_uniq = 0, n_chunk = 0, n_single = 0; // this part's lists so far
     int part_base = -1;                        // first sorted position of the part
     unsigned cur = range_lo, end = range_hi;
@@ -652,7 +672,7 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
             const bool valid = cur < rows_t;
             unsigned short *soff = reinterpret_cast<unsigned short *>(s_key[0]);
             if (!even) {
-                stage_offsets(soff, tid); // (what was kept of the lookups is not needed)
+                bags.stage<THREADS>(soff, tid); // (what was kept of the lookups is not needed)
                 __syncthreads();
             }
             int done = 0;
@@ -687,7 +707,7 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
                     const int p = s_pos[0][k], d = at + done + k;
                     sorted_pos[d] = base + p;
                     int bag = (int)args.even.div((unsigned)p);
-                    if (!even || bag_offsets[bag] > lo + p || lo + p >= bag_offsets[bag + 1]) bag = search_bag(soff, p);
+                    if (!even || bag_offsets[bag] > lo + p || lo + p >= bag_offsets[bag + 1]) bag = bags.find(soff, p);
                     if (valid) ws.sorted_bag[d] = bag;
                 }
                 done += kept;
@@ -769,7 +789,7 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
                     bag_hi[r] = bag_offsets[g + 1u];
                 }
             } else {
-                stage_offsets(soff, tid);
+                bags.stage<THREADS>(soff, tid);
             }
 
             // ---- 3. segment heads --------------------------------------------------------------------------------------
@@ -825,7 +845,7 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
             if (search) {
 #pragma unroll 1
                 for (int i = wave_at + lane, r = 0; r < rounds; ++r, i += kWave) {
-                    const int bag = search_bag(soff, i < m ? (int)spos[i] : 0);
+                    const int bag = bags.find(soff, i < m ? (int)spos[i] : 0);
                     s_rank[i] = (unsigned short)bag;
                     if (i < valid_count) ws.sorted_bag[at + i] = bag;
                 }
@@ -902,6 +922,189 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
         const int w = further ? (t + 1) * args.parts + e : 0;
         info[0] = make_int4(max(part_base, 0), n_uniq, n_chunk, n_single);
         info[1] = make_int4(s_class[0] | (s_class[1] << 16), s_class[2] | (s_class[3] << 16), s_class[4], w);
+    }
+}
+
+// Kernel 1 for launches with a workgroup per CU or more before any table is cut into ranges (several batches side by side) and at
+// most kTableCap lookups in a table: a workgroup sorts a whole table.  There is nothing to look for and nothing to piece together,
+// so a thread's items stay in registers between the sort's passes (the LDS holds them once) and every loop over them is unrolled.
+// Bound by the chains of a workgroup that has its CU to itself: LDS round trips between barriers, and fetching its code.
+// 208 tables x 8192 lookups (eight batches of 26): 40.5 us, dedupe_kernel with one range 45; with dedupe_finish_kernel 60.0 (67.3);
+// x 16384 lookups: 106 (155, two ranges).
+constexpr int kTableThreads = 1024, kTableCap = 16384;
+
+__global__ __launch_bounds__(kTableThreads) void dedupe_table_kernel(DedupeArgs args)
+{
+    constexpr int THREADS = kTableThreads, kWaves = THREADS / kWave, kItems = kTableCap / THREADS;
+    __shared__ __align__(16) unsigned s_key[kTableCap];
+    __shared__ unsigned short s_pos[kTableCap], s_head[kTableCap + 2]; // s_head: sorted index of each segment's head, and the last one's end
+    // digit counters, a row of 256 per wave, and where the wave's items of each digit go; later the bags' first positions
+    __shared__ __align__(16) unsigned short s_digits[2][kWaves * 256];
+    __shared__ int s_x[kWaves], s_back[kWaves], s_class[kChunkClasses];
+
+    const DedupeBatch &bt = args.b[blockIdx.y];
+    const BwdWs &ws = bt.ws;
+    const int t = blockIdx.x, B = args.B, tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const unsigned rows_t = (unsigned)(args.row_offsets[t + 1] - args.row_offsets[t]); // host: <= DQRM_MAX_TABLE_ROWS
+    const TableExtent x = table_extent<THREADS>(bt.offsets, t, B, bt.N, bt.limit, tid, s_back);
+    const long long lo = x.lo;
+    const int n = x.n, base = (int)lo; // host: n <= kTableCap
+    const int64_t *__restrict__ bag_offsets = bt.offsets + (long long)t * B;
+    // items, wave-striped: number r of a lane is item first + r * 64 of the table
+    const int rounds = (n + THREADS - 1) / THREADS, first = wave * rounds * kWave + lane;
+    auto each = [&](auto &&body) {
+#pragma unroll
+        for (int r = 0; r < kItems; ++r)
+            if (r < rounds) body(r, first + r * kWave);
+    };
+    long long raw[kItems];
+    each([&](int r, int i) { raw[r] = bt.indices[lo + min(i, n - 1)]; });
+
+    const bool even = (unsigned long long)args.even.d * (unsigned)B == (unsigned)n;
+    const BagSearch bags{bag_offsets, lo, B, max(0, 32 - __clz((B - 1) / (2 * kWaves * 256))), even};
+    int bad_code = tid == 0 ? x.bad_code : 0;
+    long long bad_value = x.bad_value;
+    if (n > 0) {
+        const int b = bags.disorder<THREADS>(0, B, n, tid);
+        if (b >= 0) bad_code = DQRM_ERR_BAD_OFFSETS, bad_value = (long long)t * B + b;
+    }
+    if (bad_code != 0) report(bad_code, t, bad_value);
+    if (tid < kAbsmaxSlots) *absmax_slot(ws.absmax_slots, t, tid) = 0.0f;
+    if (tid < kChunkClasses) s_class[tid] = 0; // (read after more barriers)
+
+    // ---- 1. stable LSD radix sort of the rows (or the number of rows, for a bad index), at most 8 bits per pass
+    unsigned key[kItems], pos[kItems]; // pos: in the upper half the rank inside the wave's items of the digit
+    bool bad_index = false;
+    each([&](int r, int i) {
+        const bool good = (unsigned long long)raw[r] < rows_t;
+        if (!good && i < n) bad_index = true, bad_value = raw[r];
+        // (padding: the largest digit in every pass and last in line, so it stays last)
+        key[r] = i < n ? (good ? (unsigned)raw[r] : rows_t) : ~0u;
+        pos[r] = (unsigned)i;
+    });
+    if (bad_index) report(DQRM_ERR_INDEX_OUT_OF_RANGE, t, bad_value);
+    const int nbits = 32 - __clz(rows_t | 1u), passes = (nbits + 7) / 8, bits = (nbits + passes - 1) / passes;
+    const unsigned digit_mask = (1u << bits) - 1u;
+    unsigned short *my_cnt = s_digits[0] + wave * 256, *my_place = s_digits[1] + wave * 256;
+#pragma unroll 1
+    for (int p = 0; p < passes; ++p) {
+        const int shift = bits * p;
+        // (a wave's row of counters is its own: no barrier between clearing and counting)
+        *reinterpret_cast<uint2 *>(my_cnt + 4 * lane) = make_uint2(0u, 0u);
+        each([&](int r, int) {
+            const unsigned d = (key[r] >> shift) & digit_mask;
+            const unsigned long long peers = match_digit(d, bits);
+            const unsigned prev = my_cnt[d];
+            const int rank = mask_rank(peers);
+            pos[r] = (pos[r] & 0xFFFFu) | ((prev + (unsigned)rank) << 16);
+            if (rank == 0) my_cnt[d] = (unsigned short)(prev + (unsigned)__popcll(peers));
+        });
+        __syncthreads(); // (and every thread has its items of the pass before)
+        uint2 starts;
+        *reinterpret_cast<uint2 *>(my_place + 4 * lane) = digit_places<kWaves>(s_digits[0], wave, lane, &starts);
+        each([&](int r, int) {
+            const int to = my_place[(key[r] >> shift) & digit_mask] + (int)(pos[r] >> 16);
+            s_key[to] = key[r];
+            s_pos[to] = (unsigned short)pos[r];
+        });
+        __syncthreads();
+        each([&](int r, int i) {
+            key[r] = s_key[i];
+            pos[r] = s_pos[i];
+        });
+    }
+
+    // ---- 2. bags: the guessed ones' offsets are requested now and looked at when the heads are known (half the words: a good
+    // offset fits them, and others have been reported)
+    int bag_lo[kItems], bag_hi[kItems];
+    if (even)
+        each([&](int r, int i) {
+            const unsigned g = args.even.div(i < n ? pos[r] : 0u); // below B, as the position is below n
+            bag_lo[r] = (int)bag_offsets[g];
+            bag_hi[r] = (int)bag_offsets[g + 1u];
+        });
+    else
+        bags.stage<THREADS>(s_digits[0], tid); // (all waves are through with the digits)
+
+    // ---- 3. segment heads (the valid items come first)
+    unsigned long long heads[kItems];
+    int wave_heads = 0, wave_valid = 0;
+    each([&](int r, int i) {
+        const unsigned prev = s_key[max(i - 1, 0)];
+        const bool valid = key[r] < rows_t; // (padding is not)
+        heads[r] = __ballot(valid && (i == 0 || key[r] != prev));
+        wave_heads += __popcll(heads[r]);
+        wave_valid += __popcll(__ballot(valid));
+    });
+    if (lane == 0) s_x[wave] = wave_heads | (wave_valid << 16);
+    __syncthreads();
+    const int incl = wave_incl_scan_add(lane < kWaves ? s_x[lane] : 0, lane); // (at most 16384 each)
+    const int total = __builtin_amdgcn_readlane(incl, kWaves - 1);
+    const int seg_count = total & 0xFFFF, valid_count = total >> 16;
+    const int heads_before = (__builtin_amdgcn_readlane(incl, wave) & 0xFFFF) - wave_heads;
+    int seg_at = heads_before;
+    each([&](int r, int i) {
+        if ((heads[r] >> lane) & 1ull) s_head[seg_at + mask_rank(heads[r])] = (unsigned short)i;
+        seg_at += __popcll(heads[r]);
+    });
+    if (tid == 0) s_head[seg_count] = (unsigned short)valid_count; // end of the last segment
+    bool search = !even;
+    if (even)
+        each([&](int r, int i) {
+            const int p = i < n ? (int)pos[r] : 0;
+            search |= bag_lo[r] > base + p || base + p >= bag_hi[r];
+            bag_lo[r] = (int)args.even.div((unsigned)p);
+        });
+    __syncthreads();
+    if (search) // (bags of other lengths that happen to add up to the same number are searched)
+        each([&](int r, int i) { bag_lo[r] = bags.find(s_digits[0], i < n ? (int)pos[r] : 0); });
+
+    // ---- 4. the sorted order and the lists.  Chunk heads: every DQRM_SEG_CHUNK-th item of a segment, counted from its head; a
+    // row looked up exactly once is a "single" and listed separately.  Both lists in sorted order: counted first, then written.
+    unsigned info[kItems]; // segment's first item (bits 0..14), its end (bits 15..29), single (bit 30), chunk (bit 31)
+    int wave_chunks = 0, wave_singles = 0;
+    seg_at = heads_before - 1;
+    each([&](int r, int i) {
+        const int seg = max(seg_at + mask_rank(heads[r]) + (int)((heads[r] >> lane) & 1ull), 0);
+        seg_at += __popcll(heads[r]);
+        const int start = s_head[seg], end = s_head[min(seg + 1, seg_count)];
+        const bool chead = i < valid_count && ((i - start) % DQRM_SEG_CHUNK) == 0, single = chead && i == start && end == i + 1;
+        info[r] = (unsigned)start | ((unsigned)end << 15) | (single ? 1u << 30 : 0u) | (chead && !single ? 1u << 31 : 0u);
+        wave_singles += __popcll(__ballot(single));
+        wave_chunks += __popcll(__ballot(chead && !single));
+    });
+    __syncthreads(); // (s_x is free again)
+    if (lane == 0) s_x[wave] = wave_chunks | (wave_singles << 16);
+    __syncthreads();
+    const int list_incl = wave_incl_scan_add(lane < kWaves ? s_x[lane] : 0, lane);
+    const int list_total = __builtin_amdgcn_readlane(list_incl, kWaves - 1), before = __builtin_amdgcn_readlane(list_incl, wave);
+    int chunk_at = base + (before & 0xFFFF) - wave_chunks, single_at = base + (before >> 16) - wave_singles;
+    seg_at = heads_before - 1;
+    each([&](int r, int i) {
+        const int seg = max(seg_at + mask_rank(heads[r]) + (int)((heads[r] >> lane) & 1ull), 0);
+        seg_at += __popcll(heads[r]);
+        const int start = (int)(info[r] & 0x7FFFu), end = (int)((info[r] >> 15) & 0x7FFFu);
+        const bool single = (info[r] >> 30) & 1u, chunk = info[r] >> 31;
+        const unsigned long long singles = __ballot(single), chunks = __ballot(chunk);
+        if (i < n) bt.sorted_pos[base + i] = base + (int)pos[r];
+        if (i < valid_count) ws.sorted_bag[base + i] = bag_lo[r];
+        if (single) ws.single_local[single_at + mask_rank(singles)] = make_int4(base + i, bag_lo[r], seg, (int)key[r]);
+        if (chunk) {
+            const int nchunks = (end - start + DQRM_SEG_CHUNK - 1) / DQRM_SEG_CHUNK, len = min(DQRM_SEG_CHUNK, end - i);
+            ws.chunk_local[chunk_at + mask_rank(chunks)] =
+                make_chunk_desc(base + i, len, (i - start) / DQRM_SEG_CHUNK, nchunks, seg,
+                                args.by_length ? atomicAdd(&s_class[chunk_class(len)], 1) : 0, key[r]);
+            // the arrival counter of a segment of more than one chunk starts at zero
+            if (i == start && nchunks > 1) ws.seg_count[(base + i) / DQRM_SEG_CHUNK] = 0;
+        }
+        single_at += __popcll(singles);
+        chunk_at += __popcll(chunks);
+    });
+    __syncthreads();
+    if (tid == 0) {
+        ws.part_info[2 * t] = make_int4(base, seg_count, list_total & 0xFFFF, list_total >> 16);
+        ws.part_info[2 * t + 1] = make_int4(s_class[0] | (s_class[1] << 16), s_class[2] | (s_class[3] << 16), s_class[4], 0);
     }
 }
 

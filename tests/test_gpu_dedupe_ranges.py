@@ -215,16 +215,10 @@ def test_uneven_tables(per_table, B, kind):
     assert (run.status()[0] != 0) == (kind == "hot")
 
 
-# Batches of one launch: their tables' sizes differ from batch to batch; partitioned ones; more tables than are ever partitioned.
-@pytest.mark.parametrize("batches", [
-    [[128] * 30, [128] * 29 + [60_000], [60_000] + [1] * 29], [[17_000, 16_500, 20_000], [65536, 16_400, 10_000]],
-    [[16_500] * 140]], ids=["uneven", "partitioned", "many"])
-def test_batches_of_one_launch(batches):
-    T, B = len(batches[0]), 900
-    cards = np.full(T, 3000, np.int64)
+def _dedupe_batches(data, cards, B, bound=0):
+    """The batches (indices, offsets) in one launch, checked against _expected and through the segment sums."""
+    T = len(cards)
     wl = Workload(name="batches", T=T, D=8, B=B, alpha=1.05, seed=1, cards=cards)
-    data = [_uneven(k, p, cards, B, False) for k, p in enumerate(batches)]
-    print(f"batches of {[len(i) for i, _ in data]} lookups in {T} tables", flush=True)
     most = max(len(i) for i, _ in data)
     runs = []
     for idx, off in data:
@@ -234,7 +228,7 @@ def test_batches_of_one_launch(batches):
         runs.append(run)
     b = [r.bufs for r in runs]
     runs[0].dq.dqrm_dedupe_multi(runs[0].tables, B, [(r.idx, r.off, x.sorted_pos, x.uniq_rows, x.seg_offsets, x.table_uniq_offsets,
-                                                      x.num_unique, x.workspace) for r, x in zip(runs, b)])
+                                                      x.num_unique, x.workspace) for r, x in zip(runs, b)], max_table_lookups=bound)
     for (idx, off), r, x in zip(data, runs, b):
         U = int(x.num_unique.cpu().item())
         got = dict(U=np.array([U]), sorted_pos=x.sorted_pos.cpu().numpy()[:len(idx)], uniq_rows=x.uniq_rows.cpu().numpy()[:U],
@@ -242,4 +236,45 @@ def test_batches_of_one_launch(batches):
         for k, v in _expected(wl, idx, off, B).items():
             assert_exact(got[k], v, k)
         _sums_exact(r, idx, off, B, cards, got, "batch")
-    assert runs[0].status()[0] == 0
+    return runs[0].status()
+
+
+# Batches of one launch: their tables' sizes differ from batch to batch; partitioned ones; more tables than are ever partitioned.
+@pytest.mark.parametrize("batches", [
+    [[128] * 30, [128] * 29 + [60_000], [60_000] + [1] * 29], [[17_000, 16_500, 20_000], [65536, 16_400, 10_000]],
+    [[16_500] * 140]], ids=["uneven", "partitioned", "many"])
+def test_batches_of_one_launch(batches):
+    T, B = len(batches[0]), 900
+    cards = np.full(T, 3000, np.int64)
+    print(f"batches of {[sum(p) for p in batches]} lookups in {T} tables", flush=True)
+    status = _dedupe_batches([_uneven(k, p, cards, B, False) for k, p in enumerate(batches)], cards, B)
+    assert status[0] == 0
+
+
+# A launch of so many tables that each is one workgroup's (64 tables x 2 batches, more than 2048 lookups in the average table, at
+# most 16384 in any): lookups at the edges of a workgroup's rounds, tables of one row to many bits of row, hot rows and bad indices,
+# bags of one lookup, of unequal length, unequal but adding up as if equal, and more bags than the LDS holds.
+@pytest.mark.parametrize("bags", ["one", "ragged", "pretend", "many"])
+@pytest.mark.parametrize("rows", [1, 2, 255, 256, 70_000])
+def test_whole_tables(bags, rows):
+    T = 64
+    cards = np.full(T, min(rows, 3000), np.int64)
+    cards[[0, 9, T - 1]] = rows
+    data = []
+    if bags in ("one", "pretend"):  # every table has as many lookups
+        B = {"one": 16384, "pretend": 1500}[bags] if rows != 256 else 2051
+        per_table = [B * (1 if bags == "one" else 5)] * T
+    else:
+        B = {"ragged": 700, "many": 20_001}[bags]
+        per_table = [0, 1, 2, 63, 64, 65, 1023, 1024, 1025, 16384, 16383, 15_361] + [2500] * (T - 12)
+    for k in range(2):
+        idx, off = _uneven(k, per_table, cards, B, bags in ("one", "pretend"), hot=0.3 if k else None, bad=0.01 * k)
+        if bags == "pretend":
+            lens = np.full((T, B), 5)
+            lens[:, : B // 2] += 1
+            lens[:, B - B // 2:] -= 1
+            off = np.concatenate([[0], np.cumsum(lens.reshape(-1))]).astype(np.int64)
+        data.append((idx, off))
+    print(f"whole tables: {bags}, {B} bags, {rows} rows, {max(per_table)} lookups", flush=True)
+    status = _dedupe_batches(data, cards, B, bound=16384)
+    assert status[0] == (0 if max(per_table) <= 4096 else -4)
