@@ -85,6 +85,13 @@ struct WsLayout {
         off_single_desc, off_seg_count, off_partial_full, off_partial_last, off_absmax_slots, total;
 };
 
+// Whether a batch can be partitioned by range (dedupe_partition_kernel): more lookups than one tile, and room for at least 8
+// ranges of every table.
+bool partitionable(int32_t T, int64_t N) { return N > dqrm::kDdTile && T * 8 <= dqrm::kMaxParts; }
+
+// (table, range) pairs of a batch: only where the tables alone are many is there room for more than kMaxParts
+int max_slots(int32_t T) { return 2 * T > dqrm::kMaxParts ? dqrm::kMaxSlots : dqrm::kMaxParts; }
+
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 WsLayout ws_layout(int32_t T, int32_t D, int64_t N)
@@ -97,10 +104,9 @@ WsLayout ws_layout(int32_t T, int32_t D, int64_t N)
         o = align_up(o + bytes, 256);
         return at;
     };
-    L.off_part_info = take((size_t)dqrm::kMaxSlots * 2 * sizeof(int4));
+    L.off_part_info = take((size_t)max_slots(T) * 2 * sizeof(int4));
     L.off_totals = take(4 * sizeof(int));
-    // (only a batch of more than kDdTile lookups is partitioned)
-    const size_t big = N > dqrm::kDdTile ? n : 0;
+    const size_t big = partitionable(T, N) ? n : 0;
     L.off_part_key = take(big * sizeof(unsigned));
     L.off_part_pos = take(big * sizeof(unsigned short));
     L.off_part_start = take(big ? t * dqrm::kDdTiles * dqrm::kDdRanges * sizeof(unsigned short) : 0);
@@ -422,7 +428,7 @@ int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t nu
     for (int i = 0; i < num_batches; ++i) most = std::max<int64_t>(most, std::min<int64_t>(da.b[i].N, da.b[i].limit));
     // From two tiles per table on every range's workgroup reading the whole table costs more than sorting the tiles by
     // range first: 26 x 65536 lookups 132 us, against 215 with 8 ranges that each read everything.
-    const bool partition = avg > 2 * dqrm::kDdTile && least_n > dqrm::kDdTile && most_parts >= 8;
+    const bool partition = avg > 2 * dqrm::kDdTile && partitionable(T, least_n);
     // Where the tables alone are workgroups for half of the CUs or more, none is cut (dedupe_table_kernel): 208 x 8192 lookups 60
     // (dedupe_kernel, one range: 67), 1024 x 4096 181 (187); with fewer lookups dedupe_kernel's shorter code counts for more.
     const bool whole = !partition && avg > 2048 && most <= dqrm::kTableCap && num_cus() <= wgs * 2;
@@ -448,8 +454,8 @@ int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t nu
     const int64_t light = std::max<int64_t>(cap, avg + avg / 4);
     const bool uneven = !partition && !whole && most > light;
     if (uneven) {
-        const int64_t room = dqrm::kMaxSlots - T * parts;
-        const int64_t per_range = std::max<int64_t>({cap / 2, DQRM_MAX_TABLE_LOOKUPS / dqrm::kDdMaxRanges, (max_n + room - 1) / room});
+        const int64_t room = max_slots(T) - T * parts;
+        const int64_t per_range = std::max<int64_t>({cap / 2, DQRM_MAX_TABLE_LOOKUPS / dqrm::kDdMaxRanges, room > 0 ? (max_n + room - 1) / room : max_n + 1});
         da.light = (int)light;
         da.per_range = (int)std::min<int64_t>(per_range, DQRM_MAX_TABLE_LOOKUPS);
         // the sum over the tables above `light` of ceil(n / per_range) - parts, at most

@@ -57,6 +57,9 @@ def test_workspace_bytes():
     assert f(0, 64, 8192, 10) == 0 and f(26, 12, 8192, 10) == 0 and f(26, 512, 8, 10) == 0
     assert f(26, 64, 0, 10) == 0 and f(26, 64, 8, -1) == 0 and f(2000, 64, 8, 10) == 0
     assert f(1, 8, 1, 0) > 0
+    # batches that the built-in scratch has always taken: many tables, and few
+    for T, D, N in ((1024, 8, 39647), (1024, 256, 28471), (560, 256, 32831), (129, 64, 47160), (128, 64, 51648), (26, 64, 53680), (1, 8, 59600)):
+        assert f(T, D, 1, N) <= dq.NOALLOC_SCRATCH_BYTES, (T, D, N)
 
 
 def test_validation_errors_before_any_launch():
