@@ -847,41 +847,67 @@ int64_t dense_param_count(const dqrm_dense_model_t *m)
     return p;
 }
 
-// A layer whose weight gradient [out][in] takes tiles of 64x64 (a workgroup each); narrower ones go by 32x32, and
-// their bias gradient is a column of the product.
-bool weight_grad_tile64(int in, int out) { return in >= 64 && out >= 64; }
-
-int64_t weight_grad_tiles(int in, int out) // per slice of the batch; 32x32 tiles: four to a workgroup
+// The layers' inputs and outputs, bottom MLP first.
+template <typename F>
+void each_layer(const dqrm_dense_model_t *m, F &&f)
 {
-    return weight_grad_tile64(in, out) ? (int64_t)((out + 63) / 64) * ((in + 63) / 64)
-                                       : (int64_t)((out + 31) / 32) * ((in + 1 + 31) / 32);
+    for (int l = 0; l < m->bot_layers; ++l) f(m->bot_dims[l], m->bot_dims[l + 1]);
+    for (int l = 0; l < m->top_layers; ++l) f(m->top_dims[l], m->top_dims[l + 1]);
 }
 
-// Slices of the batch dimension in the weight-gradient products (all layers share one launch).  A workgroup per CU
-// walks its slice in 1.7 us per 128 samples (a slab of 64x64 products for each of its four waves), so the slices
-// that fill whole rounds of the chip are wanted; a slice costs its partial tiles, written and added up again, at about
-// 4 TB/s.  At least one pair of slabs per wave and slice, and at least two slices (the kernel stores partial tiles only
-// when the reduction is split; a slice may be empty).
-int dense_splits(const dqrm_dense_model_t *m, int batch)
+// How the weight-gradient products [out][in] of all layers (one launch) are cut: the batch dimension in `splits` slices, and
+// whether the layers of at least 64 x 64 go by tiles of that size, a workgroup each.  Other layers go by tiles of 32x32, a wave
+// each, and their bias gradient is a column of the product.
+struct GradCut {
+    bool tile64;
+    int splits, per; // `per` samples to a slice: whole pairs of slabs (what is left of a pair takes a wave as long as several)
+    void cut(int batch, int s)
+    {
+        constexpr int kPair = 2 * dqrm::kGemmBK;
+        per = ((batch + s - 1) / s + kPair - 1) / kPair * kPair;
+        splits = std::max(2, (batch + per - 1) / per); // (the kernel stores partial tiles only when the reduction is split)
+    }
+    bool is64(int in, int out) const { return tile64 && in >= 64 && out >= 64; }
+};
+
+GradCut grad_cut(const dqrm_dense_model_t *m, int batch)
 {
-    int64_t blocks = 0;
-    double params = 0;
-    auto add = [&](int in, int out) {
-        const int64_t t = weight_grad_tiles(in, out);
-        blocks += weight_grad_tile64(in, out) ? t : (t + dqrm::kGemmWaves - 1) / dqrm::kGemmWaves;
-        params += (double)out * (in + 1);
-    };
-    for (int l = 0; l < m->bot_layers; ++l) add(m->bot_dims[l], m->bot_dims[l + 1]);
-    for (int l = 0; l < m->top_layers; ++l) add(m->top_dims[l], m->top_dims[l + 1]);
+    constexpr int kPair = 2 * dqrm::kGemmBK; // samples of a pair of slabs, which a wave takes at a time
     const int64_t cus = num_cus();
-    int best = 2;
+    int64_t tiles = 0, large = 0, small = 0; // 32x32 tiles of all layers; 64x64 tiles; and those of 32x32 beside them
+    double params = 0;
+    each_layer(m, [&](int in, int out) {
+        const int64_t t = (int64_t)((out + 31) / 32) * ((in + 1 + 31) / 32);
+        tiles += t;
+        if (in >= 64 && out >= 64)
+            large += (int64_t)((out + 63) / 64) * ((in + 63) / 64);
+        else
+            small += (t + dqrm::kGemmWaves - 1) / dqrm::kGemmWaves;
+        params += (double)out * (in + 1);
+    });
+    const int64_t most = (batch + kPair * dqrm::kGemmWaves - 1) / (kPair * dqrm::kGemmWaves); // slices of a pair of slabs per wave
+    GradCut c{large * most * 4 >= cus * 3, 2, 0};
+    if (!c.tile64) {
+        // The 64x64 tiles would leave CUs idle even at a pair of slabs per wave: about one 32x32 tile per SIMD, then, each with
+        // at least a pair of slabs.  Whole steps, us, 64x64 tiles (at most a slice per 256 samples) -> these: bottom MLP
+        // 13-48-32-16, top 52-60-48-1 at 1024 samples 80.4 -> 75.2; 13-128-128, 164-128-64-1 at 3000 106.7 -> 102.3; Kaggle's MLPs
+        // at 256 106.8 -> 105.0, but at 500 114.2 -> 115.0 (232 workgroups of 64x64 tiles).
+        const int64_t s = std::min<int64_t>((cus * 4 + tiles / 2) / std::max<int64_t>(tiles, 1), batch / kPair);
+        c.cut(batch, (int)std::max<int64_t>(2, std::min<int64_t>(s, kDenseMaxSplits)));
+        return c;
+    }
+    // A workgroup per CU walks its slice in 1.7 us per 128 samples (a slab of 64x64 products for each of its four waves), so the
+    // slices that fill whole rounds of the chip are wanted; a slice costs its partial tiles, written and added up again, at about
+    // 4 TB/s.  At least one pair of slabs per wave and slice.
     double best_us = 0;
+    int best = 2;
     for (int s = 2; s <= kDenseMaxSplits; ++s) {
-        if (s > 2 && (int64_t)s * 2 * dqrm::kGemmBK * dqrm::kGemmWaves > batch) break;
-        const double us = (double)((blocks * s + cus - 1) / cus) * batch / s / 128 * 1.7 + s * params * 8 / 4e6;
+        if (s > 2 && (int64_t)s * kPair * dqrm::kGemmWaves > batch) break;
+        const double us = (double)(((large + small) * s + cus - 1) / cus) * batch / s / 128 * 1.7 + s * params * 8 / 4e6;
         if (s == 2 || us < best_us) best = s, best_us = us;
     }
-    return best;
+    c.cut(batch, best);
+    return c;
 }
 
 int32_t check_dense_model(const dqrm_dense_model_t *m, int32_t batch)
@@ -916,7 +942,7 @@ DenseLayout dense_layout(const dqrm_dense_model_t *m, int32_t batch)
         o = align_up(o + floats * sizeof(float), 256);
         return at;
     };
-    const size_t splits = (size_t)dense_splits(m, batch);
+    const size_t splits = (size_t)grad_cut(m, batch).splits;
     for (int l = 0; l < m->bot_layers; ++l) {
         L.bot_act[l] = take((size_t)batch * m->bot_dims[l + 1]);
         L.bot_dz[l] = take((size_t)batch * m->bot_dims[l + 1]);
@@ -1031,21 +1057,19 @@ hipError_t launch_interact(hipStream_t st, const dqrm::InteractArgs &ia, bool ba
 }
 
 // One layer's weight-gradient product  [dZ^T * X | dZ^T * 1]  ([out][in + 1], the last column is the bias
-// gradient) with the batch dimension cut into `splits` slices: partials[s][out][in + 1].
-dqrm::GemmArgs weight_grad_problem(const float *dZ, const float *X, float *partials, int B, int in, int out, int splits)
+// gradient) with the batch dimension cut into slices: partials[s][out][in + 1].
+dqrm::GemmArgs weight_grad_problem(const float *dZ, const float *X, float *partials, int B, int in, int out, const GradCut &cut)
 {
-    int per = (B + splits - 1) / splits;
-    per = (per + dqrm::kGemmBK - 1) / dqrm::kGemmBK * dqrm::kGemmBK;
     dqrm::GemmArgs g{};
     g.A = dZ, g.a_si = 1, g.a_sr = out;
     g.B = X, g.b_sr = in, g.b_sj = 1;
     g.M = out, g.K = B;
-    if (weight_grad_tile64(in, out))
+    if (cut.is64(in, out))
         g.N = in, g.tile64 = 1;
     else
         g.N = in + 1, g.b_ones_last = 1;
-    g.splits = splits; // exactly the slices the workspace holds; slices past the batch come out as zeros
-    g.k_per_split = per, g.P = partials;
+    g.splits = cut.splits; // exactly the slices the workspace holds; slices past the batch come out as zeros
+    g.k_per_split = cut.per, g.P = partials;
     return g;
 }
 
@@ -1191,7 +1215,7 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
 
     // ... then every layer's weight gradient in one launch and the SGD step in another (the input gradients
     // above used the weights of before the step)
-    const int splits = dense_splits(m, B);
+    const GradCut cut = grad_cut(m, B);
     dqrm::GemmGroup wg{};
     dqrm::SgdGroup sg{};
     sg.lr = lr;
@@ -1228,7 +1252,7 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
     };
     auto add_layer = [&](const float *dZ, const float *X, float *W, float *b, float *part, int in, int out) {
         if (wg.count == dqrm::kGemmMaxGroup) flush(false);
-        const dqrm::GemmArgs g = weight_grad_problem(dZ, X, part, B, in, out, splits);
+        const dqrm::GemmArgs g = weight_grad_problem(dZ, X, part, B, in, out, cut);
         wg.p[wg.count++] = g;
         dqrm::SgdLayer &s = sg.l[sg.count++];
         s.P = part, s.W = W, s.b = b, s.S = g.splits, s.out = out, s.in = in, s.elem_begin = sg.total;
