@@ -1152,11 +1152,13 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
 
     // ---- forward
     // The bottom MLP's last layer rides along in the interaction kernels while its weights are few (64 -> 16 in the
-    // paper's Kaggle model; every sample reads them all), and a first layer with a short reduction (the 13 dense
-    // features) has a kernel of its own: both are all launch cost as products on the matrix cores.
+    // paper's Kaggle model; every sample reads them all), a little more of them at small batches, and a first layer with a
+    // short reduction (the 13 dense features) has a kernel of its own: both are all launch cost as products on the matrix
+    // cores.  (4160 to 4352 floats, us, products -> riding: 64 -> 64 at 256 samples 82.8 -> 80.1, 4096: 111.0 -> 109.5, 8192: 140 ->
+    // 148; 256 -> 16 at 256: 105.6 -> 99.8, 4096: 239 -> 236, 6000: 348 -> 353.  8448 floats, 128 -> 64 at 256: 85.2 -> 90.9.)
     const int bl_last = m->bot_layers - 1;
     const int lin_floats = (int)std::min<int64_t>((int64_t)D * dqrm::inter_lin_pitch(m->bot_dims[bl_last]), 1 << 20);
-    const bool ride = lin_floats <= dqrm::kInterLinFloats;
+    const bool ride = lin_floats <= (B <= 4096 ? dqrm::kInterLinFloatsFew : dqrm::kInterLinFloats);
     const float *x = dense_x;
     for (int l = 0; l < m->bot_layers - (ride ? 1 : 0); ++l) {
         const int in = m->bot_dims[l], out = m->bot_dims[l + 1];

@@ -923,7 +923,8 @@ __host__ __device__ inline int inter_lin_pitch(int K)
     const int q = (K + 3) / 4;
     return 4 * (q | 1);
 }
-constexpr int kInterLinFloats = 4096; // weights (with their padding) of a layer that rides along, at most (host)
+// weights (with their padding) of a layer that rides along, at most (host): of any batch, of a small one
+constexpr int kInterLinFloats = 4096, kInterLinFloatsFew = 4608;
 // floats of LDS per wave: forward (lin_k: the riding layer's input width, or 0), backward
 __host__ __device__ inline int inter_wave_floats(int V, int D, int lin_k)
 {

@@ -63,7 +63,7 @@ def _check(oracle, T, D, B, bot, top, seed=7, margin=False):
 @pytest.mark.parametrize("T,D,B,bot", [
     (1, 1, 3, [4]), (1, 16, 5, [13, 20]), (30, 12, 9, [13, 24]), (31, 20, 21, [13, 32]), (32, 8, 33, [9, 8]), (33, 24, 18, [13, 300]),
     (63, 64, 70, [13, 64]), (40, 7, 37, [5, 11]), (2, 130, 40, [13, 16]), (1, 1500, 6, [3]), (26, 64, 130, [13, 512, 256]),
-    (5, 33, 64, [17, 120]), (15, 256, 24, [7, 8])])
+    (5, 33, 64, [17, 120]), (15, 256, 24, [7, 8]), (4, 16, 40, [13, 280]), (4, 16, 41, [13, 288])])
 def test_interaction_shapes(oracle, T, D, B, bot):
     _check(oracle, T, D, B, bot, [16])
 
@@ -74,7 +74,8 @@ def test_interaction_shapes(oracle, T, D, B, bot):
 # gradients by some 1e-3 of their norm; large batches therefore keep every pre-activation away from zero.
 @pytest.mark.parametrize("T,D,B,bot,top", [
     (3, 64, 65, [13, 64, 64], [64, 65]), (2, 8, 1, [64, 128], [64, 64]), (3, 70, 129, [65, 64, 128], [63, 64, 127, 128]),
-    (2, 8, 2085, [13, 300], [321, 257]), (2, 16, 8200, [16], [120, 260]), (2, 16, 4160, [64], [160, 256, 64])])
+    (2, 8, 2085, [13, 300], [321, 257]), (2, 16, 8200, [16], [120, 260]), (2, 16, 4160, [64], [160, 256, 64]),
+    (8, 16, 1023, [13, 48, 32], [60, 48]), (8, 64, 1536, [13, 64], [128, 64]), (3, 16, 257, [13, 600], [601, 64])])
 def test_product_tiles(oracle, T, D, B, bot, top):
     _check(oracle, T, D, B, bot, top, margin=B > 1000)
 
