@@ -984,9 +984,12 @@ hipError_t launch_gemm(hipStream_t st, const dqrm::GemmArgs &g)
     return hipGetLastError();
 }
 
-// Samples per workgroup of the short-input layer: two workgroups per CU (4 waves of 2), within the kernel's limits.
-int small_k_samples(int batch)
+// Samples per workgroup of the short-input layer: two workgroups per CU (4 waves of 2), within the kernel's limits, for wide
+// layers; up to 256 outputs (one wave of the workgroup's two) reading the weights costs less than walking more samples does:
+// 8192 samples, whole steps, us, at 4 / 8 / 16 samples: 13 -> 64 78.0 / 77.9 / 81.5, 256 100.8 / 101.3 / 100.9, 512 127.8 / 121.1 / 119.0.
+int small_k_samples(int batch, int out)
 {
+    if (out <= 256) return dqrm::kSmallKMinSamples;
     return std::min(dqrm::kSmallKMaxSamples, std::max(dqrm::kSmallKMinSamples, batch / (2 * num_cus())));
 }
 
@@ -1165,7 +1168,7 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
         if (in <= dqrm::kSmallKMax && out % 4 == 0 && aligned(m->bot_b[l], 16)) {
             dqrm::SmallKArgs sk{};
             sk.X = x, sk.W = bot_wf[l], sk.bias = m->bot_b[l], sk.Y = F(L.bot_act[l]), sk.B = B, sk.N = out, sk.K = in, sk.relu = 1;
-            sk.samples = small_k_samples(B);
+            sk.samples = small_k_samples(B, out);
             hipLaunchKernelGGL(dqrm::linear_small_k_kernel, dim3((B + sk.samples - 1) / sk.samples),
                                dim3(dqrm::kSmallKThreads), 0, st, sk);
             DQRM_HIP_CHECK(hipGetLastError());

@@ -80,8 +80,9 @@ def test_product_tiles(oracle, T, D, B, bot, top):
     _check(oracle, T, D, B, bot, top, margin=B > 1000)
 
 
-# The short-input layer takes 4 samples to a workgroup while that fills 2 workgroups per CU, then up to 16: remainders of 8,
-# 16 and 16 samples (on 256 CUs).
+# The short-input layer takes 4 samples to a workgroup while that fills 2 workgroups per CU or the layer has at most 256 outputs,
+# then up to 16: remainders of 8, 16 and 16 samples (on 256 CUs).
 @pytest.mark.parametrize("B", [4099, 8195, 9001])
-def test_short_input_layer(oracle, B):
-    _check(oracle, 2, 8, B, [13, 68], [16], margin=True)
+@pytest.mark.parametrize("width", [68, 256, 260])
+def test_short_input_layer(oracle, B, width):
+    _check(oracle, 2, 8, B, [13, width], [16], margin=True)
