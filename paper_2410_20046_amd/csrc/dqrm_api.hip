@@ -1036,11 +1036,37 @@ hipError_t linear_bwd_input(hipStream_t st, const float *dZ, const float *W, con
     return launch_gemm<dqrm::kOpRC, dqrm::kOpWideVec>(st, g);
 }
 
-// The interaction, forward or backward: one wave per sample, as many waves per workgroup as the LDS holds.  Vectors of a
+// Whether the interaction of V vectors of D floats goes by the plain kernels: where it would fill only a little of the 32x32 tiles
+// that the matrix cores take it in.  Whole steps (13-64-D, x-32-1) of 8192 samples, us, matrix cores / plain, with the share:
+//   up to 32 vectors (one tile): 2 x 64 (0.01) 107 / 88, 9 x 16 (0.04) 83 / 76, 12 x 128 (0.14) 148 / 141, 27 x 8 (0.18) 104 / 101,
+//                                21 x 16 (0.22) 97.6 / 97.7, 16 x 32 (0.25) 98 / 101, 27 x 16 (0.36) 105 / 110
+//   more: 36 x 8 (0.08) 161 / 119, 33 x 32 (0.27) 181 / 160, 50 x 16 (0.31) 216 / 202, 63 x 16 (0.48) 286 / 305; but 33 x 64
+//         (0.27) 220 / 226, 46 x 32 (0.52) 219 / 252
+bool inter_plain(int V, int D)
+{
+    const int t = dqrm::inter_tiles(V) * 32;
+    const int64_t share = (int64_t)V * V * D * 100, whole = (int64_t)t * t * ((D + 31) / 32 * 32);
+    return share < whole * (V > 32 && D <= 32 ? 31 : 22);
+}
+
+// Weights (with their padding) of a bottom MLP's last layer that rides along in the interaction, at most.
+int inter_lin_floats(int V, int D, int in, int batch)
+{
+    if (batch > 2048) return dqrm::kInterLinFloats;
+    return inter_plain(V, D) && in <= 256 ? dqrm::kInterLinFloatsPlain : dqrm::kInterLinFloatsFew;
+}
+
+// The interaction, forward or backward.  On the matrix cores: one wave per sample, as many waves per workgroup as the LDS holds.  Vectors of a
 // multiple of 4 floats are read 16 bytes at a time (from any 4-byte boundary).
 hipError_t launch_interact(hipStream_t st, const dqrm::InteractArgs &ia, bool backward, int lin_floats)
 {
     const int V = ia.T + 1;
+    if (inter_plain(V, ia.D)) {
+        const size_t lds = sizeof(float) * dqrm::inter_plain_floats(V, ia.D, backward, lin_floats ? ia.lin_k : 0);
+        hipLaunchKernelGGL(backward ? dqrm::interact_bwd_plain_kernel : dqrm::interact_fwd_plain_kernel, dim3(ia.B),
+                           dim3(dqrm::kInterPlainThreads), lds, st, ia);
+        return hipGetLastError();
+    }
     const size_t per = sizeof(float) * (backward ? dqrm::inter_wave_floats_bwd(V, ia.D)
                                                  : dqrm::inter_wave_floats(V, ia.D, lin_floats ? ia.lin_k : 0));
     const size_t shared = sizeof(float) * (size_t)lin_floats;
@@ -1157,11 +1183,12 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
     // The bottom MLP's last layer rides along in the interaction kernels while its weights are few (64 -> 16 in the
     // paper's Kaggle model; every sample reads them all), a little more of them at small batches, and a first layer with a
     // short reduction (the 13 dense features) has a kernel of its own: both are all launch cost as products on the matrix
-    // cores.  (4160 to 4352 floats, us, products -> riding: 64 -> 64 at 256 samples 82.8 -> 80.1, 4096: 111.0 -> 109.5, 8192: 140 ->
-    // 148; 256 -> 16 at 256: 105.6 -> 99.8, 4096: 239 -> 236, 6000: 348 -> 353.  8448 floats, 128 -> 64 at 256: 85.2 -> 90.9.)
+    // cores.  (On the matrix cores, 4160 to 4352 floats, us, products -> riding: 256 -> 16 and 26 tables at 256 samples 105.6 ->
+    // 99.8, 2048: 157 -> 154, 8192: 404 -> 410; 64 -> 64 and 32 tables at 2048 102.5 -> 97.7, 4096: 144 -> 148.  In the plain
+    // kernels, 8320 floats, 256 -> 32 at 64: 51.2 -> 46.9, 1024: 54.5 -> 50.1, 8192: 104 -> 120; 512 -> 32 at 64: 53.7 -> 58.5.)
     const int bl_last = m->bot_layers - 1;
     const int lin_floats = (int)std::min<int64_t>((int64_t)D * dqrm::inter_lin_pitch(m->bot_dims[bl_last]), 1 << 20);
-    const bool ride = lin_floats <= (B <= 4096 ? dqrm::kInterLinFloatsFew : dqrm::kInterLinFloats);
+    const bool ride = lin_floats <= inter_lin_floats(T + 1, D, m->bot_dims[bl_last], B);
     const float *x = dense_x;
     for (int l = 0; l < m->bot_layers - (ride ? 1 : 0); ++l) {
         const int in = m->bot_dims[l], out = m->bot_dims[l + 1];

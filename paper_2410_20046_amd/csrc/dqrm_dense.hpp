@@ -923,8 +923,9 @@ __host__ __device__ inline int inter_lin_pitch(int K)
     const int q = (K + 3) / 4;
     return 4 * (q | 1);
 }
-// weights (with their padding) of a layer that rides along, at most (host): of any batch, of a small one
-constexpr int kInterLinFloats = 4096, kInterLinFloatsFew = 4608;
+// weights (with their padding) of a layer that rides along, at most (host): of any batch, of a small one, of a small one in the
+// plain kernels
+constexpr int kInterLinFloats = 4096, kInterLinFloatsFew = 4608, kInterLinFloatsPlain = 8704;
 // floats of LDS per wave: forward (lin_k: the riding layer's input width, or 0), backward
 __host__ __device__ inline int inter_wave_floats(int V, int D, int lin_k)
 {
@@ -1200,6 +1201,119 @@ __global__ __launch_bounds__(kInterThreads) void interact_bwd_kernel(InteractArg
         for (int k = lane; k < K; k += kWave) {
             float s = 0.0f;
             for (int d = 0; d < D; ++d) s = __builtin_fmaf(z[d], a.lin_w[(long long)d * K + k], s);
+            if (a.lin_mask) s = a.lin_mask[(long long)b * K + k] > 0.0f ? s : 0.0f;
+            a.lin_dx[(long long)b * K + k] = s;
+        }
+    }
+}
+
+// ---- the plain kernels: few or short vectors (inter_plain()) ------------------------------------------------------
+// The matrix cores' tiles would be mostly padding, and a wave per sample a long way for the little there is to do: a sample has a
+// workgroup, whose threads take pairs (forward) or elements (backward).  Bound by that chain of a sample (loads, LDS, the riding
+// layer, stores) and the instructions of 128 threads per sample.  9 vectors of 16, 8192 samples, with a layer 32 -> 16 riding
+// along: 8.7 and 11.8 us; the kernels above take 10.5 and 17.9.
+constexpr int kInterPlainThreads = 128;
+// floats of dynamic LDS (at most 33 KB)
+inline int inter_plain_floats(int V, int D, bool backward, int lin_k)
+{
+    return (backward ? V * D + V * (V | 1) + D : V * (D + 1)) + lin_k;
+}
+
+__global__ __launch_bounds__(kInterPlainThreads) void interact_fwd_plain_kernel(InteractArgs a)
+{
+    // rows one float apart from a multiple of the bank count: the lanes of a wave read different rows at the
+    // same d, and with a pitch of D = 16 all of them would fall into two banks
+    extern __shared__ __align__(16) float inter_lds[]; // V * (D + 1) (+ lin_k) floats (inter_plain_floats)
+    float *z = inter_lds;
+    const int b = blockIdx.x, V = a.T + 1, D = a.D, pitch = D + 1;
+    if (a.lin_w) {
+        // the embeddings travel while the layer is computed: 8 threads per output, each a strided eighth of the sum
+        for (int e = D + (int)threadIdx.x; e < V * D; e += kInterPlainThreads) {
+            const int i = e / D, d = e - i * D;
+            z[i * pitch + d] = a.emb[(long long)b * a.T * D + (e - D)];
+        }
+        float *xin = inter_lds + V * pitch; // lin_k floats
+        const int K = a.lin_k;
+        for (int k = threadIdx.x; k < K; k += kInterPlainThreads) xin[k] = a.lin_x[(long long)b * K + k];
+        __syncthreads();
+        for (int e0 = 0; e0 < D * 8; e0 += kInterPlainThreads) { // (kInterPlainThreads is a multiple of 8: teams stay whole)
+            const int e = e0 + (int)threadIdx.x;
+            const int d = min(e >> 3, D - 1), part = e & 7;
+            const float *w = a.lin_w + (long long)d * K;
+            float s = 0.0f;
+            for (int k = part; k < K; k += 8) s = __builtin_fmaf(xin[k], w[k], s);
+            s += __shfl_xor(s, 1, kWave);
+            s += __shfl_xor(s, 2, kWave);
+            s += __shfl_xor(s, 4, kWave);
+            if (part == 0 && e < D * 8) {
+                const float y = fmaxf(s + a.lin_b[d], 0.0f);
+                z[d] = y;
+                a.lin_y[(long long)b * D + d] = y;
+            }
+        }
+    } else {
+        for (int e = threadIdx.x; e < V * D; e += kInterPlainThreads) {
+            const int i = e / D, d = e - i * D;
+            z[i * pitch + d] = e < D ? a.bot[(long long)b * D + e] : a.emb[(long long)b * a.T * D + (e - D)];
+        }
+    }
+    __syncthreads();
+    const int P = V * (V - 1) / 2, W = D + P;
+    float *r = a.R + (long long)b * W;
+    for (int e = threadIdx.x; e < W; e += kInterPlainThreads) {
+        if (e < D) {
+            r[e] = z[e];
+        } else {
+            int i, j;
+            pair_of(e - D, i, j);
+            const float *zi = z + i * pitch, *zj = z + j * pitch;
+            float s = 0.0f;
+            for (int d = 0; d < D; ++d) s += zi[d] * zj[d];
+            r[e] = s;
+        }
+    }
+}
+
+// The pair gradients are spread into a symmetric matrix with a zero diagonal first, so that an element's sum runs over all j (in the
+// order 0 .. V-1) without a case distinction.
+__global__ __launch_bounds__(kInterPlainThreads) void interact_bwd_plain_kernel(InteractArgs a)
+{
+    extern __shared__ __align__(16) float inter_lds[]; // V * D + V * (V | 1) + D floats (inter_plain_floats)
+    const int b = blockIdx.x, V = a.T + 1, D = a.D, vp = V | 1; // odd pitch
+    float *z = inter_lds, *dpf = inter_lds + V * D, *dzl = dpf + V * vp; // dzl: D floats, the gradient w.r.t. bot
+    const int P = V * (V - 1) / 2, W = D + P;
+    for (int e = threadIdx.x; e < V * D; e += kInterPlainThreads)
+        z[e] = e < D ? a.bot[(long long)b * D + e] : a.emb[(long long)b * a.T * D + (e - D)];
+    const float *dr = a.dR + (long long)b * W;
+    for (int p = threadIdx.x; p < P; p += kInterPlainThreads) {
+        int i, j;
+        pair_of(p, i, j);
+        const float g = dr[D + p];
+        dpf[i * vp + j] = g;
+        dpf[j * vp + i] = g;
+    }
+    for (int i = threadIdx.x; i < V; i += kInterPlainThreads) dpf[i * vp + i] = 0.0f;
+    __syncthreads();
+    for (int e = threadIdx.x; e < V * D; e += kInterPlainThreads) {
+        const int i = e / D, d = e - i * D;
+        float s = (i == 0) ? dr[d] : 0.0f;
+        const float *row = dpf + i * vp, *col = z + d;
+        for (int j = 0; j < V; ++j) s += row[j] * col[j * D];
+        if (i == 0) {
+            const long long off = (long long)b * D + d;
+            if (a.bot_mask) s = a.bot_mask[off] > 0.0f ? s : 0.0f;
+            a.dbot[off] = s;
+            dzl[d] = s;
+        } else {
+            a.demb[(long long)b * a.T * D + (e - D)] = s;
+        }
+    }
+    if (a.lin_w && a.lin_dx) { // on to the input gradient of the bottom MLP's last layer
+        __syncthreads();
+        const int K = a.lin_k;
+        for (int k = threadIdx.x; k < K; k += kInterPlainThreads) {
+            float s = 0.0f;
+            for (int d = 0; d < D; ++d) s = __builtin_fmaf(dzl[d], a.lin_w[(long long)d * K + k], s);
             if (a.lin_mask) s = a.lin_mask[(long long)b * K + k] > 0.0f ? s : 0.0f;
             a.lin_dx[(long long)b * K + k] = s;
         }

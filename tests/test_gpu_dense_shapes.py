@@ -63,7 +63,10 @@ def _check(oracle, T, D, B, bot, top, seed=7, margin=False):
 @pytest.mark.parametrize("T,D,B,bot", [
     (1, 1, 3, [4]), (1, 16, 5, [13, 20]), (30, 12, 9, [13, 24]), (31, 20, 21, [13, 32]), (32, 8, 33, [9, 8]), (33, 24, 18, [13, 300]),
     (63, 64, 70, [13, 64]), (40, 7, 37, [5, 11]), (2, 130, 40, [13, 16]), (1, 1500, 6, [3]), (26, 64, 130, [13, 512, 256]),
-    (5, 33, 64, [17, 120]), (15, 256, 24, [7, 8]), (4, 16, 40, [13, 280]), (4, 16, 41, [13, 288])])
+    (5, 33, 64, [17, 120]), (15, 256, 24, [7, 8]), (26, 16, 40, [13, 280]), (26, 16, 41, [13, 288]),
+    # both sides of the line between the plain kernels and the matrix cores, with and without the last layer riding along
+    (31, 21, 19, [13, 64]), (62, 33, 10, [13, 48]), (20, 16, 30, [13, 64]), (21, 16, 30, [13, 64]), (15, 32, 31, [13, 256]),
+    (14, 32, 31, [13, 256]), (14, 32, 31, [13, 300]), (26, 8, 130, [13, 64]), (33, 32, 9, [13, 600]), (50, 16, 9, [13, 64]), (48, 16, 33, [13, 64])])
 def test_interaction_shapes(oracle, T, D, B, bot):
     _check(oracle, T, D, B, bot, [16])
 
