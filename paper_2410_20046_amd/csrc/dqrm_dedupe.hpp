@@ -179,8 +179,10 @@ __device__ __forceinline__ TableExtent table_extent(const int64_t *offsets, int 
 {
     constexpr int kWaves = THREADS / kWave;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    // (by every wave for itself while that is one step: the workgroup has nothing to wait for then)
+    const bool by_wave = t <= kWave;
     bool back = false;
-    for (int s = tid; s < t; s += THREADS) back |= offsets[(long long)s * B] > offsets[(long long)(s + 1) * B];
+    for (int s = by_wave ? lane : tid; s < t; s += THREADS) back |= offsets[(long long)s * B] > offsets[(long long)(s + 1) * B];
     const long long lo = offsets[(long long)t * B], hi = offsets[(long long)(t + 1) * B];
     const bool bad = lo < 0 || hi > N || lo > hi, many = !bad && hi - lo > limit;
     TableExtent x;
@@ -188,10 +190,13 @@ __device__ __forceinline__ TableExtent table_extent(const int64_t *offsets, int 
     x.bad_value = bad ? lo : hi - lo;
     x.n = bad || many ? 0 : (int)(hi - lo);
     x.lo = lo < 0 ? 0 : (lo > N ? N : lo);
-    const bool wave_back = __any(back);
-    if (lane == 0) s_back[wave] = wave_back;
-    __syncthreads();
-    if (__any(s_back[lane & (kWaves - 1)])) { // (the number of waves is a power of two)
+    bool any_back = __any(back);
+    if (!by_wave) {
+        if (lane == 0) s_back[wave] = any_back;
+        __syncthreads();
+        any_back = __any(s_back[lane & (kWaves - 1)]); // (the number of waves is a power of two)
+    }
+    if (any_back) {
         bool shared = false;
         for (int s = lane; s < t; s += kWave) {
             const long long l = offsets[(long long)s * B], h = offsets[(long long)(s + 1) * B];
@@ -1121,7 +1126,7 @@ __global__ __launch_bounds__(kTableThreads) void dedupe_table_kernel(DedupeArgs 
 // its dynamic LDS
 inline size_t finish_lds_bytes(const DedupeArgs &a)
 {
-    const size_t most = (size_t)a.T * a.parts + a.extra;
+    const size_t most = a.extra ? (size_t)a.T * a.parts + a.extra : (size_t)kMaxParts;
     return sizeof(int) * ((3 + kChunkClasses) * (most + 1) + most) + (a.extra ? 2 * sizeof(unsigned short) * most : 0);
 }
 
@@ -1135,7 +1140,7 @@ __global__ __launch_bounds__(kSegThreads) void dedupe_finish_kernel(DedupeArgs a
     constexpr int kSums = 3 + kChunkClasses, kWaves = kSegThreads / kWave;
     extern __shared__ int finish_lds[]; // finish_lds_bytes()
     __shared__ int s_w[kSums][kWaves];
-    const int T = args.T, parts = args.parts, most = T * parts + args.extra;
+    const int T = args.T, parts = args.parts, most = EXTRA ? T * parts + args.extra : kMaxParts; // (a constant where it can be: every access pays for it)
     int *s_base = finish_lds + kSums * (most + 1);
     unsigned short *s_table = reinterpret_cast<unsigned short *>(s_base + most), *s_order = s_table + most;
     auto s_sum = [&](int k) { return finish_lds + k * (most + 1); };
