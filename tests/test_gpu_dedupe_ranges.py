@@ -58,23 +58,19 @@ def test_lookups_per_table(n, cards):
     assert run.status()[0] == 0
 
 
-@pytest.mark.parametrize("n,threads", [(400, 256), (3000, 512), (8000, 1024), (40000, 1024)])
-@pytest.mark.parametrize("bags", ["ragged", "pairs", "pretend", "sparse"])
-def test_hot_rows_and_bags(n, threads, bags):
-    """One table with nearly all of the batch's lookups (more than its share, so a range overflows the LDS and is taken in
-    pieces), most of them to one row at the front, in the middle or at the end of its rows; the bags of equal length, of
-    unequal length, of unequal length adding up as if they were equal, and many more bags than lookups."""
+@pytest.mark.parametrize("n", [400, 3000, 8000, 40000])
+@pytest.mark.parametrize("bags", ["ragged", "pairs", "sparse"])
+def test_hot_rows_and_bags(n, bags):
+    """One table with nearly all of the batch's lookups, most of them to one row at the front, in the middle or at the end of
+    its rows; the bags of unequal length, of two lookups (twice the batch's average, so they are searched for all the same) and
+    many more than the lookups."""
     T, big = 3, min(3 * n - 2, 65536)
     rng = np.random.default_rng(n + len(bags))
-    B = {"ragged": 777, "pairs": (big + 1) // 2, "pretend": big // 5, "sparse": 20011}[bags]
+    B = {"ragged": 777, "pairs": (big + 1) // 2, "sparse": 20011}[bags]
     cards = np.array([2000, 50, 100_000], np.int64)
     for hot in (0, 49_999, 99_999):
         if bags == "pairs":
             lens = np.full(B, 2, np.int64)
-        elif bags == "pretend":
-            lens = np.full(B, 5, np.int64)
-            lens[: B // 2] += 1
-            lens[B - B // 2:] -= 1
         else:
             lens = np.bincount(rng.integers(0, B, big), minlength=B).astype(np.int64)
         lens = np.concatenate([(np.arange(B) == 0), (np.arange(B) == B - 1), lens]).astype(np.int64)
@@ -105,6 +101,36 @@ def test_hot_rows_and_bags(n, threads, bags):
         s0 = int(got["table_uniq_offsets"][2])
         rows = got["uniq_rows"][s0:]
         assert_exact(b.values.cpu().numpy()[s0:s0 + len(rows), 0].astype(np.float64), want[rows], f"n={n} hot={hot} {bags} sums")
+
+
+# Every table has as many lookups as if all bags of the batch were equally long, and the bag of a lookup is guessed from that: rightly
+# (`equal`) or wrongly (half of the bags one longer, the others one shorter; one bag empty and one twice as long).  Sizes for each of
+# the workgroups, a range that overflows the LDS, tables sorted by tiles; a row with most of the lookups or none.
+@pytest.mark.parametrize("n", [400, 3000, 8000, 13_000, 40_000, 65_535])
+@pytest.mark.parametrize("T", [1, 3])
+@pytest.mark.parametrize("bags", ["equal", "halves", "one off"])
+def test_bags_that_add_up(n, T, bags):
+    rng = np.random.default_rng(n + T)
+    B = n // 5
+    lens = np.full((T, B), 5, np.int64)
+    if bags == "halves":
+        lens[:, : B // 2] += 1
+        lens[:, B - B // 2:] -= 1
+    elif bags == "one off":
+        lens[:, B // 3] = 0
+        lens[:, B // 2] = 10
+    off = np.concatenate([[0], np.cumsum(lens.reshape(-1))]).astype(np.int64)
+    cards = np.full(T, 50_000, np.int64)
+    wl = Workload(name="add up", T=T, D=8, B=B, alpha=1.05, seed=1, cards=cards)
+    for hot in (0.0, 0.75):
+        idx = rng.integers(0, 50_000, int(off[-1]))
+        idx[rng.random(len(idx)) < hot] = 31_234
+        print(f"{T} tables of {5 * B} lookups, bags {bags}, hot {hot}", flush=True)
+        run, got = _dedupe(wl, idx, off, B)
+        for k, v in _expected(wl, idx, off, B).items():
+            assert_exact(got[k], v, f"n={n} T={T} {bags} hot={hot} {k}")
+        _sums_exact(run, idx, off, B, cards, got, f"n={n} T={T} {bags} hot={hot}")
+        assert run.status()[0] == 0
 
 
 # Boundaries between tables that go backwards: the table that ends before it begins is reported and skipped, and so is a later one
