@@ -457,7 +457,14 @@ def main():
         while G < D // 4:
             G *= 2
         # which kernel(s) a call launches, and the algorithmic bytes of one launch
-        dd = "dedupe_kernel + " + ("dedupe_merge_kernel + dedupe_large_kernel + " if N > 16384 and hp.max_table_lookups > 16384 else "") + "dedupe_finish_kernel"
+        # (the library's choice: sorted by tiles first, whole tables, or a table's ranges)
+        per_table, tables_at_once = N / T, T * (max(args.ahead, 1) if args.overlap == "ahead" else 1)
+        if per_table > 16384 and T <= 128:
+            dd = "dedupe_partition_kernel + dedupe_kernel + dedupe_finish_kernel"
+        elif 2048 < per_table and hp.max_table_lookups <= 16384 and 2 * tables_at_once >= torch.cuda.get_device_properties(0).multi_processor_count:
+            dd = "dedupe_table_kernel + dedupe_finish_kernel"
+        else:
+            dd = "dedupe_kernel + dedupe_finish_kernel"
         call_kernels = {
             "fwd": (f"embbag_fwd_kernel<{G},{'packed' if packed_fwd else 'master'}>", ab["fwd"]),
             "segment_sum": (f"segment_sum_kernel<{G}>" + ("" if args.fused else " + absmax_finalize_kernel"), ab["segsum"]),
