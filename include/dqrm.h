@@ -65,8 +65,7 @@ extern "C" {
 #define DQRM_MAX_DIM 256             /* dim must be a multiple of 8 in [8, 256] */
 #define DQRM_MAX_TABLES 1024
 #define DQRM_MAX_TABLE_ROWS 2147483646LL /* rows of one table */
-#define DQRM_MAX_TABLE_LOOKUPS 65536 /* lookups one table may receive in one batch (up to 16384 are sorted in LDS by
-                                        one workgroup; more take a slower path through the workspace).
+#define DQRM_MAX_TABLE_LOOKUPS 65536 /* lookups one table may receive in one batch.
                                         NOTE: a table beyond the limit is SKIPPED for that batch -- it contributes
                                         no unique rows, so its rows get no update -- and the only trace is
                                         DQRM_ERR_CAPACITY in the device status word.  The host cannot refuse such
@@ -188,20 +187,24 @@ int32_t dqrm_dedupe(const dqrm_tables_t *tables, const int64_t *indices, const i
 int32_t dqrm_segment_sum(const dqrm_tables_t *tables, int32_t batch, int64_t num_indices, const float *grad_out,
                          float *values, float *g_absmax, void *workspace, size_t workspace_bytes, void *stream);
 
-/* dqrm_dedupe for up to DQRM_MAX_DEDUPE_BATCHES batches in one launch pair.  A
- * table's sort occupies one CU, so one batch keeps only T CUs busy; the batches
- * of the next few steps (a data loader has their indices long before the model
- * needs them) fill the chip instead.  `batches` is a HOST array; each element
+/* dqrm_dedupe for up to DQRM_MAX_DEDUPE_BATCHES batches in one launch pair (or
+ * three launches where tables have many lookups on average).  One batch's tables
+ * are cut into ranges of rows to keep the chip busy, and each range's workgroup
+ * looks all of its table's lookups over; the batches of the next few steps (a data
+ * loader has their indices long before the model needs them) fill the chip without
+ * that.  `batches` is a HOST array; each element
  * holds the arguments dqrm_dedupe takes for one batch (its own outputs and its
  * own workspace of at least `workspace_bytes` bytes, sized for the largest
  * num_indices).  All batches have `batch` bags per table.
  * max_table_lookups: the lookups one table has in a batch are device data (the
- * offsets), so a batch of more than 16384 lookups costs a launch of the pass
- * that serves tables of more than 16384 lookups even when no table is that
- * large.  A caller who knows a bound on the lookups of any one table in this
- * batch (bags per table x the longest bag) states it here and is spared that
- * launch when the bound is at most 16384; 0 = no bound known (what dqrm_dedupe
- * and dqrm_embbag_bwd pass).  A table with more lookups than a stated bound is
+ * offsets), so the launches have to reckon with a table of many more than the
+ * average.  A caller who knows a bound on the lookups of any one table in this
+ * batch (bags per table x the longest bag) states it here; where it rules such
+ * tables out the kernels are those without provision for them (0.3 us less for 26
+ * tables x 2048), and with a bound of up to 16384 several batches of large tables
+ * side by side are sorted a table at a time (11 % faster at 26 tables x 8192 x 8
+ * batches).  0 = no bound known (what dqrm_dedupe and dqrm_embbag_bwd pass).
+ * A table with more lookups than a stated bound is
  * treated like one beyond DQRM_MAX_TABLE_LOOKUPS: skipped, DQRM_ERR_CAPACITY in
  * dqrm_check_status. */
 typedef struct {

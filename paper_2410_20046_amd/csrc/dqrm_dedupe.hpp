@@ -5,7 +5,7 @@
 //   A workgroup reads all of its table's lookups, keeps those of its range in lookup order (LDS), counts those below
 //   it (that is where its piece of the sorted order starts: no workgroup waits for another), sorts what it kept with a
 //   stable LSD radix sort in LDS, and writes its piece of the sorted order and its own lists of chunks and singles.
-//   A range with more lookups than the LDS holds is taken in pieces.
+//   A range with more lookups than the LDS holds is taken in pieces, and a table with far more than the others has further ranges.
 //   Tables of very many lookups are first sorted by range, a tile of lookups per workgroup (dedupe_partition_kernel), so
 //   that a range's workgroup reads only its own.
 // Kernel 2 (dedupe_finish_kernel): turns the workgroups' counts into offsets (there are at most kMaxParts of them,

@@ -142,20 +142,6 @@ __device__ __forceinline__ int wave_incl_scan_add(int v, int /*lane*/)
     return v;
 }
 
-// values must be >= -1 (the identity used for lanes without a source)
-__device__ __forceinline__ int wave_incl_scan_max(int v, int /*lane*/)
-{
-    v = max(v, dpp_or<kDppRowShr1, 0xF>(-1, v));
-    v = max(v, dpp_or<kDppRowShr2, 0xF>(-1, v));
-    v = max(v, dpp_or<kDppRowShr4, 0xF>(-1, v));
-    v = max(v, dpp_or<kDppRowShr8, 0xF>(-1, v));
-    v = max(v, dpp_or<kDppRowBcast15, 0xA>(-1, v));
-    v = max(v, dpp_or<kDppRowBcast31, 0xC>(-1, v));
-    return v;
-}
-
-__device__ __forceinline__ int wave_last(int v) { return __builtin_amdgcn_readlane(v, kWave - 1); }
-
 __device__ __forceinline__ float wave_max(float v)
 {
 #pragma unroll
