@@ -200,7 +200,7 @@ int32_t dqrm_segment_sum(const dqrm_tables_t *tables, int32_t batch, int64_t num
  * offsets), so the launches have to reckon with a table of many more than the
  * average.  A caller who knows a bound on the lookups of any one table in this
  * batch (bags per table x the longest bag) states it here; where it rules such
- * tables out the kernels are those without provision for them (0.3 us less for 26
+ * tables out the kernels are those without provision for them (0.6 us less for 26
  * tables x 2048), and with a bound of up to 16384 several batches of large tables
  * side by side are sorted a table at a time (11 % faster at 26 tables x 8192 x 8
  * batches).  0 = no bound known (what dqrm_dedupe and dqrm_embbag_bwd pass).

@@ -449,7 +449,7 @@ int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t nu
     // brackets the `parts` equally wide ranges that every table has otherwise):
     //   255 tables x  128 lookups and one of 65536: 261 (7600); one of 16384: 70 (670)
     //    25 tables x 2048 and one of 65536:          75 (472); 25 x 512 and one of 16384: 51 (135)
-    // where no table has that many: 26 x 2048 18.9 (18.5), 26 x 8192 32.4 (31.8).  A bound on a table's lookups spares that.
+    // where no table has that many: 26 x 2048 19.1 (18.5), 26 x 8192 32.5 (31.6).  A bound on a table's lookups spares that.
     const int cap = avg <= 512 ? 2048 : (avg <= 4096 && parts > 1 ? 4096 : 8192);
     const int64_t light = std::max<int64_t>(cap, avg + avg / 4);
     const bool uneven = !partition && !whole && most > light;
