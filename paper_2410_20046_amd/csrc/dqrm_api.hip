@@ -4,6 +4,7 @@
 
 #include <cstdio>
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <mutex>
 
@@ -855,59 +856,50 @@ void each_layer(const dqrm_dense_model_t *m, F &&f)
     for (int l = 0; l < m->top_layers; ++l) f(m->top_dims[l], m->top_dims[l + 1]);
 }
 
-// How the weight-gradient products [out][in] of all layers (one launch) are cut: the batch dimension in `splits` slices, and
-// whether the layers of at least 64 x 64 go by tiles of that size, a workgroup each.  Other layers go by tiles of 32x32, a wave
-// each, and their bias gradient is a column of the product.
+// How the weight-gradient products [out][in] of all layers (one launch) are cut: a layer's tiles, 128x128 or 64x64, a workgroup
+// each, and the batch dimension in slices of whole slabs of samples.
 struct GradCut {
-    bool tile64;
-    int splits, per; // `per` samples to a slice: whole pairs of slabs (what is left of a pair takes a wave as long as several)
-    void cut(int batch, int s)
-    {
-        constexpr int kPair = 2 * dqrm::kGemmBK;
-        per = ((batch + s - 1) / s + kPair - 1) / kPair * kPair;
-        splits = std::max(2, (batch + per - 1) / per); // (the kernel stores partial tiles only when the reduction is split)
-    }
-    bool is64(int in, int out) const { return tile64 && in >= 64 && out >= 64; }
+    static constexpr int kSlab = 64; // samples
+    int most;         // the largest tile
+    int per128, per64; // samples of a slice, by the tile
+    int tile(int in, int out) const { return most >= 128 && std::min(in, out) >= 128 ? 128 : 64; }
+    int per(int in, int out) const { return tile(in, out) == 128 ? per128 : per64; }
+    int splits(int in, int out, int batch) const { return (batch + per(in, out) - 1) / per(in, out); }
 };
 
 GradCut grad_cut(const dqrm_dense_model_t *m, int batch)
 {
-    constexpr int kPair = 2 * dqrm::kGemmBK; // samples of a pair of slabs, which a wave takes at a time
-    const int64_t cus = num_cus();
-    int64_t tiles = 0, large = 0, small = 0; // 32x32 tiles of all layers; 64x64 tiles; and those of 32x32 beside them
-    double params = 0;
-    each_layer(m, [&](int in, int out) {
-        const int64_t t = (int64_t)((out + 31) / 32) * ((in + 1 + 31) / 32);
-        tiles += t;
-        if (in >= 64 && out >= 64)
-            large += (int64_t)((out + 63) / 64) * ((in + 63) / 64);
-        else
-            small += (t + dqrm::kGemmWaves - 1) / dqrm::kGemmWaves;
-        params += (double)out * (in + 1);
-    });
-    const int64_t most = (batch + kPair * dqrm::kGemmWaves - 1) / (kPair * dqrm::kGemmWaves); // slices of a pair of slabs per wave
-    GradCut c{large * most * 4 >= cus * 3, 2, 0};
-    if (!c.tile64) {
-        // The 64x64 tiles would leave CUs idle even at a pair of slabs per wave: about one 32x32 tile per SIMD, then, each with
-        // at least a pair of slabs.  Whole steps, us, 64x64 tiles (at most a slice per 256 samples) -> these: bottom MLP
-        // 13-48-32-16, top 52-60-48-1 at 1024 samples 80.4 -> 75.2; 13-128-128, 164-128-64-1 at 3000 106.7 -> 102.3; Kaggle's MLPs
-        // at 256 106.8 -> 105.0, but at 500 114.2 -> 115.0 (232 workgroups of 64x64 tiles).
-        const int64_t s = std::min<int64_t>((cus * 4 + tiles / 2) / std::max<int64_t>(tiles, 1), batch / kPair);
-        c.cut(batch, (int)std::max<int64_t>(2, std::min<int64_t>(s, kDenseMaxSplits)));
-        return c;
-    }
-    // A workgroup per CU walks its slice in 1.7 us per 128 samples (a slab of 64x64 products for each of its four waves), so the
-    // slices that fill whole rounds of the chip are wanted; a slice costs its partial tiles, written and added up again, at about
-    // 4 TB/s.  At least one pair of slabs per wave and slice.
+    const int64_t cus = num_cus(), slabs = (batch + GradCut::kSlab - 1) / GradCut::kSlab;
+    // A CU has one workgroup at a time: 5 us for its beginning and end, and so many per slab (measured: 512x512 in slices of 2048
+    // samples 82 us in tiles of 128, 36 in tiles of 64); a slice costs its partial tiles, written and added up again, at about 4 TB/s.
+    constexpr double kUs128 = 2.4, kUs64 = 0.98, kUsFixed = 5;
+    auto us_of = [&](int tile, int64_t n) { return kUsFixed + (tile == 128 ? kUs128 : kUs64) * n; };
+    GradCut best{};
     double best_us = 0;
-    int best = 2;
-    for (int s = 2; s <= kDenseMaxSplits; ++s) {
-        if (s > 2 && (int64_t)s * kPair * dqrm::kGemmWaves > batch) break;
-        const double us = (double)(((large + small) * s + cus - 1) / cus) * batch / s / 128 * 1.7 + s * params * 8 / 4e6;
-        if (s == 2 || us < best_us) best = s, best_us = us;
+    for (int most : {128, 64}) {
+        GradCut c{most, 0, 0};
+        int64_t tiles[2] = {};   // of 64, of 128
+        double params[2] = {};
+        each_layer(m, [&](int in, int out) {
+            const int t = c.tile(in, out), k = t == 128;
+            tiles[k] += (int64_t)((out + t - 1) / t) * ((in + t - 1) / t);
+            params[k] += (double)out * (in + 1);
+        });
+        if (most == 128 && tiles[1] == 0) continue;
+        int64_t last = 0;
+        for (int s = 1; s <= kDenseMaxSplits; ++s) { // slices of the larger tiles; the smaller ones take no longer
+            const int64_t n = (slabs + s - 1) / s;
+            if (n == last) continue;
+            last = n;
+            const double each = us_of(most, n);
+            const int64_t n64 = most == 64 ? n : std::max<int64_t>({1, (slabs + kDenseMaxSplits - 1) / kDenseMaxSplits, std::min(slabs, (int64_t)((each - kUsFixed) / kUs64))});
+            const int64_t s64 = (slabs + n64 - 1) / n64, s128 = (slabs + n - 1) / n;
+            const double work = most == 64 ? (double)(s64 * tiles[0]) : s128 * tiles[1] + s64 * tiles[0] * us_of(64, n64) / each;
+            const double us = std::ceil(work / cus) * each + (s64 * params[0] + s128 * params[1]) * 8 / 4e6;
+            if (best_us == 0 || us < best_us) best_us = us, best = GradCut{most, (int)n * GradCut::kSlab, (int)n64 * GradCut::kSlab};
+        }
     }
-    c.cut(batch, best);
-    return c;
+    return best;
 }
 
 int32_t check_dense_model(const dqrm_dense_model_t *m, int32_t batch)
@@ -942,18 +934,19 @@ DenseLayout dense_layout(const dqrm_dense_model_t *m, int32_t batch)
         o = align_up(o + floats * sizeof(float), 256);
         return at;
     };
-    const size_t splits = (size_t)grad_cut(m, batch).splits;
+    const GradCut cut = grad_cut(m, batch);
+    auto part = [&](int in, int out) { return take((size_t)cut.splits(in, out, batch) * out * (in + 1)); };
     for (int l = 0; l < m->bot_layers; ++l) {
         L.bot_act[l] = take((size_t)batch * m->bot_dims[l + 1]);
         L.bot_dz[l] = take((size_t)batch * m->bot_dims[l + 1]);
-        L.bot_part[l] = take(splits * (size_t)m->bot_dims[l + 1] * (m->bot_dims[l] + 1));
+        L.bot_part[l] = part(m->bot_dims[l], m->bot_dims[l + 1]);
     }
     L.R = take((size_t)batch * m->top_dims[0]);
     L.dR = take((size_t)batch * m->top_dims[0]);
     for (int l = 0; l < m->top_layers; ++l) {
         L.top_act[l] = take((size_t)batch * m->top_dims[l + 1]);
         L.top_dz[l] = take((size_t)batch * m->top_dims[l + 1]);
-        L.top_part[l] = take(splits * (size_t)m->top_dims[l + 1] * (m->top_dims[l] + 1));
+        L.top_part[l] = part(m->top_dims[l], m->top_dims[l + 1]);
     }
     const size_t P = (size_t)dense_param_count(m);
     L.wq = take(P);
@@ -964,11 +957,40 @@ DenseLayout dense_layout(const dqrm_dense_model_t *m, int32_t batch)
     return L;
 }
 
+// The tile of a layer's product by planes of bfloat16, or 0: by the fp32 matrix instructions.  Those are left where a wave's 32x32
+// tile can have its reduction shared by four waves on otherwise idle SIMDs, and that is long: 512 samples, 512 -> 512, us, fp32 /
+// planes: reduction 256: 7.1 / 6.7, 384: 8.2 / 8.1, 512: 8.4 / 9.5; input gradients (B read along j) 256: 7.2 / 7.6, 200: 11.4 / 9.0.
+// Elsewhere, reduction 512: 1024x512 10.7 / 9.8, 2048x512 15.7 / 10.8, 8192x512 57 / 28.7.  Of the tiles the one whose rounds over the
+// CUs (a workgroup each) take least: 8192x512, 128 / 128x64 / 64: 28.7 / 31.4 / 38.7; 8192x256: 21.8 / 16.0 / 19.6; 2048x512: 20.6 /
+// 13.8 / 10.8.
+int plane_tile(const dqrm::GemmArgs &g, bool b_wide)
+{
+    if (!b_wide && g.K < 8) return 0; // (as much of a row is read at a time)
+    const int64_t cus = num_cus(), tiles32 = (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32);
+    if (tiles32 <= cus && g.K >= (b_wide ? 256 : 384)) return 0;
+    auto us = [&](int bm, int bn, int each) { return (((int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) + cus - 1) / cus) * each; };
+    const int64_t us64 = us(64, 64, 10), us128x64 = us(128, 64, 16), us128 = us(128, 128, 27);
+    if (us128 <= us128x64 && us128 <= us64) return 128;
+    return us128x64 < us64 ? 12864 : 64;
+}
+
 // A_MODE / B_MODE: how A / B lie in memory and are read (dqrm::kOpRC: the reduction index is the unit-stride one;
-// kOpWide, kOpWideVec: the 32-wide index i / j is).
+// kOpWide: the 32-wide index i / j is).
 template <int A_MODE, int B_MODE>
 hipError_t launch_gemm(hipStream_t st, const dqrm::GemmArgs &g)
 {
+    const int t = plane_tile(g, B_MODE == dqrm::kOpWide);
+    if (t) {
+        const int bm = t == 64 ? 64 : 128, bn = t == 128 ? 128 : 64;
+        const dim3 grid(((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn)), block(dqrm::kPlaneThreads);
+        if (t == 128)
+            hipLaunchKernelGGL((dqrm::gemm_planes_kernel<dqrm::PlaneTile128, A_MODE, B_MODE>), grid, block, 0, st, g);
+        else if (t == 64)
+            hipLaunchKernelGGL((dqrm::gemm_planes_kernel<dqrm::PlaneTile64, A_MODE, B_MODE>), grid, block, 0, st, g);
+        else
+            hipLaunchKernelGGL((dqrm::gemm_planes_kernel<dqrm::PlaneTile128x64, A_MODE, B_MODE>), grid, block, 0, st, g);
+        return hipGetLastError();
+    }
     dqrm::GemmOne one;
     one.p = g;
     // A product with fewer tiles than the chip has SIMDs (4 per CU) leaves some of them idle: let 2 or 4 waves
@@ -1000,13 +1022,10 @@ hipError_t launch_weight_grads(hipStream_t st, dqrm::GemmGroup &grp)
     for (int q = 0; q < grp.count; ++q) {
         dqrm::GemmArgs &g = grp.p[q];
         g.block_begin = blocks;
-        if (g.tile64)
-            blocks += ((g.M + 63) / 64) * ((g.N + 63) / 64) * g.splits;
-        else
-            blocks += (((g.M + 31) / 32) * ((g.N + 31) / 32) * g.splits + dqrm::kGemmWaves - 1) / dqrm::kGemmWaves;
+        blocks += ((g.M + g.tile - 1) / g.tile) * ((g.N + g.tile - 1) / g.tile) * g.splits;
     }
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(dqrm::gemm_split_group_kernel, dim3(blocks), dim3(dqrm::kGemmThreads), 0, st, grp);
+    hipLaunchKernelGGL(dqrm::gemm_split_group_kernel, dim3(blocks), dim3(dqrm::kPlaneThreads), 0, st, grp);
     return hipGetLastError();
 }
 
@@ -1019,7 +1038,7 @@ hipError_t linear_fwd(hipStream_t st, const float *X, const float *W, const floa
     g.B = W, g.b_sr = 1, g.b_sj = in;
     g.C = Y, g.c_si = out, g.c_sj = 1;
     g.M = B, g.N = out, g.K = in;
-    g.bias = b, g.relu = relu ? 1 : 0, g.splits = 1, g.k_per_split = in;
+    g.bias = b, g.relu = relu ? 1 : 0;
     return launch_gemm<dqrm::kOpRC, dqrm::kOpRC>(st, g);
 }
 
@@ -1032,8 +1051,8 @@ hipError_t linear_bwd_input(hipStream_t st, const float *dZ, const float *W, con
     g.B = W, g.b_sr = in, g.b_sj = 1;
     g.C = dX, g.c_si = in, g.c_sj = 1;
     g.M = B, g.N = in, g.K = out;
-    g.mask = mask, g.splits = 1, g.k_per_split = out;
-    return launch_gemm<dqrm::kOpRC, dqrm::kOpWideVec>(st, g);
+    g.mask = mask;
+    return launch_gemm<dqrm::kOpRC, dqrm::kOpWide>(st, g);
 }
 
 // Whether the interaction of V vectors of D floats goes by the plain kernels: where it would fill only a little of the 32x32 tiles
@@ -1092,13 +1111,8 @@ dqrm::GemmArgs weight_grad_problem(const float *dZ, const float *X, float *parti
     dqrm::GemmArgs g{};
     g.A = dZ, g.a_si = 1, g.a_sr = out;
     g.B = X, g.b_sr = in, g.b_sj = 1;
-    g.M = out, g.K = B;
-    if (cut.is64(in, out))
-        g.N = in, g.tile64 = 1;
-    else
-        g.N = in + 1, g.b_ones_last = 1;
-    g.splits = cut.splits; // exactly the slices the workspace holds; slices past the batch come out as zeros
-    g.k_per_split = cut.per, g.P = partials;
+    g.M = out, g.N = in, g.K = B;
+    g.tile = cut.tile(in, out), g.splits = cut.splits(in, out, B), g.k_per_split = cut.per(in, out), g.P = partials;
     return g;
 }
 

@@ -1,8 +1,10 @@
 // The dense part of the DLRM train step (model-architecture table of the paper):
 // bottom MLP -> pairwise-dot interaction with the pooled embeddings -> top MLP ->
 // sigmoid + mean binary cross-entropy, its backward, and plain SGD on the MLP
-// weights.  FP32 throughout (the paper's "MLP in FP32" variant); the matrix
-// products run on the matrix cores (v_mfma_f32_32x32x2_f32).
+// weights.  FP32 throughout (the paper's "MLP in FP32" variant): the matrix
+// products of long reductions over few tiles and the interaction run on the fp32
+// matrix instructions, all others on the bfloat16 ones with their operands as
+// exact sums of three bfloat16 (gemm_planes_tile), to a smaller error.
 #pragma once
 
 #include "dqrm_device.hpp"
@@ -12,7 +14,7 @@ namespace dqrm {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 // C(i,j) = epilogue( sum_r A(i,r) * B(r,j) ), all operands addressed with
-// explicit strides so that one kernel serves X*W^T, dY*W and dY^T*X.
+// explicit strides so that one kernel serves X*W^T and dY*W (and dY^T*X, split).
 //
 // One wave owns a 32x32 tile of C: it keeps the tile in the 16 accumulator
 // registers of v_mfma_f32_32x32x2_f32 and walks the reduction in slabs of 32.
@@ -29,15 +31,13 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // passed through a per-wave piece of LDS, or, when the 32-wide index is the
 // unit-stride one, also with 4-byte loads straight into place.  Nothing assumes
 // an alignment beyond 4 bytes.  No load sits under a branch: indices past the
-// edge are clamped and the value is replaced by 0 (or by 1 for the virtual
-// all-ones last column of B).
+// edge are clamped and the value is replaced by 0.
 //
-// Several split products can share one launch (the weight gradients of all layers):
-// the workgroups are dealt over the tiles of all problems.  With splits > 1 the
-// reduction is cut: slice z covers r in [z*k_per_split, ...) and stores its raw
-// partial tile to P[z][M][N]; sgd_from_partials_kernel adds the slices in order.
-// With kslices > 1 (one product per launch) the waves of a workgroup share tiles
-// and add their accumulators through LDS instead.
+// With kslices > 1 the waves of a workgroup share tiles and add their accumulators
+// through LDS.
+//
+// These are the products of few tiles with a long reduction; the others go by
+// gemm_planes_tile below.
 struct GemmArgs {
     const float *A;
     long long a_si, a_sr;
@@ -49,12 +49,13 @@ struct GemmArgs {
     const float *bias; // [N] added per column j, or null
     const float *mask; // same addressing as C: result multiplied by (mask > 0), or null
     int relu;          // max(x, 0) after the bias
-    int b_ones_last;   // B's last column (j = N-1) is all ones and is not read from memory
-    int splits;        // slices of the reduction (1: the epilogue above; > 1: partial tiles to P)
-    int k_per_split;   // reduction length per slice (multiple of 32), K if not split
-    float *P;          // [splits][M][N] partial tiles when split
-    int tile64;        // split product in tiles of 64x64: P has N + 1 columns, the last one is sum_r A(i,r)
-    int block_begin;   // first workgroup of this problem in a group (filled by the launcher)
+    // A split product (a weight gradient): slice z of the reduction covers r in [z * k_per_split, ...) and goes to P[z][M][N + 1], its
+    // last column the sums of A(i, r) over r; sgd_from_partials_kernel adds the slices in order.  Several of them share
+    // one launch: the workgroups are dealt over the tiles of all.
+    int splits, k_per_split;
+    float *P;
+    int tile;        // 64 or 128
+    int block_begin; // first workgroup of this problem in a group (filled by the launcher)
 };
 
 constexpr int kGemmMaxGroup = 16;
@@ -72,26 +73,16 @@ struct SlabRegs {
     float v[16];
 };
 
-// Wide-contiguous operand: element (wide, r) at base[wide * sw + r * sr].  Lane (h, w) reads
-// r = r0 + 16 h + s, s = 0..15, of its own wide index.  SAFE: the wide index was clamped by the caller and r
-// is clamped / zeroed here (the last partial slab, tiles of operands narrower than 32); otherwise everything
-// is known to be inside.
-template <bool SAFE>
-__device__ __forceinline__ void slab_load_direct(SlabRegs &x, const float *base, long long sw, long long sr, int wide,
-                                                 int r0, int r_end, int h, bool ones)
+// Wide-contiguous operand: element (wide, r) at base[wide + r * sr], clamped form (the last partial slab, tiles of operands narrower
+// than 32).  Lane (h, w) reads r = r0 + 16 h + s, s = 0..15, of its own wide index, which the caller has clamped.
+__device__ __forceinline__ void slab_load_direct(SlabRegs &x, const float *base, long long sr, int wide, int r0, int r_end, int h)
 {
-    if (!SAFE) {
-        const float *p = base + (long long)wide * sw + (long long)(r0 + 16 * h) * sr;
-#pragma unroll
-        for (int s = 0; s < 16; ++s) x.v[s] = p[(long long)s * sr];
-        return;
-    }
 #pragma unroll
     for (int s = 0; s < 16; ++s) {
         const int r = r0 + 16 * h + s;
         const int rc = min(r, r_end - 1);
-        const float val = base[(long long)wide * sw + (long long)rc * sr];
-        x.v[s] = r < r_end ? (ones ? 1.0f : val) : 0.0f;
+        const float val = base[wide + (long long)rc * sr];
+        x.v[s] = r < r_end ? val : 0.0f;
     }
 }
 
@@ -125,30 +116,26 @@ __device__ __forceinline__ void slab_turn(SlabRegs &x, const SlabRegs &st, float
     }
 }
 
-// How the whole slabs of an operand are read (template parameters of the kernel):
-//   kOpRC       the reduction index is the unit-stride one: 16-byte loads along it, turned through LDS
-//   kOpWide     the 32-wide index is the unit-stride one: 4-byte loads straight into place, each lane from its own
-//               (possibly clamped) wide index - the form that can serve a virtual all-ones column
-//   kOpWideVec  the same layout read with 16-byte loads along the wide index, through LDS: only for tiles whose
-//               32 wide indices all exist
-// The last partial slab, and kOpWideVec tiles of operands narrower than 32, take the clamped 4-byte path instead.
-enum { kOpRC = 0, kOpWide = 1, kOpWideVec = 2 };
+// How the whole slabs of an operand are read (template parameters of the kernels):
+//   kOpRC    the reduction index is the unit-stride one: 16-byte loads along it, turned through LDS
+//   kOpWide  the 32-wide index is the unit-stride one: 16-byte loads along it, through LDS: only for tiles whose 32 wide
+//            indices all exist
+// The last partial slab, and kOpWide tiles of operands narrower than 32, take the clamped 4-byte path instead.
+enum { kOpRC = 0, kOpWide = 1 };
 
 // four floats that are only known to start on a 4-byte boundary (a 16-byte global load needs no more)
 typedef float Float4Dw __attribute__((ext_vector_type(4), aligned(4)));
 
 // `first_wide`: the tile's first wide index, `n_wide`: the operand's extent in it (kOpRC reads row n_wide - 1 in
-// place of the rows past it; kOpWideVec needs all 32 to exist); `wide`: this lane's own, clamped (kOpWide only)
+// place of the rows past it; kOpWide needs all 32 to exist)
 template <int MODE>
 __device__ __forceinline__ void slab_fetch_fast(SlabRegs &st, const float *base, long long sw, long long sr,
-                                                int first_wide, int n_wide, int wide, int r0, int lane)
+                                                int first_wide, int n_wide, int r0, int lane)
 {
     // lane l reads four consecutive floats (l % 8) * 4 .. + 3 of lines l / 8 + 8 it, it = 0..3; a line is a
-    // row of the operand (kOpRC: along r) or one reduction index (kOpWideVec: along the wide index)
+    // row of the operand (kOpRC: along r) or one reduction index (kOpWide: along the wide index)
     const int line = lane >> 3, c4 = (lane & 7) * 4;
-    if (MODE == kOpWide) {
-        slab_load_direct<false>(st, base, sw, sr, wide, r0, 0, lane >> 5, false);
-    } else if (MODE == kOpRC) {
+    if (MODE == kOpRC) {
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
             const int row = min(first_wide + line + 8 * it, n_wide - 1);
@@ -165,32 +152,27 @@ __device__ __forceinline__ void slab_fetch_fast(SlabRegs &st, const float *base,
     }
 }
 
-// staging registers of a whole slab -> product layout (`ones`: this lane's column is the virtual one)
+// staging registers of a whole slab -> product layout
 template <int MODE>
-__device__ __forceinline__ void slab_settle_fast(SlabRegs &x, const SlabRegs &st, float *lds, int lane, bool ones)
+__device__ __forceinline__ void slab_settle_fast(SlabRegs &x, const SlabRegs &st, float *lds, int lane)
 {
-    if (MODE == kOpWide) {
+    const int line = lane >> 3, c4 = (lane & 7) * 4;
 #pragma unroll
-        for (int s = 0; s < 16; ++s) x.v[s] = ones ? 1.0f : st.v[s];
-    } else {
-        const int line = lane >> 3, c4 = (lane & 7) * 4;
+    for (int it = 0; it < 4; ++it)
+        *reinterpret_cast<float4 *>(lds + (line + 8 * it) * kGemmPitch + c4) =
+            make_float4(st.v[4 * it + 0], st.v[4 * it + 1], st.v[4 * it + 2], st.v[4 * it + 3]);
+    // (same wave: the LDS operations complete in order, no barrier needed)
+    const int w = lane & 31, h = lane >> 5;
+    if (MODE == kOpRC) { // LDS holds [wide][r]: 16 consecutive r of my wide index
+        const float4 *row = reinterpret_cast<const float4 *>(lds + w * kGemmPitch + 16 * h);
 #pragma unroll
-        for (int it = 0; it < 4; ++it)
-            *reinterpret_cast<float4 *>(lds + (line + 8 * it) * kGemmPitch + c4) =
-                make_float4(st.v[4 * it + 0], st.v[4 * it + 1], st.v[4 * it + 2], st.v[4 * it + 3]);
-        // (same wave: the LDS operations complete in order, no barrier needed)
-        const int w = lane & 31, h = lane >> 5;
-        if (MODE == kOpRC) { // LDS holds [wide][r]: 16 consecutive r of my wide index
-            const float4 *row = reinterpret_cast<const float4 *>(lds + w * kGemmPitch + 16 * h);
-#pragma unroll
-            for (int s4 = 0; s4 < 4; ++s4) {
-                const float4 q = row[s4];
-                x.v[4 * s4 + 0] = q.x, x.v[4 * s4 + 1] = q.y, x.v[4 * s4 + 2] = q.z, x.v[4 * s4 + 3] = q.w;
-            }
-        } else { // LDS holds [r][wide]: my wide index of 16 consecutive r
-#pragma unroll
-            for (int s = 0; s < 16; ++s) x.v[s] = lds[(16 * h + s) * kGemmPitch + w];
+        for (int s4 = 0; s4 < 4; ++s4) {
+            const float4 q = row[s4];
+            x.v[4 * s4 + 0] = q.x, x.v[4 * s4 + 1] = q.y, x.v[4 * s4 + 2] = q.z, x.v[4 * s4 + 3] = q.w;
         }
+    } else { // LDS holds [r][wide]: my wide index of 16 consecutive r
+#pragma unroll
+        for (int s = 0; s < 16; ++s) x.v[s] = lds[(16 * h + s) * kGemmPitch + w];
     }
 }
 
@@ -205,34 +187,29 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int local, boo
 {
     constexpr bool A_RC = A_MODE == kOpRC, B_RC = B_MODE == kOpRC;
     const int kz = wave & (ks - 1);
-    const int tiles_j = (g.N + 31) / 32, tiles_i = (g.M + 31) / 32;
-    const int z = local / (tiles_i * tiles_j);
-    local -= z * tiles_i * tiles_j;
+    const int tiles_j = (g.N + 31) / 32;
     const int i_first = (local / tiles_j) * 32, j_first = (local % tiles_j) * 32; // first row / column this tile stores
-    // this wave's part of the reduction: slice z of a split product, or slice kz of the workgroup's
-    const int k_per_wave = ks > 1 ? ((g.K + 2 * kGemmBK * ks - 1) / (2 * kGemmBK * ks)) * (2 * kGemmBK) : g.k_per_split;
-    const int r_begin = ks > 1 ? kz * k_per_wave : z * g.k_per_split;
+    // this wave's part of the reduction
+    const int k_per_wave = ks > 1 ? ((g.K + 2 * kGemmBK * ks - 1) / (2 * kGemmBK * ks)) * (2 * kGemmBK) : g.K;
+    const int r_begin = kz * k_per_wave;
     const int r_end = live ? min(g.K, r_begin + k_per_wave) : r_begin;
     const int w = lane & 31, h = lane >> 5;
 
     // The last tile of a dimension that is not a multiple of 32 is moved back so that it ends at the edge: it
     // recomputes a few rows / columns of its neighbour, stores only its own, and reads whole slabs like any
     // other.  Operands narrower than 32 cannot: their tiles re-read the last row / column (clamped indices)
-    // and those results are not stored.  The all-ones last column of B is virtual (kOpWide only: host): its lane
-    // reads the column before it and the value is replaced.
-    const int n_mem = g.b_ones_last ? g.N - 1 : g.N; // columns of B that exist in memory (>= 1: host)
+    // and those results are not stored.
     const int i0 = (i_first + 32 > g.M && g.M >= 32) ? g.M - 32 : i_first;
     const int j0 = (j_first + 32 > g.N && g.N >= 32) ? g.N - 32 : j_first;
-    // whole slabs can be read the fast way (kOpWideVec: only if the tile's 32 rows / columns all exist)
-    const bool whole = (A_MODE != kOpWideVec || i0 + 32 <= g.M) && (B_MODE != kOpWideVec || j0 + 32 <= g.N);
-    const int ia = min(i0 + w, g.M - 1), jb = min(j0 + w, n_mem - 1);
-    const bool ones = g.b_ones_last && j0 + w == g.N - 1;
+    // whole slabs can be read the fast way (kOpWide: only if the tile's 32 rows / columns all exist)
+    const bool whole = (A_RC || i0 + 32 <= g.M) && (B_RC || j0 + 32 <= g.N);
+    const int ia = min(i0 + w, g.M - 1), jb = min(j0 + w, g.N - 1);
     float *lds_a = lds_all + wave * 2 * kGemmTurnFloats, *lds_b = lds_a + kGemmTurnFloats;
     // (requested now, used in the epilogue)
-    const float bias_j = (g.bias && g.splits <= 1) ? g.bias[min(j0 + w, g.N - 1)] : 0.0f;
+    const float bias_j = g.bias ? g.bias[min(j0 + w, g.N - 1)] : 0.0f;
     // ... and so is the mask of this lane's 16 outputs (rows and columns past the edge re-read the last ones)
     float mask_v[16];
-    if (g.mask && g.splits <= 1) {
+    if (g.mask) {
         const long long mj = (long long)min(j0 + w, g.N - 1) * g.c_sj;
 #pragma unroll
         for (int v = 0; v < 16; ++v)
@@ -253,19 +230,19 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int local, boo
         if (A_RC)
             slab_load_along_r(sa[q], g.A, g.a_si, i0, g.M, r0, r_end, lane);
         else
-            slab_load_direct<true>(sa[q], g.A, g.a_si, g.a_sr, ia, r0, r_end, h, false);
+            slab_load_direct(sa[q], g.A, g.a_sr, ia, r0, r_end, h);
         if (B_RC)
-            slab_load_along_r(sb[q], g.B, g.b_sj, j0, n_mem, r0, r_end, lane);
+            slab_load_along_r(sb[q], g.B, g.b_sj, j0, g.N, r0, r_end, lane);
         else
-            slab_load_direct<true>(sb[q], g.B, g.b_sj, g.b_sr, jb, r0, r_end, h, ones);
+            slab_load_direct(sb[q], g.B, g.b_sr, jb, r0, r_end, h);
     };
     auto fetch_fast = [&](int q, int r0) { // whole tile, whole slab
-        slab_fetch_fast<A_MODE>(sa[q], g.A, g.a_si, g.a_sr, i0, g.M, ia, r0, lane);
-        slab_fetch_fast<B_MODE>(sb[q], g.B, g.b_sj, g.b_sr, j0, n_mem, jb, r0, lane);
+        slab_fetch_fast<A_MODE>(sa[q], g.A, g.a_si, g.a_sr, i0, g.M, r0, lane);
+        slab_fetch_fast<B_MODE>(sb[q], g.B, g.b_sj, g.b_sr, j0, g.N, r0, lane);
     };
     auto settle_fast = [&](int q) {
-        slab_settle_fast<A_MODE>(a, sa[q], lds_a, lane, false);
-        slab_settle_fast<B_MODE>(b, sb[q], lds_b, lane, ones);
+        slab_settle_fast<A_MODE>(a, sa[q], lds_a, lane);
+        slab_settle_fast<B_MODE>(b, sb[q], lds_b, lane);
     };
     auto settle = [&](int q) { // staging registers of the clamped path -> product layout
         if (A_RC)
@@ -304,14 +281,14 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int local, boo
             const int rn = min(r0 + 2 * kGemmBK, r_last);
             fetch_fast(0, rn);
             __builtin_amdgcn_sched_barrier(0);
-            slab_settle_fast<A_MODE>(a2, sa[1], lds_a, lane, false);
-            slab_settle_fast<B_MODE>(b2, sb[1], lds_b, lane, ones);
+            slab_settle_fast<A_MODE>(a2, sa[1], lds_a, lane);
+            slab_settle_fast<B_MODE>(b2, sb[1], lds_b, lane);
             products();
             __builtin_amdgcn_sched_barrier(0);
             fetch_fast(1, rn + kGemmBK);
             __builtin_amdgcn_sched_barrier(0);
-            slab_settle_fast<A_MODE>(a, sa[0], lds_a, lane, false);
-            slab_settle_fast<B_MODE>(b, sb[0], lds_b, lane, ones);
+            slab_settle_fast<A_MODE>(a, sa[0], lds_a, lane);
+            slab_settle_fast<B_MODE>(b, sb[0], lds_b, lane);
 #pragma unroll
             for (int s = 0; s < 16; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.v[s], b2.v[s], acc, 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
@@ -351,15 +328,6 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int local, boo
     // accumulator layout: lane l holds column j = l % 32 and rows 8*(v/4) + 4*(l/32) + v%4, v = 0..15
     const int j = j0 + w;
     if (j < j_first || j >= g.N) return; // (a moved tile stores only its own columns and rows)
-    if (g.splits > 1) {
-        float *p = g.P + (long long)z * g.M * g.N;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int i = i0 + 8 * (v >> 2) + 4 * h + (v & 3);
-            if (i >= i_first && i < g.M) p[(long long)i * g.N + j] = acc[v];
-        }
-        return;
-    }
     const float bj = bias_j;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -373,129 +341,378 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int local, boo
     }
 }
 
-// ---- split products in tiles of 64x64 (the weight gradients) ---------------------------------------------------
-// A wave with a 32x32 tile reads 8 KB for every 16 products (1024 matrix-core cycles): with one such wave on each
-// SIMD that is 32 bytes per cycle and CU out of the L2 and what lies behind it.  Four accumulators halve the bytes
-// per product, and a slab's 64 products (4096 cycles) cover the way from memory: the next slab is loaded
-// into place while one is multiplied.  A workgroup has a tile, each of its waves a quarter of the slice's reduction; then every wave finishes one
-// of the tile's four quadrants (the quarters added in their order).  The rows' sums (the bias gradient) ride along in
-// the matrix cores' shadow: as a column of ones they took a whole column of tiles wherever the width is a multiple of 64.
-// Measured: the Terabyte shape's five wide layers at batch 8192 (12.4 GFLOP) 207 -> 171 us (60 -> 73 TFLOP/s), the Kaggle
-// shape's at 2048 (1.96 GFLOP) 35.0 -> 34.5.  Both are bound by the fp32 matrix instructions, at about 70 % of their nominal
-// rate, plus the rounds' beginnings and ends.
-// (Tiles of 64x64 for the layers' own products, X W^T and dZ W: 8192x512x512 50.7 -> 51.8 us, 2048x512x512
-// 16.5 -> 20.8: these products are bound by the rate of the fp32 matrix instructions, and a single wave on a SIMD has
-// none to fill in for its LDS turns.)
+// ---- products of many tiles: three bfloat16 planes per operand ---------------------------------------------------
+// The fp32 matrix instructions run at a sixteenth of the bfloat16 ones' rate.  A float is exactly the sum of a bfloat16, the
+// bfloat16 nearest to what that leaves, and a third one's rest (three planes of 8 significant bits each): of the nine
+// products of two such sums the six that exceed 2^-26 are taken, each exact, and added up in fp32 by the matrix cores,
+// 16 of the reduction at a time: 6 x 32 matrix-core cycles for what takes 8 x 64 in fp32.  The products of the first planes have
+// an accumulator of their own, which is rounded once per 16 of the reduction, so that the error against 64 bits is a third of
+// what the fp32 instructions' is (8192x512x512: 1.3e-7 and 4.05e-7 of the 2-norm).
 //
-// M and N are at least 64 (host), so every tile is whole: the last one of a dimension is moved back to the edge and
-// stores only what is its own.  The operands' wide indices are the unit-stride ones (kOpWide).
-// LDS: per wave its four quadrants, then every wave's row sums.
-constexpr int kGemm64WaveFloats = 4 * 16 * kWave;
-constexpr int kGemm64LdsFloats = kGemmWaves * (kGemm64WaveFloats + kWave);
+// A workgroup of 8 waves has a tile of BM x BN; the reduction goes by slabs of BK.  The threads read a slab as floats (two slabs
+// ahead), split them once for the whole workgroup and leave the planes in LDS, 8 consecutive r of a row to a 16-byte
+// vector, in one of two buffers while the waves multiply from the other: one barrier per slab.  Two waves to a SIMD, as one alone
+// is bound by the 5.5 cycles that each of its instructions takes to issue: their splitting and LDS traffic goes out beside the
+// other's products.
+//
+// Not finite: an infinity's planes are infinity and NaN, and a float next to the largest rounds up to one.  A lane that ends
+// with a sum that is not finite adds its outputs up again in plain fp32, so that infinities and NaN come out as they do there.
+typedef __bf16 Bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 Bf16x8 __attribute__((ext_vector_type(8)));
+typedef float Float2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ void gemm_split_tile64(const GemmArgs &g, int local, int wave, int lane, float *lds_all)
+constexpr int kPlanes = 3;
+constexpr int kPlaneThreads = 512, kPlaneWaves = kPlaneThreads / kWave;
+
+// The shape of a workgroup's work.  KH: the parts of a slab's reduction that go to different waves (their sums meet at the end);
+// the waves of a part lie 2 x (4 / KH) over the tile.
+template <int BM_, int BN_, int BK_, int KH_>
+struct PlaneTile {
+    static constexpr int BM = BM_, BN = BN_, BK = BK_, KH = KH_;
+    static constexpr int WN = kPlaneWaves / KH / 2, FM = BM / 64; // a wave's product: FM x 1 tiles of 32 x 32
+    static_assert(BN == 32 * WN && BK / 16 % KH == 0, "a wave has one tile of columns");
+    // bytes of LDS between the groups of 8 r of a plane (a write's 8 lanes at a time are BK / 8 groups of as many rows as that
+    // takes), of a plane, of a slab
+    static constexpr int pitch(int rows) { return rows * 16 + (BK == 32 ? 32 : 16); }
+    static constexpr int plane(int rows) { return pitch(rows) * (BK / 8); }
+    static constexpr int kSlabBytes = kPlanes * (plane(BM) + plane(BN));
+};
+using PlaneTile128 = PlaneTile<128, 128, 32, 1>;
+using PlaneTile128x64 = PlaneTile<128, 64, 64, 2>;
+using PlaneTile64 = PlaneTile<64, 64, 64, 2>;
+
+// a pair of floats -> a pair of bfloat16 (round to nearest even), and what that leaves of them (exact)
+__device__ __forceinline__ unsigned split_pair(float &x0, float &x1)
 {
-    const int tiles_j = (g.N + 63) / 64, tiles_i = (g.M + 63) / 64;
-    const int z = local / (tiles_i * tiles_j);
+    const unsigned h = __builtin_bit_cast(unsigned, __builtin_convertvector((Float2){x0, x1}, Bf16x2));
+    x0 -= __uint_as_float(h << 16);
+    x1 -= __uint_as_float(h & 0xFFFF0000u);
+    return h;
+}
+
+// One operand's part of a tile, as one thread reads it: ROWS wide indices, 8 consecutive r of each slab in an item.
+// kOpRC: the reduction index is the unit-stride one; kOpWide: the wide one is.
+template <int MODE, int ROWS, int BK>
+struct PlaneOperand {
+    static constexpr int kGroups = BK / 8, kItems = ROWS * kGroups / kPlaneThreads;
+    static constexpr int kRowsPerItem = kPlaneThreads / kGroups, kGroupsPerItem = kPlaneThreads / ROWS; // kOpRC; kOpWide
+    const float *tile;     // the tile's first wide index, r = 0 (wave-uniform)
+    long long sr;          // kOpWide: between lines
+    // kOpRC: of the items' rows; kOpWide: of the first item's lines (kept, as adding a line's length 8 times costs two instructions
+    // beside each load)
+    unsigned off[MODE == kOpRC ? kItems : 8];
+    int row, kg;           // of the first item
+    float v[2][kItems][8]; // two slabs on their way
+
+    // `first`: the tile's first wide index; those past `count` re-read the last.  `whole`: the reduction has a whole slab; otherwise
+    // fetch() reads some 8 floats of the operand instead (kOpRC: the reduction has as many: host).
+    __device__ __forceinline__ void init(const float *base, long long sw, long long sr_, int first, int count, bool whole, int tid)
+    {
+        if (MODE == kOpRC) {
+            sr = sw;
+            row = tid / kGroups, kg = tid % kGroups;
+            tile = base + (long long)first * sw;
+#pragma unroll
+            for (int c = 0; c < kItems; ++c) {
+                off[c] = (unsigned)(min(first + row + c * kRowsPerItem, count - 1) - first) * (unsigned)sw + 8u * kg;
+                if (!whole) off[c] = 0u;
+            }
+        } else {
+            sr = whole ? sr_ : 0;
+            row = tid % ROWS, kg = tid / ROWS;
+            tile = base + first;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) off[k] = (8u * kg + k) * (unsigned)sr + min(row, count - 1 - first);
+        }
+    }
+    // a whole slab
+    __device__ __forceinline__ void fetch(int q, int r0)
+    {
+#pragma unroll
+        for (int c = 0; c < kItems; ++c) {
+            if (MODE == kOpRC) {
+                const float *p = tile + r0 + off[c];
+                const Float4Dw lo = *reinterpret_cast<const Float4Dw *>(p), hi = *reinterpret_cast<const Float4Dw *>(p + 4);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[q][c][k] = lo[k], v[q][c][4 + k] = hi[k];
+            } else {
+                const float *p = tile + (long long)(r0 + 8 * c * kGroupsPerItem) * sr;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) v[q][c][k] = p[off[k]];
+            }
+        }
+    }
+    // the partial slab: r past `r_end` re-reads the one before it and counts as 0
+    __device__ __forceinline__ void fetch_tail(int q, int r0, int r_end, long long line, int first, int count)
+    {
+#pragma unroll
+        for (int c = 0; c < kItems; ++c) {
+            const int r_item = r0 + 8 * (kg + (MODE == kOpRC ? 0 : c * kGroupsPerItem));
+            const int at = min(first + row + (MODE == kOpRC ? c * kRowsPerItem : 0), count - 1) - first;
+            const float *p = tile + (MODE == kOpRC ? at * sr : at);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int r = r_item + k, rc = min(r, r_end - 1);
+                const float t = p[MODE == kOpRC ? rc : rc * line];
+                v[q][c][k] = r < r_end ? t : 0.0f;
+            }
+        }
+    }
+    // split and leave in LDS
+    __device__ __forceinline__ void put(int q, char *lds)
+    {
+        constexpr int kPitch = ROWS * 16 + (BK == 32 ? 32 : 16);
+#pragma unroll
+        for (int c = 0; c < kItems; ++c) {
+            char *at = lds + (kg + (MODE == kOpRC ? 0 : c * kGroupsPerItem)) * kPitch + (row + (MODE == kOpRC ? c * kRowsPerItem : 0)) * 16;
+            float t[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) t[k] = v[q][c][k];
+#pragma unroll
+            for (int p = 0; p < kPlanes; ++p) {
+                uint4 o;
+                o.x = split_pair(t[0], t[1]), o.y = split_pair(t[2], t[3]), o.z = split_pair(t[4], t[5]), o.w = split_pair(t[6], t[7]);
+                *reinterpret_cast<uint4 *>(at + p * kPitch * kGroups) = o;
+            }
+        }
+    }
+    __device__ __forceinline__ float sum(int q) const // (kOpWide: of one row)
+    {
+        float s = 0.0f;
+#pragma unroll
+        for (int c = 0; c < kItems; ++c)
+            s += ((v[q][c][0] + v[q][c][1]) + (v[q][c][2] + v[q][c][3])) + ((v[q][c][4] + v[q][c][5]) + (v[q][c][6] + v[q][c][7]));
+        return s;
+    }
+};
+
+// Tile `local` of product g (one slice of its reduction, and the rows' sums beside it, if SPLIT).  lds0, lds1: kSlabBytes each.
+template <typename TILE, int A_MODE, int B_MODE, bool SPLIT>
+__device__ __forceinline__ void gemm_planes_tile(const GemmArgs &g, int local, char *lds0, char *lds1)
+{
+    constexpr int BM = TILE::BM, BN = TILE::BN, BK = TILE::BK, KH = TILE::KH, FM = TILE::FM, WN = TILE::WN;
+    constexpr int kA = TILE::plane(BM), kB = TILE::plane(BN), kPitchA = TILE::pitch(BM), kPitchB = TILE::pitch(BN);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int w = lane & 31, h = lane >> 5, kh = wave / (2 * WN), wm = wave & 1, wn = (wave >> 1) % WN;
+    const int tiles_j = (g.N + BN - 1) / BN, tiles_i = (g.M + BM - 1) / BM;
+    const int z = SPLIT ? local / (tiles_i * tiles_j) : 0;
     local -= z * tiles_i * tiles_j;
-    const int i_first = (local / tiles_j) * 64, j_first = (local % tiles_j) * 64;
-    const int i0 = min(i_first, g.M - 64), j0 = min(j_first, g.N - 64);
-    // the slice (empty past the end of the reduction), and this wave's quarter of it in whole pairs of slabs
-    const int z_begin = min(z * g.k_per_split, g.K), z_end = min(z_begin + g.k_per_split, g.K);
-    const int k_per_wave = (z_end - z_begin + 2 * kGemmBK * kGemmWaves - 1) / (2 * kGemmBK * kGemmWaves) * (2 * kGemmBK);
-    const int r_begin = min(z_begin + wave * k_per_wave, z_end), r_end = min(r_begin + k_per_wave, z_end);
-    const int w = lane & 31, h = lane >> 5;
+    const int i0 = local / tiles_j * BM, j0 = local % tiles_j * BN;
+    const int r_begin = SPLIT ? min(z * g.k_per_split, g.K) : 0, r_end = SPLIT ? min(r_begin + g.k_per_split, g.K) : g.K;
 
-    floatx16 acc[4]; // quadrant 2 * (row half) + (column half)
+    PlaneOperand<A_MODE, BM, BK> a;
+    PlaneOperand<B_MODE, BN, BK> b;
+    a.init(g.A, g.a_si, g.a_sr, i0, g.M, g.K >= BK, tid);
+    b.init(g.B, g.b_sj, g.b_sr, j0, g.N, g.K >= BK, tid);
+    floatx16 acc[FM], rest[FM]; // the first planes' products, and the smaller ones
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int m = 0; m < FM; ++m)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[q][v] = 0.0f;
-    float row_sum[2] = {0.0f, 0.0f};
+        for (int v = 0; v < 16; ++v) acc[m][v] = rest[m][v] = 0.0f;
+    float row_sum = 0.0f;
 
-    struct Slab {
-        SlabRegs a[2], b[2];
+    // The slabs in their order: the partial one first, if there is one (it is read in another way, and the loop below has no
+    // branch).  Requests past the last slab read some slab of the operands that exists, and nobody looks at it.
+    const int whole = (r_end - r_begin) / BK, tail = r_end - r_begin - whole * BK;
+    const int slabs = whole + (tail > 0), r_slab = r_begin - (tail > 0 ? BK : 0), r_last = max(g.K - BK, 0);
+    auto fetch = [&](int q, int s) {
+        const int r0 = min(r_slab + s * BK, r_last);
+        a.fetch(q, r0);
+        b.fetch(q, r0);
     };
-    Slab x, y;
-    auto fetch = [&](Slab &t, int r0) {
+    auto put = [&](int q, int s, char *lds) {
+        a.put(q, lds);
+        b.put(q, lds + kPlanes * kA);
+        if (SPLIT) row_sum += __uint_as_float(__float_as_uint(a.sum(q)) & (unsigned)((s - slabs) >> 31)); // (no branch)
+    };
+    // a slab's planes, as the matrix cores take them
+    constexpr int kSteps = BK / 16 / KH;
+    struct Fragments {
+        Bf16x8 a[kSteps][kPlanes][FM], b[kSteps][kPlanes];
+    };
+    auto read = [&](Fragments &f, const char *lds) {
+        const char *la = lds + (2 * kSteps * kh + h) * kPitchA + (32 * FM * wm + w) * 16;
+        const char *lb = lds + kPlanes * kA + (2 * kSteps * kh + h) * kPitchB + (32 * wn + w) * 16;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            slab_load_direct<false>(t.a[q], g.A, g.a_si, g.a_sr, i0 + 32 * q + w, r0, 0, h, false);
-            slab_load_direct<false>(t.b[q], g.B, g.b_sj, g.b_sr, j0 + 32 * q + w, r0, 0, h, false);
+        for (int s = 0; s < kSteps; ++s)
+#pragma unroll
+            for (int p = kPlanes - 1; p >= 0; --p) {
+#pragma unroll
+                for (int m = 0; m < FM; ++m)
+                    f.a[s][p][m] = *reinterpret_cast<const Bf16x8 *>(la + p * kA + 2 * s * kPitchA + m * 32 * 16);
+                f.b[s][p] = *reinterpret_cast<const Bf16x8 *>(lb + p * kB + 2 * s * kPitchB);
+            }
+    };
+    auto products = [&](const Fragments &f) {
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s)
+#pragma unroll
+            for (int sum = kPlanes - 1; sum >= 0; --sum)
+#pragma unroll
+                for (int p = 0; p <= sum; ++p)
+#pragma unroll
+                    for (int m = 0; m < FM; ++m) {
+                        floatx16 &to = sum > 0 ? rest[m] : acc[m];
+                        to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[s][p][m], f.b[s][sum - p], to, 0, 0, 0);
+                    }
+    };
+    // the order of a slab's instructions: the vector unit's between the matrix core's
+    auto interleave = [&]() {
+        constexpr int kProducts = kSteps * 6 * FM, kReads = kSteps * kPlanes * (FM + 1);
+        constexpr int kValu = (a.kItems + b.kItems) * 44 + 8;
+        __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
+#pragma unroll
+        for (int i = 0; i < kProducts; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x2, (kValu + kProducts - 1) / kProducts, 0);
         }
     };
-    auto products = [&](const Slab &t, int s_from, int s_to) {
-#pragma unroll
-        for (int s = s_from; s < s_to; ++s) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(t.a[q >> 1].v[s], t.b[q & 1].v[s], acc[q], 0, 0, 0);
-            row_sum[0] += t.a[0].v[s], row_sum[1] += t.a[1].v[s];
+    if (slabs > 0) { // (the whole workgroup, or none of it)
+        if (tail > 0) {
+            a.fetch_tail(0, r_end - tail, r_end, g.a_sr, i0, g.M);
+            b.fetch_tail(0, r_end - tail, r_end, g.b_sr, j0, g.N);
+        } else {
+            fetch(0, 0);
         }
-    };
-
-    // pairs of whole slabs; a request past the last pair re-reads the last slab (harmless, and no branch)
-    int r0 = r_begin;
-    const int r_pairs = r_begin + (r_end - r_begin) / (2 * kGemmBK) * (2 * kGemmBK);
-    if (r0 < r_pairs) {
-        const int r_last = r_pairs - kGemmBK;
-        fetch(x, r0);
-        __builtin_amdgcn_sched_barrier(0);
-        for (; r0 < r_pairs; r0 += 2 * kGemmBK) {
-            products(x, 0, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            fetch(y, r0 + kGemmBK);
-            products(x, 1, 16);
-            __builtin_amdgcn_sched_barrier(0);
-            products(y, 0, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            fetch(x, min(r0 + 2 * kGemmBK, r_last));
-            products(y, 1, 16);
-            __builtin_amdgcn_sched_barrier(0);
+        fetch(1, 1);
+        put(0, 0, lds0);
+        fetch(0, 2);
+        __syncthreads();
+        // while slab s is multiplied, s + 1 is split and written to LDS, s + 2 and s + 3 are on their way
+        for (int s = 0; s < slabs; s += 2) {
+            Fragments f;
+            read(f, lds0);
+            put(1, s + 1, lds1);
+            fetch(1, s + 3);
+            products(f);
+            interleave();
+            __syncthreads();
+            if (s + 1 < slabs) {
+                read(f, lds1);
+                put(0, s + 2, lds0);
+                fetch(0, s + 4);
+                products(f);
+                interleave();
+                __syncthreads();
+            }
         }
     }
-    // what is left: at most one whole and one partial slab, clamped (zeros past the end)
-    for (; r0 < r_end; r0 += kGemmBK) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            slab_load_direct<true>(x.a[q], g.A, g.a_si, g.a_sr, i0 + 32 * q + w, r0, r_end, h, false);
-            slab_load_direct<true>(x.b[q], g.B, g.b_sj, g.b_sr, j0 + 32 * q + w, r0, r_end, h, false);
-        }
-        products(x, 0, 16);
-    }
 
-    // the quarters meet: wave q finishes quadrant q
-    float *mine = lds_all + wave * kGemm64WaveFloats;
-    float *sums = lds_all + kGemmWaves * kGemm64WaveFloats;
+    // lane l holds column l % 32 of its products and rows 8 (v / 4) + 4 (l / 32) + v % 4
+    const int i_lane = 32 * FM * wm + 4 * h, j_lane = 32 * wn + w;
+    float finite = 0.0f;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) row_sum[q] += __shfl_xor(row_sum[q], 32);
-    sums[wave * kWave + lane] = h ? row_sum[1] : row_sum[0];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) mine[(q * 16 + v) * kWave + lane] = acc[q][v];
-    __syncthreads();
-    floatx16 sum;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) sum[v] = lds_all[(wave * 16 + v) * kWave + lane];
-    for (int k = 1; k < kGemmWaves; ++k)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) sum[v] += lds_all[k * kGemm64WaveFloats + (wave * 16 + v) * kWave + lane];
-
-    float *p = g.P + (long long)z * g.M * (g.N + 1);
-    const int i = i0 + 32 * (wave >> 1) + 4 * h, j = j0 + 32 * (wave & 1) + w;
-    if (j >= j_first) { // (a moved tile stores only its own rows and columns)
+    for (int m = 0; m < FM; ++m)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const int iv = i + 8 * (v >> 2) + (v & 3);
-            if (iv >= i_first) p[(long long)iv * (g.N + 1) + j] = sum[v];
+            acc[m][v] += rest[m][v];
+            finite = __builtin_fmaf(acc[m][v], 0.0f, finite);
+        }
+    if (__builtin_expect(finite != 0.0f, 0)) { // (NaN)
+#pragma unroll
+        for (int m = 0; m < FM; ++m)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[m][v] = 0.0f;
+#pragma unroll 1
+        for (int r = r_begin; r < r_end; ++r) {
+            if ((r - r_begin) % BK / (BK / KH) != kh) continue;
+            const float bv = g.B[(long long)min(j0 + j_lane, g.N - 1) * g.b_sj + r * g.b_sr];
+#pragma unroll
+            for (int m = 0; m < FM; ++m)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int i = i0 + i_lane + 32 * m + 8 * (v >> 2) + (v & 3);
+                    acc[m][v] = __builtin_fmaf(g.A[(long long)min(i, g.M - 1) * g.a_si + r * g.a_sr], bv, acc[m][v]);
+                }
         }
     }
-    if (wave == 0 && j_first == 0 && i0 + lane >= i_first) {
-        float t = 0.0f;
-        for (int k = 0; k < kGemmWaves; ++k) t += sums[k * kWave + lane];
-        p[(long long)(i0 + lane) * (g.N + 1) + g.N] = t;
+
+    // The tile goes through LDS: 16 bytes to a thread, and a loop of little code (a launch fetches every line of its code anew).
+    // KH = 1: rows 0..63 lie in lds0, the others in lds1; KH = 2: either has a part's sums.
+    constexpr int kPitch = BN + 4, kCols = BN / 4, kRows = kPlaneThreads / kCols;
+    static_assert((KH == 1 ? 64 : BM) * kPitch * 4 <= TILE::kSlabBytes && (KH == 2 || BM == 128), "the tile fits the slabs' room");
+    float *tile0 = reinterpret_cast<float *>(lds0), *tile1 = reinterpret_cast<float *>(lds1); // (every read is behind a barrier)
+    {
+        float *at = ((KH == 1 ? wm : kh) ? tile1 : tile0) + (KH == 1 ? 4 * h : i_lane) * kPitch + j_lane;
+#pragma unroll
+        for (int m = 0; m < FM; ++m)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) at[(32 * m + 8 * (v >> 2) + (v & 3)) * kPitch] = acc[m][v];
     }
+    const int col = tid % kCols * 4, j = j0 + col, row = tid / kCols;
+    float *out = SPLIT ? g.P + (long long)z * g.M * (g.N + 1) : g.C;
+    const long long pitch = SPLIT ? g.N + 1 : g.c_si;
+    const bool full = j + 4 <= g.N;
+    float bias[4] = {};
+    if (!SPLIT && g.bias) {
+#pragma unroll
+        for (int n = 0; n < 4; ++n) bias[n] = g.bias[min(j + n, g.N - 1)];
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int k = 0; k < BM / kRows; ++k) {
+        const int r = row + k * kRows, i = i0 + r;
+        const long long at = (long long)min(i, g.M - 1) * pitch + j;
+        float4 t = *reinterpret_cast<const float4 *>((KH == 1 && r >= 64 ? tile1 - 64 * kPitch : tile0) + r * kPitch + col);
+        if (KH == 2) {
+            const float4 u = *reinterpret_cast<const float4 *>(tile1 + r * kPitch + col);
+            t.x += u.x, t.y += u.y, t.z += u.z, t.w += u.w;
+        }
+        float x[4] = {t.x, t.y, t.z, t.w};
+        if (!SPLIT) {
+            Float4Dw mask = {1.0f, 1.0f, 1.0f, 1.0f};
+            if (g.mask) { // (one load, except at the last columns: those past the edge are not stored)
+                if (full)
+                    mask = *reinterpret_cast<const Float4Dw *>(g.mask + at);
+                else
+#pragma unroll
+                    for (int n = 0; n < 4; ++n) mask[n] = g.mask[at - j + min(j + n, g.N - 1)];
+            }
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {
+                x[n] += bias[n];
+                if (g.relu) x[n] = fmaxf(x[n], 0.0f);
+                x[n] = mask[n] > 0.0f ? x[n] : 0.0f;
+            }
+        }
+        if (i < g.M) {
+            if (full)
+                *reinterpret_cast<Float4Dw *>(out + at) = (Float4Dw){x[0], x[1], x[2], x[3]};
+            else
+#pragma unroll
+                for (int n = 0; n < 4; ++n)
+                    if (j + n < g.N) out[at + n] = x[n];
+        }
+    }
+    if (SPLIT) { // the rows' sums: several threads have a part of each
+        constexpr int kParts = kPlaneThreads / BM;
+        __syncthreads();
+        tile0[tid] = row_sum; // (kOpWide: row tid % BM)
+        __syncthreads();
+        if (j0 == 0 && tid < BM && i0 + tid < g.M) {
+            float s = tile0[tid];
+#pragma unroll
+            for (int k = 1; k < kParts; ++k) s += tile0[k * BM + tid];
+            out[(long long)(i0 + tid) * pitch + g.N] = s;
+        }
+    }
+}
+
+// Workgroups are dealt to the eight parts of the chip in turn, each with a second-level cache of its own: neighbouring tiles, which
+// share rows of A, go to the same one.
+__device__ __forceinline__ int xcd_chunk(int id, int count)
+{
+    constexpr int kXcds = 8;
+    const int each = count / kXcds, more = count % kXcds, xcd = id % kXcds;
+    return xcd * each + min(xcd, more) + id / kXcds;
+}
+
+template <typename TILE, int A_MODE, int B_MODE>
+__global__ __launch_bounds__(kPlaneThreads) void gemm_planes_kernel(GemmArgs g)
+{
+    // (two arrays: the compiler knows that what is read from one is not what is written to the other)
+    __shared__ __align__(16) char lds0[TILE::kSlabBytes], lds1[TILE::kSlabBytes];
+    gemm_planes_tile<TILE, A_MODE, B_MODE, false>(g, xcd_chunk((int)blockIdx.x, (int)gridDim.x), lds0, lds1);
 }
 
 // With kslices > 1 the waves of a workgroup meet at a barrier inside: a wave past the last tile stays, takes the
@@ -519,26 +736,24 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_wave_kernel(GemmOne one)
     gemm_wave_tile<A_MODE, B_MODE>(one.p, min(tile, one.total_tiles - 1), live, ks, wave, lane, lds);
 }
 
-// several split products in one launch (kOpWide operands): a workgroup has one 64x64 tile or four of 32x32.  Two
-// workgroups to a CU: one's first loads and last sums run beside the other's products.
-__global__ __launch_bounds__(kGemmThreads, 2) void gemm_split_group_kernel(GemmGroup grp)
+// Several split products in one launch (kOpWide operands): the weight gradients of all layers, a workgroup per tile.
+// Measured: the Terabyte shape's layers at batch 8192 (12.4 GFLOP) 98 us, the Kaggle shape's at 2048 (1.96 GFLOP) 25; on the
+// fp32 matrix instructions 171 and 34.5.
+__global__ __launch_bounds__(kPlaneThreads) void gemm_split_group_kernel(GemmGroup grp)
 {
-    __shared__ __align__(16) float lds[kGemm64LdsFloats > kGemmLdsFloats ? kGemm64LdsFloats : kGemmLdsFloats];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    constexpr int kLds = PlaneTile128::kSlabBytes > PlaneTile64::kSlabBytes ? PlaneTile128::kSlabBytes : PlaneTile64::kSlabBytes;
+    __shared__ __align__(16) char lds0[kLds], lds1[kLds];
+    const int id = xcd_chunk((int)blockIdx.x, (int)gridDim.x); // (a slice's tiles share their operands' rows)
     int pi = 0;
 #pragma unroll 1
     for (int q = 1; q < grp.count; ++q)
-        if ((int)blockIdx.x >= grp.p[q].block_begin) pi = q;
+        if (id >= grp.p[q].block_begin) pi = q;
     const GemmArgs &g = grp.p[pi];
-    const int local = (int)blockIdx.x - g.block_begin;
-    if (g.tile64) {
-        gemm_split_tile64(g, local, wave, lane, lds);
-    } else {
-        const int tile = local * kGemmWaves + wave;
-        if (tile >= ((g.M + 31) / 32) * ((g.N + 31) / 32) * g.splits) return; // whole waves leave; no barrier inside
-        gemm_wave_tile<kOpWide, kOpWide>(g, tile, true, 1, wave, lane, lds);
-    }
+    const int local = id - g.block_begin;
+    if (g.tile == 128)
+        gemm_planes_tile<PlaneTile128, kOpWide, kOpWide, true>(g, local, lds0, lds1);
+    else
+        gemm_planes_tile<PlaneTile64, kOpWide, kOpWide, true>(g, local, lds0, lds1);
 }
 
 // ---- a layer with a short input (the bottom MLP's first: 13 dense features) -------------------------------

@@ -71,7 +71,7 @@ def test_interaction_shapes(oracle, T, D, B, bot):
     _check(oracle, T, D, B, bot, [16])
 
 
-# The weight gradients' 64x64 tiles: layers just below, at and above one and two tiles, batches of one sample, one partial
+# The products' tiles: layers just below, at and above one and two tiles of 64, batches of one sample, one partial
 # slab and many slices.  Among the 2 million pre-activations of
 # such a batch about 2e6 * 2.7e-6 * 0.8 = 4 lie within their rounding of zero, and each ReLU so flipped moves the embedding
 # gradients by some 1e-3 of their norm; large batches therefore keep every pre-activation away from zero.
@@ -81,6 +81,41 @@ def test_interaction_shapes(oracle, T, D, B, bot):
     (8, 16, 1023, [13, 48, 32], [60, 48]), (8, 64, 1536, [13, 64], [128, 64]), (3, 16, 257, [13, 600], [601, 64])])
 def test_product_tiles(oracle, T, D, B, bot, top):
     _check(oracle, T, D, B, bot, top, margin=B > 1000)
+
+
+# The products by planes of bfloat16: reductions below, at and above 8 (the shortest), a slab of 32 or 64 and two of them; columns and
+# samples that end inside a tile of each size (128 x 128 and 128 x 64 from some 4096 samples on).
+@pytest.mark.parametrize("T,D,B,bot,top", [
+    (2, 16, 70, [7, 33], [9, 8]), (2, 16, 7, [8, 65], [31, 33]), (2, 8, 63, [9, 127], [63, 32]), (1, 62, 64, [20, 129], [65, 95]),
+    (1, 64, 127, [17, 191], [96, 128]), (3, 60, 300, [18, 401], [384, 70]), (2, 16, 4097, [20, 190], [257, 70]),
+    (2, 16, 8193, [8, 129], [385, 130])])
+def test_plane_products(oracle, T, D, B, bot, top):
+    _check(oracle, T, D, B, bot, top, margin=B > 1000)
+
+
+# An infinite feature, as the floats' products have it: the first layer's outputs are infinite where its weight is positive (else 0
+# after the ReLU), so the weight gradients of that feature's column and of those outputs' columns are not finite.  The second layer
+# adds up infinities of both signs: NaN, which its ReLU makes 0.  Everything else is finite.
+@pytest.mark.parametrize("B", [70, 700, 8200])
+def test_products_of_infinities(B):
+    import torch
+    import paper_2410_20046_amd as dq
+
+    T, D = 3, 32
+    rng = np.random.default_rng(3)
+    bot_dims, bw, bb, top_dims, tw, tb = _model(rng, T, D, [13, 130, 140], [140, 129])
+    x, emb = rng.standard_normal((B, 13)).astype(np.float32), rng.standard_normal((B, T, D)).astype(np.float32)
+    y = (rng.random(B) < 0.25).astype(np.float32)
+    x[B // 2, 4] = np.inf
+    dev = torch.device("cuda:0")
+    m = dq.DenseModel(T, D, bot_dims, bw, bb, top_dims, tw, tb, dev)
+    ws = torch.zeros(dq.dqrm_dense_workspace_bytes(m, B), dtype=torch.uint8, device=dev)
+    loss, grad = torch.zeros(1, device=dev), torch.zeros((B, T, D), device=dev)
+    dq.dqrm_dense_step(m, B, torch.from_numpy(x).to(dev), torch.from_numpy(emb).to(dev), torch.from_numpy(y).to(dev), 1.0, loss, grad, ws)
+    finite = [torch.isfinite(t).cpu().numpy() for t in m.bot_w]
+    assert np.array_equal(finite[0], np.broadcast_to(np.arange(13) != 4, (130, 13)))
+    assert np.array_equal(finite[1], np.broadcast_to(bw[0][:, 4] < 0, (140, 130)))
+    assert finite[2].all() and all(bool(torch.isfinite(t).all()) for t in [loss, grad] + m.bot_b + m.top_w + m.top_b)
 
 
 # The short-input layer takes 4 samples to a workgroup while that fills 2 workgroups per CU or the layer has at most 256 outputs,
