@@ -198,31 +198,36 @@ void launch_fwd(int G, dim3 grid, hipStream_t st, const dqrm::FwdArgs &a)
     }
 }
 
+template <bool REUSE>
 void launch_segsum(int G, dim3 grid, hipStream_t st, const dqrm::SegArgs &a)
 {
     using namespace dqrm;
     switch (G) {
-    case 2: hipLaunchKernelGGL((segment_sum_kernel<2>), grid, dim3(kSumThreads), 0, st, a); break;
-    case 4: hipLaunchKernelGGL((segment_sum_kernel<4>), grid, dim3(kSumThreads), 0, st, a); break;
-    case 8: hipLaunchKernelGGL((segment_sum_kernel<8>), grid, dim3(kSumThreads), 0, st, a); break;
-    case 16: hipLaunchKernelGGL((segment_sum_kernel<16>), grid, dim3(kSumThreads), 0, st, a); break;
-    case 32: hipLaunchKernelGGL((segment_sum_kernel<32>), grid, dim3(kSumThreads), 0, st, a); break;
-    default: hipLaunchKernelGGL((segment_sum_kernel<64>), grid, dim3(kSumThreads), 0, st, a); break;
+    case 2: hipLaunchKernelGGL((segment_sum_kernel<2, REUSE>), grid, dim3(kSumThreads), 0, st, a); break;
+    case 4: hipLaunchKernelGGL((segment_sum_kernel<4, REUSE>), grid, dim3(kSumThreads), 0, st, a); break;
+    case 8: hipLaunchKernelGGL((segment_sum_kernel<8, REUSE>), grid, dim3(kSumThreads), 0, st, a); break;
+    case 16: hipLaunchKernelGGL((segment_sum_kernel<16, REUSE>), grid, dim3(kSumThreads), 0, st, a); break;
+    case 32: hipLaunchKernelGGL((segment_sum_kernel<32, REUSE>), grid, dim3(kSumThreads), 0, st, a); break;
+    default: hipLaunchKernelGGL((segment_sum_kernel<64, REUSE>), grid, dim3(kSumThreads), 0, st, a); break;
     }
 }
 
+template <bool REUSE>
 void launch_segsum_multi(int G, dim3 grid, hipStream_t st, const dqrm::SegMulti &m)
 {
     using namespace dqrm;
     switch (G) {
-    case 2: hipLaunchKernelGGL((segment_sum_multi_kernel<2>), grid, dim3(kSumThreads), 0, st, m); break;
-    case 4: hipLaunchKernelGGL((segment_sum_multi_kernel<4>), grid, dim3(kSumThreads), 0, st, m); break;
-    case 8: hipLaunchKernelGGL((segment_sum_multi_kernel<8>), grid, dim3(kSumThreads), 0, st, m); break;
-    case 16: hipLaunchKernelGGL((segment_sum_multi_kernel<16>), grid, dim3(kSumThreads), 0, st, m); break;
-    case 32: hipLaunchKernelGGL((segment_sum_multi_kernel<32>), grid, dim3(kSumThreads), 0, st, m); break;
-    default: hipLaunchKernelGGL((segment_sum_multi_kernel<64>), grid, dim3(kSumThreads), 0, st, m); break;
+    case 2: hipLaunchKernelGGL((segment_sum_multi_kernel<2, REUSE>), grid, dim3(kSumThreads), 0, st, m); break;
+    case 4: hipLaunchKernelGGL((segment_sum_multi_kernel<4, REUSE>), grid, dim3(kSumThreads), 0, st, m); break;
+    case 8: hipLaunchKernelGGL((segment_sum_multi_kernel<8, REUSE>), grid, dim3(kSumThreads), 0, st, m); break;
+    case 16: hipLaunchKernelGGL((segment_sum_multi_kernel<16, REUSE>), grid, dim3(kSumThreads), 0, st, m); break;
+    case 32: hipLaunchKernelGGL((segment_sum_multi_kernel<32, REUSE>), grid, dim3(kSumThreads), 0, st, m); break;
+    default: hipLaunchKernelGGL((segment_sum_multi_kernel<64, REUSE>), grid, dim3(kSumThreads), 0, st, m); break;
     }
 }
+
+// Bags of one and a half lookups or more on average: their gradient rows are read more than once.
+bool several_lookups(int64_t num_indices, int64_t T, int64_t batch) { return num_indices >= T * batch * 3 / 2; }
 
 int32_t sparse_update_impl(const dqrm_tables_t *tables, int64_t capacity, const int64_t *uniq_rows,
                            const int32_t *table_uniq_offsets, const int8_t *gq, const int32_t *sums,
@@ -439,10 +444,9 @@ int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t nu
     da.bags_per_part = (int)((batch + parts - 1) / parts);
     da.by_parts = dqrm::FastDiv::make((unsigned)parts);
     da.even = dqrm::FastDiv::make((unsigned)std::max<int64_t>(1, max_n / ((int64_t)T * batch)));
-    // The segment sums of bags of several lookups are faster over a list ordered by chunk length (26 tables x 65536 lookups:
-    // 116 us, in sorted order 157; 13 x 10500: 21.6, 23.2), those of bags of one over one in sorted order (26 x 8192: 25.4, by
-    // length 27.4).
-    da.by_length = max_n >= (int64_t)T * batch * 3 / 2;
+    // The segment sums of bags of several lookups are faster over a list ordered by chunk length (26 tables x 65536 lookups: by a
+    // quarter), those of bags of one over one in sorted order (8 x 26 x 8192, whole steps: 461 us, by length 470; 26 x 8192: 73.2, 74.2).
+    da.by_length = several_lookups(max_n, T, batch);
     // A table far above the average would leave its few ranges' workgroups at work alone, each with piece after piece to take,
     // the more so if its popular rows lie close together: a table of more than the LDS holds (and a quarter above the average) has
     // ranges of half the LDS each, as many as that takes, chosen so that they hold about equally many lookups.  The workgroups of
@@ -529,7 +533,10 @@ int32_t dqrm_segment_sum(const dqrm_tables_t *tables, int32_t batch, int64_t num
     const int G = pow2ceil(D / 4);
     // at most one lane group per four lookups (a window of the chunk list per workgroup, a few singles per group)
     const int grid_sum = grid_for((num_indices + 3) / 4 * G, dqrm::kSumThreads, dqrm::kSumBlocksPerCu);
-    launch_segsum(G, dim3(grid_sum), st, sa);
+    if (several_lookups(num_indices, T, batch))
+        launch_segsum<true>(G, dim3(grid_sum), st, sa);
+    else
+        launch_segsum<false>(G, dim3(grid_sum), st, sa);
     if (g_absmax)
         hipLaunchKernelGGL(dqrm::absmax_finalize_kernel, dim3((T + 255) / 256), dim3(256), 0, st, sa.ws.absmax_slots,
                            T, g_absmax);
@@ -579,7 +586,10 @@ int32_t dqrm_segment_sum_multi(const dqrm_tables_t *tables, int32_t batch, int32
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int G = pow2ceil(D / 4);
     const int grid_sum = grid_for((max_n + 3) / 4 * G, dqrm::kSumThreads, dqrm::kSumBlocksPerCu);
-    launch_segsum_multi(G, dim3(grid_sum, num_batches), st, sm);
+    if (several_lookups(max_n, T, batch))
+        launch_segsum_multi<true>(G, dim3(grid_sum, num_batches), st, sm);
+    else
+        launch_segsum_multi<false>(G, dim3(grid_sum, num_batches), st, sm);
     if (any_absmax)
         hipLaunchKernelGGL(dqrm::absmax_finalize_multi_kernel, dim3((T + 255) / 256, num_batches), dim3(256), 0, st, am);
     DQRM_HIP_CHECK(hipGetLastError());

@@ -35,12 +35,15 @@ __device__ __forceinline__ float4 f4_add(float4 a, float4 b)
     return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
 }
 
-// 16 bytes of a gradient row by a streaming load, so that they do not push the lists and sums that are read again out of the
-// caches: with bags of one lookup a row is added into one segment and read once (62.3 -> 60.7 us per step that way).  A row of a
-// bag of several lookups is read once for each.
-__device__ __forceinline__ float4 load_once_f4(const float *p)
+// 16 bytes of a gradient row.  With bags of one lookup a row is added into one segment and read once: by a streaming load, so that
+// it does not push the lists and sums that are read again out of the caches (62.3 -> 60.7 us per step that way).  A row of a
+// bag of several lookups (REUSE) is read once for each, and is to stay in the cache (26 tables x 65536 lookups in bags of 8: the step
+// 341 -> 321 us with plain loads).
+template <bool REUSE>
+__device__ __forceinline__ float4 load_row_f4(const float *p)
 {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
+    if (REUSE) return *reinterpret_cast<const float4 *>(p);
     const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
     return make_float4(v[0], v[1], v[2], v[3]);
 }
@@ -101,7 +104,7 @@ __device__ __forceinline__ void load_chunk_bags(const SegArgs &a, int c, int lg,
 // compiler cannot count the loads in flight and waits for all of them before each
 // next one.)  `wave_len` is the longest chunk among the wave's groups: batches
 // and quarters of batches beyond it are skipped by the whole wave.
-template <int G>
+template <int G, bool REUSE>
 __device__ __forceinline__ float4 sum_chunk(const int (&my_bags)[kChunkIdsPerLane(G)], int len, int wave_len, int leader,
                                             const float *g0, unsigned tD)
 {
@@ -119,7 +122,7 @@ __device__ __forceinline__ float4 sum_chunk(const int (&my_bags)[kChunkIdsPerLan
                         const int i = i0 + q;
                         int b = __shfl(my_bags[i / G], leader + (i % G), kWave); // the group passes the bags round
                         b = i < len ? b : 0;
-                        g[q] = load_once_f4(g0 + (uint64_t)(unsigned)b * tD);
+                        g[q] = load_row_f4<REUSE>(g0 + (uint64_t)(unsigned)b * tD);
                     }
                 } else {
 #pragma unroll
@@ -154,34 +157,58 @@ __device__ __forceinline__ float *partial_slot(const BwdWs &ws, int head_pos, in
 // than the entire kernel when thousands of waves do it.
 __device__ __forceinline__ void park_f4(float *p, float4 v)
 {
-    __hip_atomic_store(p + 0, v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 1, v.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 2, v.z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 3, v.w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned long long *to = reinterpret_cast<unsigned long long *>(p); // (16-byte aligned)
+    auto two = [](float a, float b) { return (unsigned long long)__float_as_uint(a) | ((unsigned long long)__float_as_uint(b) << 32); };
+    __hip_atomic_store(to + 0, two(v.x, v.y), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(to + 1, two(v.z, v.w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 constexpr int kCombineBatch = 64; // chunk sums of one column requested together
 
-// One column of the sum of a segment of `nchunks` > 1 chunks: its parked chunk sums, left to right.  (4 bytes per
-// chunk and lane, so that even kCombineBatch chunks cost a single round trip: a wave per segment, a lane per column.)
-__device__ __forceinline__ float combine_column(const BwdWs &ws, int head_pos, int nchunks, int D, int col)
+// The sum of a segment of `nchunks` > 1 chunks, 64 columns of it from `base` on: its parked chunk sums, left to right, by a whole
+// wave; lane l ends with column base + combine_col(l).  A load is 16 bytes a lane, of four chunks' rows (a sixteenth of the lanes
+// each); the four are then turned, so that a lane has one column of all four.  The loads' cache policy is that of a device-scope
+// atomic load, and past the full chunks' end they read zeros.  (4 bytes a lane, 64 loads per trip: a segment of 300 chunks took 20
+// to 30 us beside the others' work, now 9 to 13; the kernel at 26 tables x 8192 lookups of bags of one 24.4 -> 22.2 us.)
+__device__ __forceinline__ int combine_col(int lane) { return 4 * (lane & 15) + (lane >> 4); }
+
+__device__ __forceinline__ float combine_columns(const BwdWs &ws, int head_pos, int nchunks, int D, int base, int lane)
 {
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    constexpr int kAgentScope = 16; // sc1
+    constexpr int kLoads = kCombineBatch / 4;
+    const int full = nchunks - 1; // chunks filed under their positions (at most 2047 rows of 1 KB); the last one is elsewhere
+    const int64_t slot = (int64_t)(head_pos / DQRM_SEG_CHUNK) * D;
+    const float last = __hip_atomic_load(ws.partial_last + slot + min(base + combine_col(lane), D - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(ws.partial_full + slot, 0, full * D * (int)sizeof(float), 0x00020000);
+    const int at = ((lane >> 4) * D + base + 4 * (lane & 15)) * (int)sizeof(float);
     float acc = 0.f;
-    for (int k0 = 0; k0 < nchunks; k0 += kCombineBatch) {
-        float pv[kCombineBatch];
+    for (int k0 = 0; k0 < full; k0 += kCombineBatch) {
+        u32x4 v[kLoads];
 #pragma unroll
-        for (int q = 0; q < kCombineBatch; ++q)
-            if (k0 + q < nchunks)
-                pv[q] = __hip_atomic_load(partial_slot(ws, head_pos, k0 + q, nchunks, D) + col, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
+        for (int q0 = 0; q0 < kLoads; q0 += 4)
+            if (q0 == 0 || k0 + 4 * q0 < full) // (wave-uniform)
 #pragma unroll
-        for (int q = 0; q < kCombineBatch; ++q)
-            if (k0 + q < nchunks) acc = (k0 + q == 0) ? pv[q] : acc + pv[q];
+                for (int q = q0; q < q0 + 4; ++q)
+                    v[q] = __builtin_amdgcn_raw_buffer_load_b128(rows, at, (k0 + 4 * q) * D * (int)sizeof(float), kAgentScope);
+#pragma unroll
+        for (int q = 0; q < kLoads; ++q) {
+            if (k0 + 4 * q < full) {
+                const u32x2 a = __builtin_amdgcn_permlane32_swap(v[q][0], v[q][2], false, false);
+                const u32x2 b = __builtin_amdgcn_permlane32_swap(v[q][1], v[q][3], false, false);
+                const u32x2 c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false), d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+                const unsigned sums[4] = {c[0], c[1], d[0], d[1]};
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (k0 + 4 * q + k < full) acc = (k0 + 4 * q + k == 0) ? __uint_as_float(sums[k]) : acc + __uint_as_float(sums[k]);
+            }
+        }
     }
-    return acc;
+    return acc + last;
 }
 
-// The same for rows narrower than a wave: the wave's lanes are split among several segments, so `head_pos` and
+// One column of such a sum for rows narrower than a wave: the wave's lanes are split among several segments, so `head_pos` and
 // `nchunks` differ from lane to lane (nchunks = 0: a lane without a column to add).  All lanes go through the
 // motions up to `wave_n`, the largest nchunks in the wave; a lane past its own last chunk asks for that chunk again.
 __device__ __forceinline__ float combine_column_shared_wave(const BwdWs &ws, int head_pos, int nchunks, int wave_n, int D,
@@ -218,7 +245,7 @@ __device__ __forceinline__ float combine_column_shared_wave(const BwdWs &ws, int
 // motions on bag 0 of table 0 and stores nothing.
 constexpr int kSinglesPerGroup = 4;
 
-template <int G>
+template <int G, bool REUSE>
 __device__ __forceinline__ void segment_sum_body(const SegArgs &a)
 {
     constexpr int kGroups = kSumThreads / G; // lane groups per workgroup
@@ -269,7 +296,7 @@ __device__ __forceinline__ void segment_sum_body(const SegArgs &a)
 #pragma unroll
         for (int k = 0; k < kSinglesPerGroup; ++k) {
             cur[k] = s0 + k < S ? sd[k] : make_int4(0, 0, 0, 0);
-            r[k] = load_once_f4(grad_col + (uint64_t)(unsigned)cur[k].x * tD + (unsigned)cur[k].z * (unsigned)D);
+            r[k] = load_row_f4<REUSE>(grad_col + (uint64_t)(unsigned)cur[k].x * tD + (unsigned)cur[k].z * (unsigned)D);
         }
         const int s_next = s0 + ngroups * kSinglesPerGroup;
 #pragma unroll
@@ -299,7 +326,7 @@ __device__ __forceinline__ void segment_sum_body(const SegArgs &a)
         const int wave_len = __builtin_amdgcn_readfirstlane(wave_max_int(len));
         const int nchunks = desc_nchunks(d), kchunk = desc_kchunk(d);
         const int t = live ? d.w : 0;
-        const float4 acc = sum_chunk<G>(my_bags, len, wave_len, leader, grad_col + (unsigned)t * (unsigned)D, tD);
+        const float4 acc = sum_chunk<G, REUSE>(my_bags, len, wave_len, leader, grad_col + (unsigned)t * (unsigned)D, tD);
         const bool parks = live && nchunks > 1;
         const int head_pos = d.x - kchunk * DQRM_SEG_CHUNK; // sorted position of the segment's head
         if (live && col_ok) {
@@ -327,10 +354,13 @@ __device__ __forceinline__ void segment_sum_body(const SegArgs &a)
                     const int s_head = __builtin_amdgcn_readlane(head_pos, src), s_n = __builtin_amdgcn_readlane(nchunks, src);
                     const int s_seg = __builtin_amdgcn_readlane(d.z, src), s_t = __builtin_amdgcn_readlane(d.w, src);
                     float m = 0.0f;
-                    for (int cc = lane; cc < D; cc += kWave) {
-                        const float sum = combine_column(a.ws, s_head, s_n, D, cc);
-                        a.values[(int64_t)s_seg * D + cc] = sum;
-                        m = fmaxf(m, fabsf(sum));
+                    for (int base = 0; base < D; base += kWave) {
+                        const float sum = combine_columns(a.ws, s_head, s_n, D, base, lane);
+                        const int cc = base + combine_col(lane);
+                        if (cc < D) {
+                            a.values[(int64_t)s_seg * D + cc] = sum;
+                            m = fmaxf(m, fabsf(sum));
+                        }
                     }
                     m = wave_max(m);
                     if (lane == 0) {
@@ -377,10 +407,10 @@ __device__ __forceinline__ void segment_sum_body(const SegArgs &a)
     amax.flush(a.ws.absmax_slots, T);
 }
 
-template <int G>
+template <int G, bool REUSE>
 __global__ __launch_bounds__(kSumThreads, 4) void segment_sum_kernel(SegArgs a)
 {
-    segment_sum_body<G>(a);
+    segment_sum_body<G, REUSE>(a);
 }
 
 // The segment sums of several batches in one launch (blockIdx.y picks the batch): small batches, such as the
@@ -390,10 +420,10 @@ struct SegMulti {
     SegArgs b[DQRM_MAX_DEDUPE_BATCHES];
 };
 
-template <int G>
+template <int G, bool REUSE>
 __global__ __launch_bounds__(kSumThreads, 4) void segment_sum_multi_kernel(SegMulti m)
 {
-    segment_sum_body<G>(m.b[blockIdx.y]);
+    segment_sum_body<G, REUSE>(m.b[blockIdx.y]);
 }
 
 // g_absmax[t] = max over the table's slots

@@ -702,7 +702,6 @@ __device__ __forceinline__ void gemm_planes_tile(const GemmArgs &g, int local, c
 // share rows of A, go to the same one.
 __device__ __forceinline__ int xcd_chunk(int id, int count)
 {
-    constexpr int kXcds = 8;
     const int each = count / kXcds, more = count % kXcds, xcd = id % kXcds;
     return xcd * each + min(xcd, more) + id / kXcds;
 }

@@ -12,6 +12,7 @@
 namespace dqrm {
 
 constexpr int kWave = 64;
+constexpr int kXcds = 8; // parts of the chip; workgroups are dealt to them in turn, each has a second-level cache of its own
 
 // ---- per-device status word ------------------------------------------------
 // Kernels record the first data-dependent problem here (they never act on the
