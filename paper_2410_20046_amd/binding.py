@@ -436,10 +436,13 @@ class StepBuffers:
 
 def dqrm_fwd_bwd_step(tables: Tables, bufs: StepBuffers, indices: torch.Tensor, offsets: torch.Tensor,
                       grad_out: torch.Tensor, lr: float, mode: int = FWD_MASTER, stream=None) -> None:
-    """One pass of the whole hot path: the five per-step C calls in order, on one stream, no host sync."""
+    """One pass of the whole hot path on one stream, no host sync: forward, dedupe, segment sums, INT8 codes and update.
+
+    The last two are dqrm_quant_update: it leaves in ``bufs`` what dqrm_grad_quant_int8 and dqrm_sparse_update do, and folds the
+    maxima too, two launches fewer."""
     dqrm_embbag_fwd(tables, indices, offsets, bufs.B, mode, bufs.out, bufs.codes, stream)
-    dqrm_embbag_bwd(tables, indices, offsets, bufs.B, grad_out, bufs.sorted_pos, bufs.uniq_rows, bufs.seg_offsets,
-                    bufs.table_uniq_offsets, bufs.num_unique, bufs.values, bufs.g_absmax, bufs.workspace, stream)
-    dqrm_grad_quant_int8(bufs.T, bufs.D, bufs.cap, bufs.values, bufs.table_uniq_offsets, bufs.g_absmax, bufs.gq,
-                         bufs.g_scale, stream)
-    dqrm_sparse_update(tables, bufs.cap, bufs.uniq_rows, bufs.table_uniq_offsets, bufs.gq, bufs.g_scale, lr, stream)
+    dqrm_dedupe(tables, indices, offsets, bufs.B, bufs.sorted_pos, bufs.uniq_rows, bufs.seg_offsets,
+                bufs.table_uniq_offsets, bufs.num_unique, bufs.workspace, stream)
+    dqrm_segment_sum(tables, bufs.B, indices.numel(), grad_out, bufs.values, None, bufs.workspace, stream)
+    dqrm_quant_update(tables, bufs.cap, indices.numel(), bufs.values, bufs.uniq_rows, bufs.table_uniq_offsets,
+                      bufs.g_absmax, bufs.gq, bufs.g_scale, lr, bufs.workspace, stream)

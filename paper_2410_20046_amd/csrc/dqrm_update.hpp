@@ -256,9 +256,10 @@ __global__ __launch_bounds__(kEwThreads) void quant_update_kernel(QuantUpdateArg
             const unsigned e = e0 + k * nthreads;
             if (e >= total) continue;
             const Scale gs = L.gs[r[k].t];
-            // the scale comes from the maximum of these very values: no quotient beyond 127 (1 + 2^-23)
-            const int c0 = int8_code_fresh(v[k].x, gs), c1 = int8_code_fresh(v[k].y, gs);
-            const int c2 = int8_code_fresh(v[k].z, gs), c3 = int8_code_fresh(v[k].w, gs);
+            // (the scale comes from the maximum of these very values, but a NaN among them may have made it the least one: the codes
+            // are grad_quant_kernel's then too)
+            const int c0 = int8_code(v[k].x, gs), c1 = int8_code(v[k].y, gs);
+            const int c2 = int8_code(v[k].z, gs), c3 = int8_code(v[k].w, gs);
             reinterpret_cast<unsigned *>(a.gq_out)[e] = pack_bytes(c0, c1, c2, c3);
             if (row[k] < 0) continue;
             const float4 x = sgd_step(w[k], c0, c1, c2, c3, gs.s, a.u.lr);
