@@ -556,17 +556,6 @@ __device__ __forceinline__ void gemm_planes_tile(const GemmArgs &g, int local, c
                         to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[s][p][m], f.b[s][sum - p], to, 0, 0, 0);
                     }
     };
-    // the order of a slab's instructions: the vector unit's between the matrix core's
-    auto interleave = [&]() {
-        constexpr int kProducts = kSteps * 6 * FM, kReads = kSteps * kPlanes * (FM + 1);
-        constexpr int kValu = (a.kItems + b.kItems) * 44 + 8;
-        __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
-#pragma unroll
-        for (int i = 0; i < kProducts; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x2, (kValu + kProducts - 1) / kProducts, 0);
-        }
-    };
     if (slabs > 0) { // (the whole workgroup, or none of it)
         if (tail > 0) {
             a.fetch_tail(0, r_end - tail, r_end, g.a_sr, i0, g.M);
@@ -585,14 +574,12 @@ __device__ __forceinline__ void gemm_planes_tile(const GemmArgs &g, int local, c
             put(1, s + 1, lds1);
             fetch(1, s + 3);
             products(f);
-            interleave();
             __syncthreads();
             if (s + 1 < slabs) {
                 read(f, lds1);
                 put(0, s + 2, lds0);
                 fetch(0, s + 4);
                 products(f);
-                interleave();
                 __syncthreads();
             }
         }
