@@ -1292,7 +1292,8 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
         if (ends_step) sg.loss_terms = F(L.loss_terms), sg.loss = loss, sg.batch = B; // one more block
         hipError_t e = launch_weight_grads(st, wg);
         if (e != hipSuccess && launch_err == hipSuccess) launch_err = e;
-        const unsigned blocks = (unsigned)std::min<long long>((sg.total + 255) / 256, 2048);
+        // (8 workgroups to each of 256 CUs, the one with the loss among them: a 2049th would start when the others end)
+        const unsigned blocks = (unsigned)std::min<long long>((sg.total + 255) / 256, 2047);
         const dim3 last_grid(blocks + (ends_step ? 1u : 0u));
         if (gbits) {
             if (blocks) hipLaunchKernelGGL(dqrm::grad_sum_absmax_kernel, dim3(blocks), dim3(256), 0, st, sg);
@@ -1313,6 +1314,8 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
         dqrm::SgdLayer &s = sg.l[sg.count++];
         s.P = part, s.W = W, s.b = b, s.S = g.splits, s.out = out, s.in = in, s.elem_begin = sg.total;
         s.flat_begin = flat, s.tensor0 = tensor;
+        s.by_cols = dqrm::FastDiv::make((unsigned)in + 1u);
+        if ((long long)out * (in + 1) > 2147483647LL) s.by_cols.d = 0;
         sg.total += (long long)out * (in + 1);
         flat += (long long)out * (in + 1);
         tensor += 2;
