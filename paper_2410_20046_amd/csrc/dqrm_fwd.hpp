@@ -17,7 +17,7 @@
 //      general path instead: the tile's index lists are turned into checked row
 //      offsets in LDS by all threads (one more round trip for the whole tile), then
 //      every bag's rows are requested kFwdBagBatch at a time and added in order
-//      (fwd_bags: groups of other lanes, 16 bytes or 8 codes of a row to a lane).
+//      (packed rows of many bags: by fwd_bags, 8 codes of a row to a lane).
 // The per-column sum is the plain left-to-right sum over the bag, so no
 // cross-lane reduction is needed and the result does not depend on the mapping.
 #pragma once
@@ -113,46 +113,23 @@ __device__ __forceinline__ void fwd_single_lookup_tile(const char *tab, const in
     }
 }
 
-// What a lane takes of a row in fwd_bags: 8 codes of a packed row (4 bytes), 4 floats of a master row.
-template <bool PACKED> struct BagPiece;
-template <> struct BagPiece<true> {
-    static constexpr int kCols = 8;
-    unsigned v;
-    __device__ __forceinline__ void load(const char *p) { v = *reinterpret_cast<const unsigned *>(p); }
-    __device__ __forceinline__ void codes(Scale, float (&q)[kCols]) const
-    {
-#pragma unroll
-        for (int k = 0; k < kCols; ++k) q[k] = (float)(int)__builtin_amdgcn_sbfe((int)v, 4 * k, 4);
-    }
-};
-template <> struct BagPiece<false> {
-    static constexpr int kCols = 4;
-    float4 w;
-    __device__ __forceinline__ void load(const char *p) { w = *reinterpret_cast<const float4 *>(p); }
-    __device__ __forceinline__ void codes(Scale s, float (&q)[kCols]) const
-    {
-        q[0] = (float)int4_code(w.x, s), q[1] = (float)int4_code(w.y, s), q[2] = (float)int4_code(w.z, s), q[3] = (float)int4_code(w.w, s);
-    }
-};
-
-// The bags of a tile whose lookups' row offsets lie in LDS.  A group of lanes walks its bags kFwdBagBatch lookups at a time, the next
+// The bags of packed rows of a tile whose lookups' row offsets lie in LDS.  A group of lanes walks its bags kFwdBagBatch lookups at a time, the next
 // ones (of the same bag or of the next) requested before the present ones are added: what bounds it is the chain of these round
 // trips, 416 bags of a tile over the workgroup's groups.  8 codes to a lane make the groups half as wide and twice as many as for
 // one lookup per bag, where the 16-byte stores decide.  No load is under a branch: a lookup past the bag's end or with a bad index
 // reads row 0 and enters the sum as 0 * q, which leaves the sum as it is.
 // Bags of 0 to 8 lookups, 26 x 8192 x 64, packed: 34.0 -> 23.8 us; bags of 8: 41.4 -> 37.8.
-template <int G, bool PACKED>
+template <int G>
 __device__ __forceinline__ void fwd_bags(const FwdArgs &a, const int64_t *s_loff, const int *s_pos, const int *s_len, const int64_t *s_beg,
                                          const int *s_slot, const Scale *s_scale, int live, int tid)
 {
-    using Piece = BagPiece<PACKED>;
-    constexpr int kCols = Piece::kCols, kLanes = PACKED ? G / 2 : G, kGroups = kFwdThreads / kLanes;
+    constexpr int kCols = 8, kLanes = G / 2, kGroups = kFwdThreads / kLanes;
     const int col = (tid & (kLanes - 1)) * kCols;
     if (col >= a.D) return; // lanes beyond the row
-    const char *tab = PACKED ? reinterpret_cast<const char *>(a.packed) + (col >> 1) : reinterpret_cast<const char *>(a.master + col);
+    const char *tab = reinterpret_cast<const char *>(a.packed) + (col >> 1);
     struct Batch {
         int i, j0, len;
-        Piece piece[kFwdBagBatch];
+        unsigned piece[kFwdBagBatch]; // 8 codes each
         unsigned valid; // bit per lookup
     };
     auto request = [&](Batch &b, int i, int j0) {
@@ -164,19 +141,21 @@ __device__ __forceinline__ void fwd_bags(const FwdArgs &a, const int64_t *s_loff
             const int64_t off = s_loff[max(pos + min(j0 + j, b.len - 1), 0)];
             const bool valid = j0 + j < b.len && off >= 0;
             b.valid |= valid ? 1u << j : 0u;
-            b.piece[j].load(tab + (valid ? off : 0));
+            b.piece[j] = *reinterpret_cast<const unsigned *>(tab + (valid ? off : 0));
         }
     };
     float acc[kCols] = {};
     auto add = [&](const Batch &b) { // and the bag's end
-        const Scale sq = s_scale[b.i];
+        const float s = s_scale[b.i].s;
 #pragma unroll
         for (int j = 0; j < kFwdBagBatch; ++j) {
-            const float m = (b.valid >> j) & 1u ? sq.s : 0.0f;
+            const float m = (b.valid >> j) & 1u ? s : 0.0f;
             float q[kCols];
-            b.piece[j].codes(sq, q);
 #pragma unroll
-            for (int k = 0; k < kCols; ++k) acc[k] = acc[k] + m * q[k];
+            for (int k = 0; k < kCols; ++k) {
+                q[k] = (float)(int)__builtin_amdgcn_sbfe((int)b.piece[j], 4 * k, 4);
+                acc[k] = acc[k] + m * q[k];
+            }
             if (a.codes && (b.valid >> j) & 1u)
 #pragma unroll
                 for (int k = 0; k < kCols; k += 4)
@@ -192,18 +171,21 @@ __device__ __forceinline__ void fwd_bags(const FwdArgs &a, const int64_t *s_loff
             }
         }
     };
-    auto next = [&](Batch &b, const Batch &from) {
-        const bool more = from.j0 + kFwdBagBatch < from.len;
-        request(b, more ? from.i : from.i + kGroups, more ? from.j0 + kFwdBagBatch : 0);
+    // one step: `now` is added while `then`, what comes after it, travels; false if nothing comes after it in the whole wave
+    auto step = [&](const Batch &now, Batch &then) {
+        const bool more = now.j0 + kFwdBagBatch < now.len;
+        const int i = more ? now.i : now.i + kGroups;
+        if (!__any(i < live)) {
+            if (now.i < live) add(now);
+            return false;
+        }
+        request(then, i, more ? now.j0 + kFwdBagBatch : 0);
+        if (now.i < live) add(now);
+        return true;
     };
     Batch x, y;
     request(x, tid / kLanes, 0);
-    while (x.i < live) {
-        next(y, x);
-        add(x);
-        if (y.i >= live) break;
-        next(x, y);
-        add(y);
+    while (step(x, y) && step(y, x)) {
     }
 }
 
@@ -314,8 +296,12 @@ __global__ __launch_bounds__(kFwdThreads) void embbag_fwd_kernel(FwdArgs a)
     }
 
     // ---- phases B and C ------------------------------------------------------------
-    if (staged) {
-        fwd_bags<G, PACKED>(a, s_loff, s_pos, s_len, s_beg, s_slot, s_scale, live, tid);
+    // Packed rows, and several bags to a group: by groups of half as many lanes (fwd_bags).  With one bag or less to a group their lanes
+    // only have twice the work: 16000 bags of 3 lookups x 64, one table, 7.7 us here and 8.6 there; bags of up to 6, 2 tables x 10901 x
+    // 40, 7.9 and 8.0.  Of master rows a lane takes 16 bytes either way, and their codes' arithmetic, not the round trips, takes the
+    // time: 20 tables x 4001 bags of up to 6 lookups x 32 14.8 here, 15.9 with the next rows requested ahead.
+    if (PACKED && staged && live > 2 * (kFwdThreads / G)) {
+        fwd_bags<G>(a, s_loff, s_pos, s_len, s_beg, s_slot, s_scale, live, tid);
         return;
     }
     constexpr int kGroups = kFwdThreads / G; // groups per workgroup
@@ -329,6 +315,39 @@ __global__ __launch_bounds__(kFwdThreads) void embbag_fwd_kernel(FwdArgs a)
 
     if (!general) {
         fwd_single_lookup_tile<G, PACKED>(tab, s_off, s_scale, s_mul, s_slot, grp, out_col, a.D, live);
+        return;
+    }
+
+    if (staged) {
+        // A bag's rows kFwdBagBatch at a time, none under a branch: a lookup past the bag's end or with a bad
+        // index reads row 0 and enters the sum as 0 * q, which leaves the sum as it is.
+        for (int i = grp; i < live; i += kGroups) {
+            const Scale sq = s_scale[i];
+            const int len = s_len[i], pos = s_pos[i];
+            const int64_t beg = s_beg[i];
+            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int j0 = 0; j0 < len; j0 += kFwdBagBatch) {
+                RowPiece<PACKED> piece[kFwdBagBatch];
+                float m[kFwdBagBatch];
+#pragma unroll
+                for (int j = 0; j < kFwdBagBatch; ++j) {
+                    const int64_t off = s_loff[pos + min(j0 + j, len - 1)];
+                    m[j] = (j0 + j < len && off >= 0) ? sq.s : 0.0f;
+                    piece[j].load(tab + (off >= 0 ? off : 0));
+                }
+#pragma unroll
+                for (int j = 0; j < kFwdBagBatch; ++j) {
+                    const float4 q = piece[j].codes(sq);
+                    acc.x = acc.x + m[j] * q.x;
+                    acc.y = acc.y + m[j] * q.y;
+                    acc.z = acc.z + m[j] * q.z;
+                    acc.w = acc.w + m[j] * q.w;
+                    if (a.codes && m[j] != 0.0f) store_codes(a.codes, beg + j0 + j, a.D, col, q);
+                }
+            }
+            const f32x4 v = {acc.x, acc.y, acc.z, acc.w};
+            __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(out_col + (size_t)(unsigned)s_slot[i] * a.D));
+        }
         return;
     }
 
