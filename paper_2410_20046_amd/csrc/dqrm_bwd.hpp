@@ -168,8 +168,9 @@ constexpr int kCombineBatch = 64; // chunk sums of one column requested together
 // The sum of a segment of `nchunks` > 1 chunks, 64 columns of it from `base` on: its parked chunk sums, left to right, by a whole
 // wave; lane l ends with column base + combine_col(l).  A load is 16 bytes a lane, of four chunks' rows (a sixteenth of the lanes
 // each); the four are then turned, so that a lane has one column of all four.  The loads' cache policy is that of a device-scope
-// atomic load, and past the full chunks' end they read zeros.  (4 bytes a lane, 64 loads per trip: a segment of 300 chunks took 20
-// to 30 us beside the others' work, now 9 to 13; the kernel at 26 tables x 8192 lookups of bags of one 24.4 -> 22.2 us.)
+// atomic load.  Those past the last full chunk or the last column read that one again: every address lies in the segment's own
+// rows (the whole offset is in the vector one, the part that the hardware checks).  (4 bytes a lane, 64 loads per trip: a segment of
+// 300 chunks took 20 to 30 us beside the others' work, now 9 to 13; the kernel at 26 tables x 8192 lookups of bags of one 24.4 -> 22.2 us.)
 __device__ __forceinline__ int combine_col(int lane) { return 4 * (lane & 15) + (lane >> 4); }
 
 __device__ __forceinline__ float combine_columns(const BwdWs &ws, int head_pos, int nchunks, int D, int base, int lane)
@@ -182,7 +183,9 @@ __device__ __forceinline__ float combine_columns(const BwdWs &ws, int head_pos, 
     const int64_t slot = (int64_t)(head_pos / DQRM_SEG_CHUNK) * D;
     const float last = __hip_atomic_load(ws.partial_last + slot + min(base + combine_col(lane), D - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(ws.partial_full + slot, 0, full * D * (int)sizeof(float), 0x00020000);
-    const int at = ((lane >> 4) * D + base + 4 * (lane & 15)) * (int)sizeof(float);
+    const int row = D * (int)sizeof(float), col = min(base + 4 * (lane & 15), D - 4) * (int)sizeof(float);
+    int at = (lane >> 4) * row + col;
+    const int at_last = (full - 1) * row + col;
     float acc = 0.f;
     for (int k0 = 0; k0 < full; k0 += kCombineBatch) {
         u32x4 v[kLoads];
@@ -190,8 +193,11 @@ __device__ __forceinline__ float combine_columns(const BwdWs &ws, int head_pos, 
         for (int q0 = 0; q0 < kLoads; q0 += 4)
             if (q0 == 0 || k0 + 4 * q0 < full) // (wave-uniform)
 #pragma unroll
-                for (int q = q0; q < q0 + 4; ++q)
-                    v[q] = __builtin_amdgcn_raw_buffer_load_b128(rows, at, (k0 + 4 * q) * D * (int)sizeof(float), kAgentScope);
+                for (int q = q0; q < q0 + 4; ++q) {
+                    v[q] = __builtin_amdgcn_raw_buffer_load_b128(rows, min(at, at_last), 0, kAgentScope);
+                    at += 4 * row;
+                    asm volatile("" : "+v"(at)); // (one offset, not 16 in as many registers)
+                }
 #pragma unroll
         for (int q = 0; q < kLoads; ++q) {
             if (k0 + 4 * q < full) {

@@ -53,3 +53,25 @@ def test_segments_of_many_chunks(oracle, D):
     assert_exact(got["values"][:U].view(np.uint32), o["values"][:U].view(np.uint32), "values bits")
     assert_exact(got["g_absmax"].view(np.uint32), o["g_absmax"].view(np.uint32), "absmax bits")
     assert run.status()[0] == 0
+
+
+# Segments of 2 .. 5 chunks that are the whole batch: one full chunk and a last one, up to more than one load of four, in a workspace
+# of exactly the size asked for.  What lies behind it is NaN and stays as it is.
+@pytest.mark.parametrize("n", [33, 64, 65, 128, 129, 160])
+@pytest.mark.parametrize("D", [40, 64, 72, 256])
+def test_one_segment_in_a_workspace_of_the_size_asked_for(oracle, D, n):
+    import torch
+
+    row_offsets, off = np.array([0, 1], np.int64), np.arange(n + 1, dtype=np.int64)
+    g = (np.random.default_rng(n).standard_normal((n, 1, D)) * 1e-4).astype(np.float32)
+    run = GpuRun(row_offsets, D, np.zeros((1, D), np.float32), n, n)
+    run.upload_batch(np.zeros(n, np.int64), off, g)
+    size = run.bufs.workspace.numel()
+    room = torch.full((size + 32768,), 0xFF, dtype=torch.uint8, device=run.dev)
+    run.bufs.workspace = room[:size]
+    got, o = run.bwd(), oracle.embbag_bwd(1, D, n, np.zeros(n, np.int64), off, g)
+    assert got["U"] == 1
+    assert_exact(got["values"][:1].view(np.uint32), o["values"][:1].view(np.uint32), "values bits")
+    assert_exact(got["g_absmax"].view(np.uint32), o["g_absmax"].view(np.uint32), "absmax bits")
+    assert bool((room[size:] == 0xFF).all())
+    assert run.status()[0] == 0
