@@ -340,7 +340,9 @@ int32_t dqrm_quant_update(const dqrm_tables_t *tables, int64_t capacity, int64_t
  * per MLP.
  *   dense_x [batch][num_dense], emb_out [batch][T][dim] (= `out` of
  *   dqrm_embbag_fwd), labels [batch] (0 or 1, as floats)  -> loss [1] (device),
- *   grad_emb [batch][T][dim] (= `grad_out` of dqrm_embbag_bwd). */
+ *   grad_emb [batch][T][dim] (= `grad_out` of dqrm_embbag_bwd).
+ * A workspace of dqrm_dense_workspace_bytes(model, batch) is enough for `batch`
+ * samples and for any smaller number (the last batch of an epoch). */
 typedef struct {
     int32_t num_dense;         /* dense features per sample (13) */
     int32_t num_tables;        /* T */

@@ -967,6 +967,17 @@ DenseLayout dense_layout(const dqrm_dense_model_t *m, int32_t batch)
     return L;
 }
 
+// A workspace for `batch` samples is enough for fewer as well, the last batch of an epoch for instance: fewer samples may be cut into
+// more slices (a slab less makes another cut the best one), so this is the most that any number of samples up to `batch`
+// takes.  The cut depends on their number of slabs only, and at most 512 of those are allowed (8192 samples: 0.1 ms on the host).
+size_t dense_workspace(const dqrm_dense_model_t *m, int32_t batch)
+{
+    size_t most = 0;
+    for (int64_t b = GradCut::kSlab; b < batch + GradCut::kSlab; b += GradCut::kSlab)
+        most = std::max(most, dense_layout(m, (int32_t)std::min<int64_t>(b, batch)).total);
+    return most;
+}
+
 // The tile of a layer's product by planes of bfloat16, or 0: by the fp32 matrix instructions.  Those are left where a wave's 32x32
 // tile can have its reduction shared by four waves on otherwise idle SIMDs, and that is long: 512 samples, 512 -> 512, us, fp32 /
 // planes: reduction 256: 7.1 / 6.7, 384: 8.2 / 8.1, 512: 8.4 / 9.5; input gradients (B read along j) 256: 7.2 / 7.6, 200: 11.4 / 9.0.
@@ -1133,7 +1144,7 @@ extern "C" {
 size_t dqrm_dense_workspace_bytes(const dqrm_dense_model_t *model, int32_t batch)
 {
     if (check_dense_model(model, batch) != DQRM_OK) return 0;
-    return dense_layout(model, batch).total;
+    return dense_workspace(model, batch);
 }
 
 int64_t dqrm_dense_param_count(const dqrm_dense_model_t *model)

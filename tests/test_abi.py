@@ -210,6 +210,25 @@ def test_validation_errors_before_any_launch():
     assert f(26, 64, 9, 10) == 0 and f(26, 12, 2, 10) == 0 and f(0, 16, 2, 10) == 0 and f(2, 16, 2, -1) == 0
 
 
+def test_dense_workspace_for_a_batch_holds_smaller_ones():
+    """Sized for the batches of an epoch, the workspace takes the last, smaller one too, whatever slices its products are cut into."""
+    def model(T, D, bot, top):
+        bot, top = bot + [D], [D + (T + 1) * T // 2] + top + [1]
+        w = lambda d: [np.zeros((o, i), np.float32) for i, o in zip(d[:-1], d[1:])]  # noqa: E731
+        b = lambda d: [np.zeros(o, np.float32) for o in d[1:]]  # noqa: E731
+        return dq.DenseModel(T, D, bot, w(bot), b(bot), top, w(top), b(top), "cpu")
+
+    rng = np.random.default_rng(1)
+    models = [model(25, 16, [7, 172, 52, 420], [256])] + [
+        model(int(rng.integers(1, 30)), 16, [13] + [int(w) for w in rng.integers(16, 520, rng.integers(1, 4))],
+              [int(w) for w in rng.integers(16, 520, rng.integers(1, 4))]) for _ in range(20)]
+    for m in models:
+        sizes = [dq.dqrm_dense_workspace_bytes(m, b) for b in list(range(64, 8193, 64)) + [8200, 16384, 32766]]
+        assert 0 < sizes[0] and all(x <= y for x, y in zip(sizes[:-1], sizes[1:]))
+        assert dq.dqrm_dense_workspace_bytes(m, 4026) <= dq.dqrm_dense_workspace_bytes(m, 4096)
+        assert dq.dqrm_dense_workspace_bytes(m, 32768) == 0
+
+
 def test_product_never_touches_the_oracle():
     """the HIP path and its binding share nothing with oracle/: no import, include, link or path."""
     pkg = os.path.join(ROOT, "paper_2410_20046_amd")
