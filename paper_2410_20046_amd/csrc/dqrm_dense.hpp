@@ -355,8 +355,11 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int local, boo
 // is bound by the 5.5 cycles that each of its instructions takes to issue: their splitting and LDS traffic goes out beside the
 // other's products.
 //
-// Not finite: an infinity's planes are infinity and NaN, and a float next to the largest rounds up to one.  A lane that ends
-// with a sum that is not finite adds its outputs up again in plain fp32, so that infinities and NaN come out as they do there.
+// Not finite: an infinity's planes are infinity and NaN, and a float next to the largest rounds up to one.  A wave with a sum that is
+// not finite adds its part of the tile up again in plain fp32, on the fp32 matrix instructions with operands straight from memory,
+// and the lanes concerned take that, so that infinities and NaN come out as they do there.  It costs only what has them: one sample, its tiles; a
+// model that has diverged altogether, the dense step of the Terabyte shape, 8192 samples, all NaN: 768 us (finite: 366); every such lane by
+// itself, a float at a time: 2389; the fp32 matrix instructions alone: 636.
 typedef __bf16 Bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 Bf16x8 __attribute__((ext_vector_type(8)));
 typedef float Float2 __attribute__((ext_vector_type(2)));
@@ -595,23 +598,48 @@ __device__ __forceinline__ void gemm_planes_tile(const GemmArgs &g, int local, c
             acc[m][v] += rest[m][v];
             finite = __builtin_fmaf(acc[m][v], 0.0f, finite);
         }
-    if (__builtin_expect(finite != 0.0f, 0)) { // (NaN)
+    if (__builtin_expect(__any(finite != 0.0f), 0)) { // (NaN: the whole wave's part again, and the lanes concerned take it)
 #pragma unroll
         for (int m = 0; m < FM; ++m)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[m][v] = 0.0f;
+            for (int v = 0; v < 16; ++v) rest[m][v] = 0.0f;
+        const float *pb = g.B + (long long)min(j0 + j_lane, g.N - 1) * g.b_sj;
+        const float *pa[FM];
+#pragma unroll
+        for (int m = 0; m < FM; ++m) pa[m] = g.A + (long long)min(i0 + 32 * (FM * wm + m) + w, g.M - 1) * g.a_si;
+        constexpr int kPart = BK / KH;
 #pragma unroll 1
-        for (int r = r_begin; r < r_end; ++r) {
-            if ((r - r_begin) % BK / (BK / KH) != kh) continue;
-            const float bv = g.B[(long long)min(j0 + j_lane, g.N - 1) * g.b_sj + r * g.b_sr];
+        for (int r0 = r_begin + kPart * kh; r0 < r_end; r0 += BK) { // the wave's part of each slab
+            // lane (h, w): r0 + h kPart / 2 .. of its row and its column, 0 past the end
+            float av[FM][kPart / 2], bv[kPart / 2];
+            auto load = [&](float *to, const float *p, long long line, bool along_r) {
+                const int r1 = r0 + kPart / 2 * h;
+                if (along_r && r0 + kPart <= r_end) {
 #pragma unroll
-            for (int m = 0; m < FM; ++m)
+                    for (int k = 0; k < kPart / 2; k += 4) {
+                        const Float4Dw t = *reinterpret_cast<const Float4Dw *>(p + r1 + k);
+                        to[k] = t[0], to[k + 1] = t[1], to[k + 2] = t[2], to[k + 3] = t[3];
+                    }
+                } else {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int i = i0 + i_lane + 32 * m + 8 * (v >> 2) + (v & 3);
-                    acc[m][v] = __builtin_fmaf(g.A[(long long)min(i, g.M - 1) * g.a_si + r * g.a_sr], bv, acc[m][v]);
+                    for (int k = 0; k < kPart / 2; ++k) {
+                        const float t = p[min(r1 + k, r_end - 1) * line];
+                        to[k] = r1 + k < r_end ? t : 0.0f;
+                    }
                 }
+            };
+            load(bv, pb, g.b_sr, B_MODE == kOpRC);
+#pragma unroll
+            for (int m = 0; m < FM; ++m) load(av[m], pa[m], g.a_sr, A_MODE == kOpRC);
+#pragma unroll
+            for (int k = 0; k < kPart / 2; ++k)
+#pragma unroll
+                for (int m = 0; m < FM; ++m) rest[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[m][k], bv[k], rest[m], 0, 0, 0);
         }
+#pragma unroll
+        for (int m = 0; m < FM; ++m)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[m][v] = finite != 0.0f ? rest[m][v] : acc[m][v];
     }
 
     // The tile goes through LDS: 16 bytes to a thread, and a loop of little code (a launch fetches every line of its code anew).
