@@ -986,7 +986,7 @@ size_t dense_workspace(const dqrm_dense_model_t *m, int32_t batch)
 // 13.8 / 10.8.
 int plane_tile(const dqrm::GemmArgs &g, bool b_wide)
 {
-    if (!b_wide && g.K < 8) return 0; // (as much of a row is read at a time)
+    if (g.K < 8 && (!b_wide || (int64_t)g.M * g.K < 8)) return 0; // (an operand with its rows along r is read 8 floats at a time)
     const int64_t cus = num_cus(), tiles32 = (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32);
     if (tiles32 <= cus && g.K >= (b_wide ? 256 : 384)) return 0;
     auto us = [&](int bm, int bn, int each) { return (((int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) + cus - 1) / cus) * each; };

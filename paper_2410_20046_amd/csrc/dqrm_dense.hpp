@@ -400,6 +400,7 @@ struct PlaneOperand {
     static constexpr int kGroups = BK / 8, kItems = ROWS * kGroups / kPlaneThreads;
     static constexpr int kRowsPerItem = kPlaneThreads / kGroups, kGroupsPerItem = kPlaneThreads / ROWS; // kOpRC; kOpWide
     const float *tile;     // the tile's first wide index, r = 0 (wave-uniform)
+    const float *slabs;    // where fetch() starts from: there, or where the operand starts
     long long sr;          // kOpWide: between lines
     // kOpRC: of the items' rows; kOpWide: of the first item's lines (kept, as adding a line's length 8 times costs two instructions
     // beside each load)
@@ -408,13 +409,14 @@ struct PlaneOperand {
     float v[2][kItems][8]; // two slabs on their way
 
     // `first`: the tile's first wide index; those past `count` re-read the last.  `whole`: the reduction has a whole slab; otherwise
-    // fetch() reads some 8 floats of the operand instead (kOpRC: the reduction has as many: host).
+    // nobody looks at what fetch() reads, and it reads the operand's first 8 floats (kOpRC; it has as many: host) or its first line.
     __device__ __forceinline__ void init(const float *base, long long sw, long long sr_, int first, int count, bool whole, int tid)
     {
         if (MODE == kOpRC) {
             sr = sw;
             row = tid / kGroups, kg = tid % kGroups;
             tile = base + (long long)first * sw;
+            slabs = whole ? tile : base;
 #pragma unroll
             for (int c = 0; c < kItems; ++c) {
                 off[c] = (unsigned)(min(first + row + c * kRowsPerItem, count - 1) - first) * (unsigned)sw + 8u * kg;
@@ -423,7 +425,7 @@ struct PlaneOperand {
         } else {
             sr = whole ? sr_ : 0;
             row = tid % ROWS, kg = tid / ROWS;
-            tile = base + first;
+            tile = slabs = base + first;
 #pragma unroll
             for (int k = 0; k < 8; ++k) off[k] = (8u * kg + k) * (unsigned)sr + min(row, count - 1 - first);
         }
@@ -434,12 +436,12 @@ struct PlaneOperand {
 #pragma unroll
         for (int c = 0; c < kItems; ++c) {
             if (MODE == kOpRC) {
-                const float *p = tile + r0 + off[c];
+                const float *p = slabs + r0 + off[c];
                 const Float4Dw lo = *reinterpret_cast<const Float4Dw *>(p), hi = *reinterpret_cast<const Float4Dw *>(p + 4);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) v[q][c][k] = lo[k], v[q][c][4 + k] = hi[k];
             } else {
-                const float *p = tile + (long long)(r0 + 8 * c * kGroupsPerItem) * sr;
+                const float *p = slabs + (long long)(r0 + 8 * c * kGroupsPerItem) * sr;
 #pragma unroll
                 for (int k = 0; k < 8; ++k) v[q][c][k] = p[off[k]];
             }
