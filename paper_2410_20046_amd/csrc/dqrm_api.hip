@@ -995,9 +995,9 @@ int plane_tile(const dqrm::GemmArgs &g, bool b_wide)
     return us128x64 < us64 ? 12864 : 64;
 }
 
-// A_MODE / B_MODE: how A / B lie in memory and are read (dqrm::kOpRC: the reduction index is the unit-stride one;
-// kOpWide: the 32-wide index i / j is).
-template <int A_MODE, int B_MODE>
+// A: the reduction index is the unit-stride one.  B_MODE: how B lies in memory and is read (dqrm::kOpRC: likewise; kOpWide: its
+// column index j is).
+template <int B_MODE>
 hipError_t launch_gemm(hipStream_t st, const dqrm::GemmArgs &g)
 {
     const int t = plane_tile(g, B_MODE == dqrm::kOpWide);
@@ -1005,11 +1005,11 @@ hipError_t launch_gemm(hipStream_t st, const dqrm::GemmArgs &g)
         const int bm = t == 64 ? 64 : 128, bn = t == 128 ? 128 : 64;
         const dim3 grid(((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn)), block(dqrm::kPlaneThreads);
         if (t == 128)
-            hipLaunchKernelGGL((dqrm::gemm_planes_kernel<dqrm::PlaneTile128, A_MODE, B_MODE>), grid, block, 0, st, g);
+            hipLaunchKernelGGL((dqrm::gemm_planes_kernel<dqrm::PlaneTile128, B_MODE>), grid, block, 0, st, g);
         else if (t == 64)
-            hipLaunchKernelGGL((dqrm::gemm_planes_kernel<dqrm::PlaneTile64, A_MODE, B_MODE>), grid, block, 0, st, g);
+            hipLaunchKernelGGL((dqrm::gemm_planes_kernel<dqrm::PlaneTile64, B_MODE>), grid, block, 0, st, g);
         else
-            hipLaunchKernelGGL((dqrm::gemm_planes_kernel<dqrm::PlaneTile128x64, A_MODE, B_MODE>), grid, block, 0, st, g);
+            hipLaunchKernelGGL((dqrm::gemm_planes_kernel<dqrm::PlaneTile128x64, B_MODE>), grid, block, 0, st, g);
         return hipGetLastError();
     }
     dqrm::GemmOne one;
@@ -1022,7 +1022,7 @@ hipError_t launch_gemm(hipStream_t st, const dqrm::GemmArgs &g)
     one.kslices = 1;
     while (one.kslices < 4 && one.total_tiles * one.kslices * 2 <= simds && pairs >= one.kslices * 2) one.kslices *= 2;
     const int waves = one.total_tiles * one.kslices;
-    hipLaunchKernelGGL((dqrm::gemm_wave_kernel<A_MODE, B_MODE>), dim3((waves + dqrm::kGemmWaves - 1) / dqrm::kGemmWaves),
+    hipLaunchKernelGGL((dqrm::gemm_wave_kernel<B_MODE>), dim3((waves + dqrm::kGemmWaves - 1) / dqrm::kGemmWaves),
                        dim3(dqrm::kGemmThreads), 0, st, one);
     return hipGetLastError();
 }
@@ -1057,10 +1057,10 @@ hipError_t linear_fwd(hipStream_t st, const float *X, const float *W, const floa
     dqrm::GemmArgs g{};
     g.A = X, g.a_si = in, g.a_sr = 1;
     g.B = W, g.b_sr = 1, g.b_sj = in;
-    g.C = Y, g.c_si = out, g.c_sj = 1;
+    g.C = Y, g.c_si = out;
     g.M = B, g.N = out, g.K = in;
     g.bias = b, g.relu = relu ? 1 : 0;
-    return launch_gemm<dqrm::kOpRC, dqrm::kOpRC>(st, g);
+    return launch_gemm<dqrm::kOpRC>(st, g);
 }
 
 // dX[B][in] = (dZ[B][out] * W[out][in]) masked by (mask[B][in] > 0)
@@ -1070,10 +1070,10 @@ hipError_t linear_bwd_input(hipStream_t st, const float *dZ, const float *W, con
     dqrm::GemmArgs g{};
     g.A = dZ, g.a_si = out, g.a_sr = 1;
     g.B = W, g.b_sr = in, g.b_sj = 1;
-    g.C = dX, g.c_si = in, g.c_sj = 1;
+    g.C = dX, g.c_si = in;
     g.M = B, g.N = in, g.K = out;
     g.mask = mask;
-    return launch_gemm<dqrm::kOpRC, dqrm::kOpWide>(st, g);
+    return launch_gemm<dqrm::kOpWide>(st, g);
 }
 
 // Whether the interaction of V vectors of D floats goes by the plain kernels: where it would fill only a little of the 32x32 tiles
@@ -1303,8 +1303,8 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
         if (ends_step) sg.loss_terms = F(L.loss_terms), sg.loss = loss, sg.batch = B; // one more block
         hipError_t e = launch_weight_grads(st, wg);
         if (e != hipSuccess && launch_err == hipSuccess) launch_err = e;
-        // (8 workgroups to each of 256 CUs, the one with the loss among them: a 2049th would start when the others end)
-        const unsigned blocks = (unsigned)std::min<long long>((sg.total + 255) / 256, 2047);
+        // (8 workgroups to each CU, the one with the loss among them: one more would start when the others end)
+        const unsigned blocks = (unsigned)std::min<long long>((sg.total + 255) / 256, num_cus() * 8 - 1);
         const dim3 last_grid(blocks + (ends_step ? 1u : 0u));
         if (gbits) {
             if (blocks) hipLaunchKernelGGL(dqrm::grad_sum_absmax_kernel, dim3(blocks), dim3(256), 0, st, sg);

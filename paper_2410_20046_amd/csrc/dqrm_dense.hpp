@@ -4,7 +4,7 @@
 // weights.  FP32 throughout (the paper's "MLP in FP32" variant): the matrix
 // products of long reductions over few tiles and the interaction run on the fp32
 // matrix instructions, all others on the bfloat16 ones with their operands as
-// exact sums of three bfloat16 (gemm_planes_tile), to a smaller error.
+// sums of three bfloat16 (gemm_planes_tile).
 #pragma once
 
 #include "dqrm_device.hpp"
@@ -27,9 +27,9 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // multiplied.
 //
 // How an operand's slab reaches the register layout depends on its memory layout
-// (the kOp* forms below): read along its unit-stride index with 16-byte loads and
-// passed through a per-wave piece of LDS, or, when the 32-wide index is the
-// unit-stride one, also with 4-byte loads straight into place.  Nothing assumes
+// (the kOp* forms below; A's is kOpRC): read along its unit-stride index with 16-byte
+// loads and passed through a per-wave piece of LDS, or, when the 32-wide index is
+// the unit-stride one, also with 4-byte loads straight into place.  Nothing assumes
 // an alignment beyond 4 bytes.  No load sits under a branch: indices past the
 // edge are clamped and the value is replaced by 0.
 //
@@ -43,8 +43,8 @@ struct GemmArgs {
     long long a_si, a_sr;
     const float *B;
     long long b_sr, b_sj;
-    float *C;
-    long long c_si, c_sj;
+    float *C; // C(i, j) at C[i * c_si + j]
+    long long c_si;
     int M, N, K;
     const float *bias; // [N] added per column j, or null
     const float *mask; // same addressing as C: result multiplied by (mask > 0), or null
@@ -181,11 +181,11 @@ constexpr int kGemmTurnFloats = 32 * kGemmPitch;
 constexpr int kGemmLdsFloats = kGemmWaves * 2 * kGemmTurnFloats;
 
 // the tile `local` (and, with ks > 1, the slice wave % ks of its reduction) of problem g, by one wave
-template <int A_MODE, int B_MODE>
+template <int B_MODE>
 __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int local, bool live, int ks, int wave, int lane,
                                                float *lds_all)
 {
-    constexpr bool A_RC = A_MODE == kOpRC, B_RC = B_MODE == kOpRC;
+    constexpr bool B_RC = B_MODE == kOpRC;
     const int kz = wave & (ks - 1);
     const int tiles_j = (g.N + 31) / 32;
     const int i_first = (local / tiles_j) * 32, j_first = (local % tiles_j) * 32; // first row / column this tile stores
@@ -201,16 +201,16 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int local, boo
     // and those results are not stored.
     const int i0 = (i_first + 32 > g.M && g.M >= 32) ? g.M - 32 : i_first;
     const int j0 = (j_first + 32 > g.N && g.N >= 32) ? g.N - 32 : j_first;
-    // whole slabs can be read the fast way (kOpWide: only if the tile's 32 rows / columns all exist)
-    const bool whole = (A_RC || i0 + 32 <= g.M) && (B_RC || j0 + 32 <= g.N);
-    const int ia = min(i0 + w, g.M - 1), jb = min(j0 + w, g.N - 1);
+    // whole slabs can be read the fast way (kOpWide: only if the tile's 32 columns all exist)
+    const bool whole = B_RC || j0 + 32 <= g.N;
+    const int jb = min(j0 + w, g.N - 1);
     float *lds_a = lds_all + wave * 2 * kGemmTurnFloats, *lds_b = lds_a + kGemmTurnFloats;
     // (requested now, used in the epilogue)
     const float bias_j = g.bias ? g.bias[min(j0 + w, g.N - 1)] : 0.0f;
     // ... and so is the mask of this lane's 16 outputs (rows and columns past the edge re-read the last ones)
     float mask_v[16];
     if (g.mask) {
-        const long long mj = (long long)min(j0 + w, g.N - 1) * g.c_sj;
+        const int mj = min(j0 + w, g.N - 1);
 #pragma unroll
         for (int v = 0; v < 16; ++v)
             mask_v[v] = g.mask[(long long)min(i0 + 8 * (v >> 2) + 4 * h + (v & 3), g.M - 1) * g.c_si + mj];
@@ -227,28 +227,22 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int local, boo
     // comes from memory, a / b hold the current slab in product layout.
     SlabRegs a, b, sa[2], sb[2];
     auto fetch_safe = [&](int q, int r0) {
-        if (A_RC)
-            slab_load_along_r(sa[q], g.A, g.a_si, i0, g.M, r0, r_end, lane);
-        else
-            slab_load_direct(sa[q], g.A, g.a_sr, ia, r0, r_end, h);
+        slab_load_along_r(sa[q], g.A, g.a_si, i0, g.M, r0, r_end, lane);
         if (B_RC)
             slab_load_along_r(sb[q], g.B, g.b_sj, j0, g.N, r0, r_end, lane);
         else
             slab_load_direct(sb[q], g.B, g.b_sr, jb, r0, r_end, h);
     };
     auto fetch_fast = [&](int q, int r0) { // whole tile, whole slab
-        slab_fetch_fast<A_MODE>(sa[q], g.A, g.a_si, g.a_sr, i0, g.M, r0, lane);
+        slab_fetch_fast<kOpRC>(sa[q], g.A, g.a_si, g.a_sr, i0, g.M, r0, lane);
         slab_fetch_fast<B_MODE>(sb[q], g.B, g.b_sj, g.b_sr, j0, g.N, r0, lane);
     };
     auto settle_fast = [&](int q) {
-        slab_settle_fast<A_MODE>(a, sa[q], lds_a, lane);
+        slab_settle_fast<kOpRC>(a, sa[q], lds_a, lane);
         slab_settle_fast<B_MODE>(b, sb[q], lds_b, lane);
     };
     auto settle = [&](int q) { // staging registers of the clamped path -> product layout
-        if (A_RC)
-            slab_turn(a, sa[q], lds_a, lane);
-        else
-            a = sa[q];
+        slab_turn(a, sa[q], lds_a, lane);
         if (B_RC)
             slab_turn(b, sb[q], lds_b, lane);
         else
@@ -281,13 +275,13 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int local, boo
             const int rn = min(r0 + 2 * kGemmBK, r_last);
             fetch_fast(0, rn);
             __builtin_amdgcn_sched_barrier(0);
-            slab_settle_fast<A_MODE>(a2, sa[1], lds_a, lane);
+            slab_settle_fast<kOpRC>(a2, sa[1], lds_a, lane);
             slab_settle_fast<B_MODE>(b2, sb[1], lds_b, lane);
             products();
             __builtin_amdgcn_sched_barrier(0);
             fetch_fast(1, rn + kGemmBK);
             __builtin_amdgcn_sched_barrier(0);
-            slab_settle_fast<A_MODE>(a, sa[0], lds_a, lane);
+            slab_settle_fast<kOpRC>(a, sa[0], lds_a, lane);
             slab_settle_fast<B_MODE>(b, sb[0], lds_b, lane);
 #pragma unroll
             for (int s = 0; s < 16; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a2.v[s], b2.v[s], acc, 0, 0, 0);
@@ -335,19 +329,20 @@ __device__ __forceinline__ void gemm_wave_tile(const GemmArgs &g, int local, boo
         if (i < i_first || i >= g.M) continue;
         float x = acc[v] + bj;
         if (g.relu) x = fmaxf(x, 0.0f);
-        const long long off = (long long)i * g.c_si + (long long)j * g.c_sj;
+        const long long off = (long long)i * g.c_si + j;
         x = mask_v[v] > 0.0f ? x : 0.0f;
         g.C[off] = x;
     }
 }
 
 // ---- products of many tiles: three bfloat16 planes per operand ---------------------------------------------------
-// The fp32 matrix instructions run at a sixteenth of the bfloat16 ones' rate.  A float is exactly the sum of a bfloat16, the
-// bfloat16 nearest to what that leaves, and a third one's rest (three planes of 8 significant bits each): of the nine
-// products of two such sums the six that exceed 2^-26 are taken, each exact, and added up in fp32 by the matrix cores,
-// 16 of the reduction at a time: 6 x 32 matrix-core cycles for what takes 8 x 64 in fp32.  The products of the first planes have
-// an accumulator of their own, which is rounded once per 16 of the reduction, so that the error against 64 bits is a third of
-// what the fp32 instructions' is (8192x512x512: 1.3e-7 and 4.05e-7 of the 2-norm).
+// The fp32 matrix instructions run at a sixteenth of the bfloat16 ones' rate.  A float of 2^-103 or more is exactly the sum of a
+// bfloat16, the bfloat16 nearest to what that leaves, and a third one's rest (three planes of 8 significant bits each; of smaller floats
+// the third plane may be subnormal or nothing).  Of the nine products of two such sums the six largest are taken, each exact, and
+// added up in fp32 by the matrix cores, 16 of the reduction at a time: 6 x 32 matrix-core cycles for what takes 8 x 64 in fp32.  The
+// three left out are 2^-24 of a product at most, half a rounding of fp32, and far less on average.  The products of the first
+// planes have an accumulator of their own, which is rounded once per 16 of the reduction: measured on normal random data, the
+// error against 64 bits is a third of what the fp32 instructions' is (8192x512x512: 1.3e-7 and 4.05e-7 of the 2-norm).
 //
 // A workgroup of 8 waves has a tile of BM x BN; the reduction goes by slabs of BK.  The threads read a slab as floats (two slabs
 // ahead), split them once for the whole workgroup and leave the planes in LDS, 8 consecutive r of a row to a 16-byte
@@ -723,12 +718,12 @@ __device__ __forceinline__ int xcd_chunk(int id, int count)
     return xcd * each + min(xcd, more) + id / kXcds;
 }
 
-template <typename TILE, int A_MODE, int B_MODE>
+template <typename TILE, int B_MODE>
 __global__ __launch_bounds__(kPlaneThreads) void gemm_planes_kernel(GemmArgs g)
 {
     // (two arrays: the compiler knows that what is read from one is not what is written to the other)
     __shared__ __align__(16) char lds0[TILE::kSlabBytes], lds1[TILE::kSlabBytes];
-    gemm_planes_tile<TILE, A_MODE, B_MODE, false>(g, xcd_chunk((int)blockIdx.x, (int)gridDim.x), lds0, lds1);
+    gemm_planes_tile<TILE, kOpRC, B_MODE, false>(g, xcd_chunk((int)blockIdx.x, (int)gridDim.x), lds0, lds1);
 }
 
 // With kslices > 1 the waves of a workgroup meet at a barrier inside: a wave past the last tile stays, takes the
@@ -739,7 +734,7 @@ struct GemmOne {
 };
 
 // one product per launch
-template <int A_MODE, int B_MODE>
+template <int B_MODE>
 __global__ __launch_bounds__(kGemmThreads) void gemm_wave_kernel(GemmOne one)
 {
     __shared__ __align__(16) float lds[kGemmLdsFloats];
@@ -749,7 +744,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_wave_kernel(GemmOne one)
     const int tile = ((int)blockIdx.x * kGemmWaves + wave) / ks;
     const bool live = tile < one.total_tiles;
     if (!live && ks == 1) return;
-    gemm_wave_tile<A_MODE, B_MODE>(one.p, min(tile, one.total_tiles - 1), live, ks, wave, lane, lds);
+    gemm_wave_tile<B_MODE>(one.p, min(tile, one.total_tiles - 1), live, ks, wave, lane, lds);
 }
 
 // Several split products in one launch (kOpWide operands): the weight gradients of all layers, a workgroup per tile.
