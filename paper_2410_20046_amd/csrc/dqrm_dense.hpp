@@ -748,7 +748,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_wave_kernel(GemmOne one)
 }
 
 // Several split products in one launch (kOpWide operands): the weight gradients of all layers, a workgroup per tile.
-// Measured: the Terabyte shape's layers at batch 8192 (12.4 GFLOP) 98 us, the Kaggle shape's at 2048 (1.96 GFLOP) 25; on the
+// Measured: the Terabyte shape's layers at batch 8192 (12.4 GFLOP) 99 us, the Kaggle shape's at 2048 (1.96 GFLOP) 23; on the
 // fp32 matrix instructions 171 and 34.5.
 __global__ __launch_bounds__(kPlaneThreads) void gemm_split_group_kernel(GemmGroup grp)
 {

@@ -118,7 +118,7 @@ __device__ __forceinline__ void fwd_single_lookup_tile(const char *tab, const in
 // trips, 416 bags of a tile over the workgroup's groups.  8 codes to a lane make the groups half as wide and twice as many as for
 // one lookup per bag, where the 16-byte stores decide.  No load is under a branch: a lookup past the bag's end or with a bad index
 // reads row 0 and enters the sum as 0 * q, which leaves the sum as it is.
-// Bags of 0 to 8 lookups, 26 x 8192 x 64, packed: 34.0 -> 23.8 us; bags of 8: 41.4 -> 37.8.
+// Bags of 0 to 8 lookups, 26 x 8192 x 64, packed: 34.0 -> 24 us in a kernel trace (a pass among others 31.6 -> 22.9); bags of 8: 41.4 -> 38.
 template <int G>
 __device__ __forceinline__ void fwd_bags(const FwdArgs &a, const int64_t *s_loff, const int *s_pos, const int *s_len, const int64_t *s_beg,
                                          const int *s_slot, const Scale *s_scale, int live, int tid)
