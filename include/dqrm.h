@@ -323,6 +323,17 @@ int32_t dqrm_quant_update(const dqrm_tables_t *tables, int64_t capacity, int64_t
                           const int64_t *uniq_rows, const int32_t *table_uniq_offsets, float *g_absmax, int8_t *gq,
                           float *g_scale, float lr, void *workspace, size_t workspace_bytes, void *stream);
 
+/* One step of the tables on one GPU: dqrm_embbag_fwd, dqrm_dedupe, dqrm_segment_sum
+ * and dqrm_quant_update, with their arguments and, bit for bit, their outputs, for a
+ * caller who has grad_out beforehand and exchanges nothing in between.  In one call
+ * the forward shares a launch with the sort, and the rest is one launch for batches
+ * of few lookups per table.  (Of several problems in a batch any one is recorded.) */
+int32_t dqrm_fwd_bwd_step(const dqrm_tables_t *tables, const int64_t *indices, const int64_t *offsets, int32_t batch,
+                          int64_t num_indices, int32_t mode, float *out, int8_t *codes_dbg, const float *grad_out, float lr,
+                          int64_t capacity, int32_t *sorted_pos, int64_t *uniq_rows, int32_t *seg_offsets,
+                          int32_t *table_uniq_offsets, int32_t *num_unique, float *values, float *g_absmax, int8_t *gq,
+                          float *g_scale, void *workspace, size_t workspace_bytes, void *stream);
+
 /* The dense part of the DLRM train step (model-architecture table; Fig. 1(a)):
  * bottom MLP over the dense features (ReLU after every layer), pairwise-dot
  * interaction of its output with the T pooled embeddings, top MLP (ReLU after

@@ -40,7 +40,7 @@ EXPORTS = ("dqrm_find_scale", "dqrm_pack_int4", "dqrm_embbag_fwd", "dqrm_embbag_
            "dqrm_embbag_bwd", "dqrm_embbag_bwd_noalloc", "dqrm_dedupe", "dqrm_dedupe_multi", "dqrm_segment_sum", "dqrm_segment_sum_multi",
            "dqrm_grad_quant_int8", "dqrm_grad_quant_int8_multi",
            "dqrm_sparse_update", "dqrm_sparse_merge_workspace_bytes", "dqrm_sparse_merge", "dqrm_sparse_update_sums",
-           "dqrm_quant_update", "dqrm_dense_workspace_bytes", "dqrm_dense_step",
+           "dqrm_quant_update", "dqrm_fwd_bwd_step", "dqrm_dense_workspace_bytes", "dqrm_dense_step",
            "dqrm_dense_param_count", "dqrm_dense_step_quant", "dqrm_check_status", "dqrm_last_hip_error", "dqrm_version")
 
 
@@ -123,6 +123,8 @@ def lib() -> C.CDLL:
         L.dqrm_grad_quant_int8_multi.argtypes = [i32, i32, i32, C.POINTER(dqrm_quant_block_t), vp]
         L.dqrm_grad_quant_int8_multi.restype = i32
         L.dqrm_quant_update.argtypes = [tp, i64, i64, vp, vp, vp, vp, vp, vp, C.c_float, vp, sz, vp]
+        L.dqrm_fwd_bwd_step.argtypes = [tp, vp, vp, i32, i64, i32, vp, vp, vp, C.c_float, i64, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+        L.dqrm_fwd_bwd_step.restype = i32
         L.dqrm_grad_quant_int8.argtypes = [i32, i32, i64, vp, vp, vp, vp, vp, vp]
         L.dqrm_sparse_update.argtypes = [tp, i64, vp, vp, vp, vp, C.c_float, vp]
         L.dqrm_sparse_update_sums.argtypes = [tp, i64, vp, vp, vp, vp, C.c_float, vp]
@@ -438,11 +440,11 @@ def dqrm_fwd_bwd_step(tables: Tables, bufs: StepBuffers, indices: torch.Tensor, 
                       grad_out: torch.Tensor, lr: float, mode: int = FWD_MASTER, stream=None) -> None:
     """One pass of the whole hot path on one stream, no host sync: forward, dedupe, segment sums, INT8 codes and update.
 
-    The last two are dqrm_quant_update: it leaves in ``bufs`` what dqrm_grad_quant_int8 and dqrm_sparse_update do, and folds the
-    maxima too, two launches fewer."""
-    dqrm_embbag_fwd(tables, indices, offsets, bufs.B, mode, bufs.out, bufs.codes, stream)
-    dqrm_dedupe(tables, indices, offsets, bufs.B, bufs.sorted_pos, bufs.uniq_rows, bufs.seg_offsets,
-                bufs.table_uniq_offsets, bufs.num_unique, bufs.workspace, stream)
-    dqrm_segment_sum(tables, bufs.B, indices.numel(), grad_out, bufs.values, None, bufs.workspace, stream)
-    dqrm_quant_update(tables, bufs.cap, indices.numel(), bufs.values, bufs.uniq_rows, bufs.table_uniq_offsets,
-                      bufs.g_absmax, bufs.gq, bufs.g_scale, lr, bufs.workspace, stream)
+    What dqrm_embbag_fwd, dqrm_dedupe, dqrm_segment_sum and dqrm_quant_update leave in ``bufs`` and the tables, bit for bit, in fewer
+    launches where the batch allows it."""
+    b = bufs
+    _check(lib().dqrm_fwd_bwd_step(tables.ref, _ptr(indices), _ptr(offsets), b.B, indices.numel(), mode, _ptr(b.out), _ptr(b.codes),
+                                   _ptr(grad_out), lr, b.cap, _ptr(b.sorted_pos), _ptr(b.uniq_rows), _ptr(b.seg_offsets),
+                                   _ptr(b.table_uniq_offsets), _ptr(b.num_unique), _ptr(b.values), _ptr(b.g_absmax), _ptr(b.gq),
+                                   _ptr(b.g_scale), _ptr(b.workspace), b.workspace.numel() * b.workspace.element_size(),
+                                   _stream(stream)), "dqrm_fwd_bwd_step")

@@ -4,6 +4,7 @@
 
 #include <cstdio>
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -16,6 +17,7 @@
 #include "dqrm_update.hpp"
 #include "dqrm_merge.hpp"
 #include "dqrm_dense.hpp"
+#include "dqrm_step.hpp"
 
 // Scratch of dqrm_embbag_bwd_noalloc: one copy per GPU, held until the process ends.  In host code
 // this name is only a handle for hipGetSymbolAddress; kernels receive the address that call returns.
@@ -261,6 +263,352 @@ int32_t sparse_update_impl(const dqrm_tables_t *tables, int64_t capacity, const 
     return DQRM_OK;
 }
 
+int32_t check_fwd(const dqrm_tables_t *tables, const int64_t *indices, const int64_t *offsets, int32_t batch, int64_t num_indices,
+                  int32_t mode, const float *out, const int8_t *codes_dbg)
+{
+    int64_t R = 0;
+    if (mode != DQRM_FWD_MASTER && mode != DQRM_FWD_PACKED) return DQRM_ERR_INVALID_ARG;
+    int32_t rc = check_tables(tables, mode == DQRM_FWD_PACKED, &R);
+    if (rc != DQRM_OK) return rc;
+    rc = check_batch(tables, indices, offsets, batch, num_indices);
+    if (rc != DQRM_OK) return rc;
+    if (!out || !aligned(out, 16) || (codes_dbg && !aligned(codes_dbg, 4))) return DQRM_ERR_INVALID_ARG;
+    return DQRM_OK;
+}
+
+dqrm::FwdArgs fwd_args(const dqrm_tables_t *tables, const int64_t *indices, const int64_t *offsets, int32_t batch, int64_t num_indices,
+                       float *out, int8_t *codes_dbg)
+{
+    dqrm::FwdArgs a;
+    a.master = tables->master;
+    a.packed = tables->packed;
+    a.w_scale = tables->w_scale;
+    a.row_offsets = tables->row_offsets_dev;
+    a.indices = indices;
+    a.offsets = offsets;
+    a.out = out;
+    a.codes = codes_dbg;
+    a.num_indices = num_indices;
+    a.T = tables->num_tables;
+    a.B = batch;
+    a.D = tables->dim;
+    a.no_rows = tables->row_offsets_host[a.T] <= 0;
+    a.tile_t = 0; // fwd_tiles()
+    return a;
+}
+
+// the tiles of workgroups of so many threads
+dim3 fwd_tiles(dqrm::FwdArgs &a, int threads)
+{
+    a.tile_t = std::min(a.T, dqrm::kFwdTileT(threads));
+    return dim3((unsigned)((a.B + dqrm::kFwdTileB - 1) / dqrm::kFwdTileB), (unsigned)((a.T + a.tile_t - 1) / a.tile_t));
+}
+
+int32_t check_dedupe(const dqrm_tables_t *tables, int32_t batch, int32_t num_batches, const dqrm_dedupe_batch_t *batches, size_t workspace_bytes)
+{
+    int64_t R = 0;
+    int32_t rc = check_tables(tables, false, &R);
+    if (rc != DQRM_OK) return rc;
+    if (!batches || num_batches < 1) return DQRM_ERR_INVALID_ARG;
+    if (num_batches > DQRM_MAX_DEDUPE_BATCHES) return DQRM_ERR_UNSUPPORTED;
+    const int T = tables->num_tables, D = tables->dim;
+    for (int i = 0; i < num_batches; ++i) {
+        const dqrm_dedupe_batch_t &b = batches[i];
+        rc = check_batch(tables, b.indices, b.offsets, batch, b.num_indices);
+        if (rc != DQRM_OK) return rc;
+        if (!b.sorted_pos || !b.uniq_rows || !b.seg_offsets || !b.table_uniq_offsets || !b.num_unique || !b.workspace ||
+            !aligned(b.workspace, 256))
+            return DQRM_ERR_INVALID_ARG;
+        if (b.max_table_lookups < 0) return DQRM_ERR_INVALID_ARG;
+        if (workspace_bytes < ws_layout(T, D, b.num_indices).total) return DQRM_ERR_WORKSPACE_TOO_SMALL;
+    }
+    return DQRM_OK;
+}
+
+// What the launches of a sort are given, and which they are.
+struct DedupePlan {
+    dqrm::DedupeArgs args;
+    int64_t max_n, most; // lookups of a batch, of a table, at most
+    int cap;             // lookups that a range's workgroup sorts at once
+    bool partition, whole, uneven;
+    dim3 grid() const { return dim3(args.T, num_batches, (unsigned)(args.parts + (args.extra + args.T - 1) / args.T)); }
+    int num_batches;
+};
+
+DedupePlan plan_dedupe(const dqrm_tables_t *tables, int32_t batch, int32_t num_batches, const dqrm_dedupe_batch_t *batches)
+{
+    const int T = tables->num_tables, D = tables->dim;
+    int64_t max_n = 0;
+    DedupePlan plan;
+    dqrm::DedupeArgs &da = plan.args;
+    std::memset(&da, 0, sizeof(da));
+    for (int i = 0; i < num_batches; ++i) {
+        const dqrm_dedupe_batch_t &b = batches[i];
+        dqrm::DedupeBatch &o = da.b[i];
+        max_n = std::max(max_n, b.num_indices);
+        o.indices = b.indices;
+        o.offsets = b.offsets;
+        o.N = b.num_indices;
+        o.limit = b.max_table_lookups > 0 ? std::min<int32_t>(b.max_table_lookups, DQRM_MAX_TABLE_LOOKUPS)
+                                          : DQRM_MAX_TABLE_LOOKUPS;
+        o.ws = ws_views(b.workspace, ws_layout(T, D, b.num_indices));
+        o.sorted_pos = b.sorted_pos;
+        o.tuo = b.table_uniq_offsets;
+        o.num_unique = b.num_unique;
+        o.uniq_rows = b.uniq_rows;
+        o.seg_offsets = b.seg_offsets;
+    }
+    da.row_offsets = tables->row_offsets_dev;
+    da.T = T;
+    da.B = batch;
+    // How many ranges a table's rows are cut into, and the workgroup: by the lookups of an average table (a table of more
+    // is sorted all the same, if need be piece by piece).  Measured (us, with dedupe_finish_kernel):
+    //   26 tables x  2048 lookups:  8 ranges of 512 threads 15.7 (1 range 19.1; one 1024-thread workgroup per table, the
+    //                               sort without ranges that this replaces: 25)
+    //   26 tables x  8192:          8 ranges of 1024 threads 22 (1: 41, 16: 30; without ranges 42)
+    //   208 tables x 8192 (eight batches): 1 range 55 (2: 64, 8: 100; without ranges 61)
+    //   208 tables x 1024:          1 range 18 (8: 63)
+    // so: a workgroup per CU or a little less, at least 256 lookups to a range, and no more than fit the LDS.
+    const int64_t avg = (max_n + T - 1) / T, wgs = (int64_t)T * num_batches;
+    const int64_t most_parts = dqrm::kMaxParts / T;
+    int64_t least_n = max_n;
+    for (int i = 0; i < num_batches; ++i) least_n = std::min<int64_t>(least_n, da.b[i].N);
+    int64_t most = 0; // lookups of any table
+    for (int i = 0; i < num_batches; ++i) most = std::max<int64_t>(most, std::min<int64_t>(da.b[i].N, da.b[i].limit));
+    // From two tiles per table on every range's workgroup reading the whole table costs more than sorting the tiles by
+    // range first: 26 x 65536 lookups 132 us, against 215 with 8 ranges that each read everything.
+    const bool partition = avg > 2 * dqrm::kDdTile && partitionable(T, least_n);
+    // Where the tables alone are workgroups for half of the CUs or more, none is cut (dedupe_table_kernel): 208 x 8192 lookups 60
+    // (dedupe_kernel, one range: 67), 1024 x 4096 181 (187); with fewer lookups dedupe_kernel's shorter code counts for more.
+    const bool whole = !partition && avg > 2048 && most <= dqrm::kTableCap && num_cus() <= wgs * 2;
+    int64_t parts = whole ? 1 : partition ? 32 : std::max<int64_t>(std::min<int64_t>({num_cus() / wgs, avg / 256, 16}), (avg - 1) / 8192 * 2);
+    parts = std::max<int64_t>(1, std::min(parts, most_parts));
+    da.parts = (int)parts;
+    da.bags_per_part = (int)((batch + parts - 1) / parts);
+    da.by_parts = dqrm::FastDiv::make((unsigned)parts);
+    da.even = dqrm::FastDiv::make((unsigned)std::max<int64_t>(1, max_n / ((int64_t)T * batch)));
+    // The segment sums of bags of several lookups are faster over a list ordered by chunk length (26 tables x 65536 lookups: by a
+    // quarter), those of bags of one over one in sorted order (8 x 26 x 8192, whole steps: 461 us, by length 470; 26 x 8192: 73.2, 74.2).
+    da.by_length = several_lookups(max_n, T, batch);
+    // A table far above the average would leave its few ranges' workgroups at work alone, each with piece after piece to take,
+    // the more so if its popular rows lie close together: a table of more than the LDS holds (and a quarter above the average) has
+    // ranges of half the LDS each, as many as that takes, chosen so that they hold about equally many lookups.  The workgroups of
+    // those beyond `parts` look up in the tables' boundaries which table is theirs.  Measured (us, with dedupe_finish_kernel; in
+    // brackets the `parts` equally wide ranges that every table has otherwise):
+    //   255 tables x  128 lookups and one of 65536: 261 (7600); one of 16384: 70 (670)
+    //    25 tables x 2048 and one of 65536:          75 (472); 25 x 512 and one of 16384: 51 (135)
+    // where no table has that many: 26 x 2048 19.1 (18.5), 26 x 8192 32.5 (31.6).  A bound on a table's lookups spares that.
+    const int cap = avg <= 512 ? 2048 : (avg <= 4096 && parts > 1 ? 4096 : 8192);
+    const int64_t light = std::max<int64_t>(cap, avg + avg / 4);
+    const bool uneven = !partition && !whole && most > light;
+    if (uneven) {
+        const int64_t room = max_slots(T) - T * parts;
+        const int64_t per_range = std::max<int64_t>({cap / 2, DQRM_MAX_TABLE_LOOKUPS / dqrm::kDdMaxRanges, room > 0 ? (max_n + room - 1) / room : max_n + 1});
+        da.light = (int)light;
+        da.per_range = (int)std::min<int64_t>(per_range, DQRM_MAX_TABLE_LOOKUPS);
+        // the sum over the tables above `light` of ceil(n / per_range) - parts, at most
+        da.extra = (int)std::min(max_n / per_range, max_n / light * std::max<int64_t>(0, (most + per_range - 1) / per_range - parts));
+    }
+    plan.max_n = max_n, plan.most = most, plan.cap = cap;
+    plan.partition = partition, plan.whole = whole, plan.uneven = uneven;
+    plan.num_batches = num_batches;
+    return plan;
+}
+
+void launch_dedupe_sort(const DedupePlan &plan, hipStream_t st)
+{
+    const dqrm::DedupeArgs &da = plan.args;
+    const dim3 grid = plan.grid();
+    if (plan.partition) {
+        hipLaunchKernelGGL(dqrm::dedupe_partition_kernel, dim3(da.T, plan.num_batches, (unsigned)((plan.most + dqrm::kDdTile - 1) / dqrm::kDdTile)),
+                           dim3(dqrm::kDdPartThreads), 0, st, da);
+        hipLaunchKernelGGL((dqrm::dedupe_kernel<1024, 8192, true, false>), grid, dim3(1024), 0, st, da);
+    } else if (plan.whole) {
+        hipLaunchKernelGGL(dqrm::dedupe_table_kernel, grid, dim3(dqrm::kTableThreads), 0, st, da);
+    } else if (plan.uneven) {
+        launch_dedupe<true>(plan.cap, grid, st, da);
+    } else {
+        launch_dedupe<false>(plan.cap, grid, st, da);
+    }
+}
+
+void launch_dedupe_finish(const DedupePlan &plan, hipStream_t st)
+{
+    const dqrm::DedupeArgs &da = plan.args;
+    // (2 workgroups per CU for one batch, 8 for eight: 256 per batch then; with 512 each the scans in front of the work take
+    // 3 us longer)
+    const int finish_blocks = std::min(grid_for(plan.max_n, dqrm::kSegThreads, 2), std::max(1, num_cus() * 8 / plan.num_batches));
+    hipLaunchKernelGGL(da.extra > 0 ? dqrm::dedupe_finish_kernel<true> : dqrm::dedupe_finish_kernel<false>,
+                       dim3(finish_blocks, plan.num_batches), dim3(dqrm::kSegThreads), dqrm::finish_lds_bytes(da), st, da);
+}
+
+int32_t check_segsum(const dqrm_tables_t *tables, int32_t batch, int64_t num_indices, const float *grad_out, const float *values,
+                     const void *workspace, size_t workspace_bytes)
+{
+    int64_t R = 0;
+    int32_t rc = check_tables(tables, false, &R);
+    if (rc != DQRM_OK) return rc;
+    if (batch < 1 || num_indices < 0) return DQRM_ERR_INVALID_ARG;
+    if (num_indices > kMaxIndices || (int64_t)batch * tables->num_tables > kMaxIndices) return DQRM_ERR_UNSUPPORTED;
+    if (!grad_out || !values || !workspace) return DQRM_ERR_INVALID_ARG;
+    if (!aligned(grad_out, 16) || !aligned(values, 16) || !aligned(workspace, 256)) return DQRM_ERR_INVALID_ARG;
+    if (workspace_bytes < ws_layout(tables->num_tables, tables->dim, num_indices).total) return DQRM_ERR_WORKSPACE_TOO_SMALL;
+    return DQRM_OK;
+}
+
+dqrm::SegArgs segsum_args(const dqrm_tables_t *tables, int32_t batch, int64_t num_indices, const float *grad_out, float *values,
+                          float *g_absmax, void *workspace)
+{
+    dqrm::SegArgs sa;
+    sa.grad_out = grad_out;
+    sa.ws = ws_views(workspace, ws_layout(tables->num_tables, tables->dim, num_indices));
+    sa.N = num_indices;
+    sa.values = values;
+    sa.g_absmax = g_absmax;
+    sa.T = tables->num_tables;
+    sa.B = batch;
+    sa.D = tables->dim;
+    return sa;
+}
+
+// at most one lane group per four lookups (a window of the chunk list per workgroup, a few singles per group)
+int segsum_blocks(int64_t num_indices, int D) { return grid_for((num_indices + 3) / 4 * pow2ceil(D / 4), dqrm::kSumThreads, dqrm::kSumBlocksPerCu); }
+
+void launch_segsum_any(const dqrm::SegArgs &sa, hipStream_t st)
+{
+    const dim3 grid(segsum_blocks(sa.N, sa.D));
+    if (several_lookups(sa.N, sa.T, sa.B))
+        launch_segsum<true>(pow2ceil(sa.D / 4), grid, st, sa);
+    else
+        launch_segsum<false>(pow2ceil(sa.D / 4), grid, st, sa);
+}
+
+int32_t check_quant_update(const dqrm_tables_t *tables, int64_t capacity, int64_t num_indices, const float *values,
+                           const int64_t *uniq_rows, const int32_t *table_uniq_offsets, const float *g_absmax, const int8_t *gq,
+                           const float *g_scale, const void *workspace, size_t workspace_bytes)
+{
+    int64_t R = 0;
+    int32_t rc = check_tables(tables, false, &R);
+    if (rc != DQRM_OK) return rc;
+    if (capacity < 0 || num_indices < 0 || !values || !uniq_rows || !table_uniq_offsets || !g_absmax || !gq ||
+        !g_scale || !workspace)
+        return DQRM_ERR_INVALID_ARG;
+    if (capacity > kMaxIndices || num_indices > kMaxIndices) return DQRM_ERR_UNSUPPORTED;
+    if (!aligned(values, 16) || !aligned(gq, 4) || !aligned(workspace, 256)) return DQRM_ERR_INVALID_ARG;
+    if (capacity * (tables->dim / 4) > kMaxRowQuarters) return DQRM_ERR_UNSUPPORTED;
+    if (workspace_bytes < ws_layout(tables->num_tables, tables->dim, num_indices).total) return DQRM_ERR_WORKSPACE_TOO_SMALL;
+    return DQRM_OK;
+}
+
+dqrm::QuantUpdateArgs quant_update_args(const dqrm_tables_t *tables, int64_t capacity, int64_t num_indices, const float *values,
+                                        const int64_t *uniq_rows, const int32_t *table_uniq_offsets, float *g_absmax, int8_t *gq,
+                                        float *g_scale, float lr, void *workspace)
+{
+    dqrm::QuantUpdateArgs a;
+    a.u.master = tables->master;
+    a.u.packed = tables->packed;
+    a.u.w_scale = tables->w_scale;
+    a.u.row_offsets = tables->row_offsets_dev;
+    a.u.uniq_rows = uniq_rows;
+    a.u.tuo = table_uniq_offsets;
+    a.u.gq = nullptr;
+    a.u.sums = nullptr;
+    a.u.g_scale = nullptr;
+    a.u.capacity = capacity;
+    a.u.lr = lr;
+    a.u.T = tables->num_tables;
+    a.u.D = tables->dim;
+    a.u.by_q4 = dqrm::FastDiv::make((unsigned)(a.u.D / 4));
+    a.values = values;
+    a.absmax_slots = ws_views(workspace, ws_layout(tables->num_tables, tables->dim, num_indices)).absmax_slots;
+    a.g_absmax = g_absmax;
+    a.gq_out = gq;
+    a.g_scale_out = g_scale;
+    return a;
+}
+
+void launch_quant_update(const dqrm::QuantUpdateArgs &a, hipStream_t st)
+{
+    hipLaunchKernelGGL(dqrm::quant_update_kernel, dim3(grid_for(a.u.capacity * (a.u.D / 4), dqrm::kEwThreads, 8)),
+                       dim3(dqrm::kEwThreads), dqrm::TableLds::bytes(a.u.T), st, a);
+}
+
+template <int THREADS, int CAP, bool PACKED>
+void launch_step_sort_for(const DedupePlan &plan, dqrm::FwdArgs &fa, hipStream_t st)
+{
+    using namespace dqrm;
+    DedupeArgs da = plan.args;
+    if (!plan.uneven) da.light = INT_MAX; // (no table has more lookups than the others by far)
+    const dim3 tiles = fwd_tiles(fa, THREADS), sort = plan.grid();
+    const int sort_groups = (int)(sort.x * sort.z);
+    const dim3 grid(sort_groups + tiles.x * tiles.y);
+    switch (pow2ceil(fa.D / 4)) {
+    case 2: hipLaunchKernelGGL((step_sort_kernel<THREADS, CAP, 2, PACKED>), grid, dim3(THREADS), 0, st, da, fa, sort_groups, (int)tiles.x); break;
+    case 4: hipLaunchKernelGGL((step_sort_kernel<THREADS, CAP, 4, PACKED>), grid, dim3(THREADS), 0, st, da, fa, sort_groups, (int)tiles.x); break;
+    case 8: hipLaunchKernelGGL((step_sort_kernel<THREADS, CAP, 8, PACKED>), grid, dim3(THREADS), 0, st, da, fa, sort_groups, (int)tiles.x); break;
+    case 16: hipLaunchKernelGGL((step_sort_kernel<THREADS, CAP, 16, PACKED>), grid, dim3(THREADS), 0, st, da, fa, sort_groups, (int)tiles.x); break;
+    case 32: hipLaunchKernelGGL((step_sort_kernel<THREADS, CAP, 32, PACKED>), grid, dim3(THREADS), 0, st, da, fa, sort_groups, (int)tiles.x); break;
+    default: hipLaunchKernelGGL((step_sort_kernel<THREADS, CAP, 64, PACKED>), grid, dim3(THREADS), 0, st, da, fa, sort_groups, (int)tiles.x); break;
+    }
+}
+
+template <bool PACKED>
+void launch_step_sort_any(const DedupePlan &plan, dqrm::FwdArgs &fa, hipStream_t st)
+{
+    if (plan.cap == 2048)
+        launch_step_sort_for<256, 2048, PACKED>(plan, fa, st);
+    else if (plan.cap == 4096)
+        launch_step_sort_for<512, 4096, PACKED>(plan, fa, st);
+    else
+        launch_step_sort_for<1024, 8192, PACKED>(plan, fa, st);
+}
+
+void launch_step_sort(const DedupePlan &plan, dqrm::FwdArgs &fa, bool packed, hipStream_t st)
+{
+    if (packed)
+        launch_step_sort_any<true>(plan, fa, st);
+    else
+        launch_step_sort_any<false>(plan, fa, st);
+}
+
+// The forward rides along with the sort (us a step, in one launch / in two: 4 tables x 128 lookups x 16 20.8 / 23.3, 26 x 2048 x 16
+// 35.4 / 38.6, 13 x 10.5 K x 40 in bags 59.7 / 70.6, 26 x 8192 x 64 67.3 / 71.4, 26 x 16000 x 16 106.1 / 115.2), but for so many large
+// bags that its tiles take two rounds behind the sort's workgroups, each of which needs most of a CU's LDS (26 x 64, bags of two, 6000
+// samples 90.0 / 94.6, 8192 samples 108.3 / 106.9).
+bool step_sorts_with_forward(const DedupePlan &plan, dqrm::FwdArgs fa)
+{
+    if (plan.partition || plan.whole) return false;
+    const dim3 tiles = fwd_tiles(fa, plan.cap / 8);
+    return !several_lookups(plan.max_n, fa.T, fa.B) || (int)(tiles.x * tiles.y) <= num_cus() * 3 / 2;
+}
+
+// A workgroup per table where a table is little work for one CU: with up to 128 KB of gradient rows to add up it spares two launches and
+// several round trips (us a step, one workgroup per table / three launches: 4 x 128 x 16 14.6 / 20.5, 26 x 1024 x 16 23.5 / 30.7,
+// 26 x 2048 x 16 33.6 / 35.4, 60 x 4000 x 8 48.1 / 63.6, 26 x 256 x 64 21.3 / 28.6; 256 KB: 26 x 1024 x 64 38.3 / 34.9).  The host knows
+// only the average table: a batch whose bags do not all look as if they held equally many lookups may have one table with most of
+// them, so all of it is to be little (1 MB in one table: about 50 us against 30).
+bool step_by_table(const DedupePlan &plan, const dqrm::SegArgs &sa)
+{
+    const int64_t row = sa.D * (int64_t)sizeof(float), T = sa.T, bags = T * sa.B;
+    return !plan.partition && plan.args.parts <= dqrm::kStepParts && (sa.N + T - 1) / T * row <= (128 << 10) &&
+           (sa.N % bags == 0 || sa.N * row <= (1 << 20));
+}
+
+void launch_step_table(const DedupePlan &plan, const dqrm::SegArgs &sa, const dqrm::QuantUpdateArgs &qa, hipStream_t st)
+{
+    using namespace dqrm;
+    const StepTableArgs a{plan.args, sa, qa, segsum_blocks(sa.N, sa.D)};
+    const dim3 grid(sa.T), threads(kStepThreads);
+    switch (pow2ceil(sa.D / 4)) {
+    case 2: hipLaunchKernelGGL(step_table_kernel<2>, grid, threads, 0, st, a); break;
+    case 4: hipLaunchKernelGGL(step_table_kernel<4>, grid, threads, 0, st, a); break;
+    case 8: hipLaunchKernelGGL(step_table_kernel<8>, grid, threads, 0, st, a); break;
+    case 16: hipLaunchKernelGGL(step_table_kernel<16>, grid, threads, 0, st, a); break;
+    case 32: hipLaunchKernelGGL(step_table_kernel<32>, grid, threads, 0, st, a); break;
+    default: hipLaunchKernelGGL(step_table_kernel<64>, grid, threads, 0, st, a); break;
+    }
+}
+
 // workspace of dqrm_sparse_merge: table offsets of the merged list, and per place the source word, the
 // first-of-its-row flag and the flags before it
 struct MergeLayout {
@@ -332,34 +680,12 @@ int32_t dqrm_pack_int4(const dqrm_tables_t *tables, void *stream)
 int32_t dqrm_embbag_fwd(const dqrm_tables_t *tables, const int64_t *indices, const int64_t *offsets, int32_t batch,
                         int64_t num_indices, int32_t mode, float *out, int8_t *codes_dbg, void *stream)
 {
-    int64_t R = 0;
-    if (mode != DQRM_FWD_MASTER && mode != DQRM_FWD_PACKED) return DQRM_ERR_INVALID_ARG;
-    int32_t rc = check_tables(tables, mode == DQRM_FWD_PACKED, &R);
+    const int32_t rc = check_fwd(tables, indices, offsets, batch, num_indices, mode, out, codes_dbg);
     if (rc != DQRM_OK) return rc;
-    rc = check_batch(tables, indices, offsets, batch, num_indices);
-    if (rc != DQRM_OK) return rc;
-    if (!out || !aligned(out, 16) || (codes_dbg && !aligned(codes_dbg, 4))) return DQRM_ERR_INVALID_ARG;
-
-    dqrm::FwdArgs a;
-    a.master = tables->master;
-    a.packed = tables->packed;
-    a.w_scale = tables->w_scale;
-    a.row_offsets = tables->row_offsets_dev;
-    a.indices = indices;
-    a.offsets = offsets;
-    a.out = out;
-    a.codes = codes_dbg;
-    a.num_indices = num_indices;
-    a.T = tables->num_tables;
-    a.B = batch;
-    a.D = tables->dim;
-    a.no_rows = tables->row_offsets_host[a.T] <= 0;
-    a.tile_t = a.T < dqrm::kFwdTileT ? a.T : dqrm::kFwdTileT;
-
+    dqrm::FwdArgs a = fwd_args(tables, indices, offsets, batch, num_indices, out, codes_dbg);
+    const dim3 grid = fwd_tiles(a, dqrm::kFwdThreads);
     const int G = pow2ceil(a.D / 4);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const dim3 grid((unsigned)((a.B + dqrm::kFwdTileB - 1) / dqrm::kFwdTileB),
-                    (unsigned)((a.T + a.tile_t - 1) / a.tile_t));
     if (mode == DQRM_FWD_PACKED)
         launch_fwd<true>(G, grid, st, a);
     else
@@ -379,110 +705,12 @@ size_t dqrm_embbag_bwd_workspace_bytes(int32_t num_tables, int32_t dim, int32_t 
 int32_t dqrm_dedupe_multi(const dqrm_tables_t *tables, int32_t batch, int32_t num_batches,
                           const dqrm_dedupe_batch_t *batches, size_t workspace_bytes, void *stream)
 {
-    int64_t R = 0;
-    int32_t rc = check_tables(tables, false, &R);
+    const int32_t rc = check_dedupe(tables, batch, num_batches, batches, workspace_bytes);
     if (rc != DQRM_OK) return rc;
-    if (!batches || num_batches < 1) return DQRM_ERR_INVALID_ARG;
-    if (num_batches > DQRM_MAX_DEDUPE_BATCHES) return DQRM_ERR_UNSUPPORTED;
-    const int T = tables->num_tables, D = tables->dim;
-    int64_t max_n = 0;
-    for (int i = 0; i < num_batches; ++i) {
-        const dqrm_dedupe_batch_t &b = batches[i];
-        rc = check_batch(tables, b.indices, b.offsets, batch, b.num_indices);
-        if (rc != DQRM_OK) return rc;
-        if (!b.sorted_pos || !b.uniq_rows || !b.seg_offsets || !b.table_uniq_offsets || !b.num_unique || !b.workspace ||
-            !aligned(b.workspace, 256))
-            return DQRM_ERR_INVALID_ARG;
-        if (b.max_table_lookups < 0) return DQRM_ERR_INVALID_ARG;
-        if (workspace_bytes < ws_layout(T, D, b.num_indices).total) return DQRM_ERR_WORKSPACE_TOO_SMALL;
-        if (b.num_indices > max_n) max_n = b.num_indices;
-    }
-    dqrm::DedupeArgs da;
-    std::memset(&da, 0, sizeof(da));
-    for (int i = 0; i < num_batches; ++i) {
-        const dqrm_dedupe_batch_t &b = batches[i];
-        dqrm::DedupeBatch &o = da.b[i];
-        o.indices = b.indices;
-        o.offsets = b.offsets;
-        o.N = b.num_indices;
-        o.limit = b.max_table_lookups > 0 ? std::min<int32_t>(b.max_table_lookups, DQRM_MAX_TABLE_LOOKUPS)
-                                          : DQRM_MAX_TABLE_LOOKUPS;
-        o.ws = ws_views(b.workspace, ws_layout(T, D, b.num_indices));
-        o.sorted_pos = b.sorted_pos;
-        o.tuo = b.table_uniq_offsets;
-        o.num_unique = b.num_unique;
-        o.uniq_rows = b.uniq_rows;
-        o.seg_offsets = b.seg_offsets;
-    }
-    da.row_offsets = tables->row_offsets_dev;
-    da.T = T;
-    da.B = batch;
+    const DedupePlan plan = plan_dedupe(tables, batch, num_batches, batches);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // How many ranges a table's rows are cut into, and the workgroup: by the lookups of an average table (a table of more
-    // is sorted all the same, if need be piece by piece).  Measured (us, with dedupe_finish_kernel):
-    //   26 tables x  2048 lookups:  8 ranges of 512 threads 15.7 (1 range 19.1; one 1024-thread workgroup per table, the
-    //                               sort without ranges that this replaces: 25)
-    //   26 tables x  8192:          8 ranges of 1024 threads 22 (1: 41, 16: 30; without ranges 42)
-    //   208 tables x 8192 (eight batches): 1 range 55 (2: 64, 8: 100; without ranges 61)
-    //   208 tables x 1024:          1 range 18 (8: 63)
-    // so: a workgroup per CU or a little less, at least 256 lookups to a range, and no more than fit the LDS.
-    const int64_t avg = (max_n + T - 1) / T, wgs = (int64_t)T * num_batches;
-    const int64_t most_parts = dqrm::kMaxParts / T;
-    int64_t least_n = max_n;
-    for (int i = 0; i < num_batches; ++i) least_n = std::min<int64_t>(least_n, da.b[i].N);
-    int64_t most = 0; // lookups of any table
-    for (int i = 0; i < num_batches; ++i) most = std::max<int64_t>(most, std::min<int64_t>(da.b[i].N, da.b[i].limit));
-    // From two tiles per table on every range's workgroup reading the whole table costs more than sorting the tiles by
-    // range first: 26 x 65536 lookups 132 us, against 215 with 8 ranges that each read everything.
-    const bool partition = avg > 2 * dqrm::kDdTile && partitionable(T, least_n);
-    // Where the tables alone are workgroups for half of the CUs or more, none is cut (dedupe_table_kernel): 208 x 8192 lookups 60
-    // (dedupe_kernel, one range: 67), 1024 x 4096 181 (187); with fewer lookups dedupe_kernel's shorter code counts for more.
-    const bool whole = !partition && avg > 2048 && most <= dqrm::kTableCap && num_cus() <= wgs * 2;
-    int64_t parts = whole ? 1 : partition ? 32 : std::max<int64_t>(std::min<int64_t>({num_cus() / wgs, avg / 256, 16}), (avg - 1) / 8192 * 2);
-    parts = std::max<int64_t>(1, std::min(parts, most_parts));
-    da.parts = (int)parts;
-    da.bags_per_part = (int)((batch + parts - 1) / parts);
-    da.by_parts = dqrm::FastDiv::make((unsigned)parts);
-    da.even = dqrm::FastDiv::make((unsigned)std::max<int64_t>(1, max_n / ((int64_t)T * batch)));
-    // The segment sums of bags of several lookups are faster over a list ordered by chunk length (26 tables x 65536 lookups: by a
-    // quarter), those of bags of one over one in sorted order (8 x 26 x 8192, whole steps: 461 us, by length 470; 26 x 8192: 73.2, 74.2).
-    da.by_length = several_lookups(max_n, T, batch);
-    // A table far above the average would leave its few ranges' workgroups at work alone, each with piece after piece to take,
-    // the more so if its popular rows lie close together: a table of more than the LDS holds (and a quarter above the average) has
-    // ranges of half the LDS each, as many as that takes, chosen so that they hold about equally many lookups.  The workgroups of
-    // those beyond `parts` look up in the tables' boundaries which table is theirs.  Measured (us, with dedupe_finish_kernel; in
-    // brackets the `parts` equally wide ranges that every table has otherwise):
-    //   255 tables x  128 lookups and one of 65536: 261 (7600); one of 16384: 70 (670)
-    //    25 tables x 2048 and one of 65536:          75 (472); 25 x 512 and one of 16384: 51 (135)
-    // where no table has that many: 26 x 2048 19.1 (18.5), 26 x 8192 32.5 (31.6).  A bound on a table's lookups spares that.
-    const int cap = avg <= 512 ? 2048 : (avg <= 4096 && parts > 1 ? 4096 : 8192);
-    const int64_t light = std::max<int64_t>(cap, avg + avg / 4);
-    const bool uneven = !partition && !whole && most > light;
-    if (uneven) {
-        const int64_t room = max_slots(T) - T * parts;
-        const int64_t per_range = std::max<int64_t>({cap / 2, DQRM_MAX_TABLE_LOOKUPS / dqrm::kDdMaxRanges, room > 0 ? (max_n + room - 1) / room : max_n + 1});
-        da.light = (int)light;
-        da.per_range = (int)std::min<int64_t>(per_range, DQRM_MAX_TABLE_LOOKUPS);
-        // the sum over the tables above `light` of ceil(n / per_range) - parts, at most
-        da.extra = (int)std::min(max_n / per_range, max_n / light * std::max<int64_t>(0, (most + per_range - 1) / per_range - parts));
-    }
-    const dim3 grid(T, num_batches, (unsigned)(parts + (da.extra + T - 1) / T));
-    if (partition) {
-        hipLaunchKernelGGL(dqrm::dedupe_partition_kernel, dim3(T, num_batches, (unsigned)((most + dqrm::kDdTile - 1) / dqrm::kDdTile)),
-                           dim3(dqrm::kDdPartThreads), 0, st, da);
-        hipLaunchKernelGGL((dqrm::dedupe_kernel<1024, 8192, true, false>), grid, dim3(1024), 0, st, da);
-    } else if (whole) {
-        hipLaunchKernelGGL(dqrm::dedupe_table_kernel, grid, dim3(dqrm::kTableThreads), 0, st, da);
-    } else if (uneven) {
-        launch_dedupe<true>(cap, grid, st, da);
-    } else {
-        launch_dedupe<false>(cap, grid, st, da);
-    }
-    // (2 workgroups per CU for one batch, 8 for eight: 256 per batch then; with 512 each the scans in front of the work take
-    // 3 us longer)
-    const int finish_blocks = std::min(grid_for(max_n, dqrm::kSegThreads, 2), std::max(1, num_cus() * 8 / num_batches));
-    hipLaunchKernelGGL(da.extra > 0 ? dqrm::dedupe_finish_kernel<true> : dqrm::dedupe_finish_kernel<false>,
-                       dim3(finish_blocks, num_batches), dim3(dqrm::kSegThreads), dqrm::finish_lds_bytes(da), st, da);
+    launch_dedupe_sort(plan, st);
+    launch_dedupe_finish(plan, st);
     DQRM_HIP_CHECK(hipGetLastError());
     return DQRM_OK;
 }
@@ -509,37 +737,14 @@ int32_t dqrm_dedupe(const dqrm_tables_t *tables, const int64_t *indices, const i
 int32_t dqrm_segment_sum(const dqrm_tables_t *tables, int32_t batch, int64_t num_indices, const float *grad_out,
                          float *values, float *g_absmax, void *workspace, size_t workspace_bytes, void *stream)
 {
-    int64_t R = 0;
-    int32_t rc = check_tables(tables, false, &R);
+    const int32_t rc = check_segsum(tables, batch, num_indices, grad_out, values, workspace, workspace_bytes);
     if (rc != DQRM_OK) return rc;
-    if (batch < 1 || num_indices < 0) return DQRM_ERR_INVALID_ARG;
-    if (num_indices > kMaxIndices || (int64_t)batch * tables->num_tables > kMaxIndices) return DQRM_ERR_UNSUPPORTED;
-    if (!grad_out || !values || !workspace) return DQRM_ERR_INVALID_ARG;
-    if (!aligned(grad_out, 16) || !aligned(values, 16) || !aligned(workspace, 256)) return DQRM_ERR_INVALID_ARG;
-    const int T = tables->num_tables, D = tables->dim;
-    const WsLayout L = ws_layout(T, D, num_indices);
-    if (workspace_bytes < L.total) return DQRM_ERR_WORKSPACE_TOO_SMALL;
-
     hipStream_t st = static_cast<hipStream_t>(stream);
-    dqrm::SegArgs sa;
-    sa.grad_out = grad_out;
-    sa.ws = ws_views(workspace, L);
-    sa.N = num_indices;
-    sa.values = values;
-    sa.g_absmax = g_absmax;
-    sa.T = T;
-    sa.B = batch;
-    sa.D = D;
-    const int G = pow2ceil(D / 4);
-    // at most one lane group per four lookups (a window of the chunk list per workgroup, a few singles per group)
-    const int grid_sum = grid_for((num_indices + 3) / 4 * G, dqrm::kSumThreads, dqrm::kSumBlocksPerCu);
-    if (several_lookups(num_indices, T, batch))
-        launch_segsum<true>(G, dim3(grid_sum), st, sa);
-    else
-        launch_segsum<false>(G, dim3(grid_sum), st, sa);
+    const dqrm::SegArgs sa = segsum_args(tables, batch, num_indices, grad_out, values, g_absmax, workspace);
+    launch_segsum_any(sa, st);
     if (g_absmax)
-        hipLaunchKernelGGL(dqrm::absmax_finalize_kernel, dim3((T + 255) / 256), dim3(256), 0, st, sa.ws.absmax_slots,
-                           T, g_absmax);
+        hipLaunchKernelGGL(dqrm::absmax_finalize_kernel, dim3((sa.T + 255) / 256), dim3(256), 0, st, sa.ws.absmax_slots,
+                           sa.T, g_absmax);
     DQRM_HIP_CHECK(hipGetLastError());
     return DQRM_OK;
 }
@@ -789,40 +994,56 @@ int32_t dqrm_quant_update(const dqrm_tables_t *tables, int64_t capacity, int64_t
                           const int64_t *uniq_rows, const int32_t *table_uniq_offsets, float *g_absmax, int8_t *gq,
                           float *g_scale, float lr, void *workspace, size_t workspace_bytes, void *stream)
 {
-    int64_t R = 0;
-    int32_t rc = check_tables(tables, false, &R);
+    const int32_t rc = check_quant_update(tables, capacity, num_indices, values, uniq_rows, table_uniq_offsets, g_absmax, gq, g_scale,
+                                          workspace, workspace_bytes);
     if (rc != DQRM_OK) return rc;
-    if (capacity < 0 || num_indices < 0 || !values || !uniq_rows || !table_uniq_offsets || !g_absmax || !gq ||
-        !g_scale || !workspace)
-        return DQRM_ERR_INVALID_ARG;
-    if (capacity > kMaxIndices || num_indices > kMaxIndices) return DQRM_ERR_UNSUPPORTED;
-    if (!aligned(values, 16) || !aligned(gq, 4) || !aligned(workspace, 256)) return DQRM_ERR_INVALID_ARG;
-    if (capacity * (tables->dim / 4) > kMaxRowQuarters) return DQRM_ERR_UNSUPPORTED;
-    const WsLayout L = ws_layout(tables->num_tables, tables->dim, num_indices);
-    if (workspace_bytes < L.total) return DQRM_ERR_WORKSPACE_TOO_SMALL;
-    dqrm::QuantUpdateArgs a;
-    a.u.master = tables->master;
-    a.u.packed = tables->packed;
-    a.u.w_scale = tables->w_scale;
-    a.u.row_offsets = tables->row_offsets_dev;
-    a.u.uniq_rows = uniq_rows;
-    a.u.tuo = table_uniq_offsets;
-    a.u.gq = nullptr;
-    a.u.sums = nullptr;
-    a.u.g_scale = nullptr;
-    a.u.capacity = capacity;
-    a.u.lr = lr;
-    a.u.T = tables->num_tables;
-    a.u.D = tables->dim;
-    a.u.by_q4 = dqrm::FastDiv::make((unsigned)(a.u.D / 4));
-    a.values = values;
-    a.absmax_slots = ws_views(workspace, L).absmax_slots;
-    a.g_absmax = g_absmax;
-    a.gq_out = gq;
-    a.g_scale_out = g_scale;
+    launch_quant_update(quant_update_args(tables, capacity, num_indices, values, uniq_rows, table_uniq_offsets, g_absmax, gq, g_scale, lr,
+                                          workspace),
+                        static_cast<hipStream_t>(stream));
+    DQRM_HIP_CHECK(hipGetLastError());
+    return DQRM_OK;
+}
+
+int32_t dqrm_fwd_bwd_step(const dqrm_tables_t *tables, const int64_t *indices, const int64_t *offsets, int32_t batch,
+                          int64_t num_indices, int32_t mode, float *out, int8_t *codes_dbg, const float *grad_out, float lr,
+                          int64_t capacity, int32_t *sorted_pos, int64_t *uniq_rows, int32_t *seg_offsets,
+                          int32_t *table_uniq_offsets, int32_t *num_unique, float *values, float *g_absmax, int8_t *gq,
+                          float *g_scale, void *workspace, size_t workspace_bytes, void *stream)
+{
+    int32_t rc = check_fwd(tables, indices, offsets, batch, num_indices, mode, out, codes_dbg);
+    if (rc != DQRM_OK) return rc;
+    const dqrm_dedupe_batch_t b{indices, offsets, num_indices, sorted_pos, uniq_rows, seg_offsets, table_uniq_offsets, num_unique, workspace, 0};
+    rc = check_dedupe(tables, batch, 1, &b, workspace_bytes);
+    if (rc != DQRM_OK) return rc;
+    rc = check_segsum(tables, batch, num_indices, grad_out, values, workspace, workspace_bytes);
+    if (rc != DQRM_OK) return rc;
+    rc = check_quant_update(tables, capacity, num_indices, values, uniq_rows, table_uniq_offsets, g_absmax, gq, g_scale, workspace,
+                            workspace_bytes);
+    if (rc != DQRM_OK) return rc;
+
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(dqrm::quant_update_kernel, dim3(grid_for(capacity * (a.u.D / 4), dqrm::kEwThreads, 8)),
-                       dim3(dqrm::kEwThreads), dqrm::TableLds::bytes(a.u.T), st, a);
+    dqrm::FwdArgs fa = fwd_args(tables, indices, offsets, batch, num_indices, out, codes_dbg);
+    const DedupePlan plan = plan_dedupe(tables, batch, 1, &b);
+    const dqrm::SegArgs sa = segsum_args(tables, batch, num_indices, grad_out, values, nullptr, workspace);
+    const dqrm::QuantUpdateArgs qa = quant_update_args(tables, capacity, num_indices, values, uniq_rows, table_uniq_offsets, g_absmax, gq,
+                                                       g_scale, lr, workspace);
+    if (step_sorts_with_forward(plan, fa)) {
+        launch_step_sort(plan, fa, mode == DQRM_FWD_PACKED, st);
+    } else {
+        const dim3 grid = fwd_tiles(fa, dqrm::kFwdThreads);
+        if (mode == DQRM_FWD_PACKED)
+            launch_fwd<true>(pow2ceil(fa.D / 4), grid, st, fa);
+        else
+            launch_fwd<false>(pow2ceil(fa.D / 4), grid, st, fa);
+        launch_dedupe_sort(plan, st);
+    }
+    if (step_by_table(plan, sa)) {
+        launch_step_table(plan, sa, qa, st);
+    } else {
+        launch_dedupe_finish(plan, st);
+        launch_segsum_any(sa, st);
+        launch_quant_update(qa, st);
+    }
     DQRM_HIP_CHECK(hipGetLastError());
     return DQRM_OK;
 }

@@ -251,6 +251,21 @@ __device__ __forceinline__ float combine_column_shared_wave(const BwdWs &ws, int
 // motions on bag 0 of table 0 and stores nothing.
 constexpr int kSinglesPerGroup = 4;
 
+// The slot that a maximum of single i, or of chunk c of a list of any order, is flushed to with `blocks` workgroups and G lanes to a
+// group (of a segment's several chunks one is as good as another).  A slot whose maximum is NaN counts as none, so where there are
+// NaN it matters which values share one.
+__device__ __forceinline__ int single_absmax_slot(int i, int blocks, int G)
+{
+    const unsigned groups = (unsigned)(kSumThreads / G);
+    return (int)((unsigned)i / kSinglesPerGroup % (blocks * groups) / groups) & (kAbsmaxSlots - 1);
+}
+__device__ __forceinline__ int chunk_absmax_slot(int c, int blocks, int G)
+{
+    const unsigned groups = (unsigned)(kSumThreads / G), waves = kSumThreads / kWave;
+    const unsigned g = (unsigned)c % (blocks * groups);
+    return (int)(G < 16 ? g % (blocks * waves) / waves : g / groups) & (kAbsmaxSlots - 1);
+}
+
 template <int G, bool REUSE>
 __device__ __forceinline__ void segment_sum_body(const SegArgs &a)
 {

@@ -426,27 +426,46 @@ static_assert(kDdPivotDepth + 2 + 32 <= kDdStack, "halving ends at a range of on
 // this short waits for its code as much as for its data.)
 // PARTITIONED: the table's lookups come from dedupe_partition_kernel, a run of this range per tile.
 // EXTRA: a table may have more than DedupeArgs::light lookups (a kernel of its own, as the others pay for its code otherwise).
+// LDS of such a workgroup
+template <int THREADS, int CAP>
+struct DedupeLds {
+    static constexpr int kWaves = THREADS / kWave;
+    // the kept lookups, twice (a sorting pass moves them from one half to the other): key relative to the range, position
+    // inside the table
+    alignas(16) unsigned key[2][CAP + 4];
+    unsigned short pos[2][CAP], rank[CAP];
+    // digit counters, a row of 256 per wave, and where the wave's items of each digit go
+    alignas(16) unsigned short cnt[kWaves * 256], place[kWaves * 256];
+    unsigned long long heads[CAP / kWave];
+    int scan[2][kWaves];
+    int4 x[kWaves];
+    int cls[kChunkClasses]; // chunks of each length class so far
+    unsigned stack[kDdStack];
+    unsigned pivot;
+    int back[kWaves];
+};
+
+// block_x: the table, block_y: the batch, block_z: the range
 template <int THREADS, int CAP, bool PARTITIONED, bool EXTRA>
-__global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
+__device__ __forceinline__ void dedupe_body(const DedupeArgs &args, DedupeLds<THREADS, CAP> &lds, int block_x, int block_y, int block_z)
 {
     constexpr int kWaves = THREADS / kWave, kCap = CAP;
     constexpr int kDdItems = CAP / THREADS; // lookups a thread requests at a time, and sorts
     static_assert(kCap % THREADS == 0 && kCap <= 8192, "ranks are 16 bits");
-    // the kept lookups, twice (a sorting pass moves them from one half to the other): key relative to the range, position
-    // inside the table
-    __shared__ __align__(16) unsigned s_key[2][kCap + 4];
-    __shared__ unsigned short s_pos[2][kCap], s_rank[kCap];
-    // digit counters, a row of 256 per wave, and where the wave's items of each digit go
-    __shared__ __align__(16) unsigned short cnt[kWaves * 256], place[kWaves * 256];
-    __shared__ unsigned long long s_heads[kCap / kWave];
-    __shared__ int s_scan[2][kWaves];
-    __shared__ int4 s_x[kWaves];
-    __shared__ int s_class[kChunkClasses]; // chunks of each length class so far
-    __shared__ unsigned s_stack[kDdStack];
-    __shared__ unsigned s_pivot;
-    __shared__ int s_back[kWaves];
+    auto &s_key = lds.key;
+    auto &s_pos = lds.pos;
+    auto &s_rank = lds.rank;
+    auto &cnt = lds.cnt;
+    auto &place = lds.place;
+    auto &s_heads = lds.heads;
+    auto &s_scan = lds.scan;
+    auto &s_x = lds.x;
+    auto &s_class = lds.cls;
+    auto &s_stack = lds.stack;
+    auto &s_pivot = lds.pivot;
+    auto &s_back = lds.back;
 
-    const DedupeBatch &bt = args.b[blockIdx.y];
+    const DedupeBatch &bt = args.b[block_y];
     const int64_t *__restrict__ indices = bt.indices;
     const int64_t *__restrict__ offsets = bt.offsets;
     const int B = args.B;
@@ -454,7 +473,7 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
     const BwdWs &ws = bt.ws;
     int32_t *__restrict__ sorted_pos = bt.sorted_pos;
 
-    int t = blockIdx.x, part = blockIdx.z; // consecutive workgroups: different tables
+    int t = block_x, part = block_z; // consecutive workgroups: different tables
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -923,13 +942,20 @@ __global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
     }
     __syncthreads();
     if (tid == 0) {
-        const int e = ((int)blockIdx.z - args.parts) * args.T + (int)blockIdx.x; // (a further range's number; the others have none)
-        const bool further = EXTRA && (int)blockIdx.z >= args.parts;
-        int4 *info = ws.part_info + 2 * (further ? args.T * args.parts + e : t * args.parts + (int)blockIdx.z);
+        const int e = (block_z - args.parts) * args.T + block_x; // (a further range's number; the others have none)
+        const bool further = EXTRA && block_z >= args.parts;
+        int4 *info = ws.part_info + 2 * (further ? args.T * args.parts + e : t * args.parts + block_z);
         const int w = further ? (t + 1) * args.parts + e : 0;
         info[0] = make_int4(max(part_base, 0), n_uniq, n_chunk, n_single);
         info[1] = make_int4(s_class[0] | (s_class[1] << 16), s_class[2] | (s_class[3] << 16), s_class[4], w);
     }
+}
+
+template <int THREADS, int CAP, bool PARTITIONED, bool EXTRA>
+__global__ __launch_bounds__(THREADS) void dedupe_kernel(DedupeArgs args)
+{
+    __shared__ DedupeLds<THREADS, CAP> lds;
+    dedupe_body<THREADS, CAP, PARTITIONED, EXTRA>(args, lds, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // Kernel 1 for launches with a workgroup per CU or more before any table is cut into ranges (several batches side by side) and at

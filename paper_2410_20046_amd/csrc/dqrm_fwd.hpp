@@ -1,7 +1,7 @@
 // Forward: gather -> INT4 fake-quant -> sum-pool (Sec. 3.1 and Sec. 4.1 of the paper).
 //
 // A workgroup owns a tile of kFwdTileB consecutive samples x up to kFwdTileT
-// consecutive tables.  The index arrays are table-major (bag = t * B + b), the
+// consecutive tables (32 of embbag_fwd_kernel's).  The index arrays are table-major (bag = t * B + b), the
 // output is sample-major (slot = b * T + t): with 16 samples per tile every
 // 128-byte line of `offsets` / `indices` is read by one workgroup only, and with
 // all tables in the tile (T <= kFwdTileT) the workgroup's output is one
@@ -27,11 +27,10 @@
 namespace dqrm {
 
 constexpr int kFwdTileB = 16;                      // samples per tile
-constexpr int kFwdTileT = 32;                      // tables per tile, at most
-constexpr int kFwdSlots = kFwdTileB * kFwdTileT;   // bags per tile, at most
-constexpr int kFwdThreads = 512;
+constexpr int kFwdThreads = 512;                   // of embbag_fwd_kernel; a workgroup has as many slots for bags as threads
+constexpr int kFwdTileT(int threads) { return threads / kFwdTileB; } // tables per tile, at most
 constexpr int kFwdBatch = 16;                      // first rows in flight per lane
-constexpr int kFwdLdsLookups = 4096;               // lookups of a tile whose row offsets fit in LDS (general bags)
+constexpr int kFwdLookupsPerSlot = 8;              // lookups of a tile whose row offsets fit in LDS (general bags), over its slots
 constexpr int kFwdBagBatch = 8;                    // rows of one bag in flight per lane (general bags)
 
 struct FwdArgs {
@@ -45,7 +44,7 @@ struct FwdArgs {
     int8_t *codes;
     int64_t num_indices;
     int T, B, D;
-    int tile_t;  // tables per tile: min(T, kFwdTileT); gridDim = (ceil(B / kFwdTileB), ceil(T / tile_t))
+    int tile_t;  // tables per tile: min(T, kFwdTileT); the tiles' grid = (ceil(B / kFwdTileB), ceil(T / tile_t))
     int no_rows; // the tables hold no row at all: nothing may be read from them
 };
 
@@ -84,19 +83,19 @@ template <> struct RowPiece<false> {
 // out = 0 + s * q, nothing else to add.  A slot without a valid lookup reads row 0 and multiplies by 0;
 // the addition turns a -0 product into the +0 of an empty sum.  Slots from `live` on do not exist
 // (samples beyond the batch); their LDS entries read as "no lookup".
-template <int G, bool PACKED>
+template <int THREADS, int G, bool PACKED>
 __device__ __forceinline__ void fwd_single_lookup_tile(const char *tab, const int64_t *s_off, const Scale *s_scale,
                                                        const float *s_mul, const int *s_slot, int grp, float *out_col,
                                                        int D, int live)
 {
-    constexpr int kGroups = kFwdThreads / G;
-    constexpr int kIters = (kFwdSlots + kGroups - 1) / kGroups;
+    constexpr int kGroups = THREADS / G;
+    constexpr int kIters = (THREADS + kGroups - 1) / kGroups;
     constexpr int kBatch = kIters < kFwdBatch ? kIters : kFwdBatch;
     for (int k0 = 0; k0 * kGroups < live; k0 += kBatch) {
         RowPiece<PACKED> piece[kBatch];
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
-            const int i = min((k0 + k) * kGroups + grp, kFwdSlots - 1);
+            const int i = min((k0 + k) * kGroups + grp, THREADS - 1);
             piece[k].load(tab + s_off[i]);
         }
 #pragma unroll
@@ -119,11 +118,11 @@ __device__ __forceinline__ void fwd_single_lookup_tile(const char *tab, const in
 // one lookup per bag, where the 16-byte stores decide.  No load is under a branch: a lookup past the bag's end or with a bad index
 // reads row 0 and enters the sum as 0 * q, which leaves the sum as it is.
 // Bags of 0 to 8 lookups, 26 x 8192 x 64, packed: 34.0 -> 24 us in a kernel trace (a pass among others 31.6 -> 22.9); bags of 8: 41.4 -> 38.
-template <int G>
+template <int THREADS, int G>
 __device__ __forceinline__ void fwd_bags(const FwdArgs &a, const int64_t *s_loff, const int *s_pos, const int *s_len, const int64_t *s_beg,
                                          const int *s_slot, const Scale *s_scale, int live, int tid)
 {
-    constexpr int kCols = 8, kLanes = G / 2, kGroups = kFwdThreads / kLanes;
+    constexpr int kCols = 8, kLanes = G / 2, kGroups = THREADS / kLanes;
     const int col = (tid & (kLanes - 1)) * kCols;
     if (col >= a.D) return; // lanes beyond the row
     const char *tab = reinterpret_cast<const char *>(a.packed) + (col >> 1);
@@ -189,25 +188,40 @@ __device__ __forceinline__ void fwd_bags(const FwdArgs &a, const int64_t *s_loff
     }
 }
 
-template <int G, bool PACKED>
-__global__ __launch_bounds__(kFwdThreads) void embbag_fwd_kernel(FwdArgs a)
+// LDS of a workgroup; an entry per slot of its tile
+template <int THREADS>
+struct FwdLds {
+    int64_t off[THREADS]; // byte offset of the first lookup's row in the table (0 if none / invalid)
+    int64_t beg[THREADS]; // position of the bag's first lookup
+    int len[THREADS];     // lookups in the bag
+    int tab[THREADS];
+    int slot[THREADS];    // output slot b * T + t (below 2^31: checked on the host)
+    Scale scale[THREADS]; // table scale (and its reciprocal)
+    float mul[THREADS];   // table scale, or 0 when the first lookup is absent or invalid
+    int general;          // some bag of the tile has more than one lookup
+    int64_t loff[THREADS * kFwdLookupsPerSlot]; // general bags: row byte offset of every lookup of the tile, -1 if bad
+    int pos[THREADS];     // ... where slot i's list starts in loff
+    int w[THREADS / kWave];
+};
+
+// Tile (block_x, block_y)
+template <int THREADS, int G, bool PACKED>
+__device__ __forceinline__ void embbag_fwd_body(const FwdArgs &a, FwdLds<THREADS> &lds, int block_x, int block_y)
 {
-    __shared__ int64_t s_off[kFwdSlots]; // byte offset of the first lookup's row in the table (0 if none / invalid)
-    __shared__ int64_t s_beg[kFwdSlots]; // position of the bag's first lookup
-    __shared__ int s_len[kFwdSlots];     // lookups in the bag
-    __shared__ int s_tab[kFwdSlots];
-    __shared__ int s_slot[kFwdSlots];    // output slot b * T + t (below 2^31: checked on the host)
-    __shared__ Scale s_scale[kFwdSlots]; // table scale (and its reciprocal)
-    __shared__ float s_mul[kFwdSlots];   // table scale, or 0 when the first lookup is absent or invalid
-    __shared__ unsigned char s_ok[kFwdSlots]; // the first lookup exists and is in range
-    __shared__ int s_general;            // some bag of the tile has more than one lookup
-    __shared__ int64_t s_loff[kFwdLdsLookups]; // general bags: row byte offset of every lookup of the tile, -1 if bad
-    __shared__ int s_pos[kFwdSlots];     // ... where slot i's list starts in s_loff
-    __shared__ int s_w[kFwdThreads / kWave];
-    static_assert(kFwdSlots == kFwdThreads, "one slot per thread");
+    auto &s_off = lds.off;
+    auto &s_beg = lds.beg;
+    auto &s_len = lds.len;
+    auto &s_tab = lds.tab;
+    auto &s_slot = lds.slot;
+    auto &s_scale = lds.scale;
+    auto &s_mul = lds.mul;
+    auto &s_general = lds.general;
+    auto &s_loff = lds.loff;
+    auto &s_pos = lds.pos;
+    auto &s_w = lds.w;
 
     const int tid = threadIdx.x;
-    const int b0 = (int)blockIdx.x * kFwdTileB, t0 = (int)blockIdx.y * a.tile_t;
+    const int b0 = block_x * kFwdTileB, t0 = block_y * a.tile_t;
     const int nb = min(kFwdTileB, a.B - b0), nt = min(a.tile_t, a.T - t0); // samples / tables of this tile
     const int live = nb * nt;                                              // its slots, a prefix in output order
     const int row_bytes = PACKED ? (a.D >> 1) : a.D * 4;
@@ -215,7 +229,8 @@ __global__ __launch_bounds__(kFwdThreads) void embbag_fwd_kernel(FwdArgs a)
     __syncthreads();
 
     // ---- phase A: one bag per thread, sample fastest ---------------------------
-    for (int s = tid; s < kFwdSlots; s += kFwdThreads) {
+    {
+        const int s = tid; // (as many slots as threads)
         const int bl = s % kFwdTileB, tl = s / kFwdTileB;
         const bool exists = bl < nb && tl < nt;
         // output-order index inside the tile; the entries past `live` are filled with "no lookup"
@@ -225,7 +240,6 @@ __global__ __launch_bounds__(kFwdThreads) void embbag_fwd_kernel(FwdArgs a)
         int len = 0;
         const int t = exists ? t0 + tl : 0, b = b0 + bl;
         float sc = 1.0f, mul = 0.0f;
-        bool ok = false;
         if (exists) {
             const int64_t bag = (int64_t)t * a.B + b;
             int64_t lo = a.offsets[bag], hi = a.offsets[bag + 1];
@@ -243,7 +257,6 @@ __global__ __launch_bounds__(kFwdThreads) void embbag_fwd_kernel(FwdArgs a)
                 if (idx >= 0 && idx < r1 - r0) {
                     off = (r0 + idx) * row_bytes;
                     mul = sc;
-                    ok = true;
                 } else {
                     report(DQRM_ERR_INDEX_OUT_OF_RANGE, t, idx);
                 }
@@ -258,7 +271,6 @@ __global__ __launch_bounds__(kFwdThreads) void embbag_fwd_kernel(FwdArgs a)
         // the packed rows hold codes already: no quotient, no reciprocal
         s_scale[i] = PACKED ? Scale(sc, 0.0f) : Scale(sc);
         s_mul[i] = mul;
-        s_ok[i] = ok;
     }
     __syncthreads();
 
@@ -266,12 +278,12 @@ __global__ __launch_bounds__(kFwdThreads) void embbag_fwd_kernel(FwdArgs a)
     const bool general = s_general != 0 || a.codes != nullptr || a.no_rows != 0;
     bool staged = false;
     if (general && !a.no_rows) {
-        // position of every slot's list in s_loff (slots in output order; kFwdThreads == kFwdSlots)
+        // position of every slot's list in s_loff (slots in output order; a slot per thread)
         const int my_len = tid < live ? s_len[tid] : 0;
         int total;
-        const int pos = block_excl_scan_add<kFwdThreads / kWave>(my_len, tid & (kWave - 1), tid / kWave, s_w, &total);
+        const int pos = block_excl_scan_add<THREADS / kWave>(my_len, tid & (kWave - 1), tid / kWave, s_w, &total);
         s_pos[tid] = pos;
-        staged = total <= kFwdLdsLookups; // block-uniform
+        staged = total <= THREADS * kFwdLookupsPerSlot; // block-uniform
         if (staged && my_len > 0) {
             const int t = s_tab[tid];
             const int64_t r0 = a.row_offsets[t], r1 = a.row_offsets[t + 1];
@@ -300,11 +312,11 @@ __global__ __launch_bounds__(kFwdThreads) void embbag_fwd_kernel(FwdArgs a)
     // only have twice the work: 16000 bags of 3 lookups x 64, one table, 7.7 us here and 8.6 there; bags of up to 6, 2 tables x 10901 x
     // 40, 7.9 and 8.0.  Of master rows a lane takes 16 bytes either way, and their codes' arithmetic, not the round trips, takes the
     // time: 20 tables x 4001 bags of up to 6 lookups x 32 14.8 here, 15.9 with the next rows requested ahead.
-    if (PACKED && staged && live > 2 * (kFwdThreads / G)) {
-        fwd_bags<G>(a, s_loff, s_pos, s_len, s_beg, s_slot, s_scale, live, tid);
+    if (PACKED && staged && live > 2 * (THREADS / G)) {
+        fwd_bags<THREADS, G>(a, s_loff, s_pos, s_len, s_beg, s_slot, s_scale, live, tid);
         return;
     }
-    constexpr int kGroups = kFwdThreads / G; // groups per workgroup
+    constexpr int kGroups = THREADS / G; // groups per workgroup
     const int lg = tid & (G - 1);
     const int grp = tid / G;
     const int col = lg * 4;
@@ -314,7 +326,7 @@ __global__ __launch_bounds__(kFwdThreads) void embbag_fwd_kernel(FwdArgs a)
     float *out_col = a.out + col;
 
     if (!general) {
-        fwd_single_lookup_tile<G, PACKED>(tab, s_off, s_scale, s_mul, s_slot, grp, out_col, a.D, live);
+        fwd_single_lookup_tile<THREADS, G, PACKED>(tab, s_off, s_scale, s_mul, s_slot, grp, out_col, a.D, live);
         return;
     }
 
@@ -380,6 +392,13 @@ __global__ __launch_bounds__(kFwdThreads) void embbag_fwd_kernel(FwdArgs a)
         const f32x4 v = {acc.x, acc.y, acc.z, acc.w};
         __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(out_col + (size_t)(unsigned)s_slot[i] * a.D));
     }
+}
+
+template <int G, bool PACKED>
+__global__ __launch_bounds__(kFwdThreads) void embbag_fwd_kernel(FwdArgs a)
+{
+    __shared__ FwdLds<kFwdThreads> lds;
+    embbag_fwd_body<kFwdThreads, G, PACKED>(a, lds, blockIdx.x, blockIdx.y);
 }
 
 } // namespace dqrm

@@ -87,3 +87,20 @@ def test_one_call_is_its_parts_for_gradients_that_are_not_finite(D):
     large = np.isfinite(a["values"]) & (a["values"] >= np.float32(3e38))
     assert a["g_scale"][2] == np.float32(1e-8) and large.sum() == 5 and (a["gq"][large] == 127).all()
     assert a["status"][0] == 0 and np.isfinite(a["values"][a["table_uniq_offsets"][5]:a["table_uniq_offsets"][6]]).all()
+
+
+# The edges of the rules that choose the step's launches: tables of as many lookups as one workgroup takes on and one more, a table with far
+# more than the others (further ranges; more rows than its workgroup keeps in LDS), rows of one lane group and of a whole wave, and
+# bags in more tiles than the forward shares a launch with.
+@pytest.mark.parametrize("D,B,rows,lens", [
+    (16, 2048, [5000, 2, 300000], 1), (16, 2049, [5000, 2, 300000], 1), (8, 1000, [1000000] + [70] * 15, "one long"),
+    (256, 128, [9, 2000, 1], 1), (128, 257, [3000, 50], 1), (64, 8193, [100000, 3], 1), (8, 6200, [900, 5], "ragged"), (24, 40, [4] * 70, "ragged"),
+    (40, 1, [7, 1], "ragged")])
+def test_one_call_is_its_parts_at_the_edges_of_its_rules(D, B, rows, lens):
+    rng = np.random.default_rng(D + B)
+    idx, off = _batch(rng, rows, B, lambda T, t, B: np.ones(B, np.int64) if lens == 1 else rng.integers(0, 5, B) if lens == "ragged"
+                      else np.full(B, 20) if t == 0 else rng.integers(0, 2, B))
+    grad = (rng.standard_normal((B, len(rows), D)) * 1e-4).astype(np.float32)
+    a, b = _runs(rows, D, B, idx, off, grad, 1)
+    _compare(a, b)
+    assert a["status"][0] == 0
