@@ -388,6 +388,15 @@ __device__ __forceinline__ unsigned split_pair(float &x0, float &x1)
     return h;
 }
 
+// The float (or what T is) `bytes` behind a wave-uniform address.  The offset is hidden from the loop around it, or the compiler would add
+// the two once before the loop and then the slab's address to that 64-bit sum beside every load: an instruction each, and twice the registers.
+template <typename T>
+__device__ __forceinline__ T load_at(const void *base, unsigned &bytes)
+{
+    asm("" : "+v"(bytes));
+    return *reinterpret_cast<const T *>(static_cast<const char *>(base) + bytes);
+}
+
 // One operand's part of a tile, as one thread reads it: ROWS wide indices, 8 consecutive r of each slab in an item.
 // kOpRC: the reduction index is the unit-stride one; kOpWide: the wide one is.
 template <int MODE, int ROWS, int BK>
@@ -397,8 +406,9 @@ struct PlaneOperand {
     const float *tile;     // the tile's first wide index, r = 0 (wave-uniform)
     const float *slabs;    // where fetch() starts from: there, or where the operand starts
     long long sr;          // kOpWide: between lines
-    // kOpRC: of the items' rows; kOpWide: of the first item's lines (kept, as adding a line's length 8 times costs two instructions
-    // beside each load)
+    // In bytes (a 32-bit byte offset beside a scalar address takes no instruction of its own: 32 of 134 vector instructions a slab of the
+    // weight gradients).  kOpRC: of the items' rows; kOpWide: of the first item's lines (kept, as adding a line's length 8 times
+    // costs two instructions beside each load)
     unsigned off[MODE == kOpRC ? kItems : 8];
     int row, kg;           // of the first item
     float v[2][kItems][8]; // two slabs on their way
@@ -414,7 +424,7 @@ struct PlaneOperand {
             slabs = whole ? tile : base;
 #pragma unroll
             for (int c = 0; c < kItems; ++c) {
-                off[c] = (unsigned)(min(first + row + c * kRowsPerItem, count - 1) - first) * (unsigned)sw + 8u * kg;
+                off[c] = ((unsigned)(min(first + row + c * kRowsPerItem, count - 1) - first) * (unsigned)sw + 8u * kg) * 4u;
                 if (!whole) off[c] = 0u;
             }
         } else {
@@ -422,7 +432,7 @@ struct PlaneOperand {
             row = tid % ROWS, kg = tid / ROWS;
             tile = slabs = base + first;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) off[k] = (8u * kg + k) * (unsigned)sr + min(row, count - 1 - first);
+            for (int k = 0; k < 8; ++k) off[k] = ((8u * kg + k) * (unsigned)sr + (unsigned)min(row, count - 1 - first)) * 4u;
         }
     }
     // a whole slab
@@ -431,14 +441,13 @@ struct PlaneOperand {
 #pragma unroll
         for (int c = 0; c < kItems; ++c) {
             if (MODE == kOpRC) {
-                const float *p = slabs + r0 + off[c];
-                const Float4Dw lo = *reinterpret_cast<const Float4Dw *>(p), hi = *reinterpret_cast<const Float4Dw *>(p + 4);
+                const Float4Dw lo = load_at<Float4Dw>(slabs + r0, off[c]), hi = load_at<Float4Dw>(slabs + r0 + 4, off[c]);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) v[q][c][k] = lo[k], v[q][c][4 + k] = hi[k];
             } else {
                 const float *p = slabs + (long long)(r0 + 8 * c * kGroupsPerItem) * sr;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) v[q][c][k] = p[off[k]];
+                for (int k = 0; k < 8; ++k) v[q][c][k] = load_at<float>(p, off[k]);
             }
         }
     }
@@ -748,7 +757,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_wave_kernel(GemmOne one)
 }
 
 // Several split products in one launch (kOpWide operands): the weight gradients of all layers, a workgroup per tile.
-// Measured: the Terabyte shape's layers at batch 8192 (12.4 GFLOP) 99 us, the Kaggle shape's at 2048 (1.96 GFLOP) 23; on the
+// Measured: the Terabyte shape's layers at batch 8192 (12.4 GFLOP) 82 us, the Kaggle shape's at 2048 (1.96 GFLOP) 21; on the
 // fp32 matrix instructions 171 and 34.5.
 __global__ __launch_bounds__(kPlaneThreads) void gemm_split_group_kernel(GemmGroup grp)
 {
