@@ -1065,7 +1065,7 @@ struct DenseLayout {
     size_t bot_dz[kMaxMlpLayers], top_dz[kMaxMlpLayers], dR;
     size_t bot_part[kMaxMlpLayers], top_part[kMaxMlpLayers];
     // the quantised variants: fake-quantised weights (layers in flat order), flat FP32 gradients, per-tensor maxima
-    size_t wq, grads, gmax;
+    size_t wq, wcodes, wscale, grads, gmax; // (wcodes, wscale: per layer, bfloat16 codes in padded rows and what rounding the weights adds to them; their rows' scales; in the order of wq)
     size_t loss_terms; // per-sample loss
     size_t total;
 };
@@ -1078,6 +1078,10 @@ int64_t dense_param_count(const dqrm_dense_model_t *m)
     for (int l = 0; l < m->bot_layers; ++l) p += (int64_t)m->bot_dims[l + 1] * (m->bot_dims[l] + 1);
     return p;
 }
+
+// Rows of bfloat16 codes are whole slabs of a product's reduction; a layer's scales start on 16 bytes.
+constexpr int code_pitch(int in) { return (in + 63) / 64 * 64; }
+constexpr int scale_rows(int out) { return (out + 3) / 4 * 4; }
 
 // The layers' inputs and outputs, bottom MLP first.
 template <typename F>
@@ -1181,6 +1185,10 @@ DenseLayout dense_layout(const dqrm_dense_model_t *m, int32_t batch)
     }
     const size_t P = (size_t)dense_param_count(m);
     L.wq = take(P);
+    size_t codes = 0, rows = 0;
+    each_layer(m, [&](int in, int out) { codes += (size_t)out * code_pitch(in), rows += scale_rows(out); });
+    L.wcodes = take(codes); // (two planes of 16 bits)
+    L.wscale = take(rows);
     L.grads = take(P);
     L.gmax = take((size_t)dqrm::kMaxGradTensors * dqrm::kGradMaxSlots * dqrm::kGradMaxStride);
     L.loss_terms = take((size_t)batch);
@@ -1222,6 +1230,17 @@ template <int B_MODE>
 hipError_t launch_gemm(hipStream_t st, const dqrm::GemmArgs &g)
 {
     const int t = plane_tile(g, B_MODE == dqrm::kOpWide);
+    if (t && g.codes) {
+        const int bm = t == 64 ? 64 : 128, bn = t == 128 ? 128 : 64;
+        const dim3 grid(((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn)), block(dqrm::kPlaneThreads);
+        if (t == 128)
+            hipLaunchKernelGGL((dqrm::gemm_planes_kernel<dqrm::CodeTile128<B_MODE>, B_MODE>), grid, block, 0, st, g);
+        else if (t == 64)
+            hipLaunchKernelGGL((dqrm::gemm_planes_kernel<dqrm::CodeTile64<B_MODE>, B_MODE>), grid, block, 0, st, g);
+        else
+            hipLaunchKernelGGL((dqrm::gemm_planes_kernel<dqrm::CodeTile128x64<B_MODE>, B_MODE>), grid, block, 0, st, g);
+        return hipGetLastError();
+    }
     if (t) {
         const int bm = t == 64 ? 64 : 128, bn = t == 128 ? 128 : 64;
         const dim3 grid(((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn)), block(dqrm::kPlaneThreads);
@@ -1271,13 +1290,21 @@ hipError_t launch_weight_grads(hipStream_t st, dqrm::GemmGroup &grp)
     return hipGetLastError();
 }
 
+// The weights that the forward and the input gradients use, and their codes and scales if they are quantised.
+struct LayerWeights {
+    const float *w;
+    const unsigned short *codes, *low;
+    const float *scale;
+};
+
 // Y[B][out] = act(X[B][in] * W[out][in]^T + b)
-hipError_t linear_fwd(hipStream_t st, const float *X, const float *W, const float *b, float *Y, int B, int in, int out,
+hipError_t linear_fwd(hipStream_t st, const float *X, const LayerWeights &W, const float *b, float *Y, int B, int in, int out,
                 bool relu)
 {
     dqrm::GemmArgs g{};
     g.A = X, g.a_si = in, g.a_sr = 1;
-    g.B = W, g.b_sr = 1, g.b_sj = in;
+    g.B = W.w, g.b_sr = 1, g.b_sj = in;
+    g.codes = W.codes, g.low = W.low, g.scale = W.scale, g.c_pitch = code_pitch(in);
     g.C = Y, g.c_si = out;
     g.M = B, g.N = out, g.K = in;
     g.bias = b, g.relu = relu ? 1 : 0;
@@ -1285,12 +1312,13 @@ hipError_t linear_fwd(hipStream_t st, const float *X, const float *W, const floa
 }
 
 // dX[B][in] = (dZ[B][out] * W[out][in]) masked by (mask[B][in] > 0)
-hipError_t linear_bwd_input(hipStream_t st, const float *dZ, const float *W, const float *mask, float *dX, int B, int in,
+hipError_t linear_bwd_input(hipStream_t st, const float *dZ, const LayerWeights &W, const float *mask, float *dX, int B, int in,
                       int out)
 {
     dqrm::GemmArgs g{};
     g.A = dZ, g.a_si = out, g.a_sr = 1;
-    g.B = W, g.b_sr = in, g.b_sj = 1;
+    g.B = W.w, g.b_sr = in, g.b_sj = 1;
+    g.codes = W.codes, g.low = W.low, g.scale = W.scale, g.c_pitch = code_pitch(in);
     g.C = dX, g.c_si = in;
     g.M = B, g.N = in, g.K = out;
     g.mask = mask;
@@ -1402,11 +1430,12 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
     const int B = batch, T = m->num_tables, D = m->dim;
 
     // ---- the weights the forward and the input gradients use: the model's, or their fake-quantised copies
-    const float *top_wf[kMaxMlpLayers], *bot_wf[kMaxMlpLayers];
-    for (int l = 0; l < m->top_layers; ++l) top_wf[l] = m->top_w[l];
-    for (int l = 0; l < m->bot_layers; ++l) bot_wf[l] = m->bot_w[l];
+    LayerWeights top_wf[kMaxMlpLayers], bot_wf[kMaxMlpLayers];
+    for (int l = 0; l < m->top_layers; ++l) top_wf[l] = {m->top_w[l], nullptr, nullptr, nullptr};
+    for (int l = 0; l < m->bot_layers; ++l) bot_wf[l] = {m->bot_w[l], nullptr, nullptr, nullptr};
     if (wbits) {
-        float *wq = quant->wq ? quant->wq : F(L.wq);
+        float *wq = quant->wq ? quant->wq : F(L.wq), *scale = F(L.wscale);
+        unsigned short *codes = reinterpret_cast<unsigned short *>(ws + L.wcodes);
         dqrm::FqGroup fq{};
         fq.qmax = (float)((1 << (wbits - 1)) - 1);
         int rows = 0;
@@ -1418,14 +1447,17 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
             rows = 0;
             return hipGetLastError();
         };
-        auto add_fq = [&](const float *W, const float **wf, int in, int out) -> hipError_t {
+        auto add_fq = [&](const float *W, LayerWeights *wf, int in, int out) -> hipError_t {
             hipError_t e = hipSuccess;
             if (fq.count == dqrm::kGemmMaxGroup) e = flush_fq();
             dqrm::FqLayer &q = fq.l[fq.count++];
-            q.W = W, q.Wq = wq, q.out = out, q.in = in, q.row_begin = rows;
+            const int pitch = code_pitch(in);
+            q.W = W, q.Wq = wq, q.codes = codes, q.low = codes + (size_t)out * pitch, q.scale = scale, q.out = out, q.in = in, q.row_begin = rows, q.pitch = pitch;
             rows += out;
-            *wf = wq;
+            *wf = {wq, q.codes, q.low, scale};
             wq += (size_t)out * in;
+            codes += 2 * (size_t)out * pitch;
+            scale += scale_rows(out);
             return e;
         };
         for (int l = 0; l < m->top_layers; ++l)
@@ -1450,7 +1482,7 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
         const int in = m->bot_dims[l], out = m->bot_dims[l + 1];
         if (in <= dqrm::kSmallKMax && out % 4 == 0 && aligned(m->bot_b[l], 16)) {
             dqrm::SmallKArgs sk{};
-            sk.X = x, sk.W = bot_wf[l], sk.bias = m->bot_b[l], sk.Y = F(L.bot_act[l]), sk.B = B, sk.N = out, sk.K = in, sk.relu = 1;
+            sk.X = x, sk.W = bot_wf[l].w, sk.bias = m->bot_b[l], sk.Y = F(L.bot_act[l]), sk.B = B, sk.N = out, sk.K = in, sk.relu = 1;
             sk.samples = small_k_samples(B, out);
             hipLaunchKernelGGL(dqrm::linear_small_k_kernel, dim3((B + sk.samples - 1) / sk.samples),
                                dim3(dqrm::kSmallKThreads), 0, st, sk);
@@ -1463,7 +1495,7 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
     dqrm::InteractArgs ia{};
     ia.bot = ride ? F(L.bot_act[bl_last]) : x, ia.emb = emb_out, ia.R = F(L.R), ia.B = B, ia.T = T, ia.D = D;
     if (ride) {
-        ia.lin_x = x, ia.lin_w = bot_wf[bl_last], ia.lin_b = m->bot_b[bl_last], ia.lin_y = F(L.bot_act[bl_last]);
+        ia.lin_x = x, ia.lin_w = bot_wf[bl_last].w, ia.lin_b = m->bot_b[bl_last], ia.lin_y = F(L.bot_act[bl_last]);
         ia.lin_k = m->bot_dims[bl_last];
     }
     DQRM_HIP_CHECK(launch_interact(st, ia, false, ride ? lin_floats : 0));
@@ -1476,7 +1508,7 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
     // the last layer (one output), the loss, and the gradient back to that layer's input in one kernel
     unsigned *gmax = reinterpret_cast<unsigned *>(ws + L.gmax);
     dqrm::HeadArgs ha{};
-    ha.X = x, ha.w = top_wf[last], ha.bias = m->top_b[last], ha.y = labels;
+    ha.X = x, ha.w = top_wf[last].w, ha.bias = m->top_b[last], ha.y = labels;
     ha.z = F(L.top_act[last]), ha.dz = F(L.top_dz[last]), ha.terms = F(L.loss_terms);
     ha.dX = last > 0 ? F(L.top_dz[last - 1]) : F(L.dR);
     ha.relu_input = last > 0; // the input of top layer l > 0 is a ReLU output; the interaction output is not

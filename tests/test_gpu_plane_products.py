@@ -78,7 +78,7 @@ def _layers(rng, dims):
             for i, o in zip(dims[:-1], dims[1:])]
 
 
-def _gpu_gradients(T, D, bot, top, x, emb, y):
+def _gpu_gradients(T, D, bot, top, x, emb, y, bits=0):
     """The step's loss, gradient of emb, and per layer (dW, db): its FP32 gradients as the buffer of a group of micro-batches has them."""
     import torch
     import paper_2410_20046_amd as dq
@@ -88,7 +88,7 @@ def _gpu_gradients(T, D, bot, top, x, emb, y):
     flat = torch.zeros(dq.dqrm_dense_param_count(m), device=dev)
     ws = torch.empty(dq.dqrm_dense_workspace_bytes(m, len(x)), dtype=torch.uint8, device=dev)
     loss, grad = torch.zeros(1, device=dev), torch.zeros(emb.shape, device=dev)
-    dq.dqrm_dense_step_quant(m, dq.DenseQuant(grad_buffer=flat, buffer_add=False, buffer_update=False), len(x),
+    dq.dqrm_dense_step_quant(m, dq.DenseQuant(weight_bits=bits, grad_buffer=flat, buffer_add=False, buffer_update=False), len(x),
                              *(torch.from_numpy(a).to(dev) for a in (x, emb, y)), 1.0, loss, grad, ws)
     torch.cuda.synchronize()
     flat, out, at = flat.cpu().numpy(), [], 0
@@ -158,3 +158,41 @@ def test_products_of_floats_next_to_the_largest(oracle, B):
     assert max(_error(got_bot[0][0][:, c], gbot[0][0][:, c]) for c in range(20)) <= 1e-5
     for g, w in zip(got_bot[1:] + got_top, gbot[1:] + gtop):
         assert _error(g[0], w[0]) <= 1e-5 and _error(g[1], w[1]) <= 1e-5
+
+
+# Quantised weights take three products, their codes as one plane (and, forward, the rounding of scale * code as another): the bound is
+# that of six.  Tiles as above (at 8190 128 x 128, 128 x 64; at 700 64 x 64), reductions of less than a slab, of whole slabs and with a
+# rest, inputs that fill a padded row and that do not.
+@pytest.mark.gpu
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("T,D,B,bot,top,seed", [
+    (3, 16, 700, [20, 100], [130, 70], 1), (2, 16, 8190, [20, 256], [512, 250], 1), (2, 8, 65, [64, 5], [4, 33], 1), (3, 64, 300, [128, 65], [97, 64], 2)])
+def test_gradients_of_quantised_weights_to_the_same_precision(oracle, T, D, B, bot, top, seed, bits):
+    rng = np.random.default_rng(seed)
+    bot, top = _layers(rng, bot + [D]), _layers(rng, [D + (T + 1) * T // 2] + top + [1])
+    used = lambda layers: [(oracle.mlp_fake_quant(w, bits)[0].reshape(w.shape), b) for w, b in layers]  # noqa: E731
+    n = B + B // 10 + 20
+    x, emb = rng.standard_normal((n, bot[0][0].shape[1])).astype(np.float32), rng.standard_normal((n, T, D)).astype(np.float32)
+    y = (rng.random(n) < 0.25).astype(np.float32)
+    keep = np.flatnonzero(_margins(used(bot), used(top), x, emb) > 1e-5)[:B]
+    x, emb, y = x[keep], emb[keep], y[keep]
+    assert len(x) == B
+    loss, demb, gbot, gtop = _oracle_gradients(oracle, used(bot), used(top), x, emb, y)
+    got_loss, got_emb, got_bot, got_top = _gpu_gradients(T, D, bot, top, x, emb, y, bits)
+    assert abs(got_loss - loss) <= BOUND * abs(loss)
+    errors = {"emb": _error(got_emb, demb)}
+    for name, got, want in (("bot", got_bot, gbot), ("top", got_top, gtop)):
+        for l, (g, w) in enumerate(zip(got, want)):
+            errors[f"{name}_w[{l}]"], errors[f"{name}_b[{l}]"] = _error(g[0], w[0]), _error(g[1], w[1])
+    print({k: float(f"{v:.2g}") for k, v in errors.items()}, flush=True)
+    assert max(errors.values()) <= BOUND, errors
+    # samples that are not finite: as with the same weights given as floats, and the others within the bound
+    odd = np.array([0, B // 3, B // 2, B - 1])
+    x[odd, 3] = np.inf, -np.inf, np.nan, 3.402e38
+    _, with_odd, _, _ = _gpu_gradients(T, D, bot, top, x, emb, y, bits)
+    _, as_floats, _, _ = _gpu_gradients(T, D, used(bot), used(top), x, emb, y)
+    others = np.setdiff1d(np.arange(B), odd)
+    assert _error(with_odd[others], demb[others]) <= BOUND  # (samples beside them are added up again too)
+    assert np.array_equal(np.isnan(with_odd[odd]), np.isnan(as_floats[odd])) and np.array_equal(np.isinf(with_odd[odd]), np.isinf(as_floats[odd]))
+    finite = np.isfinite(as_floats[odd])
+    assert np.linalg.norm(with_odd[odd][finite] - as_floats[odd][finite]) <= 10 * BOUND * np.linalg.norm(as_floats[odd][finite])
