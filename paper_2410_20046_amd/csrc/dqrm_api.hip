@@ -139,6 +139,9 @@ dqrm::BwdWs ws_views(void *workspace, const WsLayout &L)
     w.part_key = reinterpret_cast<unsigned *>(b + L.off_part_key);
     w.part_pos = reinterpret_cast<unsigned short *>(b + L.off_part_pos);
     w.part_start = reinterpret_cast<unsigned short *>(b + L.off_part_start);
+    // (needed before the dense list is written, and far smaller: only for more than kDdTile lookups and fewer tables than kMaxParts / 8)
+    w.part_bound = reinterpret_cast<unsigned *>(b + L.off_chunk_desc);
+    static_assert((size_t)dqrm::kMaxParts / 8 * (dqrm::kDdRanges + 1) * sizeof(unsigned) <= (size_t)dqrm::kDdTile * 16, "it fits");
     w.sorted_bag = reinterpret_cast<int *>(b + L.off_sorted_bag);
     w.chunk_local = reinterpret_cast<int4 *>(b + L.off_chunk_local);
     w.single_local = reinterpret_cast<int4 *>(b + L.off_single_local);
@@ -376,7 +379,7 @@ DedupePlan plan_dedupe(const dqrm_tables_t *tables, int32_t batch, int32_t num_b
     int64_t most = 0; // lookups of any table
     for (int i = 0; i < num_batches; ++i) most = std::max<int64_t>(most, std::min<int64_t>(da.b[i].N, da.b[i].limit));
     // From two tiles per table on every range's workgroup reading the whole table costs more than sorting the tiles by
-    // range first: 26 x 65536 lookups 132 us, against 215 with 8 ranges that each read everything.
+    // range first: 26 x 65536 lookups 110 us, against 215 with 8 ranges that each read everything.
     const bool partition = avg > 2 * dqrm::kDdTile && partitionable(T, least_n);
     // Where the tables alone are workgroups for half of the CUs or more, none is cut (dedupe_table_kernel): 208 x 8192 lookups 60
     // (dedupe_kernel, one range: 67), 1024 x 4096 181 (187); with fewer lookups dedupe_kernel's shorter code counts for more.
@@ -422,7 +425,7 @@ void launch_dedupe_sort(const DedupePlan &plan, hipStream_t st)
     if (plan.partition) {
         hipLaunchKernelGGL(dqrm::dedupe_partition_kernel, dim3(da.T, plan.num_batches, (unsigned)((plan.most + dqrm::kDdTile - 1) / dqrm::kDdTile)),
                            dim3(dqrm::kDdPartThreads), 0, st, da);
-        hipLaunchKernelGGL((dqrm::dedupe_kernel<1024, 8192, true, false>), grid, dim3(1024), 0, st, da);
+        hipLaunchKernelGGL((dqrm::dedupe_kernel<512, 4096, true, false>), grid, dim3(512), 0, st, da);
     } else if (plan.whole) {
         hipLaunchKernelGGL(dqrm::dedupe_table_kernel, grid, dim3(dqrm::kTableThreads), 0, st, da);
     } else if (plan.uneven) {
@@ -435,9 +438,9 @@ void launch_dedupe_sort(const DedupePlan &plan, hipStream_t st)
 void launch_dedupe_finish(const DedupePlan &plan, hipStream_t st)
 {
     const dqrm::DedupeArgs &da = plan.args;
-    // (2 workgroups per CU for one batch, 8 for eight: 256 per batch then; with 512 each the scans in front of the work take
-    // 3 us longer)
-    const int finish_blocks = std::min(grid_for(plan.max_n, dqrm::kSegThreads, 2), std::max(1, num_cus() * 8 / plan.num_batches));
+    // (Up to 4 workgroups per CU for one batch, as many as their LDS allows: 26 x 65536 lookups 283.7 us a step with 2, 279.8 with 4; 26 x
+    // 8192 71.1 with either.  8 for eight batches: 256 per batch then; with 512 each the scans in front of the work take 3 us longer.)
+    const int finish_blocks = std::min(grid_for(plan.max_n, dqrm::kSegThreads, 4), std::max(1, num_cus() * 8 / plan.num_batches));
     hipLaunchKernelGGL(da.extra > 0 ? dqrm::dedupe_finish_kernel<true> : dqrm::dedupe_finish_kernel<false>,
                        dim3(finish_blocks, plan.num_batches), dim3(dqrm::kSegThreads), dqrm::finish_lds_bytes(da), st, da);
 }

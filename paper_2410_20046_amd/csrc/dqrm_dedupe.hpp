@@ -25,6 +25,7 @@ constexpr int kDdTile = 8192;      // lookups of a table that a workgroup of ded
 constexpr int kDdTiles = DQRM_MAX_TABLE_LOOKUPS / kDdTile; // of a table, at most
 constexpr int kDdRanges = 64;      // ranges of a partitioned table, at most
 constexpr int kDdPartThreads = 1024;
+constexpr int kDdPartSample = 256; // lookups of a partitioned table that its ranges are chosen by
 constexpr int kSegThreads = 256;   // dedupe_finish_kernel
 static_assert(DQRM_MAX_TABLES <= kMaxParts && DQRM_MAX_TABLE_LOOKUPS <= 65536 && DQRM_MAX_TABLE_LOOKUPS / DQRM_SEG_CHUNK < 4096,
               "a part per table at least; positions inside a table are 16 bits; the chunk descriptor holds 12 bits of chunk count");
@@ -39,6 +40,7 @@ struct BwdWs {
     unsigned *part_key;       // [N]   rows (or the number of rows, for a bad index)
     unsigned short *part_pos; // [N]   positions inside the table
     unsigned short *part_start; // [T][kDdTiles][kDdRanges] first item of each range inside the tile
+    unsigned *part_bound;     // [T][kDdRanges + 1] first row of each range, and the number of rows + 1 (in chunk_desc's place)
     int *sorted_bag;          // [N]   bag of every sorted lookup
     int4 *chunk_local;        // [N]   chunk lists of the parts (each starts at the part's first sorted position)
     int4 *single_local;       // [N]   their lists of singles: {sorted position, bag, segment, row}
@@ -343,7 +345,10 @@ __device__ __forceinline__ uint2 digit_places(const unsigned short *cnt, int wav
 
 // Tables of many lookups: dedupe_kernel would read all of them in every range's workgroup.  Here a workgroup takes a tile
 // of kDdTile lookups and sorts it by range (one stable pass of the radix sort), so that a range's workgroup finds its
-// lookups in one run per tile.
+// lookups in one run per tile.  The ranges lie between keys of a sample, the same for all tiles of a table: they hold about equally many
+// lookups wherever the popular rows are, so a range's workgroup can be half as large, and two share a CU (26 tables x 65536 lookups, us,
+// here and in dedupe_kernel: ranges of equal width, workgroups of 1024 threads 11.2 + 107, of 512 153; by a sample of 256, of 512 17.9 + 73.5; of 512, whose ranks
+// alone are 262144 comparisons a workgroup, 25.8 + 73.6).
 __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(DedupeArgs args)
 {
     constexpr int kWaves = kDdPartThreads / kWave, kItems = kDdTile / kDdPartThreads;
@@ -351,6 +356,7 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
     __shared__ unsigned short s_pos[kDdTile];
     __shared__ __align__(16) unsigned short cnt[kWaves * 256], place[kWaves * 256];
     __shared__ int s_back[kWaves];
+    __shared__ unsigned s_split[kDdRanges], s_bound[kDdRanges + 1];
     const DedupeBatch &bt = args.b[blockIdx.y];
     const int t = blockIdx.x, tile = blockIdx.z, B = args.B;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -361,6 +367,7 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
     const int rounds = (len + kDdPartThreads - 1) / kDdPartThreads;
     const int wave_at = wave * rounds * kWave;
     const char *src = reinterpret_cast<const char *>(bt.indices + x.lo + tile * kDdTile);
+    const long long sample = bt.indices[x.lo + (unsigned)(tid % kDdPartSample) * (unsigned)x.n / kDdPartSample];
     long long raw[kItems];
     const int rounds_1 = opaque(rounds);
 #pragma unroll
@@ -368,11 +375,38 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
         if (r >= rounds_1) break;
         raw[r] = *reinterpret_cast<const long long *>(src + (unsigned)min(wave_at + r * kWave + lane, len - 1) * 8u);
     }
+    // the sample, its ranks (four threads to a key), the ranges between
+    constexpr int kShare = kDdPartThreads / kDdPartSample;
+    const int parts = args.parts;
+    if (tid < kDdPartSample) s_key[tid] = (unsigned long long)sample < rows_t ? (unsigned)sample : rows_t;
+    if (tid < kDdRanges) s_split[tid] = 0u;
+    __syncthreads();
+    {
+        const int j = tid / kShare, from = (tid % kShare) * (kDdPartSample / kShare);
+        const unsigned k = s_key[j];
+        int rank = 0;
+#pragma unroll 2
+        for (int i = from; i < from + kDdPartSample / kShare; i += 4) {
+            const uint4 o = *reinterpret_cast<const uint4 *>(s_key + i);
+            rank += (o.x < k || (o.x == k && i < j)) + (o.y < k || (o.y == k && i + 1 < j)) + (o.z < k || (o.z == k && i + 2 < j)) +
+                    (o.w < k || (o.w == k && i + 3 < j));
+        }
+#pragma unroll
+        for (int d = 1; d < kShare; d <<= 1) rank += __shfl_xor(rank, d, kWave);
+        const int p = (rank * parts + kDdPartSample - 1) / kDdPartSample; // the range that it would be the first key of
+        if (p > 0 && p < parts && p * kDdPartSample / parts == rank) s_split[p] = k;
+    }
+    __syncthreads();
+    // (a key that bounds several ranges has the first of them to itself)
+    if (tid <= parts) {
+        const unsigned b = tid == 0 ? 0u : tid == parts ? rows_t + 1u : s_split[tid] + (tid > 1 && s_split[tid] == s_split[tid - 1] ? 1u : 0u);
+        s_bound[tid] = b;
+        if (tile == 0) bt.ws.part_bound[(int64_t)t * (kDdRanges + 1) + tid] = b;
+    }
+    __syncthreads();
     unsigned short *my_cnt = cnt + wave * 256, *my_place = place + wave * 256;
     *reinterpret_cast<uint2 *>(my_cnt + 4 * lane) = make_uint2(0u, 0u);
     const int bits = 32 - __clz(args.parts); // (the digit `parts` is the padding's)
-    const unsigned share = args.by_parts.div(rows_t) + 1u;
-    const float per_share = 1.0f / (float)share;
     unsigned key[kItems], rank[kItems]; // rank: place inside the wave's items of the digit, digit in the upper half
     bool bad_index = false;
     long long bad_value = 0;
@@ -383,10 +417,10 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
         const bool exists = wave_at + r * kWave + lane < len;
         key[r] = (unsigned long long)raw[r] < rows_t ? (unsigned)raw[r] : rows_t;
         if (exists && key[r] == rows_t) bad_index = true, bad_value = raw[r];
-        // the range, key / share: at most 63, so the rounded quotient is at most one off
-        int d = (int)((float)key[r] * per_share);
-        const int rest = (int)(key[r] - (unsigned)d * share);
-        d += rest < 0 ? -1 : (rest >= (int)share ? 1 : 0);
+        int d = 0; // the last range that begins at or before it
+#pragma unroll
+        for (int step = kDdRanges / 2; step >= 1; step >>= 1)
+            if (d + step < parts && s_bound[min(d + step, kDdRanges)] <= key[r]) d += step;
         if (!exists) d = args.parts; // (padding: after every range)
         const unsigned long long peers = match_digit((unsigned)d, bits);
         const unsigned prev = my_cnt[d];
@@ -498,10 +532,16 @@ __device__ __forceinline__ void dedupe_body(const DedupeArgs &args, DedupeLds<TH
     long long bad_value = x.bad_value;
 
     // My range of the keys [0, rows_t]: a row, or rows_t for a lookup whose index is out of range (those sort after
-    // every row, and the part that holds them reports them).  The ranges of most tables are equally wide.
+    // every row, and the part that holds them reports them).  The ranges of most tables are equally wide,
+    // those of a partitioned one as dedupe_partition_kernel chose them.
     const unsigned share = args.by_parts.div(rows_t) + 1u;
     unsigned range_lo = min((unsigned)part * share, rows_t + 1u), range_hi = min(range_lo + share, rows_t + 1u);
-    static_assert(!PARTITIONED || !EXTRA, "a partitioned table's ranges are equally wide");
+    static_assert(!PARTITIONED || !EXTRA, "a partitioned table has no further ranges");
+    if constexpr (PARTITIONED) {
+        const unsigned *bound = ws.part_bound + (int64_t)t * (kDdRanges + 1) + part;
+        range_lo = n > 0 ? (unsigned)__builtin_amdgcn_readfirstlane((int)bound[0]) : 0u;
+        range_hi = n > 0 ? (unsigned)__builtin_amdgcn_readfirstlane((int)bound[1]) : 0u;
+    }
     bool sampled = EXTRA && n > args.light;
     if (__builtin_expect(sampled, 0)) {
         bool back = false;

@@ -58,6 +58,44 @@ def test_lookups_per_table(n, cards):
     assert run.status()[0] == 0
 
 
+# Ranges chosen by a sample: rows that take several ranges' share, close together, at either end, one row alone, all
+# alike; more in one range than a workgroup holds although the sample shows nothing of it (every 256th lookup is what the sample sees);
+# and beside them tables of fewer lookups than the sample has, and of none, and bad indices.
+@pytest.mark.parametrize("T", [1, 6])
+@pytest.mark.parametrize("kind", ["spread", "one row", "two rows", "cluster", "ends", "unseen"])
+def test_ranges_by_a_sample(kind, T):
+    rng = np.random.default_rng(len(kind) + T)
+    n, rows = 65_536, 3_000_000
+    lens = [n] + [0, 40, 17_001, 65_535, n][:T - 1]
+    cards = np.array([rows, 9, 70, 1, 65_536, rows][:T], np.int64)
+    idx = []
+    for c, m in zip(cards, lens):
+        v = rng.integers(0, c, m)
+        hot = rng.random(m) < 0.9
+        if kind == "one row":
+            v[:] = c // 2
+        elif kind == "two rows":
+            v = np.where(rng.random(m) < 0.5, c - 1, c // 3)
+        elif kind == "cluster":
+            v = np.where(hot, np.minimum(c // 5 + rng.integers(0, 40, m), c - 1), v)
+        elif kind == "ends":
+            v = np.where(hot, np.where(rng.random(m) < 0.5, 0, c - 1), v)
+        elif kind == "unseen":
+            v = np.where(np.arange(m) % 256 != 0, v // 100, v)
+        v[rng.integers(0, max(m, 1), m // 1000)] = rng.choice([-1, c, 2 ** 40])
+        idx.append(v)
+    idx, B = np.concatenate(idx).astype(np.int64), 512
+    starts = np.concatenate([[0], np.cumsum(lens)])
+    off = np.concatenate([np.sort(rng.integers(0, m + 1, B)) + s for m, s in zip(lens, starts)] + [[len(idx)]]).astype(np.int64)
+    off[np.arange(T) * B] = starts[:T]
+    wl = Workload(name="sample", T=T, D=8, B=B, alpha=1.0, seed=1, cards=cards)
+    print(f"sampled ranges: {kind}, {T} tables", flush=True)
+    run, got = _dedupe(wl, idx, off, B)
+    for k, v in _expected(wl, idx, off, B).items():
+        assert_exact(got[k], v, f"{kind} {k}")
+    assert run.status()[0] == run.dq.ERR_INDEX_OUT_OF_RANGE
+
+
 @pytest.mark.parametrize("n", [400, 3000, 8000, 40000])
 @pytest.mark.parametrize("bags", ["ragged", "pairs", "sparse"])
 def test_hot_rows_and_bags(n, bags):
