@@ -879,7 +879,7 @@ int32_t dqrm_grad_quant_int8(int32_t num_tables, int32_t dim, int64_t capacity, 
     a.D = dim;
     a.by_q4 = dqrm::FastDiv::make((unsigned)(dim / 4));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(dqrm::grad_quant_kernel, dim3(grid_for(capacity * (dim / 4), dqrm::kEwThreads, 8)),
+    hipLaunchKernelGGL(dqrm::grad_quant_kernel, dim3(grid_for(capacity * (dim / 4), dqrm::kEwThreads * dqrm::kGqPerThread, 8)),
                        dim3(dqrm::kEwThreads), dqrm::TableLds::bytes(num_tables), st, a);
     DQRM_HIP_CHECK(hipGetLastError());
     return DQRM_OK;
@@ -917,7 +917,7 @@ int32_t dqrm_grad_quant_int8_multi(int32_t num_tables, int32_t dim, int32_t num_
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(dqrm::grad_quant_multi_kernel,
-                       dim3(grid_for(max_cap * (dim / 4), dqrm::kEwThreads, 8), num_blocks), dim3(dqrm::kEwThreads),
+                       dim3(grid_for(max_cap * (dim / 4), dqrm::kEwThreads * dqrm::kGqPerThread, 8), num_blocks), dim3(dqrm::kEwThreads),
                        dqrm::TableLds::bytes(num_tables), st, qm);
     DQRM_HIP_CHECK(hipGetLastError());
     return DQRM_OK;

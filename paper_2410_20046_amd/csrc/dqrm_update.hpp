@@ -60,6 +60,10 @@ struct QuantArgs {
     int T, D;
 };
 
+// Bound by the round trips of a workgroup (table constants, then values); a thread has several elements in flight, so that fewer
+// workgroups, which all read the tables' constants first, do.  Eight blocks of 10 K rows x 64: 11.7 -> 8.8 us.
+constexpr int kGqPerThread = 4;
+
 __device__ __forceinline__ void grad_quant_body(const QuantArgs &a)
 {
     extern __shared__ __align__(16) unsigned char s_dyn[];
@@ -75,13 +79,21 @@ __device__ __forceinline__ void grad_quant_body(const QuantArgs &a)
     }
     __syncthreads();
     const unsigned total = clamp_u(L.tuo, T, a.capacity) * a.by_q4.d;
-    for (unsigned e = blockIdx.x * kEwThreads + threadIdx.x; e < total; e += gridDim.x * kEwThreads) {
-        const RowElem r = row_elem(e, a.by_q4, L, T);
-        const Scale gs = L.gs[r.t];
-        const float4 v = reinterpret_cast<const float4 *>(a.values)[e];
-        // the caller's g_absmax may be smaller than the values' (then codes clamp): guarded quotient
-        reinterpret_cast<unsigned *>(a.gq)[e] =
-            pack_bytes(int8_code(v.x, gs), int8_code(v.y, gs), int8_code(v.z, gs), int8_code(v.w, gs));
+    const unsigned nthreads = gridDim.x * kEwThreads;
+    // (e0 + 3 * nthreads < 2^32: total < 2^31 and nthreads <= 2^19, host)
+    for (unsigned e0 = blockIdx.x * kEwThreads + threadIdx.x; e0 < total; e0 += nthreads * kGqPerThread) {
+        float4 v[kGqPerThread];
+#pragma unroll
+        for (int k = 0; k < kGqPerThread; ++k) v[k] = reinterpret_cast<const float4 *>(a.values)[min(e0 + k * nthreads, total - 1)];
+#pragma unroll
+        for (int k = 0; k < kGqPerThread; ++k) {
+            const unsigned e = e0 + k * nthreads;
+            if (e >= total) break;
+            const Scale gs = L.gs[row_elem(e, a.by_q4, L, T).t];
+            // the caller's g_absmax may be smaller than the values' (then codes clamp): guarded quotient
+            reinterpret_cast<unsigned *>(a.gq)[e] =
+                pack_bytes(int8_code(v[k].x, gs), int8_code(v[k].y, gs), int8_code(v[k].z, gs), int8_code(v[k].w, gs));
+        }
     }
 }
 
