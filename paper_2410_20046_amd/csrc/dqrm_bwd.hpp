@@ -252,8 +252,8 @@ __device__ __forceinline__ float combine_column_shared_wave(const BwdWs &ws, int
 constexpr int kSinglesPerGroup = 4;
 
 // The slot that a maximum of single i, or of chunk c of a list of any order, is flushed to with `blocks` workgroups and G lanes to a
-// group (of a segment's several chunks one is as good as another).  A slot whose maximum is NaN counts as none, so where there are
-// NaN it matters which values share one.
+// group.  A slot whose maximum is NaN counts as none, so where there are NaN it matters which values share one.  (A segment of more
+// than one chunk has one maximum, of its whole row, which is flushed to the slot of any of its chunks: whichever arrives last.)
 __device__ __forceinline__ int single_absmax_slot(int i, int blocks, int G)
 {
     const unsigned groups = (unsigned)(kSumThreads / G);

@@ -222,9 +222,14 @@ __global__ __launch_bounds__(kStepThreads) void step_table_kernel(StepTableArgs 
             for (int q = 0; q < kStepLongBatch; ++q)
                 if (k0 + q < e.y) acc = k0 + q == 0 ? v[q] : f4_add(acc, v[q]);
         }
-        if (m < longs && col_ok) {
-            *reinterpret_cast<float4 *>(a.s.values + (int64_t)e.z * D + col) = acc;
-            add_max(e.w, f4_absmax(acc));
+        // (the maximum is of the whole row, as segment_sum_kernel takes it: NaN only if all of a narrow row is, else hidden by the others)
+        float row_max = col_ok ? f4_absmax(acc) : 0.0f;
+        if (G >= 16) row_max = fmaxf(row_max, 0.0f);
+#pragma unroll
+        for (int o = G / 2; o >= 1; o >>= 1) row_max = fmaxf(row_max, __shfl_xor(row_max, o, kWave));
+        if (m < longs) {
+            if (col_ok) *reinterpret_cast<float4 *>(a.s.values + (int64_t)e.z * D + col) = acc;
+            if (lg == 0) add_max(e.w, row_max);
         }
     }
     __syncthreads();

@@ -104,3 +104,18 @@ def test_one_call_is_its_parts_at_the_edges_of_its_rules(D, B, rows, lens):
     a, b = _runs(rows, D, B, idx, off, grad, 1)
     _compare(a, b)
     assert a["status"][0] == 0
+
+
+# A row of several chunks whose sum is not finite: NaN in all columns, and in four that one lane holds; beside a row that has the maximum,
+# and alone.  (256 lookups: of the narrowest width a workgroup has them all, so that there is one order only.)
+@pytest.mark.parametrize("D", [16, 24, 64, 128])
+@pytest.mark.parametrize("rows", [1, 2])
+@pytest.mark.parametrize("columns", [slice(None), slice(4, 8)], ids=["all", "four"])
+def test_one_call_is_its_parts_for_long_rows_that_are_not_finite(columns, rows, D):
+    rng = np.random.default_rng(D + rows)
+    idx, off = _batch(rng, [rows], 256, lambda T, t, B: np.ones(B, np.int64))
+    grad = (rng.standard_normal((256, 1, D)) * 1e-4).astype(np.float32)
+    grad[np.flatnonzero(idx == 0)[3], 0, columns] = np.nan
+    a, b = _runs([rows], D, 256, idx, off, grad, 0)
+    _compare(a, b)
+    assert np.isnan(a["values"][0, columns]).all() and a["status"][0] == 0
