@@ -1026,10 +1026,12 @@ int32_t dqrm_fwd_bwd_step(const dqrm_tables_t *tables, const int64_t *indices, c
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     dqrm::FwdArgs fa = fwd_args(tables, indices, offsets, batch, num_indices, out, codes_dbg);
-    const DedupePlan plan = plan_dedupe(tables, batch, 1, &b);
+    DedupePlan plan = plan_dedupe(tables, batch, 1, &b);
     const dqrm::SegArgs sa = segsum_args(tables, batch, num_indices, grad_out, values, nullptr, workspace);
     const dqrm::QuantUpdateArgs qa = quant_update_args(tables, capacity, num_indices, values, uniq_rows, table_uniq_offsets, g_absmax, gq,
                                                        g_scale, lr, workspace);
+    const bool by_table = step_by_table(plan, sa);
+    if (by_table) plan.args.by_length = 0; // (nobody would read the chunks' ranks by length that the sort counts for it)
     if (step_sorts_with_forward(plan, fa)) {
         launch_step_sort(plan, fa, mode == DQRM_FWD_PACKED, st);
     } else {
@@ -1040,7 +1042,7 @@ int32_t dqrm_fwd_bwd_step(const dqrm_tables_t *tables, const int64_t *indices, c
             launch_fwd<false>(pow2ceil(fa.D / 4), grid, st, fa);
         launch_dedupe_sort(plan, st);
     }
-    if (step_by_table(plan, sa)) {
+    if (by_table) {
         launch_step_table(plan, sa, qa, st);
     } else {
         launch_dedupe_finish(plan, st);

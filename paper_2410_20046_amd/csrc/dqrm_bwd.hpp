@@ -253,7 +253,8 @@ constexpr int kSinglesPerGroup = 4;
 
 // The slot that a maximum of single i, or of chunk c of a list of any order, is flushed to with `blocks` workgroups and G lanes to a
 // group.  A slot whose maximum is NaN counts as none, so where there are NaN it matters which values share one.  (A segment of more
-// than one chunk has one maximum, of its whole row, which is flushed to the slot of any of its chunks: whichever arrives last.)
+// than one chunk has one maximum, of its whole row, which is flushed to the slot of any of its chunks: whichever arrives last.  In a list
+// ordered by length the places inside a class are dealt as the sort's lanes arrive, so there it is open which values share a slot.)
 __device__ __forceinline__ int single_absmax_slot(int i, int blocks, int G)
 {
     const unsigned groups = (unsigned)(kSumThreads / G);

@@ -48,7 +48,8 @@ struct StepTableArgs {
 
 // Bound by a chain of about ten round trips of a microsecond (counts, lists, bags, rows, parked sums, values, weights) and, from
 // about 100 KB of rows per table on, by what one CU can have in flight.  The lists it reads are each range's own, in their places; the
-// dense ones are written beside the sums, so that the workspace is left as the three kernels leave it.  Rows of the update stay in
+// dense ones are written beside the sums, so that the workspace serves a later dqrm_segment_sum (the chunks in sorted order, also
+// where dedupe_finish_kernel puts the long ones first: a sum over few chunks gains nothing by that).  Rows of the update stay in
 // LDS, which lets its weights, the only data that come from far, be requested before the long segments are added up.  More loads to a
 // thread in flight, or the first ones of both lists requested together, cost more in registers and code than they save.
 // 4 tables x 128 lookups x 16: the step 20.5 -> 14.6 us; 26 x 2048 x 16: 35.4 -> 33.6.

@@ -119,3 +119,33 @@ def test_one_call_is_its_parts_for_long_rows_that_are_not_finite(columns, rows, 
     a, b = _runs([rows], D, 256, idx, off, grad, 0)
     _compare(a, b)
     assert np.isnan(a["values"][0, columns]).all() and a["status"][0] == 0
+
+
+# The workspace of the one call serves a later segment sum, as a dedupe's does: bags of one lookup and of several (whose chunks a dedupe
+# puts in another order), rows of one chunk and of more.
+@pytest.mark.parametrize("D,B,rows,bag", [(64, 100, [300, 2, 9], 1), (16, 64, [70] * 12, 4), (40, 33, [5, 70, 900], 3)])
+def test_the_workspace_of_one_call_serves_a_segment_sum(D, B, rows, bag):
+    import torch
+
+    rng = np.random.default_rng(D + B)
+    idx, off = _batch(rng, rows, B, lambda T, t, B: np.full(B, bag))
+    grad = (rng.standard_normal((2, B, len(rows), D)) * 1e-4).astype(np.float32)
+    ro = np.concatenate([[0], np.cumsum(rows)]).astype(np.int64)
+    run = GpuRun(ro, D, np.zeros((ro[-1], D), np.float32), B, len(idx))
+    b, dq = run.bufs, run.dq
+    run.upload_batch(idx, off, grad[0])
+    later = torch.from_numpy(grad[1]).to(run.dev)
+    results = []
+    for one_call in (True, False):
+        if one_call:
+            dq.dqrm_fwd_bwd_step(run.tables, b, run.idx, run.off, run.grad, 0.1, 0)
+        else:
+            dq.dqrm_dedupe(run.tables, run.idx, run.off, B, b.sorted_pos, b.uniq_rows, b.seg_offsets, b.table_uniq_offsets, b.num_unique,
+                           b.workspace)
+        b.values.zero_()
+        for _ in range(2):  # (the first sum's maxima are beside the step's own until it has folded them)
+            dq.dqrm_segment_sum(run.tables, B, len(idx), later, b.values, b.g_absmax, b.workspace)
+        results.append((b.values.cpu().numpy(), b.g_absmax.cpu().numpy()))
+    for x, y, n in zip(*results, ("values", "g_absmax")):
+        assert_exact(x.view(np.uint32), y.view(np.uint32), n)
+    assert np.abs(results[0][0]).max() > 0 and run.status()[0] == 0
