@@ -1070,8 +1070,13 @@ struct DenseLayout {
     size_t bot_dz[kMaxMlpLayers], top_dz[kMaxMlpLayers], dR;
     size_t bot_part[kMaxMlpLayers], top_part[kMaxMlpLayers];
     // the quantised variants: fake-quantised weights (layers in flat order), flat FP32 gradients, per-tensor maxima
-    size_t wq, wcodes, wscale, grads, gmax; // (wcodes, wscale: per layer, bfloat16 codes in padded rows and what rounding the weights adds to them; their rows' scales; in the order of wq)
+    size_t wq, grads, gmax;
     size_t loss_terms; // per-sample loss
+    // [late, late_end): the slices and the flat gradients, which nothing touches before the last input gradient is there.  Until then
+    // the quantised weights' codes lie there, layer by layer (LayerCodes), as far as they fit: a workspace that is enough for FP32 weights
+    // is enough for them too.  (Slices and gradients are two parameters' room for each, a row of codes and its scale is padded to
+    // 64 of them and one: only models of nothing but layers of less than 32 inputs at small batches do not fit whole.)
+    size_t late, late_end;
     size_t total;
 };
 
@@ -1084,9 +1089,19 @@ int64_t dense_param_count(const dqrm_dense_model_t *m)
     return p;
 }
 
-// Rows of bfloat16 codes are whole slabs of a product's reduction; a layer's scales start on 16 bytes.
+// Rows of bfloat16 codes are whole slabs of a product's reduction.
 constexpr int code_pitch(int in) { return (in + 63) / 64 * 64; }
-constexpr int scale_rows(int out) { return (out + 3) / 4 * 4; }
+
+// A layer's codes at `at`, what rounding the weights adds to them (both [out][pitch], 16 bits), and their rows' scales (a kernel
+// reads them 4 at a time).
+struct LayerCodes {
+    size_t codes, low, scale, end;
+    LayerCodes(size_t at, int in, int out)
+    {
+        const size_t plane = (size_t)out * code_pitch(in) * sizeof(unsigned short);
+        codes = at, low = at + plane, scale = low + plane, end = align_up(scale + (size_t)(out + 3) / 4 * 4 * sizeof(float), 256);
+    }
+};
 
 // The layers' inputs and outputs, bottom MLP first.
 template <typename F>
@@ -1179,22 +1194,20 @@ DenseLayout dense_layout(const dqrm_dense_model_t *m, int32_t batch)
     for (int l = 0; l < m->bot_layers; ++l) {
         L.bot_act[l] = take((size_t)batch * m->bot_dims[l + 1]);
         L.bot_dz[l] = take((size_t)batch * m->bot_dims[l + 1]);
-        L.bot_part[l] = part(m->bot_dims[l], m->bot_dims[l + 1]);
     }
     L.R = take((size_t)batch * m->top_dims[0]);
     L.dR = take((size_t)batch * m->top_dims[0]);
     for (int l = 0; l < m->top_layers; ++l) {
         L.top_act[l] = take((size_t)batch * m->top_dims[l + 1]);
         L.top_dz[l] = take((size_t)batch * m->top_dims[l + 1]);
-        L.top_part[l] = part(m->top_dims[l], m->top_dims[l + 1]);
     }
     const size_t P = (size_t)dense_param_count(m);
     L.wq = take(P);
-    size_t codes = 0, rows = 0;
-    each_layer(m, [&](int in, int out) { codes += (size_t)out * code_pitch(in), rows += scale_rows(out); });
-    L.wcodes = take(codes); // (two planes of 16 bits)
-    L.wscale = take(rows);
+    L.late = o;
+    for (int l = 0; l < m->bot_layers; ++l) L.bot_part[l] = part(m->bot_dims[l], m->bot_dims[l + 1]);
+    for (int l = 0; l < m->top_layers; ++l) L.top_part[l] = part(m->top_dims[l], m->top_dims[l + 1]);
     L.grads = take(P);
+    L.late_end = o;
     L.gmax = take((size_t)dqrm::kMaxGradTensors * dqrm::kGradMaxSlots * dqrm::kGradMaxStride);
     L.loss_terms = take((size_t)batch);
     L.total = o;
@@ -1295,7 +1308,7 @@ hipError_t launch_weight_grads(hipStream_t st, dqrm::GemmGroup &grp)
     return hipGetLastError();
 }
 
-// The weights that the forward and the input gradients use, and their codes and scales if they are quantised.
+// The weights that the forward and the input gradients use, and their codes and scales if they are quantised (and there is room).
 struct LayerWeights {
     const float *w;
     const unsigned short *codes, *low;
@@ -1439,8 +1452,8 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
     for (int l = 0; l < m->top_layers; ++l) top_wf[l] = {m->top_w[l], nullptr, nullptr, nullptr};
     for (int l = 0; l < m->bot_layers; ++l) bot_wf[l] = {m->bot_w[l], nullptr, nullptr, nullptr};
     if (wbits) {
-        float *wq = quant->wq ? quant->wq : F(L.wq), *scale = F(L.wscale);
-        unsigned short *codes = reinterpret_cast<unsigned short *>(ws + L.wcodes);
+        float *wq = quant->wq ? quant->wq : F(L.wq);
+        size_t free = L.late;
         dqrm::FqGroup fq{};
         fq.qmax = (float)((1 << (wbits - 1)) - 1);
         int rows = 0;
@@ -1456,13 +1469,17 @@ int32_t dqrm_dense_step_quant(const dqrm_dense_model_t *m, const dqrm_dense_quan
             hipError_t e = hipSuccess;
             if (fq.count == dqrm::kGemmMaxGroup) e = flush_fq();
             dqrm::FqLayer &q = fq.l[fq.count++];
-            const int pitch = code_pitch(in);
-            q.W = W, q.Wq = wq, q.codes = codes, q.low = codes + (size_t)out * pitch, q.scale = scale, q.out = out, q.in = in, q.row_begin = rows, q.pitch = pitch;
+            q.W = W, q.Wq = wq, q.out = out, q.in = in, q.row_begin = rows, q.pitch = code_pitch(in);
+            q.codes = q.low = nullptr, q.scale = nullptr;
+            const LayerCodes at(free, in, out);
+            if (at.end <= L.late_end) {
+                q.codes = reinterpret_cast<unsigned short *>(ws + at.codes), q.low = reinterpret_cast<unsigned short *>(ws + at.low);
+                q.scale = F(at.scale);
+                free = at.end;
+            }
             rows += out;
-            *wf = {wq, q.codes, q.low, scale};
+            *wf = {wq, q.codes, q.low, q.scale};
             wq += (size_t)out * in;
-            codes += 2 * (size_t)out * pitch;
-            scale += scale_rows(out);
             return e;
         };
         for (int l = 0; l < m->top_layers; ++l)

@@ -1229,8 +1229,8 @@ __global__ __launch_bounds__(256) void grad_quant_ec_kernel(SgdGroup grp)
 struct FqLayer {
     const float *W;
     float *Wq;
-    unsigned short *codes, *low; // [out][pitch] bfloat16, zeros from `in` on; low: see GemmArgs
-    float *scale;          // [out]
+    unsigned short *codes, *low; // [out][pitch] bfloat16, zeros from `in` on; low: see GemmArgs; null: not wanted
+    float *scale;          // [out], if they are
     int out, in, row_begin, pitch;
 };
 struct FqGroup {
@@ -1251,7 +1251,7 @@ __global__ __launch_bounds__(256) void mlp_fake_quant_kernel(FqGroup grp)
     const FqLayer &L = grp.l[q];
     const float *w = L.W + (long long)(row - L.row_begin) * L.in;
     float *wq = L.Wq + (long long)(row - L.row_begin) * L.in;
-    unsigned short *codes = L.codes + (long long)(row - L.row_begin) * L.pitch, *low = L.low + (long long)(row - L.row_begin) * L.pitch;
+    const long long code_row = (long long)(row - L.row_begin) * L.pitch;
     float m = 0.0f;
     for (int i = lane; i < L.in; i += kWave) m = fmaxf(m, fabsf(w[i]));
     m = wave_max(m);
@@ -1261,10 +1261,12 @@ __global__ __launch_bounds__(256) void mlp_fake_quant_kernel(FqGroup grp)
         const int c = code_i<false>(w[i], sc, -grp.qmax - 1.0f, grp.qmax);
         const float v = sc.s * (float)c;
         wq[i] = v;
-        low[i] = (unsigned short)(__float_as_uint(__builtin_fmaf(-sc.s, (float)c, v) * sc.y) >> 16);
-        codes[i] = (unsigned short)(__float_as_uint((float)c) >> 16); // (exact: 8 bits)
+        if (!L.codes) continue; // (wave-uniform)
+        L.low[code_row + i] = (unsigned short)(__float_as_uint(__builtin_fmaf(-sc.s, (float)c, v) * sc.y) >> 16);
+        L.codes[code_row + i] = (unsigned short)(__float_as_uint((float)c) >> 16); // (exact: 8 bits)
     }
-    for (int i = L.in + lane; i < L.pitch; i += kWave) codes[i] = low[i] = 0;
+    if (!L.codes) return;
+    for (int i = L.in + lane; i < L.pitch; i += kWave) L.codes[code_row + i] = L.low[code_row + i] = 0;
     if (lane == 0) L.scale[row - L.row_begin] = sc.s;
 }
 

@@ -229,6 +229,22 @@ def test_dense_workspace_for_a_batch_holds_smaller_ones():
         assert dq.dqrm_dense_workspace_bytes(m, 32768) == 0
 
 
+def test_dense_workspace_takes_no_more_room_for_quantised_weights():
+    """The size does not know of them: a workspace that a program has sized for FP32 weights, or for quantised ones by an earlier
+    version, stays large enough.  Sizes by version 0.1 for the Criteo shapes and for a model of narrow layers (256 CUs)."""
+    def model(T, D, bot, top):
+        bot, top = bot + [D], [D + (T + 1) * T // 2] + top + [1]
+        w = lambda d: [np.zeros((o, i), np.float32) for i, o in zip(d[:-1], d[1:])]  # noqa: E731
+        b = lambda d: [np.zeros(o, np.float32) for o in d[1:]]  # noqa: E731
+        return dq.DenseModel(T, D, bot, w(bot), b(bot), top, w(top), b(top), "cpu")
+
+    for m, sizes in ((model(26, 16, [13, 512, 256, 64], [512, 256]), (5860864, 7875840, 49382656, 146924800)),
+                     (model(26, 64, [13, 512, 256], [512, 512, 256]), (9299200, 11867136, 59660032, 183940864)),
+                     (model(2, 8, [20, 24, 17], [20]), (151040, 236544, 1562880, 5568768))):
+        for batch, most in zip((1, 128, 2048, 8192), sizes):
+            assert 0 < dq.dqrm_dense_workspace_bytes(m, batch) <= most
+
+
 def test_product_never_touches_the_oracle():
     """the HIP path and its binding share nothing with oracle/: no import, include, link or path."""
     pkg = os.path.join(ROOT, "paper_2410_20046_amd")

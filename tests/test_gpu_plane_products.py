@@ -162,11 +162,13 @@ def test_products_of_floats_next_to_the_largest(oracle, B):
 
 # Quantised weights take three products, their codes as one plane (and, forward, the rounding of scale * code as another): the bound is
 # that of six.  Tiles as above (at 8190 128 x 128, 128 x 64; at 700 64 x 64), reductions of less than a slab, of whole slabs and with a
-# rest, inputs that fill a padded row and that do not.
+# rest, inputs that fill a padded row and that do not; and layers so narrow, of so few samples, that not all codes find room (the others
+# take six products).
 @pytest.mark.gpu
 @pytest.mark.parametrize("bits", [4, 8])
 @pytest.mark.parametrize("T,D,B,bot,top,seed", [
-    (3, 16, 700, [20, 100], [130, 70], 1), (2, 16, 8190, [20, 256], [512, 250], 1), (2, 8, 65, [64, 5], [4, 33], 1), (3, 64, 300, [128, 65], [97, 64], 2)])
+    (3, 16, 700, [20, 100], [130, 70], 1), (2, 16, 8190, [20, 256], [512, 250], 1), (2, 8, 65, [64, 5], [4, 33], 1), (3, 64, 300, [128, 65], [97, 64], 2),
+    (2, 8, 40, [20, 24, 17], [20], 3)])
 def test_gradients_of_quantised_weights_to_the_same_precision(oracle, T, D, B, bot, top, seed, bits):
     rng = np.random.default_rng(seed)
     bot, top = _layers(rng, bot + [D]), _layers(rng, [D + (T + 1) * T // 2] + top + [1])
