@@ -601,6 +601,16 @@ struct CodeOperand {
     }
 };
 
+// Where a request past the last slab of a reduction of k starts.  Codes and scales are read 16 bytes at a time from addresses that
+// are multiples of that, eight r by eight; floats from any.
+constexpr __host__ __device__ int last_slab(int k, int bk, bool codes)
+{
+    const int r = k > bk ? k - bk : 0;
+    return codes ? r / 8 * 8 : r;
+}
+static_assert(last_slab(415, 32, true) == 376 && last_slab(367, 64, true) == 296 && last_slab(33, 32, true) == 0 && last_slab(512, 32, true) == 480 &&
+              last_slab(415, 32, false) == 383 && last_slab(20, 32, true) == 0, "inside the reduction, and of a whole vector");
+
 // Tile `local` of product g (one slice of its reduction, and the rows' sums beside it, if SPLIT).  lds0, lds1: kSlabBytes each.
 template <typename TILE, int A_MODE, int B_MODE, bool SPLIT>
 __device__ __forceinline__ void gemm_planes_tile(const GemmArgs &g, int local, char *lds0, char *lds1)
@@ -639,7 +649,7 @@ __device__ __forceinline__ void gemm_planes_tile(const GemmArgs &g, int local, c
     // The slabs in their order: the partial one first, if there is one (it is read in another way, and the loop below has no
     // branch).  Requests past the last slab read some slab of the operands that exists, and nobody looks at it.
     const int whole = (r_end - r_begin) / BK, tail = r_end - r_begin - whole * BK;
-    const int slabs = whole + (tail > 0), r_slab = r_begin - (tail > 0 ? BK : 0), r_last = max(g.K - BK, 0);
+    const int slabs = whole + (tail > 0), r_slab = r_begin - (tail > 0 ? BK : 0), r_last = last_slab(g.K, BK, CODES);
     auto fetch = [&](int q, int s) {
         const int r0 = min(r_slab + s * BK, r_last);
         a.fetch(q, r0);
