@@ -338,6 +338,7 @@ struct DedupePlan {
     int num_batches;
 };
 
+constexpr int kDdFullRanges = 32; // ranges of a partitioned table, if there is room
 DedupePlan plan_dedupe(const dqrm_tables_t *tables, int32_t batch, int32_t num_batches, const dqrm_dedupe_batch_t *batches)
 {
     const int T = tables->num_tables, D = tables->dim;
@@ -379,12 +380,14 @@ DedupePlan plan_dedupe(const dqrm_tables_t *tables, int32_t batch, int32_t num_b
     int64_t most = 0; // lookups of any table
     for (int i = 0; i < num_batches; ++i) most = std::max<int64_t>(most, std::min<int64_t>(da.b[i].N, da.b[i].limit));
     // From two tiles per table on every range's workgroup reading the whole table costs more than sorting the tiles by
-    // range first: 26 x 65536 lookups 110 us, against 215 with 8 ranges that each read everything.
-    const bool partition = avg > 2 * dqrm::kDdTile && partitionable(T, least_n);
+    // range first where rows are popular (26 tables, Zipf 1.1 / evenly spread, us, tiles first / everything read: 65536 lookups 115 / 220 and 83 /
+    // 110; 24000 60 / 79 and 53 / 39); where the ranges' workgroups leave half of the CUs idle, from three (4 tables, 24000: 38 / 34 and 30 / 29;
+    // 32000: 42 / 70 and 33 / 34).
+    const bool partition = avg > (wgs * kDdFullRanges * 2 <= num_cus() ? 3 : 2) * dqrm::kDdTile && partitionable(T, least_n);
     // Where the tables alone are workgroups for half of the CUs or more, none is cut (dedupe_table_kernel): 208 x 8192 lookups 60
     // (dedupe_kernel, one range: 67), 1024 x 4096 181 (187); with fewer lookups dedupe_kernel's shorter code counts for more.
     const bool whole = !partition && avg > 2048 && most <= dqrm::kTableCap && num_cus() <= wgs * 2;
-    int64_t parts = whole ? 1 : partition ? 32 : std::max<int64_t>(std::min<int64_t>({num_cus() / wgs, avg / 256, 16}), (avg - 1) / 8192 * 2);
+    int64_t parts = whole ? 1 : partition ? kDdFullRanges : std::max<int64_t>(std::min<int64_t>({num_cus() / wgs, avg / 256, 16}), (avg - 1) / 8192 * 2);
     parts = std::max<int64_t>(1, std::min(parts, most_parts));
     da.parts = (int)parts;
     da.bags_per_part = (int)((batch + parts - 1) / parts);
@@ -401,7 +404,11 @@ DedupePlan plan_dedupe(const dqrm_tables_t *tables, int32_t batch, int32_t num_b
     //   255 tables x  128 lookups and one of 65536: 261 (7600); one of 16384: 70 (670)
     //    25 tables x 2048 and one of 65536:          75 (472); 25 x 512 and one of 16384: 51 (135)
     // where no table has that many: 26 x 2048 19.1 (18.5), 26 x 8192 32.5 (31.6).  A bound on a table's lookups spares that.
-    const int cap = avg <= 512 ? 2048 : (avg <= 4096 && parts > 1 ? 4096 : 8192);
+    // Of a partitioned table the ranges hold about equally many, so half the LDS is enough, and two workgroups share a CU, unless there
+    // is a CU for each, or they hold so many that some would overflow it (Zipf 1.1 / evenly spread, us, half / whole: 8 x 65536 76 / 49 and
+    // 47 / 42; ranges of 1700, 100 x 17000 89 / 108 and 88 / 112; of 2500, 128 x 20000 142 / 129 and 132 / 136; of 3300, 100 x 32768 173 / 161
+    // and 179 / 162; of 4096, 64 x 65536 240 / 200 and 224 / 189).
+    const int cap = partition ? (avg > 2560 * parts || wgs * parts <= num_cus() ? 8192 : 4096) : avg <= 512 ? 2048 : (avg <= 4096 && parts > 1 ? 4096 : 8192);
     const int64_t light = std::max<int64_t>(cap, avg + avg / 4);
     const bool uneven = !partition && !whole && most > light;
     if (uneven) {
@@ -425,7 +432,10 @@ void launch_dedupe_sort(const DedupePlan &plan, hipStream_t st)
     if (plan.partition) {
         hipLaunchKernelGGL(dqrm::dedupe_partition_kernel, dim3(da.T, plan.num_batches, (unsigned)((plan.most + dqrm::kDdTile - 1) / dqrm::kDdTile)),
                            dim3(dqrm::kDdPartThreads), 0, st, da);
-        hipLaunchKernelGGL((dqrm::dedupe_kernel<512, 4096, true, false>), grid, dim3(512), 0, st, da);
+        if (plan.cap == 4096)
+            hipLaunchKernelGGL((dqrm::dedupe_kernel<512, 4096, true, false>), grid, dim3(512), 0, st, da);
+        else
+            hipLaunchKernelGGL((dqrm::dedupe_kernel<1024, 8192, true, false>), grid, dim3(1024), 0, st, da);
     } else if (plan.whole) {
         hipLaunchKernelGGL(dqrm::dedupe_table_kernel, grid, dim3(dqrm::kTableThreads), 0, st, da);
     } else if (plan.uneven) {

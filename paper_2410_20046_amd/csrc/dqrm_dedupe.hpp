@@ -345,10 +345,12 @@ __device__ __forceinline__ uint2 digit_places(const unsigned short *cnt, int wav
 
 // Tables of many lookups: dedupe_kernel would read all of them in every range's workgroup.  Here a workgroup takes a tile
 // of kDdTile lookups and sorts it by range (one stable pass of the radix sort), so that a range's workgroup finds its
-// lookups in one run per tile.  The ranges lie between keys of a sample, the same for all tiles of a table: they hold about equally many
-// lookups wherever the popular rows are, so a range's workgroup can be half as large, and two share a CU (26 tables x 65536 lookups, us,
-// here and in dedupe_kernel: ranges of equal width, workgroups of 1024 threads 11.2 + 107, of 512 153; by a sample of 256, of 512 17.9 + 73.5; of 512, whose ranks
-// alone are 262144 comparisons a workgroup, 25.8 + 73.6).
+// lookups in one run per tile.  Where a sample, the same for all tiles of a table, shows popular rows the ranges lie between its keys: they
+// hold about equally many lookups, so a range's workgroup can be half as large, and two share a CU.  Where it shows none they are
+// equally wide, which evenly spread lookups fill better than a sample of so few can tell (8 of the sample to a range).  The whole
+// sort, us, Zipf 1.1 / 1.05 / 0.5 / evenly spread: 26 x 65536 lookups, equally wide 174 / 210 / 111 / 110, by the sample 124 / 112 / 124 / 125,
+// as it is now 115 / 101 / 107 / 83; 8 x 65536 138 / 89 / 43 / 43, 75 / 72 / 77 / 86, 49 / 49 / 47 / 42.  (A sample of 512, whose ranks alone are 262144
+// comparisons a workgroup, costs 8 more.)
 __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(DedupeArgs args)
 {
     constexpr int kWaves = kDdPartThreads / kWave, kItems = kDdTile / kDdPartThreads;
@@ -357,6 +359,7 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
     __shared__ __align__(16) unsigned short cnt[kWaves * 256], place[kWaves * 256];
     __shared__ int s_back[kWaves];
     __shared__ unsigned s_split[kDdRanges], s_bound[kDdRanges + 1];
+    __shared__ int s_hits[kDdRanges];
     const DedupeBatch &bt = args.b[blockIdx.y];
     const int t = blockIdx.x, tile = blockIdx.z, B = args.B;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -379,9 +382,18 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
     constexpr int kShare = kDdPartThreads / kDdPartSample;
     const int parts = args.parts;
     if (tid < kDdPartSample) s_key[tid] = (unsigned long long)sample < rows_t ? (unsigned)sample : rows_t;
-    if (tid < kDdRanges) s_split[tid] = 0u;
+    if (tid < kDdRanges) s_split[tid] = 0u, s_hits[tid] = 0;
     __syncthreads();
-    {
+    // Ranges of equal width do where the sample is spread over them as chance would (four standard deviations of a count), or where
+    // each is one row: no two of them can be better.
+    const unsigned share = args.by_parts.div(rows_t) + 1u;
+    if (tid < kDdPartSample) atomicAdd(&s_hits[s_key[tid] / share], 1);
+    __syncthreads();
+    static_assert(kDdRanges == kWave, "a lane each");
+    const float expected = (float)kDdPartSample * (float)share / (float)rows_t;
+    const float per_share = 1.0f / (float)share;
+    const bool equal = __builtin_amdgcn_readfirstlane(share == 1u || wave_max_int(s_hits[lane]) <= (int)(expected + 4.0f * sqrtf(expected)));
+    if (!equal) {
         const int j = tid / kShare, from = (tid % kShare) * (kDdPartSample / kShare);
         const unsigned k = s_key[j];
         int rank = 0;
@@ -399,7 +411,7 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
     __syncthreads();
     // (a key that bounds several ranges has the first of them to itself)
     if (tid <= parts) {
-        const unsigned b = tid == 0 ? 0u : tid == parts ? rows_t + 1u : s_split[tid] + (tid > 1 && s_split[tid] == s_split[tid - 1] ? 1u : 0u);
+        const unsigned b = equal ? min((unsigned)tid * share, rows_t + 1u) : tid == 0 ? 0u : tid == parts ? rows_t + 1u : s_split[tid] + (tid > 1 && s_split[tid] == s_split[tid - 1] ? 1u : 0u);
         s_bound[tid] = b;
         if (tile == 0) bt.ws.part_bound[(int64_t)t * (kDdRanges + 1) + tid] = b;
     }
@@ -417,10 +429,16 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
         const bool exists = wave_at + r * kWave + lane < len;
         key[r] = (unsigned long long)raw[r] < rows_t ? (unsigned)raw[r] : rows_t;
         if (exists && key[r] == rows_t) bad_index = true, bad_value = raw[r];
-        int d = 0; // the last range that begins at or before it
+        int d = 0;
+        if (equal) { // key / share: at most 63, so the rounded quotient is at most one off
+            d = (int)((float)key[r] * per_share);
+            const int rest = (int)(key[r] - (unsigned)d * share);
+            d += rest < 0 ? -1 : (rest >= (int)share ? 1 : 0);
+        } else { // the last range that begins at or before it
 #pragma unroll
-        for (int step = kDdRanges / 2; step >= 1; step >>= 1)
-            if (d + step < parts && s_bound[min(d + step, kDdRanges)] <= key[r]) d += step;
+            for (int step = kDdRanges / 2; step >= 1; step >>= 1)
+                if (d + step < parts && s_bound[min(d + step, kDdRanges)] <= key[r]) d += step;
+        }
         if (!exists) d = args.parts; // (padding: after every range)
         const unsigned long long peers = match_digit((unsigned)d, bits);
         const unsigned prev = my_cnt[d];
@@ -523,6 +541,11 @@ __device__ __forceinline__ void dedupe_body(const DedupeArgs &args, DedupeLds<TH
     const unsigned rows_t = (unsigned)(args.row_offsets[t + 1] - args.row_offsets[t]); // host: <= DQRM_MAX_TABLE_ROWS
 
     const int64_t *__restrict__ bag_offsets = offsets + (long long)t * B;
+    uint2 bound = make_uint2(0u, 0u); // (requested with the boundaries of the tables; of no meaning for a table without lookups)
+    if constexpr (PARTITIONED) {
+        const unsigned *at = ws.part_bound + (int64_t)t * (kDdRanges + 1) + part;
+        bound = make_uint2(at[0], at[1]);
+    }
     const TableExtent x = table_extent<THREADS>(offsets, t, B, N, bt.limit, tid, s_back);
     const long long lo = x.lo;
     const int n = x.n, base = (int)lo;
@@ -538,9 +561,8 @@ __device__ __forceinline__ void dedupe_body(const DedupeArgs &args, DedupeLds<TH
     unsigned range_lo = min((unsigned)part * share, rows_t + 1u), range_hi = min(range_lo + share, rows_t + 1u);
     static_assert(!PARTITIONED || !EXTRA, "a partitioned table has no further ranges");
     if constexpr (PARTITIONED) {
-        const unsigned *bound = ws.part_bound + (int64_t)t * (kDdRanges + 1) + part;
-        range_lo = n > 0 ? (unsigned)__builtin_amdgcn_readfirstlane((int)bound[0]) : 0u;
-        range_hi = n > 0 ? (unsigned)__builtin_amdgcn_readfirstlane((int)bound[1]) : 0u;
+        range_lo = n > 0 ? (unsigned)__builtin_amdgcn_readfirstlane((int)bound.x) : 0u;
+        range_hi = n > 0 ? (unsigned)__builtin_amdgcn_readfirstlane((int)bound.y) : 0u;
     }
     bool sampled = EXTRA && n > args.light;
     if (__builtin_expect(sampled, 0)) {
@@ -599,9 +621,9 @@ __device__ __forceinline__ void dedupe_body(const DedupeArgs &args, DedupeLds<TH
     auto request = [&](int i, Lookup &l) {
         i = min(i, count - 1);
         if constexpr (PARTITIONED) {
-            int at = run_from[0];
+            int at = run_from[0]; // (by differences: a choice among the runs' starts becomes an array in scratch memory, and every request waits)
 #pragma unroll
-            for (int w = 1; w < kDdTiles; ++w) at = i >= run_first[w] ? run_from[w] : at;
+            for (int w = 1; w < kDdTiles; ++w) at += i >= run_first[w] ? run_from[w] - run_from[w - 1] : 0;
             l.row = ws.part_key[at + i];
             l.pos = ws.part_pos[at + i];
         } else {

@@ -96,6 +96,35 @@ def test_ranges_by_a_sample(kind, T):
     assert run.status()[0] == run.dq.ERR_INDEX_OUT_OF_RANGE
 
 
+# The rules of partitioned tables: from two tiles per table on, with few tables from three; a workgroup that sorts 4096, or, where there is
+# a CU for each or a range has many lookups, 8192.  Beside each other tables that are cut into ranges of equal width (evenly spread
+# lookups, fewer rows than ranges, a few more) and by the sample (popular rows, at one end, a single row among many), bad indices in some.
+@pytest.mark.parametrize("T,n", [(5, 16_384), (5, 16_385), (4, 24_576), (4, 24_577), (8, 16_385), (9, 30_011), (9, 65_536), (100, 27_000), (128, 16_391)])
+def test_partitioned_tables_of_all_kinds(T, n):
+    rng = np.random.default_rng(T + n)
+    cards, idx = [], []
+    for t in range(T):
+        c = [900_000, 20, 33, 70_000, 5_000_000, 1_000, 40, 3][t % 8]
+        v = rng.integers(0, c, n)
+        if t % 8 == 3:  # popular rows all over the table
+            v = (np.minimum(rng.zipf(1.1, n), c) * 7919) % c
+        elif t % 8 == 4:
+            v = np.where(rng.random(n) < 0.8, np.minimum(rng.zipf(1.3, n), c) - 1, v)
+        elif t % 8 == 5:
+            v = np.where(rng.random(n) < 0.6, c // 2, v)
+        if t % 3 == 1:
+            v[rng.integers(0, n, 5)] = rng.choice([-1, c, 2 ** 40], 5)
+        cards.append(c)
+        idx.append(v)
+    wl = Workload(name="kinds", T=T, D=8, B=n, alpha=1.0, seed=1, cards=np.array(cards, np.int64))
+    idx, off = np.concatenate(idx).astype(np.int64), np.arange(T * n + 1, dtype=np.int64)
+    print(f"partitioned: {T} tables of {n} lookups", flush=True)
+    run, got = _dedupe(wl, idx, off, n)
+    for k, v in _expected(wl, idx, off, n).items():
+        assert_exact(got[k], v, f"T={T} n={n} {k}")
+    assert run.status()[0] == run.dq.ERR_INDEX_OUT_OF_RANGE
+
+
 @pytest.mark.parametrize("n", [400, 3000, 8000, 40000])
 @pytest.mark.parametrize("bags", ["ragged", "pairs", "sparse"])
 def test_hot_rows_and_bags(n, bags):
