@@ -596,14 +596,17 @@ bool step_sorts_with_forward(const DedupePlan &plan, dqrm::FwdArgs fa)
 }
 
 // A workgroup per table where a table is little work for one CU: with up to 128 KB of gradient rows to add up it spares two launches and
-// several round trips (us a step, one workgroup per table / three launches: 4 x 128 x 16 14.6 / 20.5, 26 x 1024 x 16 23.5 / 30.7,
-// 26 x 2048 x 16 33.6 / 35.4, 60 x 4000 x 8 48.1 / 63.6, 26 x 256 x 64 21.3 / 28.6; 256 KB: 26 x 1024 x 64 38.3 / 34.9).  The host knows
-// only the average table: a batch whose bags do not all look as if they held equally many lookups may have one table with most of
-// them, so all of it is to be little (1 MB in one table: about 50 us against 30).
+// several round trips (us a step, one workgroup per table / three launches: 4 x 128 x 16 14.6 / 20.5, 26 x 1024 x 16 24.3 / 32.6,
+// 26 x 2048 x 16 33.5 / 36.3, 1 x 2048 x 16 26.9 / 28.2, 200 x 2048 x 16 55.8 / 95.6, 26 x 256 x 128 28.2 / 31.6; 256 KB: 26 x 1024 x 64 38.3 /
+// 34.9), of up to 3072 lookups while most CUs have no table (1 x 3000 x 8 30.1 / 30.3, 1 x 4096 x 8 37.0 / 32.7, 26 x 4096 x 8 44.1 / 43.5, 40 x 4096
+// x 8 49.1 / 55.2).  The host knows only the average table: a batch whose bags do not all look as if they held equally many lookups may
+// have one table with most of them, so all of it is to be little (1 MB in one table: about 50 us against 30).  As many lookups as
+// bags, or a multiple, may be unequal all the same, which no user of one lookup per bag or equally many has: 26 x 1024 bags x 16, 27 lookups a bag
+// in one table and one in the others, 113 us against 100; 26 x 2048 with all lookups in one table 192 against 156.
 bool step_by_table(const DedupePlan &plan, const dqrm::SegArgs &sa)
 {
-    const int64_t row = sa.D * (int64_t)sizeof(float), T = sa.T, bags = T * sa.B;
-    return !plan.partition && plan.args.parts <= dqrm::kStepParts && (sa.N + T - 1) / T * row <= (128 << 10) &&
+    const int64_t row = sa.D * (int64_t)sizeof(float), T = sa.T, bags = T * sa.B, avg = (sa.N + T - 1) / T;
+    return !plan.partition && plan.args.parts <= dqrm::kStepParts && avg * row <= (128 << 10) && (avg <= 3072 || T * 8 > num_cus()) &&
            (sa.N % bags == 0 || sa.N * row <= (1 << 20));
 }
 

@@ -95,7 +95,7 @@ def test_one_call_is_its_parts_for_gradients_that_are_not_finite(D):
 @pytest.mark.parametrize("D,B,rows,lens", [
     (16, 2048, [5000, 2, 300000], 1), (16, 2049, [5000, 2, 300000], 1), (8, 1000, [1000000] + [70] * 15, "one long"),
     (256, 128, [9, 2000, 1], 1), (128, 257, [3000, 50], 1), (64, 8193, [100000, 3], 1), (8, 6200, [900, 5], "ragged"), (24, 40, [4] * 70, "ragged"),
-    (40, 1, [7, 1], "ragged")])
+    (40, 1, [7, 1], "ragged"), (8, 3072, [5000, 1, 40], 1), (8, 3073, [5000, 1, 40], 1), (8, 4096, [700, 90, 3] * 11, 1)])
 def test_one_call_is_its_parts_at_the_edges_of_its_rules(D, B, rows, lens):
     rng = np.random.default_rng(D + B)
     idx, off = _batch(rng, rows, B, lambda T, t, B: np.ones(B, np.int64) if lens == 1 else rng.integers(0, 5, B) if lens == "ragged"
