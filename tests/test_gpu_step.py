@@ -17,7 +17,7 @@ def _batch(rng, rows, B, lens):
     return idx, off
 
 
-def _runs(rows, D, B, idx, off, grad, mode):
+def _runs(rows, D, B, idx, off, grad, mode, cap=None):
     """The same step twice from the same tables: in one call, and in its parts."""
     import torch
     import paper_2410_20046_amd as dq
@@ -33,6 +33,7 @@ def _runs(rows, D, B, idx, off, grad, mode):
         run.find_scale()
         run.pack()
         b = run.bufs
+        b.cap = cap or b.cap
         for step in range(2):  # (the second finds the workspace and the buffers as the first left them)
             if one_call:
                 dq.dqrm_fwd_bwd_step(run.tables, b, run.idx, run.off, run.grad, 0.1, mode)
@@ -149,3 +150,52 @@ def test_the_workspace_of_one_call_serves_a_segment_sum(D, B, rows, bag):
     for x, y, n in zip(*results, ("values", "g_absmax")):
         assert_exact(x.view(np.uint32), y.view(np.uint32), n)
     assert np.abs(results[0][0]).max() > 0 and run.status()[0] == 0
+
+
+# What the data may have wrong: bad indices at both ends of a table, offsets out of order inside a table, tables whose boundaries go back (and
+# so share lookups with others), a batch that does not start at 0 or ends beyond its indices, room for fewer rows than there are, a
+# table over the limit.  Nothing is read or written outside a table: everything is as the separate calls leave it.  (16 columns: a workgroup per
+# table; 64: three launches.  Of several problems any one is recorded.)
+@pytest.mark.parametrize("D,B", [(16, 64), (64, 1024)])
+@pytest.mark.parametrize("kind", ["indices", "inside", "boundary", "first", "last", "capacity"])
+def test_one_call_is_its_parts_for_bad_batches(kind, D, B):
+    import paper_2410_20046_amd as dq
+
+    rng = np.random.default_rng(D + len(kind))
+    rows = [50, 3, 900, 7]
+    T = len(rows)
+    idx, off = _batch(rng, rows, B, lambda T, t, B: np.ones(B, np.int64))
+    expected = {dq.ERR_BAD_OFFSETS}
+    if kind == "indices":
+        for t, bad in enumerate([-1, rows[1], 2 ** 40, rows[3]]):
+            idx[t * B], idx[t * B + B - 1], idx[t * B + 9] = bad, bad, -2 ** 40
+        expected = {dq.ERR_INDEX_OUT_OF_RANGE}
+    elif kind == "inside":
+        off[B + 5], off[B + 6], off[3 * B - 4] = off[B + 6], off[B + 5] - 2, off[3 * B - 4] + 30
+    elif kind == "boundary":
+        off[B] = 2 * B + 7
+        expected |= {dq.ERR_INDEX_OUT_OF_RANGE}  # (table 0 has indices of the others)
+    elif kind == "first":
+        off[0] = -3
+    elif kind == "last":
+        off[T * B] = T * B + 9
+    grad = (rng.standard_normal((B, T, D)) * 1e-4).astype(np.float32)
+    print(f"bad batch: {kind}, {T} tables x {B} x {D}", flush=True)
+    a, b = _runs(rows, D, B, idx, off, grad, 1, cap=60 if kind == "capacity" else None)
+    status = a.pop("status"), b.pop("status")
+    _compare(a, b)
+    assert all(s[0] == 0 if kind == "capacity" else s[0] in expected for s in status), status
+    assert a["num_unique"][0] > 60 or kind != "capacity"
+
+
+def test_one_call_is_its_parts_for_a_table_over_the_limit():
+    import paper_2410_20046_amd as dq
+
+    T, B, D = 35, 2000, 8
+    rng = np.random.default_rng(1)
+    idx, off = _batch(rng, [900] * T, B, lambda T, t, B: np.full(B, T if t == 0 else 0))
+    grad = (rng.standard_normal((B, T, D)) * 1e-4).astype(np.float32)
+    a, b = _runs([900] * T, D, B, idx, off, grad, 1)
+    assert a.pop("status")[0] == b.pop("status")[0] == dq.ERR_CAPACITY
+    _compare(a, b)
+    assert a["num_unique"][0] == 0
