@@ -325,7 +325,9 @@ int32_t dqrm_quant_update(const dqrm_tables_t *tables, int64_t capacity, int64_t
 
 /* One step of the tables on one GPU: dqrm_embbag_fwd, dqrm_dedupe, dqrm_segment_sum
  * and dqrm_quant_update, with their arguments and, bit for bit, their outputs, for a
- * caller who has grad_out beforehand and exchanges nothing in between.  In one call
+ * caller who has grad_out beforehand and exchanges nothing in between.  (Where sums are
+ * NaN and bags hold several lookups, the calls themselves leave open which maxima a NaN
+ * hides; so does this one.)  In one call
  * the forward shares a launch with the sort, and the rest is one launch for batches
  * of few lookups per table.  (Of several problems in a batch any one is recorded.) */
 int32_t dqrm_fwd_bwd_step(const dqrm_tables_t *tables, const int64_t *indices, const int64_t *offsets, int32_t batch,
@@ -376,6 +378,8 @@ int32_t dqrm_dense_step(const dqrm_dense_model_t *model, int32_t batch, const fl
  *   weight_bits = 4 (or 8): every linear layer's weights are fake-quantised channel-wise for the forward and
  *     the input gradients -- one scale per output row, s_o = max(max_i |W[o][i]| / (2^(bits-1)-1), 1e-8),
  *     Wq = s_o * clamp(rint(W / s_o)) -- while the step goes to the FP32 weights (straight-through);
+ *     the forward takes Wq as rounded to a float, the input gradients that or the product before its rounding
+ *     (2^-24 of it apart: less than a product's own error);
  *     biases and activations stay FP32 (model-quantisation appendix: "a scale for every row inside the
  *     linear layer weights"; whole-model results section).  weight_bits = 0: FP32 weights.
  *   grad_bits = 8: the gradient of every parameter tensor (each layer's weight matrix and each bias vector

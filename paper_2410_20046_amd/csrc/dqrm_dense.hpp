@@ -893,8 +893,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_wave_kernel(GemmOne one)
 }
 
 // Several split products in one launch (kOpWide operands): the weight gradients of all layers, a workgroup per tile.
-// Measured: the Terabyte shape's layers at batch 8192 (12.4 GFLOP) 82 us, the Kaggle shape's at 2048 (1.96 GFLOP) 21; on the
-// fp32 matrix instructions 171 and 34.5.
+// Measured: the Terabyte shape's layers at batch 8192 (12.4 GFLOP) 85-89 us in the step's kernel trace, the Kaggle shape's at 2048
+// (1.96 GFLOP) 20-22; on the fp32 matrix instructions 171 and 34.5.
 __global__ __launch_bounds__(kPlaneThreads) void gemm_split_group_kernel(GemmGroup grp)
 {
     constexpr int kLds = PlaneTile128::kSlabBytes > PlaneTile64::kSlabBytes ? PlaneTile128::kSlabBytes : PlaneTile64::kSlabBytes;

@@ -52,7 +52,7 @@ struct StepTableArgs {
 // where dedupe_finish_kernel puts the long ones first: a sum over few chunks gains nothing by that).  Rows of the update stay in
 // LDS, which lets its weights, the only data that come from far, be requested before the long segments are added up.  More loads to a
 // thread in flight, or the first ones of both lists requested together, cost more in registers and code than they save.
-// 4 tables x 128 lookups x 16: the step 20.5 -> 14.6 us; 26 x 2048 x 16: 35.4 -> 33.6.
+// 4 tables x 128 lookups x 16: the step 20.5 -> 14.6 us (passes one behind the other, code warm); 26 x 2048 x 16: 36.3 -> 33.5.
 template <int G>
 __global__ __launch_bounds__(kStepThreads) void step_table_kernel(StepTableArgs a)
 {
