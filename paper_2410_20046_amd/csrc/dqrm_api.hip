@@ -380,9 +380,9 @@ DedupePlan plan_dedupe(const dqrm_tables_t *tables, int32_t batch, int32_t num_b
     int64_t most = 0; // lookups of any table
     for (int i = 0; i < num_batches; ++i) most = std::max<int64_t>(most, std::min<int64_t>(da.b[i].N, da.b[i].limit));
     // From two tiles per table on every range's workgroup reading the whole table costs more than sorting the tiles by
-    // range first where rows are popular (26 tables, Zipf 1.1 / evenly spread, us, tiles first / everything read: 65536 lookups 115 / 220 and 83 /
-    // 110; 24000 60 / 79 and 53 / 39); where the ranges' workgroups leave half of the CUs idle, from three (4 tables, 24000: 38 / 34 and 30 / 29;
-    // 32000: 42 / 70 and 33 / 34).
+    // range first where rows are popular (26 tables, Zipf 1.1 / evenly spread, us, tiles first / everything read: 65536 lookups 112 / 220 and 82 /
+    // 110; 24000 57 / 79 and 53 / 39); where the ranges' workgroups leave half of the CUs idle, from three (4 tables, 24000: 38 / 34 and 30 / 29;
+    // 32000: 39 / 70 and 33 / 34).
     const bool partition = avg > (wgs * kDdFullRanges * 2 <= num_cus() ? 3 : 2) * dqrm::kDdTile && partitionable(T, least_n);
     // Where the tables alone are workgroups for half of the CUs or more, none is cut (dedupe_table_kernel): 208 x 8192 lookups 60
     // (dedupe_kernel, one range: 67), 1024 x 4096 181 (187); with fewer lookups dedupe_kernel's shorter code counts for more.

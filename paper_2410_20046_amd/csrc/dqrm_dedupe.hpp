@@ -348,9 +348,10 @@ __device__ __forceinline__ uint2 digit_places(const unsigned short *cnt, int wav
 // lookups in one run per tile.  Where a sample, the same for all tiles of a table, shows popular rows the ranges lie between its keys: they
 // hold about equally many lookups, so a range's workgroup can be half as large, and two share a CU.  Where it shows none they are
 // equally wide, which evenly spread lookups fill better than a sample of so few can tell (8 of the sample to a range).  The whole
-// sort, us, Zipf 1.1 / 1.05 / 0.5 / evenly spread: 26 x 65536 lookups, equally wide 174 / 210 / 111 / 110, by the sample 124 / 112 / 124 / 125,
-// as it is now 115 / 101 / 107 / 83; 8 x 65536 138 / 89 / 43 / 43, 75 / 72 / 77 / 86, 49 / 49 / 47 / 42.  (A sample of 512, whose ranks alone are 262144
-// comparisons a workgroup, costs 8 more.)
+// sort, us, Zipf 1.1 / 1.05 / evenly spread: 26 x 65536 lookups, equally wide 174 / 210 / 110, by the sample in any case 124 / 112 / 125, as it is
+// now 112 / 100 / 82; 8 x 65536 138 / 89 / 43, 75 / 72 / 86, 47 / 46 / 41.  Bound by vector instructions, of which a workgroup has one CU's: the
+// ranks by quarters and a search past whose last range no key lies took 18.7 -> 16.2 us of it at 26 x 65536.  (A sample of 512 has four times
+// the comparisons, 8 us more.  The items' loop not unrolled, for a kernel of 7.6 instead of 10.7 KB: 18.3.)
 __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(DedupeArgs args)
 {
     constexpr int kWaves = kDdPartThreads / kWave, kItems = kDdTile / kDdPartThreads;
@@ -359,7 +360,7 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
     __shared__ __align__(16) unsigned short cnt[kWaves * 256], place[kWaves * 256];
     __shared__ int s_back[kWaves];
     __shared__ unsigned s_split[kDdRanges], s_bound[kDdRanges + 1];
-    __shared__ int s_hits[kDdRanges];
+    __shared__ int s_hits[kDdRanges], s_rank[kDdPartSample];
     const DedupeBatch &bt = args.b[blockIdx.y];
     const int t = blockIdx.x, tile = blockIdx.z, B = args.B;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -379,9 +380,8 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
         raw[r] = *reinterpret_cast<const long long *>(src + (unsigned)min(wave_at + r * kWave + lane, len - 1) * 8u);
     }
     // the sample, its ranks (four threads to a key), the ranges between
-    constexpr int kShare = kDdPartThreads / kDdPartSample;
     const int parts = args.parts;
-    if (tid < kDdPartSample) s_key[tid] = (unsigned long long)sample < rows_t ? (unsigned)sample : rows_t;
+    if (tid < kDdPartSample) s_key[tid] = (unsigned long long)sample < rows_t ? (unsigned)sample : rows_t, s_rank[tid] = 0;
     if (tid < kDdRanges) s_split[tid] = 0u, s_hits[tid] = 0;
     __syncthreads();
     // Ranges of equal width do where the sample is spread over them as chance would (four standard deviations of a count), or where
@@ -394,26 +394,38 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
     const float per_share = 1.0f / (float)share;
     const bool equal = __builtin_amdgcn_readfirstlane(share == 1u || wave_max_int(s_hits[lane]) <= (int)(expected + 4.0f * sqrtf(expected)));
     if (!equal) {
-        const int j = tid / kShare, from = (tid % kShare) * (kDdPartSample / kShare);
+        // A wave has 64 keys and compares them with a quarter of the sample: a key counts those below it, and the equal ones in front of
+        // it, which are all of an earlier quarter and none of a later one.
+        const int mine = wave % 4 * kWave, quarter = wave / 4 * kWave, j = mine + lane;
         const unsigned k = s_key[j];
         int rank = 0;
-#pragma unroll 2
-        for (int i = from; i < from + kDdPartSample / kShare; i += 4) {
-            const uint4 o = *reinterpret_cast<const uint4 *>(s_key + i);
-            rank += (o.x < k || (o.x == k && i < j)) + (o.y < k || (o.y == k && i + 1 < j)) + (o.z < k || (o.z == k && i + 2 < j)) +
-                    (o.w < k || (o.w == k && i + 3 < j));
+        static_assert(kDdPartThreads == 4 * kDdPartSample && kDdPartSample == 4 * kWave, "quarters");
+        if (quarter == mine) { // (wave-uniform)
+#pragma unroll 4
+            for (int i = 0; i < kWave; ++i) rank += s_key[quarter + i] < k + (i < lane ? 1u : 0u);
+        } else {
+            const unsigned limit = k + (quarter < mine ? 1u : 0u);
+#pragma unroll 4
+            for (int i = 0; i < kWave; i += 4) {
+                const uint4 o = *reinterpret_cast<const uint4 *>(s_key + quarter + i);
+                rank += (o.x < limit) + (o.y < limit) + (o.z < limit) + (o.w < limit);
+            }
         }
-#pragma unroll
-        for (int d = 1; d < kShare; d <<= 1) rank += __shfl_xor(rank, d, kWave);
-        const int p = (rank * parts + kDdPartSample - 1) / kDdPartSample; // the range that it would be the first key of
-        if (p > 0 && p < parts && p * kDdPartSample / parts == rank) s_split[p] = k;
+        atomicAdd(&s_rank[j], rank);
+        __syncthreads();
+        if (tid < kDdPartSample) {
+            const int r = s_rank[tid], p = (r * parts + kDdPartSample - 1) / kDdPartSample; // the range that it would be the first key of
+            if (p > 0 && p < parts && p * kDdPartSample / parts == r) s_split[p] = k;
+        }
     }
     __syncthreads();
     // (a key that bounds several ranges has the first of them to itself)
-    if (tid <= parts) {
-        const unsigned b = equal ? min((unsigned)tid * share, rows_t + 1u) : tid == 0 ? 0u : tid == parts ? rows_t + 1u : s_split[tid] + (tid > 1 && s_split[tid] == s_split[tid - 1] ? 1u : 0u);
+    if (tid <= kDdRanges) {
+        unsigned b = equal ? min((unsigned)tid * share, rows_t + 1u) : tid == 0 ? 0u : tid == parts ? rows_t + 1u : 0u;
+        if (!equal && tid > 0 && tid < parts) b = s_split[tid] + (tid > 1 && s_split[tid] == s_split[tid - 1] ? 1u : 0u);
+        if (tid > parts) b = ~0u; // (no range)
         s_bound[tid] = b;
-        if (tile == 0) bt.ws.part_bound[(int64_t)t * (kDdRanges + 1) + tid] = b;
+        if (tile == 0 && tid <= parts) bt.ws.part_bound[(int64_t)t * (kDdRanges + 1) + tid] = b;
     }
     __syncthreads();
     unsigned short *my_cnt = cnt + wave * 256, *my_place = place + wave * 256;
@@ -436,8 +448,7 @@ __global__ __launch_bounds__(kDdPartThreads) void dedupe_partition_kernel(Dedupe
             d += rest < 0 ? -1 : (rest >= (int)share ? 1 : 0);
         } else { // the last range that begins at or before it
 #pragma unroll
-            for (int step = kDdRanges / 2; step >= 1; step >>= 1)
-                if (d + step < parts && s_bound[min(d + step, kDdRanges)] <= key[r]) d += step;
+            for (int step = kDdRanges / 2; step >= 1; step >>= 1) d = s_bound[d + step] <= key[r] ? d + step : d; // (past the last one: no key)
         }
         if (!exists) d = args.parts; // (padding: after every range)
         const unsigned long long peers = match_digit((unsigned)d, bits);
